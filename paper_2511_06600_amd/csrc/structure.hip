@@ -9,16 +9,60 @@
 namespace hef {
 namespace {
 
-__global__ void k_validate(const int32_t *eptr, const int32_t *pins, const float *w,
-                           int32_t n, int32_t m, int64_t nnz, int32_t *flag) {
+// A wave takes 64 consecutive hyperedges, lane l the hyperedge e0 + l, whose
+// pins [a0, an) are contiguous: the lanes then walk that range side by side
+// (coalesced), each finding the hyperedge of its position by a search over
+// the lanes' starts.  One thread per hyperedge walking its own pins is a
+// serial chain of |e| dependent steps: with a 2000-pin hyperedge the
+// validation took 150 us at 756k pins, and 205 us at 7.9M.
+__device__ __forceinline__ int lane_of_pos(int32_t start, int32_t j, int cnt) {
+  int lo = 0, hi = cnt;  // last lane < cnt whose start is <= j
+#pragma unroll
+  for (int s = 0; s < 6; ++s) {
+    const int mid = (lo + hi) >> 1;
+    const int32_t sm = __shfl(start, mid, 64);
+    const bool up = hi - lo > 1 && sm <= j;
+    lo = up ? mid : lo;
+    hi = (hi - lo > 1 && !up) ? mid : hi;
+  }
+  return lo;
+}
+
+__global__ void __launch_bounds__(256)
+k_validate(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+           const float *__restrict__ w, int32_t n, int32_t m, int64_t nnz,
+           int32_t *__restrict__ flag) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= m) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t e0 = e - lane;
+  if (e0 >= m) return;
+  const int cnt = m - e0 < 64 ? int(m - e0) : 64;
+  const bool on = lane < cnt;
   int bad = 0;
-  const int64_t a = eptr[e], b = eptr[e + 1];
-  if (e == 0 && a != 0) bad |= 1;
-  if (e == m - 1 && b != nnz) bad |= 1;
-  if (a < 0 || b > nnz || b - a < 2) bad |= 2;
-  if (!bad) {
+  const int64_t a = on ? eptr[e] : 0, b = on ? eptr[e + 1] : 2;
+  if (on) {
+    if (e == 0 && a != 0) bad |= 1;
+    if (e == m - 1 && b != nnz) bad |= 1;
+    if (a < 0 || b > nnz || b - a < 2) bad |= 2;
+    if (w) {
+      const float x = w[e];
+      if (!(x > 0.0f) || !isfinite(x)) bad |= 8;
+    }
+  }
+  if (__ballot(bad & 3) == 0) {
+    // every segment of the wave lies in [0, nnz) and starts where the one
+    // before it ends
+    const int32_t a32 = int32_t(a);
+    const int32_t j0 = __shfl(a32, 0, 64), j1 = __shfl(int32_t(b), cnt - 1, 64);
+    for (int64_t jb = j0; jb < j1; jb += 64) {
+      const bool in = jb + lane < j1;
+      const int32_t j = in ? int32_t(jb + lane) : j1 - 1;
+      const int32_t p = in ? pins[j] : 0;
+      const int32_t q = in && j > j0 ? pins[j - 1] : -1;
+      const int32_t start = __shfl(a32, lane_of_pos(a32, j, cnt), 64);
+      if (in && (p < 0 || p >= n || (j != start && p <= q))) bad |= 4;
+    }
+  } else if (on && !(bad & 3)) {
     int32_t prev = -1;
     for (int64_t j = a; j < b; ++j) {
       const int32_t p = pins[j];
@@ -29,19 +73,26 @@ __global__ void k_validate(const int32_t *eptr, const int32_t *pins, const float
       prev = p;
     }
   }
-  if (w) {
-    const float x = w[e];
-    if (!(x > 0.0f) || !isfinite(x)) bad |= 8;
-  }
   if (bad) atomicOr(flag, bad);
 }
 
-__global__ void k_edge_ids(const int32_t *__restrict__ eptr, uint32_t *__restrict__ eid,
-                           int32_t m) {
+// eid[j] = the hyperedge of pin position j (same walk: 36 us to about 6 us at
+// 756k pins with a 2000-pin hyperedge among them).
+__global__ void __launch_bounds__(256)
+k_edge_ids(const int32_t *__restrict__ eptr, uint32_t *__restrict__ eid, int32_t m) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= m) return;
-  const int32_t a = eptr[e], b = eptr[e + 1];
-  for (int32_t j = a; j < b; ++j) eid[j] = uint32_t(e);
+  const int lane = threadIdx.x & 63;
+  const int64_t e0 = e - lane;
+  if (e0 >= m) return;
+  const int cnt = m - e0 < 64 ? int(m - e0) : 64;
+  const int32_t a = lane < cnt ? eptr[e] : 0;
+  const int32_t j0 = __shfl(a, 0, 64), j1 = eptr[e0 + cnt];
+  for (int64_t jb = j0; jb < j1; jb += 64) {
+    const bool in = jb + lane < j1;
+    const int32_t j = in ? int32_t(jb + lane) : j1 - 1;
+    const int k = lane_of_pos(a, j, cnt);
+    if (in) eid[j] = uint32_t(e0 + k);
+  }
 }
 
 // vptr[v] = first position of a key >= v in the sorted pin keys (v <= n):
