@@ -12,18 +12,23 @@
 // a node without neighbours.
 //
 // Layout (deterministic: no floating-point atomics, every sum in ascending
-// hyperedge order):
-//  1. bound(p) = sum over the hyperedges of p of (|e| - 1), the number of
-//     (p, q, e) triples of p; the nodes are cut into batches whose bounds
-//     sum to at most max(nnz, 2^20) triples (one node never exceeds nnz);
-//  2. per batch, one wave per node emits its triples with e ascending and,
-//     within e, q ascending;
-//  3. a stable sort by q, then a stable sort by p, puts each (p, q) run in
-//     ascending e;
-//  4. one thread per node sums its runs in float64 and keeps the largest.
-#include <cfloat>
+// hyperedge order).  A group of lanes takes one node p and keeps a hash table
+// q -> r(p, q) in LDS.  It walks p's hyperedges in ascending order; within a
+// hyperedge the q are distinct, so its lanes add to distinct entries and
+// each entry receives its terms in ascending hyperedge order.  The table's
+// largest entry (ties to the smallest q) is p's result: nothing is sorted
+// and no (p, q, e) triple is stored.  bound(p) = sum over the hyperedges of
+// p of (|e| - 1), at least the number of distinct q, selects the group:
+//   up to 64     16 lanes, 128 entries   (16 nodes per workgroup);
+//   up to 512    a wave, 1024 entries    (4 nodes per workgroup);
+//   above        256 threads, 4096 entries, in passes over hash classes of
+//                the q when they do not fit at once (k_rate_big).
+// Earlier every triple was emitted and sorted by q, then by p (six radix
+// passes per million triples), and one thread per node walked its triples
+// through two indirections: 9.9 ms for the 16M triples of a 200k-node
+// netlist, the node walk itself bound by the longest node's serial chain.  Now
+0.93 ms: bound by the latency of the segment and pin loads of the big class.
 #include <cmath>
-#include <vector>
 
 #include "prims.hpp"
 #include "rating.hpp"
@@ -33,19 +38,9 @@ namespace hef {
 namespace {
 
 constexpr int kRT = 256;
-
-__global__ void k_rate_bound(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
-                             const int32_t *__restrict__ eptr, int32_t n,
-                             int32_t *__restrict__ bound) {
-  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  int64_t b = 0;
-  for (int32_t t = vptr[p]; t < vptr[p + 1]; ++t) {
-    const int32_t e = eids[t];
-    b += eptr[e + 1] - eptr[e] - 1;
-  }
-  bound[p] = int32_t(b);  // <= nnz - 1 (every triple of p is a distinct pin position)
-}
+constexpr int kRateSmall = 64, kRateMid = 512;  // largest bound(p) of a class
+constexpr int kRateBigT = 4096;                 // table of the big class
+constexpr int kRateFill = kRateBigT / 2;        // entries a pass aims at
 
 // flag |= 1 if an R value is not finite
 __global__ void k_rate_check(const float *__restrict__ R, int64_t m, int32_t *__restrict__ flag) {
@@ -53,119 +48,263 @@ __global__ void k_rate_check(const float *__restrict__ R, int64_t m, int32_t *__
   if (e < m && !isfinite(R[e])) atomicOr(flag, 1);
 }
 
-// One wave per node p of the batch [p0, p0 + nb): its triples (q, p - p0, e)
-// at off[p - p0] + running index, e ascending, q ascending within e.
-__global__ void __launch_bounds__(kRT)
-k_rate_emit(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
-            const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins, int32_t p0,
-            int32_t nb, const int32_t *__restrict__ off, uint32_t *__restrict__ kq,
-            uint32_t *__restrict__ vj, uint32_t *__restrict__ pl, int32_t *__restrict__ ee) {
-  const int64_t i = int64_t(blockIdx.x) * (kRT / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (i >= nb) return;
-  const int32_t p = p0 + int32_t(i);
-  int32_t o = off[i];
-  for (int32_t t = vptr[p]; t < vptr[p + 1]; ++t) {
-    const int32_t e = eids[t];
-    const int32_t a = eptr[e], b = eptr[e + 1];
-    for (int32_t j0 = a; j0 < b; j0 += 64) {
-      const int32_t j = j0 + lane;
-      const int32_t q = j < b ? pins[j] : p;
-      const bool take = q != p;
-      const uint64_t mask = __ballot(take);
-      const int32_t pos = __popcll(mask & ((uint64_t(1) << lane) - 1));
-      if (take) {
-        const int32_t k = o + pos;
-        kq[k] = uint32_t(q);
-        vj[k] = uint32_t(k);
-        pl[k] = uint32_t(i);
-        ee[k] = e;
+// Multiplication by an odd constant is a bijection of the 32-bit integers:
+// its top bits index a table, other bits split the q into classes.
+__device__ __forceinline__ uint32_t rate_hash(int32_t q) { return uint32_t(q) * 2654435769u; }
+
+// The entry of q in a table of T keys (-1: free), claimed if absent; -1 when
+// the table is full.
+template <int T>
+__device__ __forceinline__ int rate_slot(int32_t *key, int32_t q) {
+  uint32_t h = rate_hash(q) >> (32 - __builtin_ctz(T));
+  for (int t = 0; t < T; ++t) {
+    int32_t k = key[h];
+    if (k == -1) k = atomicCAS(&key[h], -1, q);
+    if (k == -1 || k == q) return int(h);
+    h = (h + 1) & (T - 1);
+  }
+  return -1;
+}
+
+// w(e) / (R_e - shift), 0 for a zero denominator
+__device__ __forceinline__ double rate_term(const float *w, const float *R, double shift,
+                                            int32_t e) {
+  const double den = double(R[e]) - shift;
+  return den != 0.0 ? double(w ? w[e] : 1.0f) / den : 0.0;
+}
+
+struct RateBest {
+  int32_t q;
+  double r;
+  __device__ __forceinline__ void take(int32_t oq, double orr) {
+    if (oq >= 0 && (q < 0 || orr > r || (orr == r && oq < q))) {
+      q = oq;
+      r = orr;
+    }
+  }
+};
+
+// One node of the classes that fit their table: G lanes of one wave.
+// bound is the same on all G lanes and at most T / 2.
+template <int G, int T>
+__device__ __forceinline__ void
+rate_node(int32_t p, int32_t v0, int32_t deg, int gl, const int32_t *__restrict__ eids,
+          const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+          const float *__restrict__ w, const float *__restrict__ R, double shift, int32_t *key,
+          double *acc, int32_t *__restrict__ best, double *__restrict__ rating) {
+  for (int i = gl; i < T; i += G) {
+    key[i] = -1;
+    acc[i] = 0.0;
+  }
+  wave_sync();
+  for (int32_t t0 = 0; t0 < deg; t0 += G) {
+    // G hyperedges' segments and terms at once, then one hyperedge at a time
+    int32_t ea = 0, eb = 0;
+    double et = 0.0;
+    if (t0 + gl < deg) {
+      const int32_t e = eids[v0 + t0 + gl];
+      ea = eptr[e];
+      eb = eptr[e + 1];
+      et = rate_term(w, R, shift, e);
+    }
+    const int nt = deg - t0 < G ? int(deg - t0) : G;
+    for (int t = 0; t < nt; ++t) {
+      const int32_t a = __shfl(ea, t, G), b = __shfl(eb, t, G);
+      const double term = __shfl(et, t, G);
+      for (int64_t j = a + gl; j < b; j += G) {
+        const int32_t q = pins[j];
+        if (q != p) {
+          const int h = rate_slot<T>(key, q);
+          if (h >= 0) acc[h] += term;
+        }
       }
-      o += __popcll(mask);
+      wave_sync();
     }
+  }
+  RateBest bst{-1, 0.0};
+  for (int i = gl; i < T; i += G) bst.take(key[i], acc[i]);
+#pragma unroll
+  for (int off = G / 2; off > 0; off >>= 1) {
+    const int32_t oq = __shfl_xor(bst.q, off, G);
+    const double orr = __shfl_xor(bst.r, off, G);
+    bst.take(oq, orr);
+  }
+  if (gl == 0) {
+    best[p] = bst.q;
+    rating[p] = bst.q < 0 ? 0.0 : bst.r;
   }
 }
 
-__global__ void k_rate_pkeys(const uint32_t *__restrict__ order, const uint32_t *__restrict__ pl,
-                             uint32_t *__restrict__ kp, uint32_t *__restrict__ vp, int64_t cnt) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= cnt) return;
-  const uint32_t j = order[i];
-  kp[i] = pl[j];
-  vp[i] = j;
-}
-
-// One thread per node of the batch: its triples sit at [off[i], off[i+1]) in
-// (q, e) order; every run of one q is summed in float64, e ascending.
-__global__ void k_rate_best(const int32_t *__restrict__ off, const uint32_t *__restrict__ order,
-                            const uint32_t *__restrict__ kq, const int32_t *__restrict__ ee,
-                            const float *__restrict__ w, const float *__restrict__ R,
-                            double shift, int32_t p0, int32_t nb, int32_t *__restrict__ best,
-                            double *__restrict__ rating) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nb) return;
-  int32_t bq = -1;
-  double br = 0.0;
-  int32_t cq = -1;
-  double acc = 0.0;
-  for (int32_t k = off[i]; k < off[i + 1]; ++k) {
-    const uint32_t j = order[k];
-    const int32_t q = int32_t(kq[j]);
-    const int32_t e = ee[j];
-    if (q != cq) {
-      if (cq >= 0 && (bq < 0 || acc > br)) { bq = cq; br = acc; }
-      cq = q;
-      acc = 0.0;
-    }
-    const double den = double(R[e]) - shift;
-    if (den != 0.0) acc += double(w ? w[e] : 1.0f) / den;
+// Every node: bound(p), then the node itself (small class) or its place in a
+// list (order irrelevant: each node's result stands alone).
+__global__ void __launch_bounds__(kRT)
+k_rate_small(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
+             const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+             const float *__restrict__ w, const float *__restrict__ R, double shift, int32_t n,
+             int32_t *__restrict__ mid, int32_t *__restrict__ big, int32_t *__restrict__ counts,
+             int32_t *__restrict__ best, double *__restrict__ rating) {
+  constexpr int G = 16, T = 2 * kRateSmall, NG = kRT / G;
+  __shared__ int32_t key[NG][T];
+  __shared__ double acc[NG][T];
+  const int gi = threadIdx.x / G, gl = threadIdx.x % G;
+  const int64_t p = int64_t(blockIdx.x) * NG + gi;
+  if (p >= n) return;
+  const int32_t v0 = vptr[p], deg = vptr[p + 1] - v0;
+  int32_t bound = 0;
+  for (int32_t t = gl; t < deg; t += G) {
+    const int32_t e = eids[v0 + t];
+    bound += eptr[e + 1] - eptr[e] - 1;
   }
-  if (cq >= 0 && (bq < 0 || acc > br)) { bq = cq; br = acc; }
-  best[p0 + i] = bq;
-  rating[p0 + i] = bq < 0 ? 0.0 : br;
+#pragma unroll
+  for (int off = G / 2; off > 0; off >>= 1) bound += __shfl_xor(bound, off, G);
+  if (bound > kRateSmall) {
+    if (gl == 0) {
+      int32_t *list = bound <= kRateMid ? mid : big;
+      list[atomicAdd(&counts[bound <= kRateMid ? 0 : 1], 1)] = int32_t(p);
+    }
+    return;
+  }
+  rate_node<G, T>(int32_t(p), v0, deg, gl, eids, eptr, pins, w, R, shift, key[gi], acc[gi], best,
+                  rating);
 }
 
-__global__ void k_rate_scatter(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ idx,
-                               uint32_t *__restrict__ out, int64_t cnt) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < cnt) out[idx[i]] = keys[i];
+__global__ void __launch_bounds__(kRT)
+k_rate_mid(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
+           const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
+           const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+           const float *__restrict__ w, const float *__restrict__ R, double shift,
+           int32_t *__restrict__ best, double *__restrict__ rating) {
+  constexpr int T = 2 * kRateMid, NW = kRT / 64;
+  __shared__ int32_t key[NW][T];
+  __shared__ double acc[NW][T];
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int32_t cnt = counts[0];
+  for (int32_t i = blockIdx.x * NW + wv; i < cnt; i += gridDim.x * NW) {
+    const int32_t p = list[i];
+    const int32_t v0 = vptr[p], deg = vptr[p + 1] - v0;
+    rate_node<64, T>(p, v0, deg, lane, eids, eptr, pins, w, R, shift, key[wv], acc[wv], best,
+                     rating);
+    wave_sync();
+  }
+}
+
+// A workgroup per node.  The q are split into 2^cb classes by bits of their
+// hash below the table's; pass c takes class c.  cb starts so that a pass
+// meets about kRateFill distinct q at most and grows by one, restarting the
+// class sweep, whenever a table fills up; the hash is a bijection, so the
+// classes separate any set of q and the sweep ends.
+__global__ void __launch_bounds__(kRT)
+k_rate_big(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
+           const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
+           const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+           const float *__restrict__ w, const float *__restrict__ R, double shift, int32_t n,
+           int32_t *__restrict__ best, double *__restrict__ rating) {
+  constexpr int T = kRateBigT;
+  constexpr int kTableBits = 12;  // the hash bits that index the table
+  static_assert(1 << kTableBits == T, "table size");
+  __shared__ int32_t key[T];
+  __shared__ double acc[T];
+  __shared__ int32_t full;
+  __shared__ int32_t rq[kRT / 64];
+  __shared__ double rr[kRT / 64];
+  __shared__ long long bsum;
+  const int tid = threadIdx.x;
+  const int32_t cnt = counts[1];
+  for (int32_t i = blockIdx.x; i < cnt; i += gridDim.x) {
+    const int32_t p = list[i];
+    const int32_t v0 = vptr[p], deg = vptr[p + 1] - v0;
+    if (tid == 0) bsum = 0;
+    __syncthreads();
+    long long my = 0;
+    for (int32_t t = tid; t < deg; t += kRT) {
+      const int32_t e = eids[v0 + t];
+      my += eptr[e + 1] - eptr[e] - 1;
+    }
+    atomicAdd(reinterpret_cast<unsigned long long *>(&bsum), (unsigned long long)my);
+    __syncthreads();
+    const int64_t most = bsum < n - 1 ? int64_t(bsum) : int64_t(n - 1);  // distinct q
+    int cb = 0;
+    while (cb < 32 - kTableBits && (most >> cb) > kRateFill) ++cb;
+    RateBest bst{-1, 0.0};
+    for (uint32_t c = 0; c < (1u << cb);) {
+      for (int k = tid; k < T; k += kRT) {
+        key[k] = -1;
+        acc[k] = 0.0;
+      }
+      if (tid == 0) full = 0;
+      __syncthreads();
+      for (int32_t t = 0; t < deg; ++t) {
+        const int32_t e = eids[v0 + t];
+        const int32_t a = eptr[e], b = eptr[e + 1];
+        const double term = rate_term(w, R, shift, e);
+        for (int64_t j = a + tid; j < b; j += kRT) {
+          const int32_t q = pins[j];
+          // class: the hash bits right below the table's (cb = 0: one class)
+          const uint32_t cls = (rate_hash(q) << kTableBits) >> 1 >> (31 - cb);
+          if (q != p && cls == c) {
+            const int h = rate_slot<T>(key, q);
+            if (h >= 0) acc[h] += term;
+            else full = 1;
+          }
+        }
+        __syncthreads();
+      }
+      if (full) {  // (the same on every thread)
+        // halve the classes and start over
+        ++cb;
+        c = 0;
+        bst = RateBest{-1, 0.0};
+        __syncthreads();
+        continue;
+      }
+      for (int k = tid; k < T; k += kRT) bst.take(key[k], acc[k]);
+      __syncthreads();
+      ++c;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const int32_t oq = __shfl_xor(bst.q, off, 64);
+      const double orr = __shfl_xor(bst.r, off, 64);
+      bst.take(oq, orr);
+    }
+    if ((tid & 63) == 0) {
+      rq[tid >> 6] = bst.q;
+      rr[tid >> 6] = bst.r;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      for (int k = 1; k < kRT / 64; ++k) bst.take(rq[k], rr[k]);
+      best[p] = bst.q;
+      rating[p] = bst.q < 0 ? 0.0 : bst.r;
+    }
+    __syncthreads();
+  }
 }
 
 inline unsigned gr(int64_t n) { return unsigned(std::max<int64_t>(1, cdiv(n, kRT))); }
 
-int64_t rating_cap(int64_t nnz) { return std::max<int64_t>(nnz, int64_t(1) << 20); }
-
 }  // namespace
 
 size_t rating_bytes(int64_t n, int64_t m, int64_t nnz) {
-  const int64_t cap = rating_cap(nnz);
   Arena a;
   Structure st;
   structure_carve(a, n, m, nnz, st);
   a.take<int32_t>(4);
-  a.take<int32_t>(n + 1);  // bound
-  a.take<int32_t>(n + 2);  // batch offsets
-  for (int i = 0; i < 7; ++i) a.take<uint32_t>(cap);
-  const size_t scratch = std::max(structure_build_ws(n, m, nnz),
-                                  radix_ws_bytes(cap) + scan_ws_bytes(n + 1) + 4096);
-  return a.mark() + scratch + 4096;
+  a.take<int32_t>(n + 1);  // the lists of the middle and the big class
+  a.take<int32_t>(n + 1);
+  return a.mark() + structure_build_ws(n, m, nnz) + 4096;
 }
 
 hef_status rating_run(const Level &L, const float *R, float shift, int32_t *best, double *rating,
                       void *ws, size_t ws_bytes, hipStream_t s) {
   const int64_t n = L.n, m = L.m, nnz = L.nnz;
-  const int64_t cap = rating_cap(nnz);
   Arena a;
   a.base = static_cast<char *>(ws);
   a.cap = ws_bytes;
   Structure st;
   structure_carve(a, n, m, nnz, st);
   int32_t *flags = a.take<int32_t>(4);
-  int32_t *bound = a.take<int32_t>(n + 1);
-  int32_t *off = a.take<int32_t>(n + 2);
-  uint32_t *kq = a.take<uint32_t>(cap), *vj = a.take<uint32_t>(cap), *pl = a.take<uint32_t>(cap);
-  int32_t *ee = reinterpret_cast<int32_t *>(a.take<uint32_t>(cap));
-  uint32_t *k1 = a.take<uint32_t>(cap), *v1 = a.take<uint32_t>(cap), *k2 = a.take<uint32_t>(cap);
+  int32_t *mid = a.take<int32_t>(n + 1), *big = a.take<int32_t>(n + 1);
   HEF_WS_CHECK(a);
   int32_t bad = 0;
   HEF_TRY(validate_device(L, flags, &bad, s));
@@ -188,41 +327,21 @@ hef_status rating_run(const Level &L, const float *R, float shift, int32_t *best
   if (n == 0) return HEF_OK;
   TimedScope ts(kStRating, s);
   HEF_TRY(structure_build(L, st, a, s));
-  k_rate_bound<<<gr(n), kRT, 0, s>>>(st.vptr, st.eids, L.eptr, int32_t(n), bound);
-  HEF_LAUNCH_CHECK();
-  std::vector<int32_t> hb(n);
-  HEF_HIP(hipMemcpyAsync(hb.data(), bound, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
-  HEF_HIP(hipStreamSynchronize(s));
   const double sh = double(shift);
-  for (int64_t p0 = 0; p0 < n;) {
-    // the batch [p0, p1): as many nodes as fit in cap triples
-    int64_t p1 = p0, tot = 0;
-    while (p1 < n && tot + hb[p1] <= cap) tot += hb[p1++];
-    const int32_t nb = int32_t(p1 - p0);
-    HEF_TRY(exclusive_scan_i32(bound + p0, off, nb, a, s));
-    k_rate_emit<<<unsigned(cdiv(nb, kRT / 64)), kRT, 0, s>>>(st.vptr, st.eids, L.eptr, L.pins,
-                                                            int32_t(p0), nb, off, kq, vj, pl, ee);
-    HEF_LAUNCH_CHECK();
-    const uint32_t *order = vj;
-    if (tot > 0) {
-      // by q (stable, so e stays ascending within a q), then by node
-      HEF_TRY(radix_sort_pairs(kq, vj, k1, v1, tot, bits_for(n - 1), a, s));
-      // the sort clobbered kq and vj: the q values are in k1 (sorted) with
-      // their emission indices in v1; node keys in q order go to k2, and kq
-      // is rebuilt by emission index
-      k_rate_pkeys<<<gr(tot), kRT, 0, s>>>(v1, pl, k2, vj, tot);
-      HEF_LAUNCH_CHECK();
-      k_rate_scatter<<<gr(tot), kRT, 0, s>>>(k1, v1, kq, tot);
-      HEF_LAUNCH_CHECK();
-      HEF_TRY(radix_sort_pairs(k2, vj, k1, v1, tot, bits_for(std::max<int64_t>(nb - 1, 1)), a, s));
-      order = v1;
-    }
-    k_rate_best<<<gr(nb), kRT, 0, s>>>(off, order, kq, ee, L.w, R, sh, int32_t(p0), nb, best,
-                                       rating);
-    HEF_LAUNCH_CHECK();
-    HEF_HIP(hipStreamSynchronize(s));  // the batch buffers are reused
-    p0 = p1;
-  }
+  HEF_TRY(zero_async(flags, 2 * sizeof(int32_t), s));
+  k_rate_small<<<unsigned(cdiv(n, kRT / 16)), kRT, 0, s>>>(st.vptr, st.eids, L.eptr, L.pins, L.w,
+                                                          R, sh, int32_t(n), mid, big, flags,
+                                                          best, rating);
+  HEF_LAUNCH_CHECK();
+  // (grids that walk their lists: the lists' lengths stay on the device)
+  const unsigned nbm = unsigned(std::min<int64_t>(cdiv(n, kRT / 64), 4096));
+  k_rate_mid<<<nbm, kRT, 0, s>>>(mid, flags, st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh, best,
+                                 rating);
+  HEF_LAUNCH_CHECK();
+  k_rate_big<<<unsigned(std::min<int64_t>(n, 1024)), kRT, 0, s>>>(
+      big, flags, st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh, int32_t(n), best, rating);
+  HEF_LAUNCH_CHECK();
+  HEF_HIP(hipStreamSynchronize(s));
   return HEF_OK;
 }
 

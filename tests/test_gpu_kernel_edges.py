@@ -66,3 +66,40 @@ def test_device_validation_at_wave_edges(m):
         if p[b - 2] < p[b]:
             p[b - 1] = p[b]
         assert status(p) == ""
+
+
+def _star_of(n, bound, seed, pool=None, parts=3):
+    """Hyperedges around node 0 whose other pins are `bound` distinct nodes,
+    then two small ones that repeat some of them."""
+    rng = np.random.default_rng(seed)
+    others = rng.permutation(np.arange(1, n) if pool is None else pool)[:bound]
+    edges = [np.concatenate([[0], c]) for c in np.array_split(others, min(parts, bound))]
+    edges += [np.array([0, others[0]]), np.array([1, 2, 3])]
+    edges = [np.sort(e) for e in edges]
+    eptr = np.concatenate([[0], np.cumsum([len(e) for e in edges])]).astype(np.int64)
+    w = rng.uniform(0.5, 2.0, len(edges)).astype(np.float32)
+    return Hypergraph(n=n, m=len(edges), eptr=eptr, pins=np.concatenate(edges).astype(np.int32),
+                      w=w)
+
+
+@pytest.mark.parametrize("bound", [62, 63, 64, 510, 511, 512, 2047, 2049, 4500, "one class"])
+def test_rating_class_edges(bound):
+    """The node's table changes at 64 and 512 triples and is swept in hash
+    classes above 2048 neighbours; in the last case the neighbours all fall
+    in one of the first sweep's four classes, which overflows its table."""
+    from oracle import rating as orat
+    say(f"case: rating bound={bound}")
+    n, pool = 6000, None
+    if bound == "one class":
+        n = 60000
+        q = np.arange(4, n, dtype=np.uint64)
+        h = (q * 2654435769) & 0xFFFFFFFF
+        pool = q[((h >> 18) & 3) == 1].astype(np.int64)[:4500]
+        bound = len(pool)
+    hg = _star_of(n, bound, 11, pool)
+    R = np.random.default_rng(5).uniform(0.01, 1.0, hg.m).astype(np.float32)
+    best, val = hef.rating(to_device(hg), torch.as_tensor(R, device="cuda"), 0.0)
+    nodes = np.unique(np.concatenate([[0, 1, 2, 3], hg.pins[:200:17], [n - 1]]))
+    rb, rv = orat.best_neighbours(hg.n, hg.m, hg.eptr, hg.pins, hg.w, R, 0.0, nodes)
+    assert np.array_equal(best.cpu().numpy()[nodes], rb)
+    assert np.array_equal(val.cpu().numpy()[nodes], rv)
