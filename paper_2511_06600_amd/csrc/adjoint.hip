@@ -260,10 +260,9 @@ k_sadj_c(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
     if (c0 + q < K) dst[q] = float(acc[q]);
 }
 
-__global__ void k_pos_pairs(const int32_t *__restrict__ pins, uint32_t *__restrict__ keys,
-                            uint32_t *__restrict__ vals, int64_t nnz) {
+__global__ void k_positions(uint32_t *__restrict__ vals, int64_t nnz) {
   const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j < nnz) { keys[j] = uint32_t(pins[j]); vals[j] = uint32_t(j); }
+  if (j < nnz) vals[j] = uint32_t(j);
 }
 
 // ------------------------------------------------------------ 2. joint QR
@@ -936,10 +935,13 @@ hef_status reverse_sweep(const Level &L, const hef_params &p, const float *dR, f
     uint32_t *vals = a.take<uint32_t>(nnz);
     uint32_t *keys_out = a.take<uint32_t>(nnz);
     HEF_WS_CHECK(a);
-    k_pos_pairs<<<cdiv(nnz, 256), 256, 0, s>>>(L.pins, keys, vals, nnz);
+    const int bits = bits_for(n > 0 ? n - 1 : 0);
+    uint32_t *cslot = reinterpret_cast<uint32_t *>(w.cslot);
+    uint32_t *pos = radix_src(bits, vals, cslot);
+    k_positions<<<cdiv(nnz, 256), 256, 0, s>>>(pos, nnz);
     HEF_LAUNCH_CHECK();
-    HEF_TRY(radix_sort_pairs(keys, vals, keys_out, reinterpret_cast<uint32_t *>(w.cslot), nnz,
-                             bits_for(n > 0 ? n - 1 : 0), a, s));
+    HEF_TRY(radix_sort_pairs(reinterpret_cast<const uint32_t *>(L.pins), pos, keys, vals,
+                             keys_out, cslot, nnz, bits, a, s));
     a.reset(mk);
   }
   if (K > 256) HEF_TRY(score_adjoint_t<8>(L, st, w.chi, K, w.qh, dR, w, s));

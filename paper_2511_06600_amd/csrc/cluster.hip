@@ -1254,9 +1254,10 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
   {
     TimedScope ts(kStClusterUpdate, s);
     if (m > 0) {
-      k_eta_update<<<g1(m), kT, 0, s>>>(L.eptr, L.pins, R, eta, w.R_upd, w.k0, w.v0, int32_t(m));
+      uint32_t *sk = radix_src(32, w.k0, w.k1), *sv = radix_src(32, w.v0, w.v1);
+      k_eta_update<<<g1(m), kT, 0, s>>>(L.eptr, L.pins, R, eta, w.R_upd, sk, sv, int32_t(m));
       HEF_LAUNCH_CHECK();
-      HEF_TRY(radix_sort_pairs(w.k0, w.v0, w.k1, w.v1, m, 32, ws, s));
+      HEF_TRY(radix_sort_pairs(sk, sv, w.k0, w.v0, w.k1, w.v1, m, 32, ws, s));
       int64_t dpos = int64_t(std::ceil(double(percentile) * double(m))) - 1;
       dpos = std::min<int64_t>(std::max<int64_t>(dpos, 0), m - 1);
       k_rank<<<g1(m), kT, 0, s>>>(w.v1, w.R_upd, int32_t(m), dpos, w.rank, w.state, w.delta);
@@ -1402,26 +1403,42 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
     }
     *n_groups_out = ngroups;
     if (n > 0 && ngroups > 0) {
-      // cluster contributions sorted by (group, label)
-      k_items_clusters<<<g1(n), kT, 0, s>>>(w.prov, label_out, pos_cl, w.k0, w.v0, int32_t(n));
+      // cluster contributions sorted by (group, label), the labels to ibuf
+      // (whose positions the items have taken by then)
+      const int gbits = bits_for(ngroups);
+      uint32_t *ck = radix_src(gbits, w.k0, w.k1), *cv = radix_src(gbits, w.v0, w.v1);
+      k_items_clusters<<<g1(n), kT, 0, s>>>(w.prov, label_out, pos_cl, ck, cv, int32_t(n));
       HEF_LAUNCH_CHECK();
-      HEF_TRY(radix_sort_pairs(w.k0, w.v0, w.k1, w.v1, ncl, bits_for(ngroups), ws, s));
+      HEF_TRY(radix_sort_pairs(ck, cv, w.k0, w.v0, w.k1, reinterpret_cast<uint32_t *>(w.ibuf),
+                               ncl, gbits, ws, s));
       k_seg_ptr<<<g1(int64_t(ngroups) + 1), kT, 0, s>>>(w.k1, ncl, ngroups, w.cl_ptr);
-      HEF_HIP(hipMemcpyAsync(w.ibuf, w.v1, sizeof(int32_t) * std::max(ncl, 1), hipMemcpyDeviceToDevice, s));
-      // pair contributions sorted by (group, min, max)
+      HEF_LAUNCH_CHECK();
+      // pair contributions sorted by (group, min, max): stable sorts by max,
+      // by min and by group; (ka, va) holds the items, (kb, vb) is the other
+      // pair of buffers
+      uint32_t *ka = w.k0, *va = w.v0, *kb = w.k1, *vb = w.v1;
+      auto sort_pairs = [&](int bits) -> hef_status {
+        if (radix_src(bits, false, true)) {  // an even number of passes: back in place
+          return radix_sort_pairs(ka, va, kb, vb, ka, va, npr, bits, ws, s);
+        }
+        HEF_TRY(radix_sort_pairs(ka, va, ka, va, kb, vb, npr, bits, ws, s));
+        std::swap(ka, kb);
+        std::swap(va, vb);
+        return HEF_OK;
+      };
       if (npr > 0) {
-        k_items_pairs<<<g1(n), kT, 0, s>>>(w.best_label, w.flag, pos_pr, w.k0, w.v0, int32_t(n));
+        k_items_pairs<<<g1(n), kT, 0, s>>>(w.best_label, w.flag, pos_pr, ka, va, int32_t(n));
         HEF_LAUNCH_CHECK();
-        HEF_TRY(radix_sort_pairs(w.k0, w.v0, w.k1, w.v1, npr, bits_for(n), ws, s));      // by max
-        k_rekey_min<<<g1(npr), kT, 0, s>>>(w.best_label, w.v1, w.k1, npr);
-        HEF_TRY(radix_sort_pairs(w.k1, w.v1, w.k0, w.v0, npr, bits_for(n), ws, s));      // by min
-        k_rekey_group<<<g1(npr), kT, 0, s>>>(label_out, w.v0, w.k0, npr);
-        HEF_TRY(radix_sort_pairs(w.k0, w.v0, w.k1, w.v1, npr, bits_for(ngroups), ws, s)); // by group
+        HEF_TRY(sort_pairs(bits_for(n)));  // by max
+        k_rekey_min<<<g1(npr), kT, 0, s>>>(w.best_label, va, ka, npr);
+        HEF_TRY(sort_pairs(bits_for(n)));  // by min
+        k_rekey_group<<<g1(npr), kT, 0, s>>>(label_out, va, ka, npr);
+        HEF_TRY(sort_pairs(gbits));  // by group
         HEF_LAUNCH_CHECK();
       }
-      k_seg_ptr<<<g1(int64_t(ngroups) + 1), kT, 0, s>>>(w.k1, npr, ngroups, w.pr_ptr);
+      k_seg_ptr<<<g1(int64_t(ngroups) + 1), kT, 0, s>>>(ka, npr, ngroups, w.pr_ptr);
       k_group_eta<<<g1(ngroups), kT, 0, s>>>(w.cl_ptr, w.ibuf, w.prov_eta, w.pr_ptr,
-                                             reinterpret_cast<const int32_t *>(w.v1), w.best_d,
+                                             reinterpret_cast<const int32_t *>(va), w.best_d,
                                              ngroups, eta_out);
       HEF_LAUNCH_CHECK();
     }
@@ -1480,17 +1497,28 @@ hef_status rebuild_level(const Level &L, const Structure &st, const int32_t *lab
   }
   // a hyperedge beyond the LDS sort: global sorts of the slots by label,
   // then stably by hyperedge, i.e. (edge, label) order
-  k_pin_labels<<<g1(nnz), kT, 0, s>>>(L.pins, label, k0, v0, nnz);
-  HEF_LAUNCH_CHECK();
-  HEF_TRY(radix_sort_pairs(k0, v0, k1, v1, nnz, bits_for(std::max<int32_t>(n2 - 1, 0)), ws, s));
-  k_slot_edge<<<g1(m), kT, 0, s>>>(L.eptr, eid, int32_t(m));
-  k_gather_u32<<<g1(nnz), kT, 0, s>>>(eid, v1, k0, nnz);       // edge of each sorted slot
-  HEF_LAUNCH_CHECK();
-  HEF_TRY(radix_sort_pairs(k0, v1, k1, v0, nnz, bits_for(m - 1), ws, s));
-  // v0 = slots in (edge, label) order; k0 = their labels
-  k_pin_labels<<<g1(nnz), kT, 0, s>>>(L.pins, label, k1, v1, nnz);
-  k_gather_u32<<<g1(nnz), kT, 0, s>>>(k1, v0, k0, nnz);
-  HEF_LAUNCH_CHECK();
+  {
+    const int lbits = bits_for(std::max<int32_t>(n2 - 1, 0)), ebits = bits_for(m - 1);
+    uint32_t *sk = radix_src(lbits, k1, k0), *sv = radix_src(lbits, v1, v0);
+    k_pin_labels<<<g1(nnz), kT, 0, s>>>(L.pins, label, sk, sv, nnz);
+    HEF_LAUNCH_CHECK();
+    HEF_TRY(radix_sort_pairs(sk, sv, k1, v1, k0, v0, nnz, lbits, ws, s));
+    k_slot_edge<<<g1(m), kT, 0, s>>>(L.eptr, eid, int32_t(m));
+    k_gather_u32<<<g1(nnz), kT, 0, s>>>(eid, v0, k0, nnz);  // edge of each sorted slot
+    HEF_LAUNCH_CHECK();
+    // (k0, v0) sorted by edge: back in place, or in (k1, v1)
+    uint32_t *slot = v0, *other = v1;
+    if (radix_src(ebits, false, true)) {
+      HEF_TRY(radix_sort_pairs(k0, v0, k1, v1, k0, v0, nnz, ebits, ws, s));
+    } else {
+      HEF_TRY(radix_sort_pairs(k0, v0, k0, v0, k1, v1, nnz, ebits, ws, s));
+      std::swap(slot, other);
+    }
+    // slot = slots in (edge, label) order; k0 = their labels
+    k_pin_labels<<<g1(nnz), kT, 0, s>>>(L.pins, label, k1, other, nnz);
+    k_gather_u32<<<g1(nnz), kT, 0, s>>>(k1, slot, k0, nnz);
+    HEF_LAUNCH_CHECK();
+  }
   k_distinct<<<g1(m), kT, 0, s>>>(L.eptr, k0, cnt, int32_t(m));
   HEF_LAUNCH_CHECK();
   HEF_TRY(emit(nullptr));

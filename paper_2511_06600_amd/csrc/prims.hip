@@ -9,6 +9,26 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
 
+// Inclusive scan of one value per thread over a workgroup of NT threads;
+// wtot holds one entry per wave.  Ends with every thread past the barriers.
+template <int NT>
+__device__ __forceinline__ int32_t block_inclusive(int32_t x, int tid, int32_t *wtot) {
+  const int lane = tid & 63, wv = tid >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t o = __shfl_up(x, off, 64);
+    if (lane >= off) x += o;
+  }
+  if (lane == 63) wtot[wv] = x;
+  __syncthreads();
+  int32_t add = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w)
+    if (w < wv) add += wtot[w];
+  __syncthreads();
+  return x + add;
+}
+
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_tiles(const int32_t *in, int32_t *out, int32_t *tile_sums, int64_t n) {
   __shared__ int32_t sh[kScanThreads];
@@ -80,9 +100,13 @@ k_scan_add(int32_t *out, const int32_t *tile_off, int64_t n) {
 // kFinishTiles tiles this replaces the two kernels above: re-reading the
 // earlier sums (at most kFinishTiles^2 / 2 reads, from L2) costs less than a
 // launch.
+// COMPACT: the items were flags; idx[position] = i for every set flag (the
+// positions need not be stored) and *total = their number.
 constexpr int64_t kFinishTiles = 2048;
+template <bool COMPACT>
 __global__ void __launch_bounds__(kScanThreads)
-k_scan_finish(int32_t *out, const int32_t *tile_sums, int64_t n, int64_t ntiles) {
+k_scan_finish(int32_t *out, const int32_t *tile_sums, int64_t n, int64_t ntiles,
+              const int32_t *flag, int32_t *idx, int32_t *total) {
   __shared__ int32_t red[kScanThreads / 64];
   const int tid = threadIdx.x;
   const int64_t t = blockIdx.x;
@@ -98,25 +122,82 @@ k_scan_finish(int32_t *out, const int32_t *tile_sums, int64_t n, int64_t ntiles)
   const int64_t base = t * kScanTile;
   for (int i = tid; i < kScanTile; i += kScanThreads) {
     const int64_t q = base + i;
-    if (q < n) out[q] += add;
+    if (q < n) {
+      if constexpr (COMPACT) {
+        if (flag[q]) idx[out[q] + add] = int32_t(q);
+      } else {
+        out[q] += add;
+      }
+    }
   }
-  if (t == ntiles - 1 && tid == 0) out[n] = add + tile_sums[t];
+  if (t == ntiles - 1 && tid == 0) *total = add + tile_sums[t];
+}
+
+// Scan (COMPACT: compaction of flags, as above) of at most kScanOne items in
+// one workgroup and one launch; two launches cost more than the second
+// workgroups would bring at these sizes.
+constexpr int kScanOneThreads = 1024;
+constexpr int kScanOneItems = 16;
+constexpr int kScanOne = kScanOneThreads * kScanOneItems;
+template <bool COMPACT>
+__global__ void __launch_bounds__(kScanOneThreads)
+k_scan_one(const int32_t *in, int32_t *out, int n, int32_t *total) {
+  __shared__ int32_t wtot[kScanOneThreads / 64];
+  const int tid = threadIdx.x;
+  const int base = tid * kScanOneItems;
+  int32_t v[kScanOneItems];
+#pragma unroll
+  for (int i = 0; i < kScanOneItems; ++i) {
+    const int32_t x = base + i < n ? in[base + i] : 0;
+    v[i] = COMPACT ? (x != 0) : x;
+  }
+  int32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < kScanOneItems; ++i) sum += v[i];
+  const int32_t incl = block_inclusive<kScanOneThreads>(sum, tid, wtot);
+  int32_t at = incl - sum;
+#pragma unroll
+  for (int i = 0; i < kScanOneItems; ++i) {
+    if (base + i < n) {
+      if constexpr (COMPACT) {
+        if (v[i]) out[at] = base + i;
+      } else {
+        out[base + i] = at;
+      }
+    }
+    at += v[i];
+  }
+  if (tid == kScanOneThreads - 1) *total = incl;
 }
 
 constexpr int kRadixBits = 8;
 constexpr int kBins = 1 << kRadixBits;
 constexpr int kRadixThreads = 256;
+constexpr int kRadixWaves = kRadixThreads / 64;
+// Items per workgroup of a pass: 4096, or 1024 up to kRadixSmallN items.
+// With 4096 a sort of a few hundred thousand items fills a fraction of the
+// 256 CUs (15 to 20 us a pass at 70k to 760k items, 6 to 9 with 1024); from
+// about a million items on the chip is full either way and the larger tile
+// writes longer runs per digit.
 constexpr int kRadixRounds = 16;
+constexpr int kRadixRoundsSmall = 4;
+constexpr int64_t kRadixSmallN = int64_t(1) << 20;
 constexpr int kRadixTile = kRadixThreads * kRadixRounds;
+constexpr int kRadixTileSmall = kRadixThreads * kRadixRoundsSmall;
 
+inline int64_t radix_tile(int64_t n) { return n <= kRadixSmallN ? kRadixTileSmall : kRadixTile; }
+
+template <int ROUNDS>
 __global__ void __launch_bounds__(kRadixThreads)
-k_radix_hist(const uint32_t *keys, int64_t n, int shift, int32_t *hist, int nblocks) {
+k_radix_hist(const uint32_t *__restrict__ keys, int64_t n, int shift, int32_t *__restrict__ hist,
+             int nblocks) {
   __shared__ int32_t cnt[kBins];
   const int tid = threadIdx.x;
   cnt[tid] = 0;
   __syncthreads();
-  const int64_t base = int64_t(blockIdx.x) * kRadixTile;
-  for (int r = 0; r < kRadixRounds; ++r) {
+  const int64_t base = int64_t(blockIdx.x) * (kRadixThreads * ROUNDS);
+#pragma unroll 4
+  for (int r = 0; r < ROUNDS; ++r) {
     int64_t i = base + int64_t(r) * kRadixThreads + tid;
     if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (kBins - 1)], 1);
   }
@@ -131,27 +212,76 @@ k_radix_hist(const uint32_t *keys, int64_t n, int shift, int32_t *hist, int nblo
 constexpr int kTileRun = 8;
 constexpr int kRadixScanTiles = kRadixThreads * kTileRun;
 
-// Each block re-reads its tile and places every item at
-// offset[digit][block] + (items of the same digit earlier in the tile).
+// Ranks of a wave's ROUNDS x 64 consecutive items among the items of the same
+// digit before them in the wave; cnt[d] (the wave's own row of LDS counters,
+// zero on entry) ends as the wave's count of digit d.  Only this wave touches
+// cnt, so the rounds need no barrier.  Items past `left` take no part.
+template <int ROUNDS>
+__device__ __forceinline__ void wave_ranks(const uint32_t (&k)[ROUNDS], int shift, int64_t left,
+                                           int lane, int32_t *cnt, int32_t (&rank)[ROUNDS]) {
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const bool valid = 64 * r + lane < left;
+    const uint32_t d = (k[r] >> shift) & (kBins - 1);
+    uint64_t peer = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < kRadixBits; ++b) {
+      const bool bit = (d >> b) & 1u;
+      const uint64_t bb = __ballot(bit);
+      peer &= bit ? bb : ~bb;
+    }
+    const int before = __popcll(peer & lt);
+    const int32_t c = valid ? cnt[d] : 0;
+    wave_sync();
+    if (valid && before == 0) cnt[d] = c + __popcll(peer);
+    wave_sync();
+    rank[r] = c + before;
+  }
+}
+
+// One pass's scatter.  Wave w ranks its own ROUNDS * 64 consecutive items of
+// the tile, the digits' counts are scanned over the waves and the digits, and
+// the tile is put in digit order in LDS, so that the stores to global memory
+// go out in runs of one digit (16 items on average at 4096 a tile) instead of
+// one by one.  Bound by the launch and its load latency at small sizes, by
+// the read and write of the items at large ones: 8 bits of 7.9M pairs in 40
+// to 45 us (126 MB moved) against 100 us for the earlier pass, which ranked
+// round by round behind four barriers each.
 // offs holds the exclusive scan of the histogram (digit-major), or with
 // tile_sums given its scan within scan tiles, to which the block adds the
 // sum of the scan tiles before each entry's.
+template <int ROUNDS>
 __global__ void __launch_bounds__(kRadixThreads)
-k_radix_scatter(const uint32_t *kin, const uint32_t *vin, uint32_t *kout,
-                uint32_t *vout, int64_t n, int shift, const int32_t *offs, int nblocks,
-                const int32_t *tile_sums, int ntiles) {
-  __shared__ int32_t base_cnt[kBins];
-  __shared__ int32_t wcnt[kRadixThreads / 64][kBins];
+k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
+                uint32_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t n, int shift,
+                const int32_t *__restrict__ offs, int nblocks,
+                const int32_t *__restrict__ tile_sums, int ntiles) {
+  constexpr int TILE = kRadixThreads * ROUNDS;
+  __shared__ int32_t gbase[kBins];              // global position of the tile's first item per digit
+  __shared__ int32_t lbase[kBins];              // its position within the tile
+  __shared__ int32_t wcnt[kRadixWaves][kBins];  // per wave: counts, then offsets within the digit
+  __shared__ int32_t wtot[kRadixWaves];
+  // the reordered tile; before that, the scan-tile prefixes
+  __shared__ uint32_t pool[2 * TILE > kRadixScanTiles ? 2 * TILE : kRadixScanTiles];
+  uint32_t *sk = pool, *sv = pool + TILE;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wv = tid >> 6;
+  const int64_t base = int64_t(blockIdx.x) * TILE;
+  const int64_t wbase = base + int64_t(wv) * (64 * ROUNDS);
+  uint32_t k[ROUNDS], v[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int64_t i = wbase + 64 * r + lane;
+    k[r] = i < n ? kin[i] : 0u;
+    v[r] = i < n ? vin[i] : 0u;
+  }
   const int64_t hidx = int64_t(tid) * nblocks + blockIdx.x;
-  base_cnt[tid] = offs[hidx];
+  int32_t gb = offs[hidx];
   if (tile_sums) {
-    // exclusive prefix of the tile sums: a run of kTileRun per thread, a
-    // scan of the run totals (in wcnt[0], free until the rounds below),
-    // then each run's prefixes
-    __shared__ int32_t tpre[kRadixScanTiles];
+    // the sum of the scan tiles before hidx's: a run of kTileRun per thread,
+    // scanned over the block
     int32_t run[kTileRun];
     int32_t tot = 0;
 #pragma unroll
@@ -160,52 +290,122 @@ k_radix_scatter(const uint32_t *kin, const uint32_t *vin, uint32_t *kout,
       run[q] = tot;
       tot += t < ntiles ? tile_sums[t] : 0;
     }
-    wcnt[0][tid] = tot;
-    __syncthreads();
-    for (int off = 1; off < kRadixThreads; off <<= 1) {
-      const int32_t x = tid >= off ? wcnt[0][tid - off] : 0;
-      __syncthreads();
-      wcnt[0][tid] += x;
-      __syncthreads();
-    }
-    const int32_t before = wcnt[0][tid] - tot;
+    const int32_t before = block_inclusive<kRadixThreads>(tot, tid, wtot) - tot;
 #pragma unroll
-    for (int q = 0; q < kTileRun; ++q) tpre[tid * kTileRun + q] = before + run[q];
+    for (int q = 0; q < kTileRun; ++q) pool[tid * kTileRun + q] = uint32_t(before + run[q]);
     __syncthreads();
-    base_cnt[tid] += tpre[hidx / kScanTile];
+    gb += int32_t(pool[hidx / kScanTile]);
   }
-  const int64_t base = int64_t(blockIdx.x) * kRadixTile;
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int r = 0; r < kRadixRounds; ++r) {
+  gbase[tid] = gb;
 #pragma unroll
-    for (int w = 0; w < kRadixThreads / 64; ++w) wcnt[w][tid] = 0;
-    __syncthreads();
-    const int64_t i = base + int64_t(r) * kRadixThreads + tid;
-    const bool valid = i < n;
-    const uint32_t k = valid ? kin[i] : 0u;
-    const uint32_t d = (k >> shift) & (kBins - 1);
-    uint64_t peer = __ballot(valid);
+  for (int w = 0; w < kRadixWaves; ++w) wcnt[w][tid] = 0;
+  __syncthreads();
+  int32_t rank[ROUNDS];
+  wave_ranks<ROUNDS>(k, shift, n - wbase, lane, wcnt[wv], rank);
+  __syncthreads();
+  int32_t tot = 0;
 #pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bb = __ballot(bit);
-      peer &= bit ? bb : ~bb;
+  for (int w = 0; w < kRadixWaves; ++w) {
+    const int32_t c = wcnt[w][tid];
+    wcnt[w][tid] = tot;
+    tot += c;
+  }
+  lbase[tid] = block_inclusive<kRadixThreads>(tot, tid, wtot) - tot;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    if (wbase + 64 * r + lane < n) {
+      const uint32_t d = (k[r] >> shift) & (kBins - 1);
+      const int32_t at = lbase[d] + wcnt[wv][d] + rank[r];
+      sk[at] = k[r];
+      sv[at] = v[r];
     }
-    const int rank = __popcll(peer & lt);
-    if (valid && rank == 0) wcnt[wv][d] = __popcll(peer);
+  }
+  __syncthreads();
+  const int cnt = n - base < TILE ? int(n - base) : TILE;
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int i = r * kRadixThreads + tid;
+    if (i < cnt) {
+      const uint32_t key = sk[i];
+      const uint32_t d = (key >> shift) & (kBins - 1);
+      const int32_t pos = gbase[d] + (i - lbase[d]);
+      kout[pos] = key;
+      vout[pos] = sv[i];
+    }
+  }
+}
+
+// All passes of a sort of at most 1024 * ROUNDS items in one workgroup: the
+// items stay in registers and pass through LDS once per pass.  Replaces
+// three launches per pass (about 4 us each when the chip is otherwise idle).
+constexpr int kOneThreads = 1024;
+constexpr int kOneWaves = kOneThreads / 64;
+constexpr int kOneRounds = 16;
+
+template <int ROUNDS>
+__global__ void __launch_bounds__(kOneThreads)
+k_radix_one(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout, int n,
+            int passes) {
+  __shared__ uint32_t buf[kOneThreads * ROUNDS];
+  __shared__ int32_t wcnt[kOneWaves][kBins];
+  __shared__ int32_t lbase[kBins];
+  __shared__ int32_t wtot[kOneWaves];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = tid >> 6;
+  const int wbase = wv * (64 * ROUNDS);
+  uint32_t k[ROUNDS], v[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int i = wbase + 64 * r + lane;
+    k[r] = i < n ? kin[i] : 0u;
+    v[r] = i < n ? vin[i] : 0u;
+  }
+  for (int p = 0; p < passes; ++p) {
+    const int shift = p * kRadixBits;
+    for (int i = tid; i < kOneWaves * kBins; i += kOneThreads) (&wcnt[0][0])[i] = 0;
     __syncthreads();
-    if (valid) {
-      int32_t pos = base_cnt[d] + rank;
-      for (int w = 0; w < wv; ++w) pos += wcnt[w][d];
-      kout[pos] = k;
-      vout[pos] = vin[i];
+    int32_t rank[ROUNDS];
+    wave_ranks<ROUNDS>(k, shift, n - wbase, lane, wcnt[wv], rank);
+    __syncthreads();
+    int32_t tot = 0;
+    if (tid < kBins) {
+#pragma unroll
+      for (int w = 0; w < kOneWaves; ++w) {
+        const int32_t c = wcnt[w][tid];
+        wcnt[w][tid] = tot;
+        tot += c;
+      }
+    }
+    const int32_t incl = block_inclusive<kOneThreads>(tot, tid, wtot);
+    if (tid < kBins) lbase[tid] = incl - tot;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const uint32_t d = (k[r] >> shift) & (kBins - 1);
+      rank[r] += lbase[d] + wcnt[wv][d];
+      if (wbase + 64 * r + lane < n) buf[rank[r]] = k[r];
     }
     __syncthreads();
-    int32_t add = 0;
 #pragma unroll
-    for (int w = 0; w < kRadixThreads / 64; ++w) add += wcnt[w][tid];
-    base_cnt[tid] += add;
+    for (int r = 0; r < ROUNDS; ++r) k[r] = buf[wbase + 64 * r + lane];
     __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+      if (wbase + 64 * r + lane < n) buf[rank[r]] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) v[r] = buf[wbase + 64 * r + lane];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int i = wbase + 64 * r + lane;
+    if (i < n) {
+      kout[i] = k[r];
+      vout[i] = v[r];
+    }
   }
 }
 
@@ -266,11 +466,6 @@ __global__ void k_zero_bytes(uint8_t *p, int64_t n) {
     p[i] = 0u;
 }
 
-__global__ void k_flag_copy(const int32_t *flag, int32_t *out, int64_t n) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = flag[i] ? 1 : 0;
-}
-
 }  // namespace
 
 hef_status zero_async(void *p, size_t bytes, hipStream_t s) {
@@ -322,9 +517,16 @@ hef_status exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Arena 
     ws.reset(mk);
     return HEF_OK;
   }
+  if (n <= kScanOne) {
+    k_scan_one<false><<<1, kScanOneThreads, 0, s>>>(in, out, int(n), out + n);
+    HEF_LAUNCH_CHECK();
+    ws.reset(mk);
+    return HEF_OK;
+  }
   k_scan_tiles<<<ntiles, kScanThreads, 0, s>>>(in, out, sums, n);
   if (ntiles <= kFinishTiles) {
-    k_scan_finish<<<ntiles, kScanThreads, 0, s>>>(out, sums, n, ntiles);
+    k_scan_finish<false><<<ntiles, kScanThreads, 0, s>>>(out, sums, n, ntiles, nullptr, nullptr,
+                                                         out + n);
   } else {
     k_scan_sums<<<1, 1024, 0, s>>>(sums, ntiles, out + n);
     k_scan_add<<<ntiles, kScanThreads, 0, s>>>(out, sums, n);
@@ -335,44 +537,62 @@ hef_status exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Arena 
 }
 
 size_t radix_ws_bytes(int64_t n) {
-  const int64_t nb = cdiv(n, kRadixTile);
+  const int64_t nb = cdiv(n, radix_tile(n));
   Arena a;
   a.take<int32_t>(nb * kBins + 1);
   return a.mark() + scan_ws_bytes(nb * kBins) + 512;
 }
 
-hef_status radix_sort_pairs(uint32_t *keys, uint32_t *vals, uint32_t *keys_out,
-                            uint32_t *vals_out, int64_t n, int bits, Arena &ws,
-                            hipStream_t s) {
+hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
+                            uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n,
+                            int bits, Arena &ws, hipStream_t s) {
   if (n == 0) return HEF_OK;
-  const int64_t nb = cdiv(n, kRadixTile);
+  const int passes = (bits + kRadixBits - 1) / kRadixBits;
+  if (n <= kOneThreads * kOneRounds) {
+    if (n <= kOneThreads * 4)
+      k_radix_one<4><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n), passes);
+    else if (n <= kOneThreads * 8)
+      k_radix_one<8><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n), passes);
+    else
+      k_radix_one<kOneRounds><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n),
+                                                        passes);
+    HEF_LAUNCH_CHECK();
+    return HEF_OK;
+  }
+  const bool small = n <= kRadixSmallN;
+  const int64_t nb = cdiv(n, radix_tile(n));
   const size_t mk = ws.mark();
   int32_t *hist = ws.take<int32_t>(nb * kBins + 1);
   HEF_WS_CHECK(ws);
-  const int passes = (bits + kRadixBits - 1) / kRadixBits;
-  uint32_t *ka = keys, *va = vals, *kb = keys_out, *vb = vals_out;
   // the histogram's scan tiles: when there are at most kRadixScanTiles
   // (n up to 64M keys) the scatter adds their prefixes itself
   const int64_t htiles = cdiv(nb * kBins, kScanTile);
   int32_t *tsum = htiles <= kRadixScanTiles ? ws.take<int32_t>(htiles) : nullptr;
   HEF_WS_CHECK(ws);
+  const uint32_t *ka = src_k, *va = src_v;
   for (int p = 0; p < passes; ++p) {
     const int shift = p * kRadixBits;
-    k_radix_hist<<<nb, kRadixThreads, 0, s>>>(ka, n, shift, hist, int(nb));
+    // the last pass writes out, the ones before alternate
+    const bool to_out = ((passes - 1 - p) & 1) == 0;
+    uint32_t *kb = to_out ? out_k : tmp_k, *vb = to_out ? out_v : tmp_v;
+    if (small)
+      k_radix_hist<kRadixRoundsSmall><<<nb, kRadixThreads, 0, s>>>(ka, n, shift, hist, int(nb));
+    else
+      k_radix_hist<kRadixRounds><<<nb, kRadixThreads, 0, s>>>(ka, n, shift, hist, int(nb));
     if (tsum) {
       k_scan_tiles<<<htiles, kScanThreads, 0, s>>>(hist, hist, tsum, nb * kBins);
     } else {
       HEF_TRY(exclusive_scan_i32(hist, hist, nb * kBins, ws, s));
     }
-    k_radix_scatter<<<nb, kRadixThreads, 0, s>>>(ka, va, kb, vb, n, shift, hist, int(nb), tsum,
-                                                 int(htiles));
+    if (small)
+      k_radix_scatter<kRadixRoundsSmall><<<nb, kRadixThreads, 0, s>>>(
+          ka, va, kb, vb, n, shift, hist, int(nb), tsum, int(htiles));
+    else
+      k_radix_scatter<kRadixRounds><<<nb, kRadixThreads, 0, s>>>(ka, va, kb, vb, n, shift, hist,
+                                                                 int(nb), tsum, int(htiles));
     HEF_LAUNCH_CHECK();
-    std::swap(ka, kb);
-    std::swap(va, vb);
-  }
-  if (ka != keys_out) {
-    HEF_HIP(hipMemcpyAsync(keys_out, ka, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    HEF_HIP(hipMemcpyAsync(vals_out, va, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+    ka = kb;
+    va = vb;
   }
   ws.reset(mk);
   return HEF_OK;
@@ -384,9 +604,24 @@ hef_status compact_flags(const int32_t *flag, int32_t *scratch, int32_t *idx_out
     HEF_TRY(zero_async(count_dev, sizeof(int32_t), s));
     return HEF_OK;
   }
-  k_flag_copy<<<cdiv(n, 256), 256, 0, s>>>(flag, scratch, n);
-  HEF_TRY(exclusive_scan_i32(scratch, scratch, n, ws, s));
-  k_compact<<<cdiv(n, 256), 256, 0, s>>>(flag, scratch, idx_out, count_dev, n);
+  if (n <= kScanOne) {
+    k_scan_one<true><<<1, kScanOneThreads, 0, s>>>(flag, idx_out, int(n), count_dev);
+    HEF_LAUNCH_CHECK();
+    return HEF_OK;
+  }
+  const int64_t ntiles = cdiv(n, kScanTile);
+  if (ntiles <= kFinishTiles) {
+    const size_t mk = ws.mark();
+    int32_t *sums = ws.take<int32_t>(ntiles + 1);
+    HEF_WS_CHECK(ws);
+    k_scan_tiles<<<ntiles, kScanThreads, 0, s>>>(flag, scratch, sums, n);
+    k_scan_finish<true><<<ntiles, kScanThreads, 0, s>>>(scratch, sums, n, ntiles, flag, idx_out,
+                                                        count_dev);
+    ws.reset(mk);
+  } else {
+    HEF_TRY(exclusive_scan_i32(flag, scratch, n, ws, s));
+    k_compact<<<cdiv(n, 256), 256, 0, s>>>(flag, scratch, idx_out, count_dev, n);
+  }
   HEF_LAUNCH_CHECK();
   return HEF_OK;
 }

@@ -15,15 +15,22 @@ hef_status exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n,
 
 // Workspace bytes for radix_sort_pairs over `n` items.
 size_t radix_ws_bytes(int64_t n);
-// Stable LSD radix sort of (keys, vals) by the low `bits` bits of keys.
-// On return the sorted data is in (keys_out, vals_out); the inputs are
-// clobbered (used as ping-pong buffers).
-hef_status radix_sort_pairs(uint32_t *keys, uint32_t *vals, uint32_t *keys_out,
-                            uint32_t *vals_out, int64_t n, int bits, Arena &ws,
-                            hipStream_t s);
+// Stable LSD radix sort of n (key, value) pairs by the low `bits` bits of
+// the keys, 8 bits a pass: src -> out, with tmp as the other ping-pong buffer
+// (both n items; the last pass writes out, so nothing is copied at the end).
+// src may be buffers of its own (left as they are), or the buffers that the
+// first pass does not write: out when the number of passes is even, tmp when
+// it is odd (radix_src picks them).
+hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
+                            uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n,
+                            int bits, Arena &ws, hipStream_t s);
+template <class T>
+inline T radix_src(int bits, T tmp, T out) {
+  return ((bits + 7) / 8) % 2 == 0 ? out : tmp;
+}
 
-// idx_out[0..count) = ascending indices i < n with flag[i] != 0;
-// *count_dev = count.  Uses `scratch` of n+1 int32.
+// idx_out[0..count) = ascending indices i < n with flag[i] = 1 (flags are 0
+// or 1); *count_dev = count.  Uses `scratch` of n+1 int32.
 hef_status compact_flags(const int32_t *flag, int32_t *scratch, int32_t *idx_out,
                          int32_t *count_dev, int64_t n, Arena &ws, hipStream_t s);
 

@@ -276,10 +276,12 @@ extern "C" hef_status hef_conductance(const hef_hypergraph *hg, const int32_t *l
   }
   HEF_TRY(zero_async(q.bad, sizeof(int32_t), stream));
   HEF_TRY(zero_async(q.split, m * sizeof(int32_t), stream));
+  const int bits = bits_for(nc - 1);
+  uint32_t *sk = radix_src(bits, q.k0, q.k1), *sv = radix_src(bits, q.v0, q.v1);
   k_qual_emit<<<cdiv(nnz, kQT), kQT, 0, stream>>>(L.eptr, L.pins, label, int32_t(m), nnz, nc,
-                                                   q.k0, q.v0, q.split, q.bad);
+                                                   sk, sv, q.split, q.bad);
   HEF_LAUNCH_CHECK();
-  HEF_TRY(radix_sort_pairs(q.k0, q.v0, q.k1, q.v1, nnz, bits_for(nc - 1), a, stream));
+  HEF_TRY(radix_sort_pairs(sk, sv, q.k0, q.v0, q.k1, q.v1, nnz, bits, a, stream));
   k_qual_seg<<<cdiv(int64_t(nc) + 1, kQT), kQT, 0, stream>>>(q.k1, nnz, nc, q.seg);
   HEF_LAUNCH_CHECK();
   k_qual_cluster<<<cdiv(int64_t(nc) * 64, kQT), kQT, 0, stream>>>(L.w, q.v1, q.seg, q.split, nc,

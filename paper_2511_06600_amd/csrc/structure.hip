@@ -107,11 +107,6 @@ __global__ void k_seg_bounds(const uint32_t *__restrict__ key, int64_t nnz, int3
   for (int64_t v = prev + 1; v <= cur; ++v) vptr[v] = int32_t(j);
 }
 
-__global__ void k_copy_pins(const int32_t *pins, uint32_t *keys, int64_t nnz) {
-  const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j < nnz) keys[j] = uint32_t(pins[j]);
-}
-
 // Per hyperedge: alpha_e = sqrt(w_e)/|e|, beta_e = w_e/(|e|(|e|-1)); flag
 // big; the float64 terms w_e/|e| and beta_e of the node sums.
 __global__ void k_edge_scales(const int32_t *__restrict__ eptr, const float *__restrict__ w,
@@ -184,16 +179,35 @@ void structure_carve(Arena &a, int64_t n, int64_t m, int64_t nnz, Structure &st)
   st.n_big = a.take<int32_t>(2);
 }
 
+// Scratch of the build: the sort's buffers, then in their place the arrays
+// of the scales and lists.
+struct SortWs {
+  uint32_t *tmp_k, *tmp_v, *out_k;
+};
+struct ScaleWs {
+  int32_t *flags, *scratch;
+  double *tdb, *tcb;  // per-hyperedge terms of the node sums
+};
+static void carve_sort(Arena &a, int64_t nnz, SortWs &w) {
+  w.tmp_k = a.take<uint32_t>(nnz);
+  w.tmp_v = a.take<uint32_t>(nnz);
+  w.out_k = a.take<uint32_t>(nnz);
+}
+static void carve_scale(Arena &a, int64_t n, int64_t m, ScaleWs &w) {
+  w.flags = a.take<int32_t>(std::max(n, m) + 1);
+  w.scratch = a.take<int32_t>(std::max(n, m) + 1);
+  w.tdb = a.take<double>(std::max<int64_t>(m, 1));
+  w.tcb = a.take<double>(std::max<int64_t>(m, 1));
+}
+
 size_t structure_build_ws(int64_t n, int64_t m, int64_t nnz) {
-  Arena a;
-  a.take<uint32_t>(nnz);  // keys
-  a.take<uint32_t>(nnz);  // vals
-  a.take<uint32_t>(nnz);  // keys out
-  a.take<int32_t>(std::max(n, m) + 1);  // flags
-  a.take<int32_t>(std::max(n, m) + 1);  // compaction scratch
-  a.take<double>(std::max<int64_t>(m, 1));  // per-edge node-sum terms
-  a.take<double>(std::max<int64_t>(m, 1));
-  return a.mark() + radix_ws_bytes(nnz) + scan_ws_bytes(std::max(n, m) + 1) + 4096;
+  Arena a, c;
+  SortWs sw;
+  ScaleWs cw;
+  carve_sort(a, nnz, sw);
+  carve_scale(c, n, m, cw);
+  return std::max(a.mark() + radix_ws_bytes(nnz),
+                  c.mark() + scan_ws_bytes(std::max(n, m) + 1)) + 4096;
 }
 
 hef_status validate_device(const Level &L, int32_t *flag_dev, int32_t *bad_host,
@@ -211,42 +225,42 @@ hef_status structure_build(const Level &L, Structure &st, Arena &ws, hipStream_t
   const int64_t n = L.n, m = L.m, nnz = L.nnz;
   TimedScope ts(kStStructure, s);
   const size_t mk = ws.mark();
-  uint32_t *keys = ws.take<uint32_t>(nnz);
-  uint32_t *vals = ws.take<uint32_t>(nnz);
-  uint32_t *keys_out = ws.take<uint32_t>(nnz);
-  int32_t *flags = ws.take<int32_t>(std::max(n, m) + 1);
-  int32_t *scratch = ws.take<int32_t>(std::max(n, m) + 1);
-  double *tdb = ws.take<double>(std::max<int64_t>(m, 1));
-  double *tcb = ws.take<double>(std::max<int64_t>(m, 1));
-  HEF_WS_CHECK(ws);
-
   // eids: stable sort of (pin, edge) by pin; input is in edge order, so
   // each node's hyperedges come out ascending.  vptr from the sorted pins.
   if (nnz > 0) {
-    k_copy_pins<<<cdiv(nnz, 256), 256, 0, s>>>(L.pins, keys, nnz);
-    k_edge_ids<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, vals, int32_t(m));
+    SortWs w;
+    carve_sort(ws, nnz, w);
+    HEF_WS_CHECK(ws);
+    const int bits = bits_for(n > 0 ? n - 1 : 0);
+    uint32_t *eids = reinterpret_cast<uint32_t *>(st.eids);
+    uint32_t *ids = radix_src(bits, w.tmp_v, eids);
+    k_edge_ids<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, ids, int32_t(m));
     HEF_LAUNCH_CHECK();
-    HEF_TRY(radix_sort_pairs(keys, vals, keys_out, reinterpret_cast<uint32_t *>(st.eids),
-                             nnz, bits_for(n > 0 ? n - 1 : 0), ws, s));
-    k_seg_bounds<<<cdiv(nnz + 1, 256), 256, 0, s>>>(keys_out, nnz, int32_t(n), st.vptr);
+    HEF_TRY(radix_sort_pairs(reinterpret_cast<const uint32_t *>(L.pins), ids, w.tmp_k, w.tmp_v,
+                             w.out_k, eids, nnz, bits, ws, s));
+    k_seg_bounds<<<cdiv(nnz + 1, 256), 256, 0, s>>>(w.out_k, nnz, int32_t(n), st.vptr);
     HEF_LAUNCH_CHECK();
   } else {
     HEF_TRY(zero_async(st.vptr, (n + 1) * sizeof(int32_t), s));
   }
+  ws.reset(mk);  // (the stream orders the reuse)
 
   // scales and big-segment lists
+  ScaleWs w;
+  carve_scale(ws, n, m, w);
+  HEF_WS_CHECK(ws);
   if (m > 0) {
-    k_edge_scales<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, L.w, st.alpha, st.beta, flags, tdb, tcb,
-                                               int32_t(m));
+    k_edge_scales<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, L.w, st.alpha, st.beta, w.flags, w.tdb,
+                                               w.tcb, int32_t(m));
     HEF_LAUNCH_CHECK();
   }
-  HEF_TRY(compact_flags(flags, scratch, st.big_e, st.n_big, m, ws, s));
+  HEF_TRY(compact_flags(w.flags, w.scratch, st.big_e, st.n_big, m, ws, s));
   if (n > 0) {
-    k_node_scales<<<cdiv(n, 256), 256, 0, s>>>(st.vptr, st.eids, tdb, tcb, st.s, st.gam,
-                                              flags, int32_t(n));
+    k_node_scales<<<cdiv(n, 256), 256, 0, s>>>(st.vptr, st.eids, w.tdb, w.tcb, st.s, st.gam,
+                                              w.flags, int32_t(n));
     HEF_LAUNCH_CHECK();
   }
-  HEF_TRY(compact_flags(flags, scratch, st.big_v, st.n_big + 1, n, ws, s));
+  HEF_TRY(compact_flags(w.flags, w.scratch, st.big_v, st.n_big + 1, n, ws, s));
   ws.reset(mk);
   return HEF_OK;
 }

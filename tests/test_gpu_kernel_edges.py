@@ -103,3 +103,41 @@ def test_rating_class_edges(bound):
     rb, rv = orat.best_neighbours(hg.n, hg.m, hg.eptr, hg.pins, hg.w, R, 0.0, nodes)
     assert np.array_equal(best.cpu().numpy()[nodes], rb)
     assert np.array_equal(val.cpu().numpy()[nodes], rv)
+
+
+@pytest.mark.parametrize("nnz", [2, 1023, 1025, 4095, 4097, 8193, 16384, 16385, 70001, 1048577])
+def test_sort_and_compaction_sizes(nnz):
+    """The incidence sort runs in one workgroup up to 16384 items (4, 8 or 16
+    a thread), in tiles of 1024 up to 2^20 and of 4096 above; node counts
+    that need one to three digit passes.  The operator's rows depend on every
+    node's hyperedges being complete and in order."""
+    say(f"case: sort sizes nnz={nnz}")
+    for n in (200, 60000, 70000):
+        if nnz == 2 and n != 200:
+            continue
+        m = max(nnz // 3, 1)
+        rng = np.random.default_rng(nnz + n)
+        first = rng.integers(0, n - 2 * (nnz - 2 * m + 1), m) if n > 2 * (nnz - 2 * m + 1) \
+            else rng.integers(0, n - 3, m)
+        sizes = np.full(m, 2)
+        left = nnz - 2 * m
+        sizes[rng.permutation(m)[:left]] += 1 if left <= m else 0
+        eptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+        pins = (np.repeat(first, sizes) + np.arange(eptr[-1]) - np.repeat(eptr[:-1], sizes))
+        h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins.astype(np.int32), w=np.ones(m, np.float32))
+        label = torch.arange(n, dtype=torch.int32, device="cuda")
+        # every node its own cluster: vol = degree, cut = degree (all split)
+        cut, vol, _, _ = hef.conductance(to_device(h), label, n)
+        deg = np.bincount(h.pins, minlength=n).astype(np.float64)
+        assert np.array_equal(vol.cpu().numpy(), deg) and np.array_equal(cut.cpu().numpy(), deg)
+        # star operator on hyperedge indicators: y_u = s_u sum_e alpha_e x_e
+        x = torch.zeros((n + m, 1), device="cuda")
+        x[n:, 0] = torch.arange(m, device="cuda") % 13
+        y = hef.debug_apply(to_device(h), 0, x).cpu().numpy()[:n, 0].astype(np.float64)
+        inv = 1.0 / sizes
+        db = np.bincount(h.pins, weights=np.repeat(inv, sizes), minlength=n)
+        ref = np.bincount(h.pins, weights=np.repeat(inv * (np.arange(m) % 13), sizes), minlength=n)
+        ref = np.where(db > 0, ref / np.sqrt(np.where(db > 0, db, 1.0)), 0.0)
+        # float32 scales and terms: (degree + 4) roundings of relative 2^-24
+        tol = (deg.max() + 4) * 2.0 ** -24
+        assert np.abs(y - ref).max() <= tol * max(np.abs(ref).max(), 1.0)
