@@ -912,7 +912,7 @@ hef_status taped_forward(const Level &L, const hef_params &p, const float *start
                       use_clique, ko, a, s, &w.tape));
   HEF_TRY(orthonormalize_pool(w.P, w.chi, kPoolF32, n, K, double(p.drop_tol), 1, nullptr, a, s,
                               w.rinvJ));
-  HEF_TRY(score_pool(L, w.chi, kPoolF32, K, w.qh, w.R, a, s, w.sfwd));
+  HEF_TRY(score_pool(L, st, w.chi, kPoolF32, K, w.qh, w.R, w.P, a, s, w.sfwd));
   return HEF_OK;
 }
 

@@ -225,7 +225,7 @@ hef_status estimate_level(const Level &L, const hef_params &p, uint64_t seed, in
   ws.reset(mk);
   HEF_TRY(orthonormalize_pool(pool2, pool, ko.pool_type, n, K, double(p.drop_tol),
                               p.orth_passes, nullptr, ws, s, nullptr, rho));
-  HEF_TRY(score_pool(L, pool, ko.pool_type, K, qh, R, ws, s));
+  HEF_TRY(score_pool(L, st, pool, ko.pool_type, K, qh, R, pool2, ws, s));
   return HEF_OK;
 }
 

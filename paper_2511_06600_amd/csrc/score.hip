@@ -3,6 +3,7 @@
 // For every hyperedge e and pool column i the two most distant pins along
 // chi^(i) are its largest and smallest entries, so the numerator of Eq. (13)
 // is s_e^(i) = (max_{p in e} chi_p^(i) - min_{p in e} chi_p^(i))^2.
+// A first pass takes the extremes of the long hyperedges (k_score_long).
 // Pass 1 forms Q_H(chi^(i)) = sum_e w_e s_e^(i) (Eq. (9)) and stores the
 // m x K numerators s (float32, row e contiguous); pass 2 streams them back
 // to form R_e = max_i s_e^(i) / Q_H(chi^(i)) (Eq. (14)).  Streaming s costs
@@ -113,15 +114,106 @@ __device__ __forceinline__ void edge_spread(const int32_t *__restrict__ pins, co
   }
 }
 
+// Pool values of columns c0.. (exact: they are pool values).
+template <int CPL, int PT>
+__device__ __forceinline__ void store_cols(void *pool, int64_t row, int K, int c0,
+                                           const PoolVal<PT> (&v)[CPL]) {
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {
+    if (c0 + q >= K) continue;
+    if constexpr (PT == kPoolF64)
+      reinterpret_cast<double *>(pool)[row * K + c0 + q] = v[q];
+    else if constexpr (PT == kPoolF32)
+      reinterpret_cast<float *>(pool)[row * K + c0 + q] = v[q];
+    else
+      reinterpret_cast<uint16_t *>(pool)[row * K + c0 + q] =
+          uint16_t(__float_as_uint(v[q]) >> 16);
+  }
+}
+
+// Largest and smallest pool values of every hyperedge of more than longseg
+// pins, a workgroup per hyperedge of the list: its groups of LPR lanes take
+// 4 pins at a time, then their extremes meet in LDS.  Row 2 i of `ext`
+// receives the largest, row 2 i + 1 the smallest values, i = (first pin
+// position) / longseg, which no two such hyperedges share.  Maxima do not
+// depend on the order, so the ratios keep their bits.
+constexpr int kLongThreads = 512;
+
+template <int CPL, int PT>
+__global__ void __launch_bounds__(kLongThreads)
+k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
+             const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+             const void *__restrict__ pool, int K, int LPR, int longseg, void *__restrict__ ext) {
+  using T = PoolVal<PT>;
+  constexpr T kBig = PT == kPoolF64 ? T(DBL_MAX) : T(FLT_MAX);
+  __shared__ T smx[kLongThreads * CPL], smn[kLongThreads * CPL];
+  const int tid = threadIdx.x;
+  const int ngrp = kLongThreads / LPR;
+  const int grp = tid / LPR;
+  const int c0 = (tid % LPR) * CPL;
+  const int W = LPR * CPL;  // columns of a group's LDS row
+  const int32_t cnt = *count;
+  for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
+    const int32_t e = list[bi];
+    const int32_t a = eptr[e], b = eptr[e + 1];
+    if (b - a <= longseg) continue;  // (the same on every thread)
+    T mx[CPL], mn[CPL];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) { mx[q] = -kBig; mn[q] = kBig; }
+    if (c0 < K) {
+      for (int64_t j0 = a + 4 * grp; j0 < b; j0 += 4 * ngrp) {
+        int32_t pp[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) pp[u] = pins[j0 + u < b ? j0 + u : b - 1];
+        T v[4][CPL];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_cols<CPL, PT>(pool, pp[u], K, c0, v[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) {
+            mx[q] = vmax(mx[q], v[u][q]);
+            mn[q] = vmin(mn[q], v[u][q]);
+          }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      smx[grp * W + c0 + q] = mx[q];
+      smn[grp * W + c0 + q] = mn[q];
+    }
+    __syncthreads();
+    if (grp == 0 && c0 < K) {
+      for (int g = 1; g < ngrp; ++g)
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+          mx[q] = vmax(mx[q], smx[g * W + c0 + q]);
+          mn[q] = vmin(mn[q], smn[g * W + c0 + q]);
+        }
+      const int64_t row = 2 * int64_t(a / longseg);
+      store_cols<CPL, PT>(ext, row, K, c0, mx);
+      store_cols<CPL, PT>(ext, row + 1, K, c0, mn);
+    }
+    __syncthreads();
+  }
+}
+
 // A workgroup takes kEdgesPerBlk consecutive hyperedges [e0, e1); group grp
 // (LPR lanes, ngrp groups) takes e0 + grp + ngrp k, in rounds of LPR: lane j
 // of the group fetches the pin range of the round's j-th hyperedge up front.
+// Hyperedges of more than longseg pins take their extremes from `ext`
+// (k_score_long): one group walking 2000 pins is a chain of 500 dependent
+// gathers, 0.2 to 0.4 ms whatever the size of the launch.  Measured with
+// that chain / without (this pass plus k_score_long): 20k nodes, K = 464,
+// 204 / 128 us; 200k nodes, K = 160, 410 / 190 us; 2M nodes, K = 480,
+// 3.85 / 3.65 ms.
 template <int CPL, int PT>
 __global__ void __launch_bounds__(kThreads)
 k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
            const float *__restrict__ w, const void *__restrict__ pool, int K, int LPR,
-           int64_t m, double *__restrict__ partial, float *__restrict__ sbuf) {
-  __shared__ double comb[512];
+           int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
+           const void *__restrict__ ext) {
+  __shared__ double comb[kThreads * CPL];
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -149,7 +241,19 @@ k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       const double we = double(__shfl(ew, k, LPR));
       if (c0 < K) {
         double s[CPL];
-        edge_spread<CPL, PT>(pins, pool, K, c0, a, b, s);
+        if (b - a > longseg) {
+          PoolVal<PT> mx[CPL], mn[CPL];
+          const int64_t row = 2 * int64_t(a / longseg);
+          load_cols<CPL, PT>(ext, row, K, c0, mx);
+          load_cols<CPL, PT>(ext, row + 1, K, c0, mn);
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) {
+            const double d = double(mx[q]) - double(mn[q]);
+            s[q] = d * d;
+          }
+        } else {
+          edge_spread<CPL, PT>(pins, pool, K, c0, a, b, s);
+        }
 #pragma unroll
         for (int q = 0; q < CPL; ++q) acc[q] = fma(we, s[q], acc[q]);
         float *out = sbuf + (e0 + grp + int64_t(ngrp) * (k0 + k)) * K + c0;
@@ -166,15 +270,15 @@ k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       }
     }
   }
-  for (int g = 0; g < ngrp; ++g) {
-    if (grp == g && c0 < K) {
+  // the groups' sums, added in group order
 #pragma unroll
-      for (int q = 0; q < CPL; ++q)
-        if (c0 + q < K) comb[c0 + q] = (g == 0) ? acc[q] : comb[c0 + q] + acc[q];
-    }
-    __syncthreads();
+  for (int q = 0; q < CPL; ++q) comb[grp * LPR * CPL + c0 + q] = acc[q];
+  __syncthreads();
+  for (int c = tid; c < K; c += kThreads) {
+    double t = comb[c];
+    for (int g = 1; g < ngrp; ++g) t = t + comb[g * LPR * CPL + c];
+    partial[blk * K + c] = t;
   }
-  for (int c = tid; c < K; c += kThreads) partial[blk * K + c] = comb[c];
 }
 
 // R_e = max_i s_e^(i) / Q_H^(i) from the stored numerators: LPR lanes per
@@ -228,13 +332,18 @@ int lanes_for(int K, int CPL) {
 }
 
 template <int CPL, int PT>
-hef_status score_t(const Level &L, const void *pool, int K, double *qh, float *R,
-                   double *partial, float *sbuf, int64_t nblk, hipStream_t s) {
+hef_status score_t(const Level &L, const Structure &st, const void *pool, int K, double *qh,
+                   float *R, double *partial, float *sbuf, int64_t nblk, int longseg, void *ext,
+                   hipStream_t s) {
   const int LPR = lanes_for(K, CPL);
   {
   TimedScope ts(kStScoreQ, s);
+  const int nlong = int(std::min<int64_t>(L.nnz / longseg, 2048));
+  if (nlong > 0)
+    k_score_long<CPL, PT><<<nlong, kLongThreads, 0, s>>>(st.big_e, st.n_big, L.eptr, L.pins,
+                                                         pool, K, LPR, longseg, ext);
   k_score_qh<CPL, PT><<<nblk, kThreads, 0, s>>>(L.eptr, L.pins, L.w, pool, K, LPR, L.m, partial,
-                                                sbuf);
+                                                sbuf, longseg, ext);
   HEF_LAUNCH_CHECK();
   }
   {
@@ -256,8 +365,8 @@ size_t score_ws_bytes(int64_t m, int K) {
   return a.mark();
 }
 
-hef_status score_pool(const Level &L, const void *pool, int pool_type, int K, double *qh,
-                      float *R, Arena &ws, hipStream_t s, float *keep_s) {
+hef_status score_pool(const Level &L, const Structure &st, const void *pool, int pool_type, int K,
+                      double *qh, float *R, void *ext, Arena &ws, hipStream_t s, float *keep_s) {
   if (K > 512) return HEF_ERR_UNSUPPORTED;
   if (L.m == 0) return HEF_OK;
   const int64_t nblk = cdiv(L.m, kEdgesPerBlk);
@@ -265,19 +374,24 @@ hef_status score_pool(const Level &L, const void *pool, int pool_type, int K, do
   double *partial = ws.take<double>(nblk * K);
   float *sbuf = keep_s ? keep_s : ws.take<float>(int64_t(L.m) * K);
   HEF_WS_CHECK(ws);
-  hef_status st;
+  // the shortest hyperedge taken as long: more than kSmallSeg pins (those of
+  // the structure's list), or more where nnz / longseg + 1 pairs of rows
+  // would not fit ext's oct_rows(n) rows
+  int64_t longseg = kSmallSeg;
+  while (2 * (L.nnz / longseg + 1) > oct_rows(L.n)) longseg *= 2;
+  hef_status rc;
   const bool wide = K > 256;
   if (pool_type == kPoolF32)
-    st = wide ? score_t<8, kPoolF32>(L, pool, K, qh, R, partial, sbuf, nblk, s)
-              : score_t<4, kPoolF32>(L, pool, K, qh, R, partial, sbuf, nblk, s);
+    rc = wide ? score_t<8, kPoolF32>(L, st, pool, K, qh, R, partial, sbuf, nblk, int(longseg), ext, s)
+              : score_t<4, kPoolF32>(L, st, pool, K, qh, R, partial, sbuf, nblk, int(longseg), ext, s);
   else if (pool_type == kPoolF64)
-    st = wide ? score_t<8, kPoolF64>(L, pool, K, qh, R, partial, sbuf, nblk, s)
-              : score_t<4, kPoolF64>(L, pool, K, qh, R, partial, sbuf, nblk, s);
+    rc = wide ? score_t<8, kPoolF64>(L, st, pool, K, qh, R, partial, sbuf, nblk, int(longseg), ext, s)
+              : score_t<4, kPoolF64>(L, st, pool, K, qh, R, partial, sbuf, nblk, int(longseg), ext, s);
   else
-    st = wide ? score_t<8, kPoolBF16>(L, pool, K, qh, R, partial, sbuf, nblk, s)
-              : score_t<4, kPoolBF16>(L, pool, K, qh, R, partial, sbuf, nblk, s);
+    rc = wide ? score_t<8, kPoolBF16>(L, st, pool, K, qh, R, partial, sbuf, nblk, int(longseg), ext, s)
+              : score_t<4, kPoolBF16>(L, st, pool, K, qh, R, partial, sbuf, nblk, int(longseg), ext, s);
   ws.reset(mk);
-  return st;
+  return rc;
 }
 
 }  // namespace hef

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "structure.hpp"
 
 namespace hef {
 
@@ -12,7 +13,11 @@ size_t score_ws_bytes(int64_t m, int K);
 // R[e] = max_{i: qh[i] > 0} (max - min)^2 / qh[i]  (0 if no usable column).
 // The numerators (max - min)^2 are formed as float32, m x K with row e
 // contiguous; with keep_s they are left there (caller-owned, m * K floats).
-hef_status score_pool(const Level &L, const void *pool, int pool_type, int K, double *qh,
-                      float *R, Arena &ws, hipStream_t s, float *keep_s = nullptr);
+// `ext` is scratch of oct_rows(n) x K pool values (the pool before its
+// orthonormalisation, which is done with by then): the extremes of the long
+// hyperedges.
+hef_status score_pool(const Level &L, const Structure &st, const void *pool, int pool_type, int K,
+                      double *qh, float *R, void *ext, Arena &ws, hipStream_t s,
+                      float *keep_s = nullptr);
 
 }  // namespace hef

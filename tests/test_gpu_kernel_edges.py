@@ -141,3 +141,29 @@ def test_sort_and_compaction_sizes(nnz):
         # float32 scales and terms: (degree + 4) roundings of relative 2^-24
         tol = (deg.max() + 4) * 2.0 ** -24
         assert np.abs(y - ref).max() <= tol * max(np.abs(ref).max(), 1.0)
+
+
+@pytest.mark.parametrize("k,b,basis", [(4, 1, "fp32"), (5, 2, "bf16"), (17, 8, "fp32"),
+                                       (9, 4, "fp64")])
+@pytest.mark.parametrize("nodes", ["many", "few"])
+def test_long_hyperedge_ratios(k, b, basis, nodes):
+    """Hyperedges of 32, 33, 64, 65 and 700 pins, first and last among them,
+    side by side; with few nodes per pin only longer ones go to the separate
+    pass.  Q_H and R of the returned pool against float64 on that pool: the
+    maxima are exact, a float64 sum of m terms is within m 2^-53 of any other
+    order, R carries one float32 rounding of the numerator and one of the
+    ratio."""
+    from oracle import resistance as orr
+    say(f"case: long hyperedges k={k} b={b} {basis} {nodes}")
+    n = 3000 if nodes == "many" else 710
+    sizes = [700, 33, 32, 65, 64] + _mixed_sizes(900, 3) + [40, 300, 33]
+    sizes += [] if nodes == "many" else [60] * 300
+    h = _hg(n, sizes, 9, np.random.default_rng(1).uniform(0.5, 2, len(sizes)).astype(np.float32))
+    R, qh, chi = hef.resistance(to_device(h), hef.Params(k=k, b=b, basis=basis), return_pool=True)
+    c = chi.cpu().double().numpy()
+    s = orr.edge_spread(h.eptr, h.pins, c)
+    q = h.w.astype(np.float64) @ s
+    qg = qh.cpu().numpy()
+    assert np.abs(qg - q).max() <= 2 * h.m * 2.0 ** -53 * q.max()
+    ref = (s / q[None, :]).max(1)
+    np.testing.assert_allclose(R.cpu().numpy(), ref, rtol=2.0 ** -22, atol=0)
