@@ -364,6 +364,28 @@ struct ApplyPair {
   int64_t nb0;
 };
 
+// The 8 rows of one (octet, column) of the pool, as float32, bfloat16 or, for
+// the float64 debug basis, float64.
+__device__ __forceinline__ void pool_store8(void *pool, int pool_type, int64_t off,
+                                            const float (&v)[8]) {
+  if (pool_type == kPoolF32) {
+    float4 *pp = reinterpret_cast<float4 *>(reinterpret_cast<float *>(pool) + off);
+    pp[0] = make_float4(v[0], v[1], v[2], v[3]);
+    pp[1] = make_float4(v[4], v[5], v[6], v[7]);
+  } else if (pool_type == kPoolF64) {
+    double2 *pp = reinterpret_cast<double2 *>(reinterpret_cast<double *>(pool) + off);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) pp[q] = make_double2(double(v[2 * q]), double(v[2 * q + 1]));
+  } else {
+    uint32_t wv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      wv[q] = uint32_t(f2bf(v[2 * q])) | (uint32_t(f2bf(v[2 * q + 1])) << 16);
+    *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(pool) + off) =
+        make_uint4(wv[0], wv[1], wv[2], wv[3]);
+  }
+}
+
 template <int B>
 __global__ void __launch_bounds__(256)
 k_lapply(const ApplyPair P, void *__restrict__ pool, int pool_type, int64_t pool_rows, int K) {
@@ -473,22 +495,132 @@ k_lapply(const ApplyPair P, void *__restrict__ pool, int pool_type, int64_t pool
       for (int u = 0; u < 8; ++u)
         v[u] = (8 * o + u < nrow && gr0 + u < pool_rows) ? sm[0][(8 * o + u) * LDR + c] : 0.0f;
       const int64_t off = ((gr0 >> 3) * K + col0 + c) * 8;
-      if (pool_type == kPoolF32) {
-        float4 *pp = reinterpret_cast<float4 *>(reinterpret_cast<float *>(pool) + off);
-        pp[0] = make_float4(v[0], v[1], v[2], v[3]);
-        pp[1] = make_float4(v[4], v[5], v[6], v[7]);
-      } else if (pool_type == kPoolF64) {
-        double2 *pp = reinterpret_cast<double2 *>(reinterpret_cast<double *>(pool) + off);
+      pool_store8(pool, pool_type, off, v);
+    }
+  }
+}
+
+// k_lapply for both expansions when the product with A comes next: a
+// workgroup takes RB / 2 node rows of both expansions, or RB hyperedge rows
+// of the star expansion, and the node workgroups also write the next
+// product's gather rows U[p] = [s_p x_V[p] | s_p x_c[p]] (spmm.hip).  A node
+// row's halves meet in one workgroup, so U leaves in whole 128-byte lines
+// (from separate workgroups per expansion every line was written in two
+// parts, and the apply took 302 us instead of 157 at 2M nodes, b = 8).  The
+// prep pass, which read both blocks again, and its launch are gone.  A thread
+// holds its row of the inputs in registers and only the new rows pass through
+// LDS (the pool's octets, coalesced stores); with the inputs staged in LDS as
+// in k_lapply the kernel took 237 us.  Per step, apply + prep -> this kernel:
+// 2M nodes, b = 8, 159 + 41 -> 190 us (5.5 TB/s over its 1.05 GB: the copy
+// rate); 200k, b = 4, 9.6 + 3.7 -> 11.9 us; 20k, b = 8, 5.2 + 2.9 -> 7.8 us;
+// 2k, b = 1, 4.0 + 2.2 -> 3.5 us.  Same operations per row, same bits.
+template <int B>
+__global__ void __launch_bounds__(256)
+k_lapply_u(const ApplyPair P, int64_t n, int64_t nbn, const float *__restrict__ scale,
+           float *__restrict__ U, void *__restrict__ pool, int pool_type, int K) {
+  static_assert(B <= 8, "one thread per row");
+  constexpr int RB = 256;     // rows per workgroup (both sides counted)
+  constexpr int RN = RB / 2;  // node rows per side
+  constexpr int LDR = B + 1;  // LDS row stride (odd: no bank conflicts)
+  constexpr int CH = B < 4 ? B : 4;
+  __shared__ float sm[RB * LDR];
+  __shared__ float sc[RN];
+  const int tid = threadIdx.x;
+  // node workgroups and hyperedge workgroups each spread over the XCDs
+  const bool nodes = int64_t(blockIdx.x) < nbn;
+  const int64_t lb = nodes ? xcd_block(blockIdx.x, nbn)
+                           : xcd_block(int64_t(blockIdx.x) - nbn, int64_t(gridDim.x) - nbn);
+  const int64_t row0 = nodes ? lb * RN : n + lb * RB;
+  const int64_t rend = nodes ? n : P.s[0].rows;
+  const int cap = nodes ? RN : RB;
+  const int nrow = int(rend - row0 < cap ? rend - row0 : cap);
+  const int sides = nodes ? 2 : 1;
+  if (nodes && tid < nrow) sc[tid] = scale[row0 + tid];
+  // (a wave's rows lie on one side, so its T is uniform: scalar loads)
+  const int side = __builtin_amdgcn_readfirstlane(nodes ? tid / RN : 0);
+  const int rr = nodes ? tid % RN : tid;
+  const ApplySide &S = side ? P.s[1] : P.s[0];
+  // a thread reads its row of the three inputs straight into registers
+  float x[3][B];
+  const int64_t row = row0 + (rr < nrow ? rr : nrow - 1);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) pp[q] = make_double2(double(v[2 * q]), double(v[2 * q + 1]));
-      } else {
-        uint32_t wv[4];
+  for (int a = 0; a < 3; ++a) {
+    const float *src = a == 0 ? S.v0 : a == 1 ? S.v1 : S.y;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          wv[q] = uint32_t(f2bf(v[2 * q])) | (uint32_t(f2bf(v[2 * q + 1])) << 16);
-        *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(pool) + off) =
-            make_uint4(wv[0], wv[1], wv[2], wv[3]);
+    for (int u = 0; u < B; ++u) x[a][u] = 0.0f;
+    if (src != nullptr) {
+#pragma unroll
+      for (int u = 0; u < B; u += CH) {
+        float t[CH];
+        ld<CH>(src + row * B + u, t);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) x[a][u + c] = t[c];
       }
+    }
+  }
+  {
+    double out[B];
+#pragma unroll
+    for (int c = 0; c < B; ++c) out[c] = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if ((a == 0 && S.v0 == nullptr) || (a == 1 && S.v1 == nullptr)) continue;
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const double md = double(x[a][u]);
+        const double *trow = S.T + (a * B + u) * B;
+#pragma unroll
+        for (int c = 0; c < B; ++c) out[c] = fma(md, trow[c], out[c]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < B; ++c) sm[tid * LDR + c] = float(out[c]);
+  }
+  __syncthreads();
+  // coalesced stores of the new rows, the gather rows, the pool columns
+  for (int q = 0; q < sides; ++q) {
+    float *vbase = (q ? P.s[1].vn : P.s[0].vn) + row0 * B;
+    const float *o = sm + q * RN * LDR;
+    if constexpr (B >= 4) {
+      for (int i = tid; i < nrow * B / 4; i += 256) {
+        const float *d = o + (4 * i / B) * LDR + (4 * i) % B;
+        reinterpret_cast<float4 *>(vbase)[i] = make_float4(d[0], d[1], d[2], d[3]);
+      }
+    } else {
+      for (int i = tid; i < nrow * B; i += 256) vbase[i] = o[(i / B) * LDR + i % B];
+    }
+  }
+  if (!nodes) return;
+  if (U) {
+    float *ub = U + row0 * 2 * B;
+    if constexpr (B >= 4) {
+      for (int i = tid; i < nrow * B / 2; i += 256) {
+        const int q = i / (B / 2), f = 4 * (i % (B / 2));  // row, first column of 2 B
+        const float *d = sm + ((f / B) * RN + q) * LDR + f % B;
+        const float g = sc[q];
+        reinterpret_cast<float4 *>(ub)[i] =
+            make_float4(d[0] * g, d[1] * g, d[2] * g, d[3] * g);
+      }
+    } else {
+      for (int i = tid; i < nrow * 2 * B; i += 256) {
+        const int q = i / (2 * B), f = i % (2 * B);
+        ub[i] = sm[((f / B) * RN + q) * LDR + f % B] * sc[q];
+      }
+    }
+  }
+  if (pool) {
+    // row-octet layout: per (octet, column) 8 consecutive values; rows past n
+    // are zero (row0 is a multiple of 8)
+    const int noct = (nrow + 7) / 8;
+    for (int i = tid; i < 2 * noct * B; i += 256) {
+      const int q = i / (noct * B), k = i % (noct * B);
+      const int o = k / B, c = k % B;
+      const float *d = sm + q * RN * LDR + c;
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = 8 * o + u < nrow ? d[(8 * o + u) * LDR] : 0.0f;
+      const int col = (q ? P.s[1].col0 : P.s[0].col0) + c;
+      pool_store8(pool, pool_type, (((row0 >> 3) + o) * K + col) * 8, v);
     }
   }
 }
@@ -527,6 +659,35 @@ hef_status apply_t(const ApplySide &a, const ApplySide &b, void *pool, int pool_
   k_lapply<B><<<nblk, 256, 0, s>>>(P, pool, pool_type, pool_rows, K);
   HEF_LAUNCH_CHECK();
   return HEF_OK;
+}
+
+// Both expansions of n node rows (a: star with n + m rows, b: clique) with
+// the next product's gather rows.
+template <int B>
+hef_status apply_u_t(const ApplySide &a, const ApplySide &b, const float *scale, float *U,
+                     void *pool, int pool_type, int K, hipStream_t s) {
+  ApplyPair P;
+  P.s[0] = a;
+  P.s[1] = b;
+  P.nb0 = 0;
+  const int64_t n = b.rows, nbn = cdiv(n, 128);
+  const int64_t nblk = nbn + cdiv(a.rows - n, 256);
+  if (nblk == 0) return HEF_OK;
+  TimedScope ts(kStLanczosApply, s);
+  k_lapply_u<B><<<nblk, 256, 0, s>>>(P, n, nbn, scale, U, pool, pool_type, K);
+  HEF_LAUNCH_CHECK();
+  return HEF_OK;
+}
+
+hef_status lapply_u(int B, const ApplySide &a, const ApplySide &b, const float *scale, float *U,
+                    void *pool, int pool_type, int K, hipStream_t s) {
+  switch (B) {
+    case 1: return apply_u_t<1>(a, b, scale, U, pool, pool_type, K, s);
+    case 2: return apply_u_t<2>(a, b, scale, U, pool, pool_type, K, s);
+    case 4: return apply_u_t<4>(a, b, scale, U, pool, pool_type, K, s);
+    case 8: return apply_u_t<8>(a, b, scale, U, pool, pool_type, K, s);
+    default: return HEF_ERR_UNSUPPORTED;
+  }
 }
 
 hef_status lapply2(int B, const ApplySide &a, const ApplySide &b, void *pool, int pool_type,
@@ -703,6 +864,13 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
   const size_t scr = spmm_scratch_floats(n, m, B);
   const int K = out.K;
   const int64_t bk = int64_t(B) * k;
+  // step j's SpMM scratch; with both expansions the apply before the step
+  // fills its gather rows U
+  // (b = 16 keeps the prep pass: k_lapply_u would hold 48 inputs a row and,
+  // at 174 registers, 2 waves per SIMD)
+  const bool both = use_star && use_clique && B <= 8;
+  auto t_scr = [&](int j) { return full ? tape->t + size_t(j - 1) * scr : tb; };
+  auto u_of = [&](int j) { return t_scr(j) + spmm_u_offset(m, B); };
   // V_0 = X R^-1 (no pool write)
   if (use_star)
     HEF_HIP(hipMemcpyAsync(sb[2], start_star, Ns * B * sizeof(float), hipMemcpyDeviceToDevice, s));
@@ -717,7 +885,10 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
   {
     const ApplySide as{nullptr, nullptr, sb[2], t_of(0), sb[3], use_star ? Ns : 0, 0};
     const ApplySide ac{nullptr, nullptr, cb[2], t_of(0) + C * B, cb[3], use_clique ? n : 0, 0};
-    HEF_TRY(lapply2(B, as, ac, nullptr, 0, 0, K, s));
+    if (both)
+      HEF_TRY(lapply_u(B, as, ac, st.s, u_of(1), nullptr, 0, K, s));
+    else
+      HEF_TRY(lapply2(B, as, ac, nullptr, 0, 0, K, s));
   }
   HEF_TRY(checkpoint(0, nullptr, sb[3], nullptr, cb[3]));
   float *sp = nullptr, *sc = sb[3], *cp = nullptr, *cc = cb[3];  // prev (absent), cur
@@ -730,9 +901,8 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
   for (int j = 1; j <= k; ++j) {
     float *sy = full ? tape->y_s + size_t(j - 1) * Ns * B : sb[2];
     float *cy = full ? tape->y_c + size_t(j - 1) * n * B : cb[2];
-    float *tj = full ? tape->t + size_t(j - 1) * scr : tb;
     HEF_TRY(spmm_apply(L, st, B, use_star ? sc : nullptr, use_star ? sy : nullptr,
-                       use_clique ? cc : nullptr, use_clique ? cy : nullptr, tj, s));
+                       use_clique ? cc : nullptr, use_clique ? cy : nullptr, t_scr(j), s, both));
     HEF_TRY(lgram2(B, sp, sc, use_star ? sy : nullptr, Ns, ps, Gs, cp, cc,
                    use_clique ? cy : nullptr, n, pc, Gc, s));
     double *Tj = t_of(j);
@@ -750,7 +920,11 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
     {
       const ApplySide as{sp, sc, sy, Tj, sn, use_star ? Ns : 0, int(col_s)};
       const ApplySide ac{cp, cc, cy, Tj + C * B, cn, use_clique ? n : 0, int(col_c)};
-      HEF_TRY(lapply2(B, as, ac, out.pool, out.pool_type, n, K, s));
+      if (both)
+        HEF_TRY(lapply_u(B, as, ac, st.s, j < k ? u_of(j + 1) : nullptr, out.pool, out.pool_type,
+                         K, s));
+      else
+        HEF_TRY(lapply2(B, as, ac, out.pool, out.pool_type, n, K, s));
     }
     HEF_TRY(checkpoint(j, sc, sn, cc, cn));
     sp = sc;

@@ -25,8 +25,11 @@ struct Blocks {
 // U (n x 2B, [s_p x_V | s_p x_c]); after the call T_e is at
 // scratch[e * 2B + B + c].  Either expansion may be skipped (null pointers).
 inline int64_t spmm_scratch_floats(int64_t n, int64_t m, int B) { return 2 * int64_t(B) * (n + m); }
+// With u_ready U (at spmm_u_offset) is already filled.
+inline int64_t spmm_u_offset(int64_t m, int B) { return 2 * int64_t(B) * m; }
 hef_status spmm_apply(const Level &L, const Structure &st, int B, const float *xs,
-                      float *ys, const float *xc, float *yc, float *scratch, hipStream_t s);
+                      float *ys, const float *xc, float *yc, float *scratch, hipStream_t s,
+                      bool u_ready = false);
 
 // Pool column storage.
 enum PoolType { kPoolF32 = 0, kPoolBF16 = 1, kPoolF64 = 2 };

@@ -4,7 +4,8 @@
 // is materialised: a CSR pass over hyperedges gathers node rows, a CSC pass
 // over nodes gathers hyperedge rows.  Both passes gather one interleaved
 // row of 2B floats per incidence: U[p] = [s_p x_V[p] | s_p x_c[p]] (scaled
-// node rows, written by a short prep pass) and W[e] = [alpha_e x_E[e] | T_e]
+// node rows, written by the Lanczos apply of the step before, or by a short
+// prep pass where a caller has none) and W[e] = [alpha_e x_E[e] | T_e]
 // (written by the CSR pass), so each incidence costs one 8B-byte gather and
 // no scale gathers.  Segments up to kSmallSeg go to lane groups (2B/CH
 // lanes per segment, one lane per CH-float chunk of a row); longer segments
@@ -402,16 +403,16 @@ static_assert(kBigGrid % 8 == 0, "the XCD of a workgroup must not depend on its 
 
 template <int B>
 hef_status spmm_t(const Level &L, const Structure &st, const float *xs, float *ys,
-                  const float *xc, float *yc, float *scratch, hipStream_t s) {
+                  const float *xc, float *yc, float *scratch, hipStream_t s, bool u_ready) {
   using G = Geo<B>;
   const int64_t n = L.n, m = L.m;
   const float *xE = xs ? xs + n * B : nullptr;
   float *yE = ys ? ys + n * B : nullptr;
   float *W = scratch;
-  float *U = scratch + m * G::RW;
+  float *U = scratch + spmm_u_offset(m, B);
   const int on = (xs ? 1 : 0) | (xc ? 2 : 0);
   TimedScope step(kStSpmmStep, s);
-  if (n > 0) {
+  if (n > 0 && !u_ready) {
     TimedScope ts(kStSpmmPrep, s);
     k_prep<B><<<cdiv(n * G::LPS, kThreads), kThreads, 0, s>>>(n, st.s, xs, xc, U);
     HEF_LAUNCH_CHECK();
@@ -436,13 +437,14 @@ hef_status spmm_t(const Level &L, const Structure &st, const float *xs, float *y
 }  // namespace
 
 hef_status spmm_apply(const Level &L, const Structure &st, int B, const float *xs, float *ys,
-                      const float *xc, float *yc, float *scratch, hipStream_t s) {
+                      const float *xc, float *yc, float *scratch, hipStream_t s,
+                      bool u_ready) {
   switch (B) {
-    case 1: return spmm_t<1>(L, st, xs, ys, xc, yc, scratch, s);
-    case 2: return spmm_t<2>(L, st, xs, ys, xc, yc, scratch, s);
-    case 4: return spmm_t<4>(L, st, xs, ys, xc, yc, scratch, s);
-    case 8: return spmm_t<8>(L, st, xs, ys, xc, yc, scratch, s);
-    case 16: return spmm_t<16>(L, st, xs, ys, xc, yc, scratch, s);
+    case 1: return spmm_t<1>(L, st, xs, ys, xc, yc, scratch, s, u_ready);
+    case 2: return spmm_t<2>(L, st, xs, ys, xc, yc, scratch, s, u_ready);
+    case 4: return spmm_t<4>(L, st, xs, ys, xc, yc, scratch, s, u_ready);
+    case 8: return spmm_t<8>(L, st, xs, ys, xc, yc, scratch, s, u_ready);
+    case 16: return spmm_t<16>(L, st, xs, ys, xc, yc, scratch, s, u_ready);
     default: set_error("block width %d is not a power of two in 1..16", B);
              return HEF_ERR_UNSUPPORTED;
   }

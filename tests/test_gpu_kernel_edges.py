@@ -167,3 +167,29 @@ def test_long_hyperedge_ratios(k, b, basis, nodes):
     assert np.abs(qg - q).max() <= 2 * h.m * 2.0 ** -53 * q.max()
     ref = (s / q[None, :]).max(1)
     np.testing.assert_allclose(R.cpu().numpy(), ref, rtol=2.0 ** -22, atol=0)
+
+
+@pytest.mark.parametrize("b", [1, 2, 4, 8])
+@pytest.mark.parametrize("n,m", [(127, 255), (128, 256), (129, 257), (300, 20)])
+def test_krylov_step_at_workgroup_edges(b, n, m):
+    """The Lanczos apply takes 128 node rows of both expansions or 256
+    hyperedge rows per workgroup and hands the next product its gather rows:
+    the estimate against the oracle at the edges of both, and against the
+    single-expansion passes' columns (which keep the separate prep pass)."""
+    from oracle import resistance as orr
+    from tests.gpu_common import r_errors, starts
+    k = 3
+    say(f"case: krylov step n={n} m={m} b={b}")
+    h = _hg(n, _mixed_sizes(m, n + m), n)
+    Xs, Xc, xs, xc = starts(h, b)
+    est = orr.resistance(h.n, h.m, h.eptr, h.pins, h.w, Xs, Xc, k)
+    R, qh, _ = hef.resistance(to_device(h), hef.Params(k=k, b=b), xs, xc)
+    norm, p999, _ = r_errors(R.cpu().numpy(), est.R)
+    assert norm <= 1e-4 and p999 <= 1e-4
+    star = hef.resistance(to_device(h), hef.Params(k=k, b=b, star_only=True), xs, None,
+                          return_pool=True)[2] if b * k > 4 else None
+    both = hef.resistance(to_device(h), hef.Params(k=k, b=b), xs, xc, return_pool=True)[2]
+    # the star columns come first in the joint Gram-Schmidt
+    if star is not None:
+        d = (both[:, :k * b] - star).abs().max().item()
+        assert d <= 1e-6
