@@ -189,49 +189,26 @@ k_lgram(const GramPair P) {
   }
 }
 
-// G = the column sums of the partials (float64: 32 row lanes of eight
-// accumulators each, then a fixed tree), written for the entries in blocks
-// on or above the diagonal and mirrored into the blocks below it.
-// 256 threads = 8 columns x 32 row lanes.
-// Two expansions per launch: workgroups [0, nbh) reduce (in0, nrows0) into
-// G0, the rest (in1, nrows1) into G1.
-__global__ void __launch_bounds__(256)
+// G = the column sums of the partials (float64, ColSum's order), written for
+// the entries in blocks on or above the diagonal and mirrored into the blocks
+// below it.  Two expansions per launch: workgroups [0, nbh) reduce (in0,
+// nrows0) into G0, the rest (in1, nrows1) into G1.
+__global__ void __launch_bounds__(1024)
 k_gram_reduce(const double *__restrict__ in0, int64_t nrows0, double *__restrict__ G0,
               const double *__restrict__ in1, int64_t nrows1, double *__restrict__ G1, int nbh,
               int C, int S) {
-  __shared__ double red[32][9];
+  __shared__ double red[ColSum<4>::kLds];
   const bool second = int(blockIdx.x) >= nbh;
   const double *__restrict__ in = second ? in1 : in0;
   const int64_t nrows = second ? nrows1 : nrows0;
   double *__restrict__ G = second ? G1 : G0;
-  const int cl = threadIdx.x & 7, rl = threadIdx.x >> 3;
-  const int64_t c = int64_t(int(blockIdx.x) - (second ? nbh : 0)) * 8 + cl;
-  const int64_t ncols = int64_t(C) * C;
-  const int i = int(c / C), j = int(c % C);
-  const bool upper = c < ncols && i / S <= j / S;
-  double acc[8] = {};
-  if (upper) {
-    int64_t r = rl;
-    for (; r + 7 * 32 < nrows; r += 8 * 32) {
-      double t[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) t[q] = in[(r + 32 * q) * ncols + c];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] += t[q];
-    }
-#pragma unroll
-    for (int q = 0; q < 7; ++q)
-      if (r + 32 * q < nrows) acc[q] += in[(r + 32 * q) * ncols + c];
-  }
-  red[rl][cl] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-  __syncthreads();
-  for (int off = 16; off > 0; off >>= 1) {
-    if (rl < off) red[rl][cl] += red[rl + off][cl];
-    __syncthreads();
-  }
-  if (rl == 0 && upper) {
-    G[int64_t(i) * C + j] = red[0][cl];
-    if (i / S < j / S) G[int64_t(j) * C + i] = red[0][cl];
+  const int c = (int(blockIdx.x) - (second ? nbh : 0)) * 8 + int(threadIdx.x & 7);
+  const int i = c / C, j = c % C;
+  const bool upper = c < C * C && i / S <= j / S;
+  const double t = ColSum<4>::run(in, nrows, int64_t(C) * C, c, upper, red);
+  if (threadIdx.x < 8 && upper) {
+    G[int64_t(i) * C + j] = t;
+    if (i / S < j / S) G[int64_t(j) * C + i] = t;
   }
 }
 
@@ -745,11 +722,11 @@ hef_status lgram2(int B, const float *v0a, const float *v1a, const float *ya, in
   TimedScope ts(kStLanczosReduce, s);
   const int nbh = int(cdiv(int64_t(C) * C, 8));
   if (nb[0] > 0 && nb[1] > 0)
-    k_gram_reduce<<<2 * nbh, 256, 0, s>>>(partiala, nb[0], Ga, partialb, nb[1], Gb, nbh, C, S);
+    k_gram_reduce<<<2 * nbh, 1024, 0, s>>>(partiala, nb[0], Ga, partialb, nb[1], Gb, nbh, C, S);
   else if (nb[0] > 0)
-    k_gram_reduce<<<nbh, 256, 0, s>>>(partiala, nb[0], Ga, nullptr, 0, nullptr, nbh, C, S);
+    k_gram_reduce<<<nbh, 1024, 0, s>>>(partiala, nb[0], Ga, nullptr, 0, nullptr, nbh, C, S);
   else
-    k_gram_reduce<<<nbh, 256, 0, s>>>(partialb, nb[1], Gb, nullptr, 0, nullptr, nbh, C, S);
+    k_gram_reduce<<<nbh, 1024, 0, s>>>(partialb, nb[1], Gb, nullptr, 0, nullptr, nbh, C, S);
   HEF_LAUNCH_CHECK();
   return HEF_OK;
 }

@@ -416,41 +416,20 @@ __global__ void k_compact(const int32_t *flag, const int32_t *pos, int32_t *idx_
   if (i == 0) *count_dev = pos[n];
 }
 
-// 256 threads = 8 columns x 32 row lanes.
-__global__ void __launch_bounds__(256)
+template <int QG>
+__global__ void __launch_bounds__(256 * QG)
 k_reduce_cols(const double *__restrict__ in0, int64_t nrows0, double *__restrict__ out0,
               const double *__restrict__ in1, int64_t nrows1, double *__restrict__ out1,
               int64_t nbc, int64_t ncols) {
-  __shared__ double red[32][9];
+  __shared__ double red[ColSum<QG>::kLds];
   // workgroups [0, nbc) reduce side 0, the rest side 1
   const bool second = int64_t(blockIdx.x) >= nbc;
   const double *__restrict__ in = second ? in1 : in0;
   const int64_t nrows = second ? nrows1 : nrows0;
   double *__restrict__ out = second ? out1 : out0;
-  const int cl = threadIdx.x & 7, rl = threadIdx.x >> 3;
-  const int64_t c = (int64_t(blockIdx.x) - (second ? nbc : 0)) * 8 + cl;
-  // eight independent loads in flight per row lane
-  double acc[8] = {};
-  if (c < ncols) {
-    int64_t r = rl;
-    for (; r + 7 * 32 < nrows; r += 8 * 32) {
-      double t[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) t[q] = in[(r + 32 * q) * ncols + c];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] += t[q];
-    }
-#pragma unroll
-    for (int q = 0; q < 7; ++q)
-      if (r + 32 * q < nrows) acc[q] += in[(r + 32 * q) * ncols + c];
-  }
-  red[rl][cl] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-  __syncthreads();
-  for (int off = 16; off > 0; off >>= 1) {
-    if (rl < off) red[rl][cl] += red[rl + off][cl];
-    __syncthreads();
-  }
-  if (rl == 0 && c < ncols) out[c] = red[0][cl];
+  const int64_t c = (int64_t(blockIdx.x) - (second ? nbc : 0)) * 8 + (threadIdx.x & 7);
+  const double t = ColSum<QG>::run(in, nrows, ncols, c, c < ncols, red);
+  if (threadIdx.x < 8 && c < ncols) out[c] = t;
 }
 
 // 4-byte words when the pointer and the size allow it, else bytes.
@@ -481,23 +460,31 @@ hef_status zero_async(void *p, size_t bytes, hipStream_t s) {
   return HEF_OK;
 }
 
-hef_status reduce_cols_f64(const double *in, int64_t nrows, int64_t ncols, double *out,
-                           hipStream_t s) {
-  if (ncols <= 0) return HEF_OK;
-  k_reduce_cols<<<cdiv(ncols, 8), 256, 0, s>>>(in, nrows, out, nullptr, 0, nullptr,
-                                                cdiv(ncols, 8), ncols);
-  HEF_LAUNCH_CHECK();
-  return HEF_OK;
-}
+// With few columns there are few workgroups (8 columns each), and the rows
+// are split over four times the threads; from kWideCols columns on the
+// workgroups fill the chip and hold few rows each.  200k nodes, b = 4: the
+// 1.6k x 48 step products of the adjoint 10.7 -> 4.8 us, the Lanczos Gram's
+// 0.9k x 144 partials (k_gram_reduce) 5.4 -> 4.0 us; 2M nodes, b = 8: the
+// Gram's 1k x 576 partials 7.1 -> 4.8 us, the 17k x 480 Q_H partials 48 -> 45
+// us (60 workgroups: bound by their number).
+constexpr int64_t kWideCols = 8192;
 
 hef_status reduce_cols_f64_pair(const double *in0, int64_t nrows0, double *out0,
                                 const double *in1, int64_t nrows1, double *out1, int64_t ncols,
                                 hipStream_t s) {
   if (ncols <= 0) return HEF_OK;
-  const int64_t nbc = cdiv(ncols, 8);
-  k_reduce_cols<<<2 * nbc, 256, 0, s>>>(in0, nrows0, out0, in1, nrows1, out1, nbc, ncols);
+  const int64_t nbc = cdiv(ncols, 8), nb = out1 ? 2 * nbc : nbc;
+  if (ncols < kWideCols)
+    k_reduce_cols<4><<<nb, 1024, 0, s>>>(in0, nrows0, out0, in1, nrows1, out1, nbc, ncols);
+  else
+    k_reduce_cols<1><<<nb, 256, 0, s>>>(in0, nrows0, out0, in1, nrows1, out1, nbc, ncols);
   HEF_LAUNCH_CHECK();
   return HEF_OK;
+}
+
+hef_status reduce_cols_f64(const double *in, int64_t nrows, int64_t ncols, double *out,
+                           hipStream_t s) {
+  return reduce_cols_f64_pair(in, nrows, out, nullptr, 0, nullptr, ncols, s);
 }
 
 size_t scan_ws_bytes(int64_t n) {

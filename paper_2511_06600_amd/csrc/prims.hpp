@@ -44,6 +44,63 @@ hef_status reduce_cols_f64_pair(const double *in0, int64_t nrows0, double *out0,
                                 const double *in1, int64_t nrows1, double *out1, int64_t ncols,
                                 hipStream_t s);
 
+// The column sums above for a workgroup of 256 QG threads on 8 columns: thread
+// (column, row lane l < 32, part < QG) adds the rows l + 32 (8 i + q) of its
+// 8 / QG accumulators q, i ascending, eight loads in flight; the accumulators
+// are added pairwise and the row lanes by halves, so every QG gives the same
+// bits.  `ok`: the thread's column c is inside.  The sums are returned on
+// threads 0 .. 7.
+template <int QG>
+struct ColSum {
+  static constexpr int kLds = 32 * 9 * QG;
+  static constexpr int kQ = 8 / QG;  // accumulators per thread
+  static __device__ __forceinline__ double run(const double *__restrict__ in, int64_t nrows,
+                                               int64_t ncols, int64_t c, bool ok, double *red) {
+    constexpr int kI = QG;  // row groups per round
+    const int cl = threadIdx.x & 7, rl = (threadIdx.x >> 3) & 31, part = threadIdx.x >> 8;
+    double acc[kQ] = {};
+    if (ok) {
+      for (int64_t r = rl + 32 * kQ * part; r < nrows; r += 256 * kI) {
+        double t[kI][kQ];
+#pragma unroll
+        for (int i = 0; i < kI; ++i)
+#pragma unroll
+          for (int q = 0; q < kQ; ++q) {
+            const int64_t rr = r + 256 * i + 32 * q;
+            t[i][q] = in[(rr < nrows ? rr : r) * ncols + c];
+          }
+#pragma unroll
+        for (int i = 0; i < kI; ++i)
+#pragma unroll
+          for (int q = 0; q < kQ; ++q)
+            if (r + 256 * i + 32 * q < nrows) acc[q] += t[i][q];
+      }
+    }
+    double v = 0.0;
+    if constexpr (QG == 1) v = ((acc[0] + acc[1]) + (acc[2] + acc[3])) +
+                               ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    else v = acc[0] + acc[1];
+    static_assert(QG == 1 || QG == 4, "parts");
+    red[(part * 32 + rl) * 9 + cl] = v;
+    __syncthreads();
+    double x = 0.0;
+    if (threadIdx.x < 64) {
+      // lane (column, k < 8) takes row lanes k, k + 8, k + 16, k + 24
+      double y[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int at = ((threadIdx.x >> 3) + 8 * k) * 9 + cl;
+        if constexpr (QG == 1) y[k] = red[at];
+        else y[k] = (red[at] + red[32 * 9 + at]) + (red[2 * 32 * 9 + at] + red[3 * 32 * 9 + at]);
+      }
+      x = (y[0] + y[2]) + (y[1] + y[3]);
+#pragma unroll
+      for (int off = 32; off >= 8; off >>= 1) x += __shfl_down(x, off, 64);
+    }
+    return x;
+  }
+};
+
 // Zeroes `bytes` bytes at p on stream s with a fill kernel rather than
 // hipMemsetAsync, so that a caller capturing the stream into a HIP graph
 // records kernel nodes only.
