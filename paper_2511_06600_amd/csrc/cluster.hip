@@ -306,28 +306,32 @@ k_cperm(const int32_t *__restrict__ prov, const int32_t *__restrict__ owner,
   }
 }
 
-// Bounds of one column's term (x - c)^2 / Q_H from the float16 copy h of c:
-// |h - c| <= 2^-10 |h| + 2^-24 (float16 rounding of the float32 rounding of
-// c, subnormals included; |c| <= 1 for an orthonormal basis; the factor
-// 2^-10 is twice the rounding bound, which leaves room for the float32
-// rounding below), so |x - c| sqrt(1 / Q_H) lies within
-// |x - h| sv -/+ (|h| e1 + e0) with sv = sqrt(1 / Q_H), e1 = 2^-10 sv,
-// e0 = 2^-24 sv.  The running maxima lo, up over the 8 float16 values of v
-// (columns q0 .. q0+8) are kept in this square-root scale; their squares
-// bound the term from below and above to within a relative 1e-6.
-__device__ __forceinline__ void bounds16_8(const uint4 v, const float *xs, const float *sv,
-                                           const float *e1, const float *e0, int q0, float &lo,
-                                           float &up) {
-  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+// The screen of one candidate: z = max_i |x_i - h_i| sv_i with h the float16
+// copy of the centroid c and sv = sqrt(1 / Q_H), over the columns met so far.
+// |h - c| <= 2^-10 |h| + 2^-24 (float16 rounding of the float32 rounding of c,
+// subnormals included; the factor 2^-10 is twice the rounding bound, which
+// leaves room for the float32 roundings here), and |h| <= |x| + |x - h|, so
+// with t = max_i sv_i (2^-10 |x_i| + 2^-24), one number per node p,
+//   kLoScale z - t  <=  max_i |x_i - c_i| sv_i  <=  kHiScale z + t
+// (the right side once all columns are in).  Distances are of the order of
+// |x| sv in every column (Q_H scales them), so a common t costs little: the
+// survivors do not grow, while a column takes a mixed-precision fused
+// multiply-add and a maximum instead of an unpack, a subtraction, three
+// fused multiply-adds and two maxima, and a candidate carries one number
+// instead of two.
+constexpr float kLoScale = 1.0f - 0x1.02p-10f;
+constexpr float kHiScale = 1.0f + 0x1.02p-10f;
+
+// z over the 8 float16 values of v, columns q0 .. q0+8; xv = x sv, nv = -sv
+__device__ __forceinline__ void screen16_8(const uint4 v, const float *xv, const float *nv, int q0,
+                                           float &z) {
+  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  const h8 h = __builtin_bit_cast(h8, v);
+  float d[8];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const uint32_t bits = (w[u >> 1] >> (16 * (u & 1))) & 0xFFFFu;
-    const float h = float(__builtin_bit_cast(_Float16, uint16_t(bits)));
-    const float a = fabsf(xs[q0 + u] - h);
-    const float es = __builtin_fmaf(fabsf(h), e1[q0 + u], e0[q0 + u]);
-    lo = fmaxf(lo, __builtin_fmaf(a, sv[q0 + u], -es));
-    up = fmaxf(up, __builtin_fmaf(a, sv[q0 + u], es));
-  }
+  for (int u = 0; u < 8; ++u) d[u] = __builtin_fmaf(float(h[u]), nv[q0 + u], xv[q0 + u]);
+#pragma unroll
+  for (int u = 0; u < 8; u += 2) z = fmaxf(z, fmaxf(fabsf(d[u]), fabsf(d[u + 1])));
 }
 
 // Exact float64 distance d(p, C) = max_i (chi_p^(i) - c_C^(i))^2 / Q_H(i)
@@ -386,14 +390,14 @@ __device__ __forceinline__ double exact_d(int32_t C, int32_t cr, int lane, const
 
 // One wave per isolated node p; its candidates are the clusters C = prov[v]
 // of the co-pins v of its hyperedges, and best(p) = (smallest exact float64
-// d(p, C), smallest label).  The wave bounds d(p, C) from float16 copies of
+// d(p, C), smallest label).  The wave screens d(p, C) from float16 copies of
 // the centroids, columns in the permuted order (largest weights first), in
-// stages over growing column ranges, each stage keeping running lower and
-// upper bounds:
+// stages over growing column ranges, each stage keeping the running z of
+// screen16_8:
 //   stage A  one lane per candidate, columns [0, 128);
 //   stage B  8 lanes per candidate, columns [128, 256);
-//   stage C  8 lanes per candidate, columns [256, Kq): the upper bound now
-//            covers every column.
+//   stage C  8 lanes per candidate, columns [256, Kq): z now covers every
+//            column and bounds the distance from above too.
 // u is the smallest complete upper bound (or exact distance) met so far.  A
 // candidate whose lower bound exceeds u (1 + 1e-5) is farther than some other
 // candidate, so it is neither the minimum nor tied with it, and is dropped
@@ -404,6 +408,10 @@ __device__ __forceinline__ double exact_d(int32_t C, int32_t cr, int lane, const
 // the exact argmin whatever the visiting order.  The first candidate batch
 // seeds u with stages B and C of its smallest stage-A bound; hyperedges of
 // at most kSeedSeg pins are visited first.
+// Bound by the float16 rows' gather latency and the screen's arithmetic: at
+// 2M nodes, K = 480, three levels, 11.9 ms; 14.2 ms with separate lower and
+// upper bounds per column.  Held to 4 waves per SIMD it spills 31 registers:
+// 14 ms.
 constexpr int kQCap = 72;   // stage-B queue: 8 + one batch of 64
 constexpr int kQ2Cap = 16;  // stage-C queue: 8 + one stage-B batch
 constexpr int kFCap = 64;   // stage-C survivors awaiting their exact distance
@@ -423,40 +431,32 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
        const float *__restrict__ inv32, const void *__restrict__ pool, int K,
        const double *__restrict__ qh, const int32_t *__restrict__ list,
        const int32_t *__restrict__ count, int32_t *__restrict__ best_label,
-       double *__restrict__ best_d) {
+       double *__restrict__ best_d, int32_t *__restrict__ pairs) {
   constexpr int NW = kBT / 64;
   // one wave per listed isolated node; workgroups past the list leave at once
   const int32_t cnt = *count;
   if (int64_t(blockIdx.x) * NW >= cnt) return;
-  __shared__ float sv[512];                // sqrt(1 / Q_H), 2^-10 and 2^-24 times
-  __shared__ float s10[512];               // it, permuted order (zero for unused
-  __shared__ float s24[512];               // columns)
+  __shared__ float nv[512];                // -sqrt(1 / Q_H), permuted order (zero for
+                                           // unused columns)
   __shared__ double qd[512];               // Q_H, column order
-  __shared__ int32_t pm[512];              // the permutation
-  __shared__ float xs_all[NW][512];        // p's row, permuted order
+  __shared__ float xv_all[NW][512];        // p's row times sqrt(1 / Q_H), permuted order
   __shared__ float xn_all[NW][512];        // p's row, column order
   __shared__ int32_t es_all[NW][kEB];      // first pin position per hyperedge (batch order)
   __shared__ int32_t ep_all[NW][kEB + 1];  // exclusive prefix of sizes
-  __shared__ int32_t qc_all[NW][kQCap];    // stage-B queue: candidate, bounds
-  __shared__ float ql_all[NW][kQCap];
-  __shared__ float qu_all[NW][kQCap];
-  __shared__ int32_t rc_all[NW][kQ2Cap];   // stage-C queue: candidate, bounds
-  __shared__ float rl_all[NW][kQ2Cap];
-  __shared__ float ru_all[NW][kQ2Cap];
-  __shared__ int32_t fc_all[NW][kFCap];    // survivors: candidate, crow, lower bound
+  __shared__ int32_t qc_all[NW][kQCap];    // stage-B queue: candidate, z
+  __shared__ float qz_all[NW][kQCap];
+  __shared__ int32_t rc_all[NW][kQ2Cap];   // stage-C queue: candidate, z
+  __shared__ float rz_all[NW][kQ2Cap];
+  __shared__ int32_t fc_all[NW][kFCap];    // survivors: candidate, crow, z
   __shared__ int32_t fr_all[NW][kFCap];
-  __shared__ float fl_all[NW][kFCap];
+  __shared__ float fz_all[NW][kFCap];
   const int w = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int g = lane >> 3, a8 = lane & 7;
   const uint64_t lt_mask = (uint64_t(1) << lane) - 1;
   for (int q = threadIdx.x; q < 512; q += kBT) {
-    const float r = sqrtf(inv32[q]);
-    sv[q] = r;
-    s10[q] = 0x1p-10f * r;
-    s24[q] = 0x1p-24f * r;
+    nv[q] = -sqrtf(inv32[q]);
     qd[q] = q < K ? qh[q] : 0.0;
-    pm[q] = perm[q];
   }
   __syncthreads();
   const int64_t i = int64_t(blockIdx.x) * NW + w;
@@ -464,25 +464,27 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   const int64_t p = list[i];
   const int32_t v0 = vptr[p], deg = vptr[p + 1] - v0;
   if (owner[p] >= 0 || deg == 0) {
-    if (lane == 0) best_label[p] = -1;
+    if (lane == 0) {
+      best_label[p] = -1;
+      pairs[i] = 0;
+    }
     return;
   }
   constexpr float kMargin = 1.0f + 1e-5f;
   constexpr float kUbScale = 1.0f + 2e-6f;
   constexpr float kUpScale = 1.0f + 1e-5f;
-  float *xs = xs_all[w];
+  float *xv = xv_all[w];
   float *xn = xn_all[w];
   int32_t *es = es_all[w];
   int32_t *ep = ep_all[w];
   int32_t *qc = qc_all[w];
-  float *ql = ql_all[w];
-  float *qu = qu_all[w];
+  float *qz = qz_all[w];
   int32_t *rc = rc_all[w];
-  float *rl = rl_all[w];
-  float *ru = ru_all[w];
+  float *rz = rz_all[w];
   int32_t *fc = fc_all[w];
   int32_t *fr = fr_all[w];
-  float *fl = fl_all[w];
+  float *fz = fz_all[w];
+  float tn = 0.0f;  // t of screen16_8
   {
     // p's row: unconditional loads (column clamped to K - 1), then selects
     float t[8];
@@ -497,9 +499,20 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int q = lane + 64 * j;
-      xs[q] = q < Kq ? xn[pm[q]] : 0.0f;
+      const float x = q < Kq ? xn[perm[q]] : 0.0f;
+      xv[q] = -x * nv[q];
+      tn = fmaxf(tn, -nv[q] * __builtin_fmaf(fabsf(x), 0x1p-10f, 0x1p-24f));
     }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) tn = fmaxf(tn, __shfl_xor(tn, off, 64));
+    // (room for the roundings of t itself and of the two uses below)
+    tn *= 1.0f + 0x1p-20f;
   }
+  // whether a candidate of screen value z lies above u
+  auto above = [&](float z, float u) __attribute__((always_inline)) {
+    const float lo = fmaxf(__builtin_fmaf(z, kLoScale, -tn), 0.0f);
+    return lo * lo > u;
+  };
   const int ka = Kq < kAq ? Kq : kAq;  // stage-A width (a multiple of 64)
   wave_sync();
 
@@ -518,7 +531,7 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   // exact distances of the survivors, smallest lower bound first
   auto resolve = [&]() __attribute__((always_inline)) {
     while (nf > 0) {
-      float l = lane < nf ? fl[lane] : FLT_MAX;
+      float l = lane < nf ? fz[lane] : FLT_MAX;
       int i = lane;
       for (int off = 1; off < 64; off <<= 1) {
         const float ol = __shfl_xor(l, off, 64);
@@ -528,7 +541,7 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
           i = oi;
         }
       }
-      if (l * l > ub * kMargin) {
+      if (above(l, ub * kMargin)) {
         nf = 0;
         break;
       }
@@ -537,7 +550,7 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       if (lane == 0) {
         fc[i] = fc[nf - 1];
         fr[i] = fr[nf - 1];
-        fl[i] = fl[nf - 1];
+        fz[i] = fz[nf - 1];
       }
       --nf;
       wave_sync();
@@ -548,15 +561,14 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   // the list, and their complete upper bounds tighten u
   auto stage_c = [&](int cnt) __attribute__((always_inline)) {
     int32_t C = -1, cr = -1;
-    float lo = FLT_MAX, up = 0.0f;
+    float z = 0.0f;
     if (g < cnt) {
       C = rc[nr - cnt + g];
-      lo = rl[nr - cnt + g];
-      up = ru[nr - cnt + g];
+      z = rz[nr - cnt + g];
     }
     nr -= cnt;
     wave_sync();
-    const bool live = C >= 0 && C != bl && !(lo * lo > ub * kMargin);
+    const bool live = C >= 0 && C != bl && !above(z, ub * kMargin);
     if (live) {
       // lane a8 of the group takes columns kBq + 8 a8 + 64 it (Kq <= 512)
       cr = crow[C];
@@ -570,31 +582,29 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
 #pragma unroll
       for (int it = 0; it < 4; ++it) {
         const int q0 = kBq + 8 * a8 + 64 * it;
-        if (q0 < Kq) bounds16_8(v[it], xs, sv, s10, s24, q0, lo, up);
+        if (q0 < Kq) screen16_8(v[it], xv, nv, q0, z);
       }
     }
-    for (int off = 4; off > 0; off >>= 1) {
-      lo = fmaxf(lo, __shfl_xor(lo, off, 8));
-      up = fmaxf(up, __shfl_xor(up, off, 8));
-    }
+    for (int off = 4; off > 0; off >>= 1) z = fmaxf(z, __shfl_xor(z, off, 8));
+    const float up = __builtin_fmaf(z, kHiScale, tn);
     float um = live ? up * up * kUpScale : FLT_MAX;
     for (int off = 8; off < 64; off <<= 1) um = fminf(um, __shfl_xor(um, off, 64));
     ub = fminf(ub, um);
-    const bool keep = live && a8 == 0 && !(lo * lo > ub * kMargin);
+    const bool keep = live && a8 == 0 && !above(z, ub * kMargin);
     const uint64_t m = __ballot(keep);
     const int nk = __popcll(m);
     if (nf + nk > kFCap) {
       // drop the survivors u now excludes, then resolve if still full
-      const bool k2 = lane < nf && !(fl[lane] * fl[lane] > ub * kMargin);
+      const bool k2 = lane < nf && !above(fz[lane], ub * kMargin);
       const int32_t c2 = k2 ? fc[lane] : 0, r2 = k2 ? fr[lane] : 0;
-      const float l2 = k2 ? fl[lane] : 0.0f;
+      const float l2 = k2 ? fz[lane] : 0.0f;
       const uint64_t m2 = __ballot(k2);
       wave_sync();
       if (k2) {
         const int at = __popcll(m2 & lt_mask);
         fc[at] = c2;
         fr[at] = r2;
-        fl[at] = l2;
+        fz[at] = l2;
       }
       nf = __popcll(m2);
       wave_sync();
@@ -604,7 +614,7 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       const int at = nf + __popcll(m & lt_mask);
       fc[at] = C;
       fr[at] = cr;
-      fl[at] = lo;
+      fz[at] = z;
     }
     nf += nk;
     wave_sync();
@@ -613,15 +623,14 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   // stage-C queue, which is drained in batches of 8
   auto stage_b = [&](int cnt) __attribute__((always_inline)) {
     int32_t C = -1;
-    float lo = FLT_MAX, up = 0.0f;
+    float z = 0.0f;
     if (g < cnt) {
       C = qc[nq - cnt + g];
-      lo = ql[nq - cnt + g];
-      up = qu[nq - cnt + g];
+      z = qz[nq - cnt + g];
     }
     nq -= cnt;
     wave_sync();
-    const bool live = C >= 0 && C != bl && !(lo * lo > ub * kMargin);
+    const bool live = C >= 0 && C != bl && !above(z, ub * kMargin);
     if (live) {
       // lane a8 of the group takes columns kAq + 8 a8 + 64 it
       const uint4 *row = reinterpret_cast<const uint4 *>(cperm + int64_t(C) * Kq);
@@ -634,20 +643,16 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
 #pragma unroll
       for (int it = 0; it < 2; ++it) {
         const int q0 = kAq + 8 * a8 + 64 * it;
-        if (q0 < Kq) bounds16_8(v[it], xs, sv, s10, s24, q0, lo, up);
+        if (q0 < Kq) screen16_8(v[it], xv, nv, q0, z);
       }
     }
-    for (int off = 4; off > 0; off >>= 1) {
-      lo = fmaxf(lo, __shfl_xor(lo, off, 8));
-      up = fmaxf(up, __shfl_xor(up, off, 8));
-    }
-    const bool keep = live && a8 == 0 && !(lo * lo > ub * kMargin);
+    for (int off = 4; off > 0; off >>= 1) z = fmaxf(z, __shfl_xor(z, off, 8));
+    const bool keep = live && a8 == 0 && !above(z, ub * kMargin);
     const uint64_t m = __ballot(keep);
     if (keep) {
       const int at = nr + __popcll(m & lt_mask);
       rc[at] = C;
-      rl[at] = lo;
-      ru[at] = up;
+      rz[at] = z;
     }
     nr += __popcll(m);
     wave_sync();
@@ -679,6 +684,8 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       if (lane >= off) inc += o;
     }
     const int32_t total = __shfl(inc, 63, 64);
+    // candidates screened: the pins of p's hyperedges but p itself
+    if (lane == 0) pairs[i] = (e0 > 0 ? pairs[i] : 0) + total - nb;
     wave_sync();
     if (lane < nb) ep[lane] = inc - my;
     if (lane == 0) ep[nb] = total;
@@ -686,7 +693,7 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
     for (int32_t t0 = 0; t0 < total; t0 += 64) {
       const int32_t t = t0 + lane;
       int32_t C = -1;
-      float lo = FLT_MAX, up = 0.0f;
+      float z = 0.0f;
       if (t < total) {
         int lo_i = 0, hi_i = nb;  // last i with ep[i] <= t
         while (hi_i - lo_i > 1) {
@@ -698,36 +705,32 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       }
       if (C >= 0) {
         // 64 columns (one 128-byte line) per round, loads ahead of use
-        lo = 0.0f;
         const uint4 *row = reinterpret_cast<const uint4 *>(cperm + int64_t(C) * Kq);
         for (int q0 = 0; q0 < ka; q0 += 64) {
           uint4 v[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u) v[u] = row[q0 / 8 + u];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) bounds16_8(v[u], xs, sv, s10, s24, q0 + 8 * u, lo, up);
+          for (int u = 0; u < 8; ++u) screen16_8(v[u], xv, nv, q0 + 8 * u, z);
         }
       }
       int32_t seed = -1;
       if (ub == FLT_MAX) {
         // seed u: stages B and C of the smallest (bound, label) of this batch
-        float sl = lo, su = up;
+        float sl = C >= 0 ? z : FLT_MAX;
         int32_t sc = C >= 0 ? C : INT32_MAX;
         for (int off = 1; off < 64; off <<= 1) {
           const float ol = __shfl_xor(sl, off, 64);
-          const float ou = __shfl_xor(su, off, 64);
           const int32_t oc = __shfl_xor(sc, off, 64);
           if (ol < sl || (ol == sl && oc < sc)) {
             sl = ol;
-            su = ou;
             sc = oc;
           }
         }
         if (sc != INT32_MAX) {
           if (lane == 0) {
             qc[nq] = sc;
-            ql[nq] = sl;
-            qu[nq] = su;
+            qz[nq] = sl;
           }
           ++nq;
           wave_sync();
@@ -736,13 +739,12 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
           seed = sc;
         }
       }
-      const bool ok = C >= 0 && C != bl && C != seed && !(lo * lo > ub * kMargin);
+      const bool ok = C >= 0 && C != bl && C != seed && !above(z, ub * kMargin);
       const uint64_t m = __ballot(ok);
       if (ok) {
         const int at2 = nq + __popcll(m & lt_mask);
         qc[at2] = C;
-        ql[at2] = lo;
-        qu[at2] = up;
+        qz[at2] = z;
       }
       nq += __popcll(m);
       wave_sync();
@@ -759,37 +761,24 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   }
 }
 
-// *out += the (isolated node, candidate cluster) pairs k_best screens: one
-// per co-pin occurrence of every listed node p, sum_{e ∋ p} (|e| - 1).  A
-// thread per listed node, a block sum, one integer atomic per workgroup.
-__global__ void __launch_bounds__(256)
-k_count_candidates(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
-                   const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
-                   const int32_t *__restrict__ eptr, unsigned long long *__restrict__ out) {
-  __shared__ unsigned long long part[256];
+// *out += pairs[0 .. *count), the pairs k_best screened per listed node (a
+// block sum, one integer atomic per workgroup).
+__global__ void __launch_bounds__(kT)
+k_sum_pairs(const int32_t *__restrict__ pairs, const int32_t *__restrict__ count,
+            unsigned long long *__restrict__ out) {
+  __shared__ unsigned long long part[kT / 64];
   const int64_t cnt = *count;
   unsigned long long acc = 0;
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < cnt;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const int32_t p = list[i];
-    const int32_t j1 = vptr[p + 1];
-    // four hyperedges' loads at a time (independent), then their sizes
-    for (int32_t j = vptr[p]; j < j1; j += 4) {
-      int32_t e[4];
+  for (int64_t i = int64_t(blockIdx.x) * kT + threadIdx.x; i < cnt; i += int64_t(gridDim.x) * kT)
+    acc += unsigned(pairs[i]);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) e[u] = j + u < j1 ? eids[j + u] : -1;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (e[u] >= 0) acc += unsigned(eptr[e[u] + 1] - eptr[e[u]] - 1);
-    }
-  }
-  part[threadIdx.x] = acc;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (int(threadIdx.x) < off) part[threadIdx.x] += part[threadIdx.x + off];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int q = 1; q < kT / 64; ++q) acc += part[q];
+    if (acc) atomicAdd(out, acc);
   }
-  if (threadIdx.x == 0 && part[0]) atomicAdd(out, part[0]);
 }
 
 // ---- union-find over the attach pairs (roots end as component minima) ------
@@ -1316,6 +1305,7 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
       // the isolated nodes, listed in node order (sort buffers are free here)
       int32_t *sflag = reinterpret_cast<int32_t *>(w.k1);
       int32_t *slist = reinterpret_cast<int32_t *>(w.v0);
+      int32_t *pairs = reinterpret_cast<int32_t *>(w.v1);  // per listed node
       k_single_flag<<<g1(n), kT, 0, s>>>(w.owner, st.vptr, int32_t(n), sflag);
       HEF_LAUNCH_CHECK();
       HEF_TRY(compact_flags(sflag, reinterpret_cast<int32_t *>(w.k0), slist, w.small + 7, n, ws, s));
@@ -1328,7 +1318,7 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
           k_best<kPoolF32><<<cdiv(n, kBT / 64), kBT, 0, s>>>(L.eptr, L.pins, st.vptr, st.eids,
                                                      w.owner, w.prov, w.crow, w.cent, w.cperm, Kq,
                                                      w.perm, w.inv32, pool, K, qh, slist,
-                                                     w.small + 7, w.best_label, w.best_d);
+                                                     w.small + 7, w.best_label, w.best_d, pairs);
         }
       } else {
         k_centroids<kPoolBF16><<<2048, kT, 0, s>>>(L.eptr, L.pins, w.in_list, w.small + 1, pool, K, w.cent);
@@ -1339,12 +1329,11 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
           k_best<kPoolBF16><<<cdiv(n, kBT / 64), kBT, 0, s>>>(L.eptr, L.pins, st.vptr, st.eids,
                                                      w.owner, w.prov, w.crow, w.cent, w.cperm, Kq,
                                                      w.perm, w.inv32, pool, K, qh, slist,
-                                                     w.small + 7, w.best_label, w.best_d);
+                                                     w.small + 7, w.best_label, w.best_d, pairs);
         }
       }
-      if (work)  // (about one listed node per thread at the finest level)
-        k_count_candidates<<<std::min<int64_t>(cdiv(n, 256), 4096), 256, 0, s>>>(
-            slist, w.small + 7, st.vptr, st.eids, L.eptr, work);
+      if (work)
+        k_sum_pairs<<<std::min<int64_t>(cdiv(n, 4 * kT), 512), kT, 0, s>>>(pairs, w.small + 7, work);
       HEF_LAUNCH_CHECK();
     }
     // union-find over {p, best(p)}
