@@ -148,15 +148,96 @@ k_sadj_a(const float *__restrict__ sfwd, int K, int LPR, int64_t m, const double
 // Pass B: with qbar_i = -qsum_i (dL/dQ_H(i)), per (e, i) the spread's
 // adjoint sbar = [i = i*] c_e / Q_H(i) + w_e qbar_i, the positions of the
 // largest / smallest pin (first in CSR order) and dbar = 2 (max - min) sbar;
-// per hyperedge the direct term sum_i qbar_i s_e^(i).
+// per hyperedge the direct term sum_i qbar_i s_e^(i).  k_sadj_b takes the
+// hyperedges of up to kSmallSeg pins, a lane group each; k_sadj_long the
+// longer ones, a workgroup each (one group walking 2000 pins is a chain of
+// 500 dependent gathers: 845 us at 200k nodes, K = 160, against 420 us for
+// the two).
+struct SadjOut {
+  int32_t *slot_a, *slot_b;
+  float *dbar;
+  double *wdirect;
+};
+
+// extremes of this lane's columns and their first positions
+template <int CPL>
+struct Extremes {
+  float mx[CPL], mn[CPL];
+  int32_t ja[CPL], jb[CPL];
+  __device__ __forceinline__ void start(const float *__restrict__ chi,
+                                        const int32_t *__restrict__ pins, int32_t j, int K,
+                                        int c0) {
+    float v[CPL];
+    load_row<CPL>(chi, pins[j], K, c0, v);
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) { mx[q] = v[q]; mn[q] = v[q]; ja[q] = j; jb[q] = j; }
+  }
+  // pins j0 .. j0 + 3 in CSR order (ids first, then rows); past the end the
+  // last pin again, which never beats itself strictly
+  __device__ __forceinline__ void take4(const float *__restrict__ chi,
+                                        const int32_t *__restrict__ pins, int64_t j0, int32_t b,
+                                        int K, int c0) {
+    int32_t pp[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pp[u] = pins[j0 + u < b ? j0 + u : b - 1];
+    float v[4][CPL];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) load_row<CPL>(chi, pp[u], K, c0, v[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int32_t j = j0 + u < b ? int32_t(j0 + u) : b - 1;
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) {
+        if (v[u][q] > mx[q]) { mx[q] = v[u][q]; ja[q] = j; }
+        if (v[u][q] < mn[q]) { mn[q] = v[u][q]; jb[q] = j; }
+      }
+    }
+  }
+};
+
+// what follows the extremes of hyperedge e, on its LPR lanes
+template <int CPL>
+__device__ __forceinline__ void sadj_finish(int64_t e, const Extremes<CPL> &x, int c0, int K,
+                                            int LPR, const double (&inv)[CPL],
+                                            const double (&qb)[CPL], int is, double ce, double we,
+                                            const SadjOut &o) {
+  double wd = 0.0;
+  if (c0 < K) {
+    const int64_t off = e * K + c0;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      if (c0 + q < K) {
+        const double d = double(x.mx[q]) - double(x.mn[q]);
+        const double sbar = we * qb[q] + (c0 + q == is ? ce * inv[q] : 0.0);
+        wd += qb[q] * (d * d);
+        o.slot_a[off + q] = x.ja[q];
+        o.slot_b[off + q] = x.jb[q];
+        o.dbar[off + q] = float(2.0 * d * sbar);
+      }
+    }
+  }
+  for (int t = LPR / 2; t > 0; t >>= 1) wd += __shfl_xor(wd, t, LPR);
+  if (c0 == 0) o.wdirect[e] = wd;
+}
+
+template <int CPL>
+__device__ __forceinline__ void sadj_cols(int c0, int K, const double *__restrict__ qh,
+                                          const double *__restrict__ qsum, double (&inv)[CPL],
+                                          double (&qb)[CPL]) {
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {
+    const double qv = (c0 + q < K) ? qh[c0 + q] : 0.0;
+    inv[q] = qv > 0.0 ? 1.0 / qv : 0.0;
+    qb[q] = (c0 + q < K) ? -qsum[c0 + q] : 0.0;
+  }
+}
+
 template <int CPL>
 __global__ void __launch_bounds__(kThreads)
 k_sadj_b(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
          const float *__restrict__ chi, int K, int LPR, int64_t m, const double *__restrict__ qh,
          const float *__restrict__ dR, const float *__restrict__ w,
-         const int32_t *__restrict__ istar, const double *__restrict__ qsum,
-         int32_t *__restrict__ slot_a, int32_t *__restrict__ slot_b, float *__restrict__ dbar,
-         double *__restrict__ wdirect) {
+         const int32_t *__restrict__ istar, const double *__restrict__ qsum, const SadjOut o) {
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -165,61 +246,70 @@ k_sadj_b(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   const int64_t e0 = blk * kEdgesPerBlk;
   const int64_t e1 = e0 + kEdgesPerBlk < m ? e0 + kEdgesPerBlk : m;
   double inv[CPL], qb[CPL];
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    const double qv = (c0 + q < K) ? qh[c0 + q] : 0.0;
-    inv[q] = qv > 0.0 ? 1.0 / qv : 0.0;
-    qb[q] = (c0 + q < K) ? -qsum[c0 + q] : 0.0;
-  }
+  sadj_cols<CPL>(c0, K, qh, qsum, inv, qb);
   for (int64_t e = e0 + grp; e < e1; e += ngrp) {
     const int32_t a = eptr[e], b = eptr[e + 1];
-    float mx[CPL], mn[CPL];
-    int32_t ja[CPL], jb[CPL];
-    {
-      float v[CPL];
-      load_row<CPL>(chi, pins[a], K, c0, v);
+    if (b - a > kSmallSeg) continue;
+    Extremes<CPL> x;
+    x.start(chi, pins, a, K, c0);
+    for (int64_t j0 = a + 1; j0 < b; j0 += 4) x.take4(chi, pins, j0, b, K, c0);
+    sadj_finish<CPL>(e, x, c0, K, LPR, inv, qb, istar[e], double(dR[e]),
+                     w ? double(w[e]) : 1.0, o);
+  }
+}
+
+constexpr int kLongThreads = 512;
+
+template <int CPL>
+__global__ void __launch_bounds__(kLongThreads)
+k_sadj_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
+            const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+            const float *__restrict__ chi, int K, int LPR, const double *__restrict__ qh,
+            const float *__restrict__ dR, const float *__restrict__ w,
+            const int32_t *__restrict__ istar, const double *__restrict__ qsum, const SadjOut o) {
+  __shared__ float smx[kLongThreads * CPL], smn[kLongThreads * CPL];
+  __shared__ int32_t sja[kLongThreads * CPL], sjb[kLongThreads * CPL];
+  const int tid = threadIdx.x;
+  const int ngrp = kLongThreads / LPR;
+  const int grp = tid / LPR;
+  const int c0 = (tid % LPR) * CPL;
+  const int W = LPR * CPL;
+  double inv[CPL], qb[CPL];
+  sadj_cols<CPL>(c0, K, qh, qsum, inv, qb);
+  const int32_t cnt = *count;
+  for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
+    const int32_t e = list[bi];
+    const int32_t a = eptr[e], b = eptr[e + 1];
+    // group g takes pins a + 4 g .. + 3, then every 4 ngrp on (the first of
+    // them starts its extremes)
+    Extremes<CPL> x;
+    const int64_t first = a + 4 * int64_t(grp);
+    x.start(chi, pins, int32_t(first < b ? first : b - 1), K, c0);
+    for (int64_t j0 = first; j0 < b; j0 += 4 * ngrp) x.take4(chi, pins, j0, b, K, c0);
 #pragma unroll
-      for (int q = 0; q < CPL; ++q) { mx[q] = v[q]; mn[q] = v[q]; ja[q] = a; jb[q] = a; }
+    for (int q = 0; q < CPL; ++q) {
+      smx[grp * W + c0 + q] = x.mx[q];
+      smn[grp * W + c0 + q] = x.mn[q];
+      sja[grp * W + c0 + q] = x.ja[q];
+      sjb[grp * W + c0 + q] = x.jb[q];
     }
-    // pins in chunks of 4 in CSR order (ids first, then rows); a chunk past
-    // the end repeats the last pin, which never beats it strictly
-    for (int32_t j0 = a + 1; j0 < b; j0 += 4) {
-      int32_t pp[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) pp[u] = pins[j0 + u < b ? j0 + u : b - 1];
-      float v[4][CPL];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) load_row<CPL>(chi, pp[u], K, c0, v[u]);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int32_t j = j0 + u < b ? j0 + u : b - 1;
+    __syncthreads();
+    if (grp == 0) {
+      // the first position among equal values
+      for (int g = 1; g < ngrp; ++g) {
 #pragma unroll
         for (int q = 0; q < CPL; ++q) {
-          if (v[u][q] > mx[q]) { mx[q] = v[u][q]; ja[q] = j; }
-          if (v[u][q] < mn[q]) { mn[q] = v[u][q]; jb[q] = j; }
+          const int at = g * W + c0 + q;
+          const float vx = smx[at], vn = smn[at];
+          const int32_t px = sja[at], pn = sjb[at];
+          if (vx > x.mx[q] || (vx == x.mx[q] && px < x.ja[q])) { x.mx[q] = vx; x.ja[q] = px; }
+          if (vn < x.mn[q] || (vn == x.mn[q] && pn < x.jb[q])) { x.mn[q] = vn; x.jb[q] = pn; }
         }
       }
+      sadj_finish<CPL>(e, x, c0, K, LPR, inv, qb, istar[e], double(dR[e]),
+                       w ? double(w[e]) : 1.0, o);
     }
-    const int is = istar[e];
-    const double ce = double(dR[e]);
-    const double we = w ? double(w[e]) : 1.0;
-    double wd = 0.0;
-    if (c0 < K) {
-      const int64_t off = e * K + c0;
-#pragma unroll
-      for (int q = 0; q < CPL; ++q) {
-        if (c0 + q < K) {
-          const double d = double(mx[q]) - double(mn[q]);
-          const double sbar = we * qb[q] + (c0 + q == is ? ce * inv[q] : 0.0);
-          wd += qb[q] * (d * d);
-          slot_a[off + q] = ja[q];
-          slot_b[off + q] = jb[q];
-          dbar[off + q] = float(2.0 * d * sbar);
-        }
-      }
-    }
-    for (int o = LPR / 2; o > 0; o >>= 1) wd += __shfl_xor(wd, o, LPR);
-    if (tid % LPR == 0) wdirect[e] = wd;
+    __syncthreads();
   }
 }
 
@@ -863,8 +953,13 @@ hef_status score_adjoint_t(const Level &L, const Structure &st, const float *chi
   int32_t *slot_a = reinterpret_cast<int32_t *>(w.big);
   int32_t *slot_b = slot_a + int64_t(L.m) * K;
   float *dbar = reinterpret_cast<float *>(slot_b + int64_t(L.m) * K);
+  const SadjOut so{slot_a, slot_b, dbar, w.wdirect};
+  const int nlong = int(std::min<int64_t>(L.nnz / kSmallSeg, 2048));
+  if (nlong > 0)
+    k_sadj_long<CPL><<<nlong, kLongThreads, 0, s>>>(st.big_e, st.n_big, L.eptr, L.pins, chi, K, LPR,
+                                                qh, dR, L.w, w.istar, w.qsum, so);
   k_sadj_b<CPL><<<nblk, kThreads, 0, s>>>(L.eptr, L.pins, chi, K, LPR, L.m, qh, dR, L.w, w.istar,
-                                          w.qsum, slot_a, slot_b, dbar, w.wdirect);
+                                          w.qsum, so);
   HEF_LAUNCH_CHECK();
   const int ngrp = kThreads / LPR;
   if (L.n > 0) {

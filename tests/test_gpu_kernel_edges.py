@@ -193,3 +193,22 @@ def test_krylov_step_at_workgroup_edges(b, n, m):
     if star is not None:
         d = (both[:, :k * b] - star).abs().max().item()
         assert d <= 1e-6
+
+
+@pytest.mark.parametrize("k,b", [(5, 1), (6, 4), (17, 8)])
+def test_gradient_with_long_hyperedges(k, b):
+    """Hyperedges of 32, 33, 64 and 300 pins (a workgroup each above 32) in the
+    score adjoint, narrow and wide lane groups, against the float64 autograd
+    oracle at the adjoint tests' bound of 1e-3."""
+    from oracle import gradient as ogr
+    from tests.gpu_common import starts
+    say(f"case: adjoint long hyperedges k={k} b={b}")
+    sizes = [300, 32, 33, 64] + _mixed_sizes(700, 3) + [65, 33]
+    w = np.random.default_rng(2).uniform(0.5, 2.0, len(sizes)).astype(np.float32)
+    h = _hg(800, sizes, 21, w)
+    Xs, Xc, xs, xc = starts(h, b)
+    coef = np.random.default_rng(3).standard_normal(h.m).astype(np.float32)
+    _, ref, _ = ogr.loss_and_grad(h.n, h.m, h.eptr, h.pins, h.w, Xs, Xc, k, coef)
+    dw = hef.resistance_backward(to_device(h), hef.Params(k=k, b=b),
+                                 torch.as_tensor(coef, device="cuda"), xs, xc).cpu().numpy()
+    assert np.linalg.norm(dw - ref) <= 1e-3 * np.linalg.norm(ref)
