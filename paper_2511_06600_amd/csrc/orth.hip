@@ -326,6 +326,12 @@ __device__ __forceinline__ int2 pair_of(int p, int nsb) {
   return make_int2(0, 0);
 }
 
+// Whether the 32 x 32 tile (ti, tj) of super-tile pair ab is formed: on or
+// above the diagonal (diagonal pairs) and not past column K.
+__device__ __forceinline__ bool gram_tile_on(bool diag, int2 ab, int ti, int tj, int K) {
+  return !(diag && tj < ti) && ab.x * kSB + 32 * ti < K && ab.y * kSB + 32 * tj < K;
+}
+
 // 8 consecutive pool values (columns c..c+7 of row `row`) as floats; zeros
 // past the matrix.  Vector loads when the row stride allows.
 __device__ __forceinline__ void load8(const void *pool, int pool_type, int64_t row, int64_t rows,
@@ -574,12 +580,13 @@ k_jgram(const float *__restrict__ pool, const float *__restrict__ poolB, int64_t
     __syncthreads();
     buf ^= 1;
   }
+  if (!on) return;  // (k_gram_finish reads the tiles that are on)
   double *out = partial + (chunk * npairs + pair) * (16 * 1024);
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int i = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int j = lane & 31;
-    out[(ti * 4 + tj) * 1024 + i * 32 + j] = on ? d[v] + double(acc[v]) : 0.0;
+    out[(ti * 4 + tj) * 1024 + i * 32 + j] = d[v] + double(acc[v]);
   }
 }
 
@@ -707,37 +714,69 @@ k_jgram_dma(const float *__restrict__ pool, int64_t n, int K, int nsb, int npair
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
   }
+  if (!on) return;  // (k_gram_finish reads the tiles that are on)
   double *out = partial + (chunk * npairs + pair) * (16 * 1024);
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int i = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int j = lane & 31;
-    out[(ti * 4 + tj) * 1024 + i * 32 + j] = on ? d[v] + double(acc[v]) : 0.0;
+    out[(ti * 4 + tj) * 1024 + i * 32 + j] = d[v] + double(acc[v]);
   }
 }
 
-// G[gi][gj] from the chunk-summed tiles (mirrored unless `cross`).
-__global__ void k_jgram_scatter(const double *__restrict__ sums, int nsb, int npairs, int K,
-                                int cross, double *__restrict__ G) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= int64_t(npairs) * 16 * 1024) return;
-  const int pair = int(e / (16 * 1024));
-  const int rem = int(e % (16 * 1024));
-  const int wt = rem / 1024, ij = rem % 1024;
-  const int ti = wt / 4, tj = wt % 4, i = ij / 32, j = ij % 32;
+// G[gi][gj] (mirrored unless `cross`; also to A, the Cholesky's trailing
+// matrix, if given) from the row chunks' tiles, in float64: the sum over the
+// chunks in ColSum's order (32 row lanes of 8 accumulators).  A workgroup
+// takes 64 entries of a tile, coalesced; wave v takes the row lanes
+// v, v + 4, ..., whose sums combine as ColSum's lanes do.  Only the tiles that
+// were formed are read (15 of 48 at K = 160, 120 of 160 at K = 480); the
+// separate column sum over all of them, 8 columns per workgroup, half lines
+// at a time, took 66 us at 20k nodes, K = 464 (268 MB), 70 at 200k, K = 160,
+// and 85 at 2M, K = 480, against 30, 21 and 42 us here.
+__global__ void __launch_bounds__(256)
+k_gram_finish(const double *__restrict__ partial, int nchunks, int nsb, int npairs, int K,
+              int cross, double *__restrict__ G, double *__restrict__ A) {
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
+  const int pair = int(blockIdx.x >> 8), wt = int(blockIdx.x >> 4) & 15;
+  const int ti = wt / 4, tj = wt % 4;
   const int2 ab = cross ? make_int2(pair / nsb, pair % nsb) : pair_of(pair, nsb);
-  if (!cross && ab.x == ab.y && tj < ti) return;
-  const int gi = ab.x * kSB + 32 * ti + i;
-  const int gj = ab.y * kSB + 32 * tj + j;
+  if (!gram_tile_on(!cross && ab.x == ab.y, ab, ti, tj, K)) return;
+  const int ij = (int(blockIdx.x) & 15) * 64 + lane;
+  const int64_t ncols = int64_t(npairs) * 16 * 1024;
+  const double *src = partial + (int64_t(pair) * 16 + wt) * 1024 + ij;
+  double y[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    double acc[8] = {};
+    for (int r = v + 4 * k; r < nchunks; r += 256) {
+      double t[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) t[q] = src[(r + 32 * q < nchunks ? r + 32 * q : r) * ncols];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (r + 32 * q < nchunks) acc[q] += t[q];
+    }
+    y[k] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  }
+  red[v][lane] = ((y[0] + y[4]) + (y[2] + y[6])) + ((y[1] + y[5]) + (y[3] + y[7]));
+  __syncthreads();
+  if (v != 0) return;
+  const double s = (red[0][lane] + red[2][lane]) + (red[1][lane] + red[3][lane]);
+  const int gi = ab.x * kSB + 32 * ti + ij / 32;
+  const int gj = ab.y * kSB + 32 * tj + ij % 32;
   if (gi >= K || gj >= K) return;
-  const double s = sums[e];
   G[int64_t(gi) * K + gj] = s;
   if (!cross) G[int64_t(gj) * K + gi] = s;
+  if (A) {
+    A[int64_t(gi) * K + gj] = s;
+    A[int64_t(gj) * K + gi] = s;
+  }
 }
 
 // The Gram of a float64 pool in the row-octet layout (the float64 debug
 // basis): workgroup = (row chunk, super-block pair a <= b), its partial in
-// the layout k_jgram_scatter reads (16 tiles of 32 x 32 per pair).  Thread
+// the layout k_gram_finish reads (16 tiles of 32 x 32 per pair).  Thread
 // (ty, tx) accumulates rows 8 ty .. 8 ty + 7 of block a against columns
 // 8 tx .. 8 tx + 7 of block b in float64, over the chunk's rows staged 16 at
 // a time in LDS.
@@ -1357,8 +1396,8 @@ k_jgram_bf16(const uint16_t *__restrict__ pool, int oct, int64_t n, int K, int n
   const int w = tid >> 6;
   const int ti = w >> 1;
   const int tj0 = 2 * (w & 1);
-  const bool on0 = !diag || tj0 >= ti;
-  const bool on1 = !diag || tj0 + 1 >= ti;
+  const bool on0 = gram_tile_on(diag, ab, ti, tj0, K);
+  const bool on1 = gram_tile_on(diag, ab, ti, tj0 + 1, K);
   const int64_t r0 = chunk * rows_per_chunk;
   const int64_t r1 = r0 + rows_per_chunk < n ? r0 + rows_per_chunk : n;
   floatx16 acc0, acc1;
@@ -1473,8 +1512,8 @@ k_jgram_bf16(const uint16_t *__restrict__ pool, int oct, int64_t n, int K, int n
   for (int v = 0; v < 16; ++v) {
     const int i = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int j = lane & 31;
-    out[(ti * 4 + tj0) * 1024 + i * 32 + j] = on0 ? d0[v] + double(acc0[v]) : 0.0;
-    out[(ti * 4 + tj0 + 1) * 1024 + i * 32 + j] = on1 ? d1[v] + double(acc1[v]) : 0.0;
+    if (on0) out[(ti * 4 + tj0) * 1024 + i * 32 + j] = d0[v] + double(acc0[v]);
+    if (on1) out[(ti * 4 + tj0 + 1) * 1024 + i * 32 + j] = d1[v] + double(acc1[v]);
   }
 }
 
@@ -1627,14 +1666,11 @@ GramPlan gram_plan(int64_t n, int K, bool cross = false) {
 }
 
 hef_status gram_run(const void *pool, const void *poolB, int pool_type, int64_t n, int K,
-                    double *G, Arena &ws, hipStream_t s, bool oct = false) {
+                    double *G, Arena &ws, hipStream_t s, bool oct = false, double *A = nullptr) {
   const GramPlan p = gram_plan(n, K, poolB != nullptr);
   const size_t mk = ws.mark();
   double *partial = ws.take<double>(size_t(p.nchunks) * p.npairs * 16 * 1024);
-  const int64_t tot = int64_t(p.npairs) * 16 * 1024;
-  double *sums = ws.take<double>(tot);
   HEF_WS_CHECK(ws);
-  HEF_TRY(zero_async(G, sizeof(double) * K * K, s));
   {
   TimedScope ts(kStOrthGram, s);
   if (pool_type == kPoolF64) {
@@ -1665,8 +1701,8 @@ hef_status gram_run(const void *pool, const void *poolB, int pool_type, int64_t 
   HEF_LAUNCH_CHECK();
   }
   TimedScope ts(kStOrthReduce, s);
-  HEF_TRY(reduce_cols_f64(partial, p.nchunks, tot, sums, s));
-  k_jgram_scatter<<<cdiv(tot, 256), 256, 0, s>>>(sums, p.nsb, p.npairs, K, poolB != nullptr, G);
+  k_gram_finish<<<p.npairs * 256, 256, 0, s>>>(partial, p.nchunks, p.nsb, p.npairs, K,
+                                              poolB != nullptr, G, A);
   HEF_LAUNCH_CHECK();
   ws.reset(mk);
   return HEF_OK;
@@ -1731,8 +1767,8 @@ size_t orth_ws_bytes(int64_t n, int K) {
   p.nchunks = int(gram_max_chunks(n, K, false));
   Arena a;
   a.take<double>(int64_t(K) * K);    // G
-  a.take<double>(int64_t(K) * K);    // LT
   a.take<double>(int64_t(K) * K);    // trailing matrix of the Cholesky
+  a.take<double>(int64_t(K) * K);    // LT
   a.take<double>(int64_t(Kp) * Kp);  // Rinv
   a.take<float>(int64_t(Kp) * Kp);   // Rinv32
   a.take<float>(int64_t(Kp) * Kp);   // its transpose
@@ -1740,7 +1776,6 @@ size_t orth_ws_bytes(int64_t n, int K) {
   a.take<uint16_t>(int64_t(Kp) * Kp);  // RlT
   a.take<int32_t>(K);                // keep
   a.take<double>(size_t(p.nchunks) * p.npairs * 16 * 1024);
-  a.take<double>(size_t(p.npairs) * 16 * 1024);
   return a.mark() + 1024;
 }
 
@@ -1754,7 +1789,6 @@ size_t gram_cross_ws_bytes(int64_t n, int K) {
   p.nchunks = int(gram_max_chunks(n, K, true));
   Arena a;
   a.take<double>(size_t(p.nchunks) * p.npairs * 16 * 1024);
-  a.take<double>(size_t(p.npairs) * 16 * 1024);
   return a.mark() + 1024;
 }
 
@@ -1781,8 +1815,9 @@ hef_status orthonormalize_pool(void *P, void *out, int pool_type, int64_t n, int
   const int Kp = (K + 31) / 32 * 32;
   const size_t mk = ws.mark();
   double *G = ws.take<double>(int64_t(K) * K);
+  double *A = ws.take<double>(int64_t(K) * K);  // trailing matrix of the Cholesky
+  // (LT to RinvT32 are cleared together)
   double *LT = ws.take<double>(int64_t(K) * K);
-  double *A = ws.take<double>(int64_t(K) * K);
   double *Rinv = ws.take<double>(int64_t(Kp) * Kp);
   float *Rinv32 = ws.take<float>(int64_t(Kp) * Kp);
   float *RinvT32 = ws.take<float>(int64_t(Kp) * Kp);
@@ -1796,17 +1831,14 @@ hef_status orthonormalize_pool(void *P, void *out, int pool_type, int64_t n, int
     const bool oct = pass == 0;
     const void *src = pass == 0 ? P : out;
     void *dst = pass == 0 ? out : P;
-    HEF_TRY(gram_run(src, nullptr, pool_type, n, K, G, ws, s, oct));
+    HEF_TRY(gram_run(src, nullptr, pool_type, n, K, G, ws, s, oct, A));
     {
       TimedScope ts(kStOrthChol, s);
       const size_t lds_c = size_t(K) * kPS * sizeof(double);
       HEF_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_jtrinv),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_c)));
-      HEF_TRY(zero_async(Rinv, sizeof(double) * Kp * Kp, s));
-      HEF_TRY(zero_async(Rinv32, sizeof(float) * Kp * Kp, s));
-      HEF_TRY(zero_async(RinvT32, sizeof(float) * Kp * Kp, s));
-      HEF_HIP(hipMemcpyAsync(A, G, sizeof(double) * K * K, hipMemcpyDeviceToDevice, s));
-      HEF_TRY(zero_async(LT, sizeof(double) * K * K, s));
+      HEF_TRY(zero_async(LT, size_t(reinterpret_cast<char *>(RinvT32 + int64_t(Kp) * Kp) -
+                                    reinterpret_cast<char *>(LT)), s));
       for (int c0 = 0; c0 < K; c0 += kPW) {
         const int w = K - c0 < kPW ? K - c0 : kPW;
         const int nb = K - c0 - w > 0 ? int(cdiv(K - c0 - w, kCR)) : 1;
