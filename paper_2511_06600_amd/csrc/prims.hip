@@ -143,13 +143,24 @@ template <bool COMPACT>
 __global__ void __launch_bounds__(kScanOneThreads)
 k_scan_one(const int32_t *in, int32_t *out, int n, int32_t *total) {
   __shared__ int32_t wtot[kScanOneThreads / 64];
+  // the items pass through LDS both ways: coalesced in global memory, a run
+  // of 16 per thread in between (a pad word per 32, so that runs 16 apart
+  // start on different banks)
+  __shared__ int32_t buf[kScanOne + kScanOne / 32];
   const int tid = threadIdx.x;
   const int base = tid * kScanOneItems;
+#pragma unroll
+  for (int i = 0; i < kScanOneItems; ++i) {
+    const int j = i * kScanOneThreads + tid;
+    if (i * kScanOneThreads < n) buf[j + (j >> 5)] = j < n ? in[j] : 0;
+  }
+  __syncthreads();
   int32_t v[kScanOneItems];
 #pragma unroll
   for (int i = 0; i < kScanOneItems; ++i) {
-    const int32_t x = base + i < n ? in[base + i] : 0;
-    v[i] = COMPACT ? (x != 0) : x;
+    const int j = base + i;
+    v[i] = j < n ? buf[j + (j >> 5)] : 0;
+    if (COMPACT) v[i] = v[i] != 0;
   }
   int32_t sum = 0;
 #pragma unroll
@@ -158,14 +169,21 @@ k_scan_one(const int32_t *in, int32_t *out, int n, int32_t *total) {
   int32_t at = incl - sum;
 #pragma unroll
   for (int i = 0; i < kScanOneItems; ++i) {
-    if (base + i < n) {
-      if constexpr (COMPACT) {
-        if (v[i]) out[at] = base + i;
-      } else {
-        out[base + i] = at;
-      }
+    const int j = base + i;
+    if constexpr (COMPACT) {
+      if (v[i]) out[at] = j;
+    } else {
+      buf[j + (j >> 5)] = at;
     }
     at += v[i];
+  }
+  if constexpr (!COMPACT) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kScanOneItems; ++i) {
+      const int j = i * kScanOneThreads + tid;
+      if (j < n) out[j] = buf[j + (j >> 5)];
+    }
   }
   if (tid == kScanOneThreads - 1) *total = incl;
 }
@@ -338,10 +356,12 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
 
 // All passes of a sort of at most 1024 * ROUNDS items in one workgroup: the
 // items stay in registers and pass through LDS once per pass.  Replaces
-// three launches per pass (about 4 us each when the chip is otherwise idle).
+// three launches per pass (about 4 us each when the chip is otherwise idle):
+// two passes over 7k items 18 us.  At 16 items a thread two passes took 42 us,
+// more than the six launches, so the line lies at 8.
 constexpr int kOneThreads = 1024;
 constexpr int kOneWaves = kOneThreads / 64;
-constexpr int kOneRounds = 16;
+constexpr int kOneRounds = 8;
 
 template <int ROUNDS>
 __global__ void __launch_bounds__(kOneThreads)
@@ -538,8 +558,6 @@ hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32
   if (n <= kOneThreads * kOneRounds) {
     if (n <= kOneThreads * 4)
       k_radix_one<4><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n), passes);
-    else if (n <= kOneThreads * 8)
-      k_radix_one<8><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n), passes);
     else
       k_radix_one<kOneRounds><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n),
                                                         passes);

@@ -105,10 +105,10 @@ def test_rating_class_edges(bound):
     assert np.array_equal(val.cpu().numpy()[nodes], rv)
 
 
-@pytest.mark.parametrize("nnz", [2, 1023, 1025, 4095, 4097, 8193, 16384, 16385, 70001, 1048577])
+@pytest.mark.parametrize("nnz", [2, 1023, 1025, 4096, 4097, 8192, 8193, 16385, 70001, 1048577])
 def test_sort_and_compaction_sizes(nnz):
-    """The incidence sort runs in one workgroup up to 16384 items (4, 8 or 16
-    a thread), in tiles of 1024 up to 2^20 and of 4096 above; node counts
+    """The incidence sort runs in one workgroup up to 8192 items (4 or 8 a
+    thread), in tiles of 1024 up to 2^20 and of 4096 above; node counts
     that need one to three digit passes.  The operator's rows depend on every
     node's hyperedges being complete and in order."""
     say(f"case: sort sizes nnz={nnz}")
@@ -212,3 +212,30 @@ def test_gradient_with_long_hyperedges(k, b):
     dw = hef.resistance_backward(to_device(h), hef.Params(k=k, b=b),
                                  torch.as_tensor(coef, device="cuda"), xs, xc).cpu().numpy()
     assert np.linalg.norm(dw - ref) <= 1e-3 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 1024, 16383, 16384, 16385, 40000])
+def test_level_maps_at_scan_sizes(n):
+    """Labels, clusters and pairs are placed by scans that run in one workgroup
+    up to 16384 items: one clustering level against the oracle, bit for bit."""
+    from oracle import clustering as ocl
+    if n < 4:
+        h = _hg(4, [2] * n, 3)
+    else:
+        h = _hg(n, _mixed_sizes(max(n // 2, 1), n), n)
+    say(f"case: level map n={h.n} m={h.m}")
+    rng = np.random.default_rng(n)
+    K = 8
+    p = hef.Params(k=4, b=1)
+    R = rng.random(h.m).astype(np.float32)
+    chi = rng.standard_normal((h.n, K)).astype(np.float32) / np.sqrt(h.n)
+    qh = rng.uniform(0.5, 2.0, K)
+    cl, nc, eta = hef.cluster_level(to_device(h), p, torch.as_tensor(R, device="cuda"), None,
+                                    torch.as_tensor(chi.astype(np.float32), device="cuda"),
+                                    torch.as_tensor(qh, device="cuda"))
+    chi32 = chi.astype(np.float32)
+    ref = ocl.cluster_level(h.n, h.m, h.eptr, h.pins, R, np.zeros(h.n, np.float32), chi32, qh,
+                            0.5, True)
+    assert nc == ref.n_clusters
+    assert np.array_equal(cl.cpu().numpy(), ref.label)
+    assert np.array_equal(eta.cpu().numpy(), ref.eta.astype(np.float32))
