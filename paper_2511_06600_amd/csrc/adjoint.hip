@@ -991,14 +991,8 @@ hef_status taped_forward(const Level &L, const hef_params &p, const float *start
   const bool use_clique = !(p.flags & HEF_FLAG_STAR_ONLY);
   const Structure &st = w.st;
   HEF_TRY(structure_build(L, w.st, a, s));
-  if (use_star && !start_star) {
-    HEF_TRY(start_block(p.seed, 0, 0, Ns, B, w.xs, s));
-    start_star = w.xs;
-  }
-  if (use_clique && !start_clique) {
-    HEF_TRY(start_block(p.seed, 0, 1, n, B, w.xc, s));
-    start_clique = w.xc;
-  }
+  HEF_TRY(start_blocks(p.seed, 0, n, m, B, use_star ? &start_star : nullptr,
+                       use_clique ? &start_clique : nullptr, w.xs, w.xc, s));
   KrylovOut ko;
   ko.pool = w.P;
   ko.K = K;

@@ -201,19 +201,8 @@ hef_status estimate_level(const Level &L, const hef_params &p, uint64_t seed, in
   const bool use_clique = !(p.flags & HEF_FLAG_STAR_ONLY);
   HEF_TRY(structure_build(L, st, ws, s));
   const size_t mk = ws.mark();
-  float *xs = nullptr, *xc = nullptr;
-  if (use_star && !start_star) {
-    xs = ws.take<float>((n + m) * B);
-    HEF_WS_CHECK(ws);
-    HEF_TRY(start_block(seed, level, 0, n + m, B, xs, s));
-    start_star = xs;
-  }
-  if (use_clique && !start_clique) {
-    xc = ws.take<float>(n * B);
-    HEF_WS_CHECK(ws);
-    HEF_TRY(start_block(seed, level, 1, n, B, xc, s));
-    start_clique = xc;
-  }
+  HEF_TRY(start_blocks(seed, level, n, m, B, use_star ? &start_star : nullptr,
+                       use_clique ? &start_clique : nullptr, ws, s));
   // the Krylov pool (row-octet layout) in pool2, its orthonormal basis in pool
   KrylovOut ko;
   ko.pool = pool2;
@@ -419,12 +408,16 @@ hef_status resistance_call(const hef_hypergraph *hg, const hef_params *p, const 
   void *pool2 = a.take<char>(pool_bytes(oct_rows(n), K, p->basis));
   double *qh_ws = a.take<double>(K);
   float *R_ws = a.take<float>(m);
+  if (p->flags & HEF_FLAG_ASSUME_VALID) {  // unchecked: straight to the caller
+    R_ws = R;
+    if (qh) qh_ws = qh;
+  }
   if (a.overflow) { set_error("workspace carve overflow"); return HEF_ERR_WORKSPACE_TOO_SMALL; }
   const Level L = level_of(hg);
   const bool check = !(p->flags & HEF_FLAG_ASSUME_VALID);
   if (check) {
     int32_t bad = 0;
-    HEF_TRY(validate_device(L, flags, &bad, stream));
+    HEF_TRY(validate_device(L, flags, &bad, stream, 2));
     if (bad) {
       set_error("invalid hypergraph (code %d: 1 eptr ends, 2 segment bounds or |e|<2, 4 pins, 8 weights)", bad);
       return HEF_ERR_INVALID_HYPERGRAPH;
@@ -437,19 +430,21 @@ hef_status resistance_call(const hef_hypergraph *hg, const hef_params *p, const 
   HEF_TRY(estimate_level(L, *p, p->seed, 0, start_star, start_clique, st, pool, pool2, qh_ws,
                          R_ws, a, stream));
   if (check) {
-    HEF_TRY(zero_async(flags, sizeof(int32_t), stream));
-    k_check_finite<<<cdiv(std::max<int64_t>(m, K), 256), 256, 0, stream>>>(R_ws, m, qh_ws, K, flags);
+    k_check_finite<<<cdiv(std::max<int64_t>(m, K), 256), 256, 0, stream>>>(R_ws, m, qh_ws, K,
+                                                                           flags + 1);
     HEF_LAUNCH_CHECK();
     int32_t f = 0;
-    HEF_HIP(hipMemcpyAsync(&f, flags, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+    HEF_HIP(hipMemcpyAsync(&f, flags + 1, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
     HEF_HIP(hipStreamSynchronize(stream));
     if ((f & 1) || !(f & 2)) {
       set_error("numerical failure: %s", (f & 1) ? "non-finite value" : "every quadratic form vanished");
       return HEF_ERR_NUMERICAL;
     }
   }
-  HEF_HIP(hipMemcpyAsync(R, R_ws, m * sizeof(float), hipMemcpyDeviceToDevice, stream));
-  if (qh) HEF_HIP(hipMemcpyAsync(qh, qh_ws, K * sizeof(double), hipMemcpyDeviceToDevice, stream));
+  if (R != R_ws)
+    HEF_HIP(hipMemcpyAsync(R, R_ws, m * sizeof(float), hipMemcpyDeviceToDevice, stream));
+  if (qh && qh != qh_ws)
+    HEF_HIP(hipMemcpyAsync(qh, qh_ws, K * sizeof(double), hipMemcpyDeviceToDevice, stream));
   return HEF_OK;
 }
 

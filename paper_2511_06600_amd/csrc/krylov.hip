@@ -219,13 +219,9 @@ k_gram_reduce(const double *__restrict__ in0, int64_t nrows0, double *__restrict
 // length is 0 or its Schur pivot d_c <= tau^2 * G_cc.  L goes to LDS; lane c
 // then forms column c of R^-1 = L^-T by back substitution.
 template <int C>
-__global__ void __launch_bounds__(64)
-k_lsolve(const double *__restrict__ Gall, int B, double tau, double *__restrict__ Tall,
-         int32_t *__restrict__ drops, double *__restrict__ Rall) {
-  __shared__ double Ls[C * C];
-  const double *G = Gall + blockIdx.x * C * C;
-  double *T = Tall + blockIdx.x * C * B;
-  const int t = threadIdx.x;
+__device__ __forceinline__ void lsolve_wave(const double *G, int B, double tau, double *T,
+                                            double *Rf, double *Ls) {
+  const int t = threadIdx.x & 63;
   double a[C], l[C];
 #pragma unroll
   for (int j = 0; j < C; ++j) {
@@ -259,7 +255,7 @@ k_lsolve(const double *__restrict__ Gall, int B, double tau, double *__restrict_
 #pragma unroll
     for (int j = 0; j < C; ++j) Ls[t * C + j] = l[j];
   }
-  __syncthreads();
+  wave_sync();
   // column c of R^-1 (R = L^T): L^T x = e_c, rows c, c-1, ..., 0
   const int c = t;
   const bool kc = c < C && ((keep >> c) & 1);
@@ -278,24 +274,93 @@ k_lsolve(const double *__restrict__ Gall, int B, double tau, double *__restrict_
 #pragma unroll
     for (int i = 0; i < C; ++i) T[i * B + (c - 2 * B)] = x[i];
   }
-  if (t < B && !((keep >> (2 * B + t)) & 1)) atomicAdd(&drops[blockIdx.x], 1);
   // optionally the whole R^-1 (row-major C x C), zero rows/columns for drops
-  if (Rall && c < C) {
-    double *Rf = Rall + blockIdx.x * C * C;
+  if (Rf && c < C) {
 #pragma unroll
     for (int i = 0; i < C; ++i) Rf[i * C + c] = x[i];
   }
 }
 
+template <int C>
+__global__ void __launch_bounds__(64)
+k_lsolve(const double *__restrict__ Gall, int B, double tau, double *__restrict__ Tall,
+         double *__restrict__ Rall) {
+  __shared__ double Ls[C * C];
+  lsolve_wave<C>(Gall + blockIdx.x * C * C, B, tau, Tall + blockIdx.x * C * B,
+                 Rall ? Rall + blockIdx.x * C * C : nullptr, Ls);
+}
+
+// The reduce of the Gram partials and the solve in one launch, a workgroup
+// per expansion (mask bit x: expansion x takes part): for C <= 6 (b <= 2) the
+// partials are at most 1024 x 36 values, and the second launch of the step
+// costs more than the workgroups it brings (2k nodes, b = 1: 2.6 + 2.2 us and
+// a launch -> 2.8; 20k, b = 2: 4.6 + 3.3 and a launch -> 5.8).  The sums
+// are ColSum's, as in k_gram_reduce.
+template <int C, int S>
+__global__ void __launch_bounds__(1024)
+k_lreduce_solve(const double *__restrict__ in0, int64_t nrows0, const double *__restrict__ in1,
+                int64_t nrows1, int mask, int B, double tau, double *__restrict__ Tall,
+                double *__restrict__ Rall) {
+  constexpr int NG = (C * C + 7) / 8;  // groups of 8 columns, all loaded together
+  __shared__ double red[NG][4][32][9];
+  __shared__ double G[C * C], Ls[C * C];
+  const int x = blockIdx.x;
+  if (!((mask >> x) & 1)) return;
+  const double *__restrict__ in = x ? in1 : in0;
+  const int64_t nrows = x ? nrows1 : nrows0;
+  const int cl = threadIdx.x & 7, rl = (threadIdx.x >> 3) & 31, part = threadIdx.x >> 8;
+  double acc[NG][2] = {};
+  for (int64_t r = rl + 64 * part; r < nrows; r += 256) {
+    double t[NG][2];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int c = 8 * g + cl < C * C ? 8 * g + cl : C * C - 1;
+        t[g][q] = in[(r + 32 * q < nrows ? r + 32 * q : r) * (C * C) + c];
+      }
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (r + 32 * q < nrows) acc[g][q] += t[g][q];
+  }
+#pragma unroll
+  for (int g = 0; g < NG; ++g) red[g][part][rl][cl] = acc[g][0] + acc[g][1];
+  __syncthreads();
+  // wave g finishes group g: lane (column, k < 8) takes row lanes k + 8 i
+  const int g = threadIdx.x >> 6;
+  if (g < NG) {
+    const int k = (threadIdx.x >> 3) & 7;
+    double y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      y[i] = (red[g][0][k + 8 * i][cl] + red[g][1][k + 8 * i][cl]) +
+             (red[g][2][k + 8 * i][cl] + red[g][3][k + 8 * i][cl]);
+    double t = (y[0] + y[2]) + (y[1] + y[3]);
+#pragma unroll
+    for (int off = 32; off >= 8; off >>= 1) t += __shfl_down(t, off, 64);
+    const int c = 8 * g + cl;
+    const int i = c / C, j = c % C;
+    if (k == 0 && c < C * C && i / S <= j / S) {
+      G[i * C + j] = t;
+      if (i / S < j / S) G[j * C + i] = t;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 64)
+    lsolve_wave<C>(G, B, tau, Tall + x * C * B, Rall ? Rall + x * C * C : nullptr, Ls);
+}
+
 // the solve for C = 3B columns (B in {1, 2, 4, 8, 16})
-hef_status lsolve_launch(const double *G, int B, double tau, double *T, int32_t *drops,
-                         double *R, hipStream_t s) {
+hef_status lsolve_launch(const double *G, int B, double tau, double *T, double *R,
+                         hipStream_t s) {
   switch (B) {
-    case 1: k_lsolve<3><<<2, 64, 0, s>>>(G, B, tau, T, drops, R); break;
-    case 2: k_lsolve<6><<<2, 64, 0, s>>>(G, B, tau, T, drops, R); break;
-    case 4: k_lsolve<12><<<2, 64, 0, s>>>(G, B, tau, T, drops, R); break;
-    case 8: k_lsolve<24><<<2, 64, 0, s>>>(G, B, tau, T, drops, R); break;
-    case 16: k_lsolve<48><<<2, 64, 0, s>>>(G, B, tau, T, drops, R); break;
+    case 1: k_lsolve<3><<<2, 64, 0, s>>>(G, B, tau, T, R); break;
+    case 2: k_lsolve<6><<<2, 64, 0, s>>>(G, B, tau, T, R); break;
+    case 4: k_lsolve<12><<<2, 64, 0, s>>>(G, B, tau, T, R); break;
+    case 8: k_lsolve<24><<<2, 64, 0, s>>>(G, B, tau, T, R); break;
+    case 16: k_lsolve<48><<<2, 64, 0, s>>>(G, B, tau, T, R); break;
     default: return HEF_ERR_UNSUPPORTED;
   }
   HEF_LAUNCH_CHECK();
@@ -610,15 +675,33 @@ __host__ __device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
 }
 
 // N(0,1) element i of stream (seed, level, expansion): splitmix64 counter and
-// Box-Muller, float64.
-__global__ void k_start(uint64_t h, int64_t total, float *out) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= total) return;
+// Box-Muller, float64.  Two streams in one launch: elements [0, n0) are the
+// first's, the others the second's.
+__global__ void k_start(uint64_t h0, int64_t n0, float *__restrict__ out0, uint64_t h1, int64_t n1,
+                        float *__restrict__ out1) {
+  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n0 + n1) return;
+  const bool second = i >= n0;
+  if (second) i -= n0;
+  const uint64_t h = second ? h1 : h0;
   const uint64_t a = splitmix64(h + 2ull * uint64_t(i));
   const uint64_t c = splitmix64(h + 2ull * uint64_t(i) + 1ull);
   const double u1 = (double((a >> 11)) + 1.0) * 0x1.0p-53;
   const double u2 = double(c >> 11) * 0x1.0p-53;
-  out[i] = float(sqrt(-2.0 * log(u1)) * cos(2.0 * M_PI * u2));
+  (second ? out1 : out0)[i] = float(sqrt(-2.0 * log(u1)) * cos(2.0 * M_PI * u2));
+}
+
+uint64_t stream_hash(uint64_t seed, int level, int expansion) {
+  return splitmix64(splitmix64(seed) + 2ull * uint64_t(level) + uint64_t(expansion));
+}
+
+hef_status start_launch(uint64_t h0, int64_t n0, float *out0, uint64_t h1, int64_t n1, float *out1,
+                        hipStream_t s) {
+  if (n0 + n1 == 0) return HEF_OK;
+  TimedScope ts(kStStart, s);
+  k_start<<<cdiv(n0 + n1, 256), 256, 0, s>>>(h0, n0, out0, h1, n1, out1);
+  HEF_LAUNCH_CHECK();
+  return HEF_OK;
 }
 
 // Sides with zero rows launch nothing.
@@ -679,19 +762,14 @@ hef_status lapply2(int B, const ApplySide &a, const ApplySide &b, void *pool, in
   }
 }
 
-hef_status lapply(int B, const float *v0, const float *v1, const float *y, const double *T,
-                  float *vn, int64_t rows, void *pool, int pool_type, int64_t pool_rows, int K,
-                  int col0, hipStream_t s) {
-  const ApplySide a{v0, v1, y, T, vn, rows, col0};
-  const ApplySide none{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
-  return lapply2(B, a, none, pool, pool_type, pool_rows, K, s);
-}
-
 // The Grams of up to two expansions (a side with y == nullptr is skipped),
-// each over its own rows, in one Gram launch and one reduce launch.
-hef_status lgram2(int B, const float *v0a, const float *v1a, const float *ya, int64_t rowsa,
-                  double *partiala, double *Ga, const float *v0b, const float *v1b,
-                  const float *yb, int64_t rowsb, double *partialb, double *Gb, hipStream_t s) {
+// each over its own rows, and the solves of both: T = R^-1[:, y columns] and
+// (if given) all of R^-1.
+hef_status lgram_solve(int B, const float *v0a, const float *v1a, const float *ya, int64_t rowsa,
+                       double *partiala, double *Ga, const float *v0b, const float *v1b,
+                       const float *yb, int64_t rowsb, double *partialb, double *Gb, double tau,
+                       double *T, double *R, hipStream_t s) {
+  double *const G = Ga;  // (Ga and Gb are consecutive C x C matrices)
   const int C = 3 * B;
   const int S = (C % 6 == 0) ? 6 : 3;
   GramPair P;
@@ -719,6 +797,17 @@ hef_status lgram2(int B, const float *v0a, const float *v1a, const float *ya, in
   }
   HEF_LAUNCH_CHECK();
   }
+  if (C <= 6) {
+    TimedScope ts(kStLanczosSolve, s);
+    const int mask = (nb[0] > 0 ? 1 : 0) | (nb[1] > 0 ? 2 : 0);
+    if (C == 3)
+      k_lreduce_solve<3, 3><<<2, 1024, 0, s>>>(partiala, nb[0], partialb, nb[1], mask, B, tau, T, R);
+    else
+      k_lreduce_solve<6, 6><<<2, 1024, 0, s>>>(partiala, nb[0], partialb, nb[1], mask, B, tau, T, R);
+    HEF_LAUNCH_CHECK();
+    return HEF_OK;
+  }
+  {
   TimedScope ts(kStLanczosReduce, s);
   const int nbh = int(cdiv(int64_t(C) * C, 8));
   if (nb[0] > 0 && nb[1] > 0)
@@ -728,34 +817,12 @@ hef_status lgram2(int B, const float *v0a, const float *v1a, const float *ya, in
   else
     k_gram_reduce<<<nbh, 1024, 0, s>>>(partialb, nb[1], Gb, nullptr, 0, nullptr, nbh, C, S);
   HEF_LAUNCH_CHECK();
-  return HEF_OK;
-}
-
-hef_status lgram(const float *v0, const float *v1, const float *y, int64_t rows, int B,
-                 double *partial, double *G, hipStream_t s) {
-  return lgram2(B, v0, v1, y, rows, partial, G, nullptr, nullptr, nullptr, 0, nullptr, nullptr, s);
+  }
+  TimedScope ts(kStLanczosSolve, s);
+  return lsolve_launch(G, B, tau, T, R, s);
 }
 
 }  // namespace
-
-size_t lanczos_partial_elems(int B) { return size_t(kGramBlocks) * 9 * B * B; }
-
-hef_status lanczos_gram(const float *v0, const float *v1, const float *y, int64_t rows, int B,
-                        double *partial, double *G, hipStream_t s) {
-  return lgram(v0, v1, y, rows, B, partial, G, s);
-}
-
-hef_status lanczos_solve(const double *G2, int B, double tau, double *T2, int32_t *drops,
-                         double *R2, hipStream_t s) {
-  TimedScope ts(kStLanczosSolve, s);
-  return lsolve_launch(G2, B, tau, T2, drops, R2, s);
-}
-
-hef_status lanczos_apply(int B, const float *v0, const float *v1, const float *y, const double *T,
-                         float *vn, int64_t rows, void *pool, int pool_type, int64_t pool_rows,
-                         int K, int col0, hipStream_t s) {
-  return lapply(B, v0, v1, y, T, vn, rows, pool, pool_type, pool_rows, K, col0, s);
-}
 
 hef_status lanczos_apply_pair(int B, const float *v0a, const float *v1a, const float *ya,
                               const double *Ta, float *vna, int64_t rowsa, const float *v0b,
@@ -774,20 +841,31 @@ size_t krylov_ws_bytes(int64_t n, int64_t m, int B) {
   a.take<double>(size_t(2) * kGramBlocks * 9 * B * B);
   a.take<double>(2 * 48 * 48);
   a.take<double>(2 * 48 * 16);
-  a.take<int32_t>(2);
   return a.mark();
 }
 
 hef_status start_block(uint64_t seed, int level, int expansion, int64_t rows, int B,
                        float *out, hipStream_t s) {
-  const uint64_t base = splitmix64(seed);
-  const uint64_t h = splitmix64(base + 2ull * uint64_t(level) + uint64_t(expansion));
-  const int64_t total = rows * B;
-  if (total == 0) return HEF_OK;
-  TimedScope ts(kStStart, s);
-  k_start<<<cdiv(total, 256), 256, 0, s>>>(h, total, out);
-  HEF_LAUNCH_CHECK();
+  return start_launch(stream_hash(seed, level, expansion), rows * B, out, 0, 0, nullptr, s);
+}
+
+hef_status start_blocks(uint64_t seed, int level, int64_t n, int64_t m, int B,
+                        const float **star, const float **clique, float *xs, float *xc,
+                        hipStream_t s) {
+  const bool ds = star && !*star, dc = clique && !*clique;
+  HEF_TRY(start_launch(stream_hash(seed, level, 0), ds ? (n + m) * B : 0, xs,
+                       stream_hash(seed, level, 1), dc ? n * B : 0, xc, s));
+  if (ds) *star = xs;
+  if (dc) *clique = xc;
   return HEF_OK;
+}
+
+hef_status start_blocks(uint64_t seed, int level, int64_t n, int64_t m, int B,
+                        const float **star, const float **clique, Arena &ws, hipStream_t s) {
+  float *xs = star && !*star ? ws.take<float>((n + m) * B) : nullptr;
+  float *xc = clique && !*clique ? ws.take<float>(n * B) : nullptr;
+  HEF_WS_CHECK(ws);
+  return start_blocks(seed, level, n, m, B, star, clique, xs, xc, s);
 }
 
 hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double tau,
@@ -804,13 +882,12 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
   double *partial = ws.take<double>(size_t(2) * kGramBlocks * 9 * B * B);
   double *G = ws.take<double>(2 * 48 * 48);
   double *Tm = ws.take<double>(2 * 48 * 16);
-  int32_t *drops = ws.take<int32_t>(2);
   HEF_WS_CHECK(ws);
   const int C = 3 * B;
   double *Gs = G, *Gc = G + C * C;
   double *ps = partial, *pc = partial + size_t(kGramBlocks) * 9 * B * B;
-  HEF_TRY(zero_async(drops, 2 * sizeof(int32_t), s));
-  HEF_TRY(zero_async(G, 2 * 48 * 48 * sizeof(double), s));
+  // (the solve reads both expansions' Grams)
+  if (!(use_star && use_clique)) HEF_TRY(zero_async(G, 2 * 48 * 48 * sizeof(double), s));
   // per-step T (and R^-1 for the adjoint)
   auto t_of = [&](int j) { return tape ? tape->T + size_t(j) * 2 * C * B : Tm; };
   auto r_of = [&](int j) { return tape ? tape->Rinv + size_t(j) * 2 * C * C : nullptr; };
@@ -848,20 +925,22 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
   const bool both = use_star && use_clique && B <= 8;
   auto t_scr = [&](int j) { return full ? tape->t + size_t(j - 1) * scr : tb; };
   auto u_of = [&](int j) { return t_scr(j) + spmm_u_offset(m, B); };
-  // V_0 = X R^-1 (no pool write)
-  if (use_star)
+  // V_0 = X R^-1 (no pool write).  The start blocks are read where they are,
+  // or copied when a caller's are not aligned for 16-byte loads.
+  const float *ys = start_star, *yc = start_clique;
+  if (use_star && (reinterpret_cast<uintptr_t>(start_star) & 15)) {
     HEF_HIP(hipMemcpyAsync(sb[2], start_star, Ns * B * sizeof(float), hipMemcpyDeviceToDevice, s));
-  if (use_clique)
-    HEF_HIP(hipMemcpyAsync(cb[2], start_clique, n * B * sizeof(float), hipMemcpyDeviceToDevice, s));
-  HEF_TRY(lgram2(B, nullptr, nullptr, use_star ? sb[2] : nullptr, Ns, ps, Gs, nullptr, nullptr,
-                 use_clique ? cb[2] : nullptr, n, pc, Gc, s));
-  {
-    TimedScope ts(kStLanczosSolve, s);
-    HEF_TRY(lsolve_launch(G, B, tau, t_of(0), drops, r_of(0), s));
+    ys = sb[2];
   }
+  if (use_clique && (reinterpret_cast<uintptr_t>(start_clique) & 15)) {
+    HEF_HIP(hipMemcpyAsync(cb[2], start_clique, n * B * sizeof(float), hipMemcpyDeviceToDevice, s));
+    yc = cb[2];
+  }
+  HEF_TRY(lgram_solve(B, nullptr, nullptr, use_star ? ys : nullptr, Ns, ps, Gs, nullptr, nullptr,
+                      use_clique ? yc : nullptr, n, pc, Gc, tau, t_of(0), r_of(0), s));
   {
-    const ApplySide as{nullptr, nullptr, sb[2], t_of(0), sb[3], use_star ? Ns : 0, 0};
-    const ApplySide ac{nullptr, nullptr, cb[2], t_of(0) + C * B, cb[3], use_clique ? n : 0, 0};
+    const ApplySide as{nullptr, nullptr, ys, t_of(0), sb[3], use_star ? Ns : 0, 0};
+    const ApplySide ac{nullptr, nullptr, yc, t_of(0) + C * B, cb[3], use_clique ? n : 0, 0};
     if (both)
       HEF_TRY(lapply_u(B, as, ac, st.s, u_of(1), nullptr, 0, K, s));
     else
@@ -880,13 +959,9 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
     float *cy = full ? tape->y_c + size_t(j - 1) * n * B : cb[2];
     HEF_TRY(spmm_apply(L, st, B, use_star ? sc : nullptr, use_star ? sy : nullptr,
                        use_clique ? cc : nullptr, use_clique ? cy : nullptr, t_scr(j), s, both));
-    HEF_TRY(lgram2(B, sp, sc, use_star ? sy : nullptr, Ns, ps, Gs, cp, cc,
-                   use_clique ? cy : nullptr, n, pc, Gc, s));
     double *Tj = t_of(j);
-    {
-      TimedScope ts(kStLanczosSolve, s);
-      HEF_TRY(lsolve_launch(G, B, tau, Tj, drops, r_of(j), s));
-    }
+    HEF_TRY(lgram_solve(B, sp, sc, use_star ? sy : nullptr, Ns, ps, Gs, cp, cc,
+                        use_clique ? cy : nullptr, n, pc, Gc, tau, Tj, r_of(j), s));
     // V_j: a tape step buffer (j < k, full tape) or the spare rolling buffer
     float *sn = (full && j < k) ? tape->v_s + size_t(j - 1) * Ns * B
                                 : spare(sb, sp, sc, full ? sb[2] : sy);

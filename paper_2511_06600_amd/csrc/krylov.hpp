@@ -67,7 +67,7 @@ struct KrylovTape {
 // block is orthonormalised against the previous two in a float64 Gram
 // metric, with the drop rule for breakdowns); writes the pool columns
 // [star steps 1..k | clique steps 1..k], b columns per step, star node rows
-// only.  `start_star` ((n+m) x B) and `start_clique` (n x B) are consumed.
+// only.  `start_star` ((n+m) x B) and `start_clique` (n x B) are only read.
 // `use_star` / `use_clique` select the expansions (the pool then holds
 // b*k columns of the one selected).  `tape` (nullable) records what the
 // adjoint needs.
@@ -76,29 +76,23 @@ hef_status krylov_pool(const Level &L, const Structure &st, int B, int k, double
                        bool use_clique, KrylovOut &out, Arena &ws, hipStream_t s,
                        const KrylovTape *tape = nullptr);
 
-// The steps of one block-Lanczos iteration, for callers that drive the
-// recurrence themselves (the adjoint):
-//  * lanczos_gram: G (3B x 3B, float64) of M = [v0 | v1 | y] (null = zero
-//    block) over `rows` rows; `partial` holds lanczos_partial_elems(B);
-//  * lanczos_solve: for two expansions' Grams G2 = [G_star | G_clique]
-//    (C x C each, C = 3B, consecutive), Cholesky with the drop rule and
-//    T2 = [T_star | T_clique], T = R^-1[:, y columns] (C x B each); R2
-//    (nullable) receives both whole R^-1 (C x C each, consecutive);
-//  * lanczos_apply: vn = M T (float64 arithmetic), optional pool write;
-//  * lanczos_apply_pair: two lanczos_apply without pool writes (sides a and
-//    b, a side with zero rows skipped) in one launch.
-size_t lanczos_partial_elems(int B);
-hef_status lanczos_gram(const float *v0, const float *v1, const float *y, int64_t rows, int B,
-                        double *partial, double *G, hipStream_t s);
-hef_status lanczos_solve(const double *G2, int B, double tau, double *T2, int32_t *drops,
-                         double *R2, hipStream_t s);
-hef_status lanczos_apply(int B, const float *v0, const float *v1, const float *y, const double *T,
-                         float *vn, int64_t rows, void *pool, int pool_type, int64_t pool_rows,
-                         int K, int col0, hipStream_t s);
+// The apply of one block-Lanczos iteration, for callers that drive the
+// recurrence themselves (the adjoint): vn = [v0 | v1 | y] T (null = zero
+// block, float64 arithmetic) of two sides, a side with zero rows skipped, in
+// one launch.
 hef_status lanczos_apply_pair(int B, const float *v0a, const float *v1a, const float *ya,
                               const double *Ta, float *vna, int64_t rowsa, const float *v0b,
                               const float *v1b, const float *yb, const double *Tb, float *vnb,
                               int64_t rowsb, int K, hipStream_t s);
+
+// The start blocks a caller did not give (star / clique point at its
+// pointers, null where the expansion is off), drawn into xs and xc, or into
+// `ws`, in one launch; the pointers are set to them.
+hef_status start_blocks(uint64_t seed, int level, int64_t n, int64_t m, int B,
+                        const float **star, const float **clique, float *xs, float *xc,
+                        hipStream_t s);
+hef_status start_blocks(uint64_t seed, int level, int64_t n, int64_t m, int B,
+                        const float **star, const float **clique, Arena &ws, hipStream_t s);
 
 // Counter-based N(0,1) start block (splitmix64 + Box-Muller in float64).
 hef_status start_block(uint64_t seed, int level, int expansion, int64_t rows, int B,

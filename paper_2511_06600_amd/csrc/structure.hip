@@ -76,11 +76,14 @@ k_validate(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   if (bad) atomicOr(flag, bad);
 }
 
-// eid[j] = the hyperedge of pin position j (same walk: 36 us to about 6 us at
-// 756k pins with a 2000-pin hyperedge among them).
+// eid[j] = the hyperedge of pin position j (same walk: 36 us to about 12 us at
+// 756k pins with a 2000-pin hyperedge among them); also clears the list
+// lengths of the long segments for the kernels after it.
 __global__ void __launch_bounds__(256)
-k_edge_ids(const int32_t *__restrict__ eptr, uint32_t *__restrict__ eid, int32_t m) {
+k_edge_ids(const int32_t *__restrict__ eptr, uint32_t *__restrict__ eid, int32_t m,
+           int32_t *__restrict__ n_big) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e < 2) n_big[e] = 0;
   const int lane = threadIdx.x & 63;
   const int64_t e0 = e - lane;
   if (e0 >= m) return;
@@ -107,20 +110,36 @@ __global__ void k_seg_bounds(const uint32_t *__restrict__ key, int64_t nnz, int3
   for (int64_t v = prev + 1; v <= cur; ++v) vptr[v] = int32_t(j);
 }
 
-// Per hyperedge: alpha_e = sqrt(w_e)/|e|, beta_e = w_e/(|e|(|e|-1)); flag
-// big; the float64 terms w_e/|e| and beta_e of the node sums.
+// Appends the ids of a workgroup's threads with `take` to list[0 .. *count),
+// one reservation per workgroup.  The long-segment lists need no order: every
+// entry is handled by itself.  (Flags, their scan and a compaction are three
+// launches per list.)
+__device__ __forceinline__ void append_ids(bool take, int32_t id, int32_t *__restrict__ list,
+                                           int32_t *__restrict__ count) {
+  __shared__ int32_t n, base;
+  if (threadIdx.x == 0) n = 0;
+  __syncthreads();
+  const int32_t at = take ? atomicAdd(&n, 1) : 0;
+  __syncthreads();
+  if (threadIdx.x == 0 && n > 0) base = atomicAdd(count, n);
+  __syncthreads();
+  if (take) list[base + at] = id;
+}
+
+// Per hyperedge: alpha_e = sqrt(w_e)/|e|, beta_e = w_e/(|e|(|e|-1)); lists
+// the long ones; the float64 terms w_e/|e| and beta_e of the node sums.
 __global__ void k_edge_scales(const int32_t *__restrict__ eptr, const float *__restrict__ w,
                               float *__restrict__ alpha, float *__restrict__ beta,
-                              int32_t *__restrict__ big, double *__restrict__ tdb,
-                              double *__restrict__ tcb, int32_t m) {
+                              int32_t *__restrict__ big, int32_t *__restrict__ n_big,
+                              double *__restrict__ tdb, double *__restrict__ tcb, int32_t m) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int32_t sz = e < m ? eptr[e + 1] - eptr[e] : 0;
+  append_ids(sz > kSmallSeg, int32_t(e), big, n_big);
   if (e >= m) return;
-  const int32_t sz = eptr[e + 1] - eptr[e];
   const double we = w ? double(w[e]) : 1.0;
   const double k = double(sz);
   alpha[e] = float(sqrt(we) / k);
   beta[e] = float(we / (k * (k - 1.0)));
-  big[e] = sz > kSmallSeg ? 1 : 0;
   tdb[e] = we / k;
   tcb[e] = we / (k * (k - 1.0));
 }
@@ -130,11 +149,12 @@ __global__ void k_edge_scales(const int32_t *__restrict__ eptr, const float *__r
 __global__ void k_node_scales(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
                               const double *__restrict__ tdb, const double *__restrict__ tcb,
                               float *__restrict__ s_out, float *__restrict__ gam,
-                              int32_t *__restrict__ big, int32_t n) {
+                              int32_t *__restrict__ big, int32_t *__restrict__ n_big, int32_t n) {
   const int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int32_t a = u < n ? vptr[u] : 0, b = u < n ? vptr[u + 1] : 0;
+  append_ids(b - a > kSmallSeg, int32_t(u), big, n_big);
   if (u >= n) return;
   double db = 0.0, cb = 0.0;
-  const int32_t a = vptr[u], b = vptr[u + 1];
   // Incidence ids are loaded four at a time before the dependent loads, and
   // the terms are added in incidence order.
   int32_t j = a;
@@ -162,7 +182,6 @@ __global__ void k_node_scales(const int32_t *__restrict__ vptr, const int32_t *_
   const double sv = db > 0.0 ? 1.0 / sqrt(db) : 0.0;
   s_out[u] = float(sv);
   gam[u] = float(sv * sv * cb);
-  big[u] = (b - a) > kSmallSeg ? 1 : 0;
 }
 
 }  // namespace
@@ -185,7 +204,6 @@ struct SortWs {
   uint32_t *tmp_k, *tmp_v, *out_k;
 };
 struct ScaleWs {
-  int32_t *flags, *scratch;
   double *tdb, *tcb;  // per-hyperedge terms of the node sums
 };
 static void carve_sort(Arena &a, int64_t nnz, SortWs &w) {
@@ -193,9 +211,7 @@ static void carve_sort(Arena &a, int64_t nnz, SortWs &w) {
   w.tmp_v = a.take<uint32_t>(nnz);
   w.out_k = a.take<uint32_t>(nnz);
 }
-static void carve_scale(Arena &a, int64_t n, int64_t m, ScaleWs &w) {
-  w.flags = a.take<int32_t>(std::max(n, m) + 1);
-  w.scratch = a.take<int32_t>(std::max(n, m) + 1);
+static void carve_scale(Arena &a, int64_t m, ScaleWs &w) {
   w.tdb = a.take<double>(std::max<int64_t>(m, 1));
   w.tcb = a.take<double>(std::max<int64_t>(m, 1));
 }
@@ -205,14 +221,13 @@ size_t structure_build_ws(int64_t n, int64_t m, int64_t nnz) {
   SortWs sw;
   ScaleWs cw;
   carve_sort(a, nnz, sw);
-  carve_scale(c, n, m, cw);
-  return std::max(a.mark() + radix_ws_bytes(nnz),
-                  c.mark() + scan_ws_bytes(std::max(n, m) + 1)) + 4096;
+  carve_scale(c, m, cw);
+  return std::max(a.mark() + radix_ws_bytes(nnz), c.mark()) + 4096;
 }
 
 hef_status validate_device(const Level &L, int32_t *flag_dev, int32_t *bad_host,
-                           hipStream_t s) {
-  HEF_TRY(zero_async(flag_dev, sizeof(int32_t), s));
+                           hipStream_t s, int clear) {
+  HEF_TRY(zero_async(flag_dev, clear * sizeof(int32_t), s));
   if (L.m > 0)
     k_validate<<<cdiv(L.m, 256), 256, 0, s>>>(L.eptr, L.pins, L.w, L.n, L.m, L.nnz, flag_dev);
   HEF_LAUNCH_CHECK();
@@ -234,7 +249,7 @@ hef_status structure_build(const Level &L, Structure &st, Arena &ws, hipStream_t
     const int bits = bits_for(n > 0 ? n - 1 : 0);
     uint32_t *eids = reinterpret_cast<uint32_t *>(st.eids);
     uint32_t *ids = radix_src(bits, w.tmp_v, eids);
-    k_edge_ids<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, ids, int32_t(m));
+    k_edge_ids<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, ids, int32_t(m), st.n_big);
     HEF_LAUNCH_CHECK();
     HEF_TRY(radix_sort_pairs(reinterpret_cast<const uint32_t *>(L.pins), ids, w.tmp_k, w.tmp_v,
                              w.out_k, eids, nnz, bits, ws, s));
@@ -242,25 +257,24 @@ hef_status structure_build(const Level &L, Structure &st, Arena &ws, hipStream_t
     HEF_LAUNCH_CHECK();
   } else {
     HEF_TRY(zero_async(st.vptr, (n + 1) * sizeof(int32_t), s));
+    HEF_TRY(zero_async(st.n_big, 2 * sizeof(int32_t), s));
   }
   ws.reset(mk);  // (the stream orders the reuse)
 
   // scales and big-segment lists
   ScaleWs w;
-  carve_scale(ws, n, m, w);
+  carve_scale(ws, m, w);
   HEF_WS_CHECK(ws);
   if (m > 0) {
-    k_edge_scales<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, L.w, st.alpha, st.beta, w.flags, w.tdb,
-                                               w.tcb, int32_t(m));
+    k_edge_scales<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, L.w, st.alpha, st.beta, st.big_e, st.n_big,
+                                               w.tdb, w.tcb, int32_t(m));
     HEF_LAUNCH_CHECK();
   }
-  HEF_TRY(compact_flags(w.flags, w.scratch, st.big_e, st.n_big, m, ws, s));
   if (n > 0) {
     k_node_scales<<<cdiv(n, 256), 256, 0, s>>>(st.vptr, st.eids, w.tdb, w.tcb, st.s, st.gam,
-                                              w.flags, int32_t(n));
+                                              st.big_v, st.n_big + 1, int32_t(n));
     HEF_LAUNCH_CHECK();
   }
-  HEF_TRY(compact_flags(w.flags, w.scratch, st.big_v, st.n_big + 1, n, ws, s));
   ws.reset(mk);
   return HEF_OK;
 }

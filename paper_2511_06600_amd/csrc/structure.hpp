@@ -18,7 +18,8 @@ struct Structure {
   //   alpha[e] = sqrt(w_e)/|e|  (star edge factor, d_b(e) = w_e)
   //   beta[e]  = w_e/(|e|(|e|-1))  (half the clique pair weight c_e)
   float *s = nullptr, *gam = nullptr, *alpha = nullptr, *beta = nullptr;
-  // Hyperedges / nodes whose segment exceeds kSmallSeg, ascending, and counts.
+  // Hyperedges / nodes whose segment exceeds kSmallSeg (in no set order), and
+  // counts.
   int32_t *big_e = nullptr, *big_v = nullptr;
   int32_t *n_big = nullptr;  // [2]: big edges, big nodes
 };
@@ -27,9 +28,10 @@ struct Structure {
 void structure_carve(Arena &a, int64_t n, int64_t m, int64_t nnz, Structure &st);
 size_t structure_build_ws(int64_t n, int64_t m, int64_t nnz);
 
-// Device validation of a CSR hypergraph; *bad_host != 0 if invalid.
+// Device validation of a CSR hypergraph; *bad_host != 0 if invalid.  Clears
+// flag_dev[0 .. clear) and uses flag_dev[0].
 hef_status validate_device(const Level &L, int32_t *flag_dev, int32_t *bad_host,
-                           hipStream_t s);
+                           hipStream_t s, int clear = 1);
 
 // Builds CSC, scales and big-segment lists for one level.
 hef_status structure_build(const Level &L, Structure &st, Arena &ws, hipStream_t s);
