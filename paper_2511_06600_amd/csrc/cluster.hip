@@ -50,30 +50,47 @@ constexpr int kRoundsPerSync = 4;
 constexpr int32_t kStUndecided = 0, kStIn = 1, kStOut = 2, kStNone = 3;
 
 // ---- a6: Eq. (15) -----------------------------------------------------------
-__global__ void k_eta_update(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
-                             const float *__restrict__ R, const float *__restrict__ eta,
-                             float *__restrict__ R_upd, uint32_t *__restrict__ keys,
-                             uint32_t *__restrict__ vals, int32_t m) {
+// A thread per hyperedge of up to kWaveSeg pins, the wave for a longer one
+// (64 pins' eta side by side, added in pin order).
+__global__ void __launch_bounds__(kT)
+k_eta_update(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+             const float *__restrict__ R, const float *__restrict__ eta,
+             float *__restrict__ R_upd, uint32_t *__restrict__ keys,
+             uint32_t *__restrict__ vals, int32_t m) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= m) return;
+  const int lane = threadIdx.x & 63;
   double acc = 0.0;
   if (eta) {
-    const int32_t a = eptr[e], b = eptr[e + 1];
-    // pins loaded four at a time ahead of the dependent loads; the terms are
+    const int32_t a = e < m ? eptr[e] : 0, b = e < m ? eptr[e + 1] : 0;
+    const bool lng = b - a > kWaveSeg;
+    // pins loaded eight at a time ahead of the dependent loads; the terms are
     // added in pin order
-    int32_t j = a;
-    for (; j + 4 <= b; j += 4) {
-      int32_t p[4];
-      float t[4];
+    if (!lng) {
+      for (int32_t j = a; j < b; j += 8) {
+        int32_t p[8];
+        float t[8];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) p[q] = pins[j + q];
+        for (int q = 0; q < 8; ++q) p[q] = pins[j + q < b ? j + q : b - 1];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) t[q] = eta[p[q]];
+        for (int q = 0; q < 8; ++q) t[q] = eta[p[q]];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc = acc + double(t[q]);
+        for (int q = 0; q < 8; ++q)
+          if (j + q < b) acc = acc + double(t[q]);
+      }
     }
-    for (; j < b; ++j) acc = acc + double(eta[pins[j]]);
+    for (uint64_t left = __ballot(lng); left != 0; left &= left - 1) {
+      const int l = __ffsll(static_cast<long long>(left)) - 1;
+      const int32_t la = __builtin_amdgcn_readlane(a, l), lb = __builtin_amdgcn_readlane(b, l);
+      double sum = 0.0;
+      for (int32_t j = la; j < lb; j += 64) {
+        const int cnt = lb - j < 64 ? lb - j : 64;
+        const double t = double(eta[pins[lane < cnt ? j + lane : lb - 1]]);
+        sum = ordered_sum(sum, t, cnt);
+      }
+      if (lane == l) acc = sum;
+    }
   }
+  if (e >= m) return;
   const float r = float(acc + double(R[e]));
   R_upd[e] = r;
   keys[e] = __float_as_uint(r);  // r >= 0: bit order = numeric order
@@ -96,9 +113,9 @@ __global__ void k_rank(const uint32_t *__restrict__ order, const float *__restri
 // ---- a7: contraction rounds --------------------------------------------------
 // packed[p] = max over undecided candidates e ∋ p of (round << 32 | ~rank[e])
 // = the newest round's smallest rank.  First checks whether e is blocked.
-// `undecided` becomes nonzero while candidates remain: a plain store of 1 by
-// one lane per wave (a same-address counter updated by every wave serialises
-// at the memory side and dominated the round).
+// `undecided` holds the last round that met candidates: a plain store of the
+// round by one lane per wave (a same-address counter updated by every wave
+// serialises at the memory side and dominated the round).
 __global__ void k_round_propose(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
                                 const int32_t *__restrict__ rank, int32_t *__restrict__ state,
                                 const int32_t *__restrict__ owner,
@@ -116,7 +133,7 @@ __global__ void k_round_propose(const int32_t *__restrict__ eptr, const int32_t 
       (static_cast<unsigned long long>(round) << 32) | uint32_t(~uint32_t(rank[e]));
   for (int32_t j = a; j < b; ++j) atomicMax(&packed[pins[j]], key);
   const uint64_t act = __ballot(1);
-  if ((threadIdx.x & 63) == __ffsll(static_cast<long long>(act)) - 1) *undecided = 1;
+  if ((threadIdx.x & 63) == __ffsll(static_cast<long long>(act)) - 1) *undecided = int32_t(round);
 }
 
 __global__ void k_round_select(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
@@ -791,22 +808,31 @@ __device__ __forceinline__ int32_t find_root(const int32_t *parent, int32_t x) {
   return x;
 }
 
-__global__ void k_uf_init(int32_t *__restrict__ parent, int32_t n) {
-  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (v < n) parent[v] = int32_t(v);
-}
-
-__global__ void k_uf_hook(const int32_t *__restrict__ best_label, int32_t *__restrict__ parent,
-                          int32_t n, int32_t *__restrict__ changed) {
+// One pass settles the forest: the roots of p and best(p) are linked, the
+// larger under the smaller, by a compare-and-swap that is tried again from
+// the roots it finds when another thread linked first.  A node's parent
+// changes once, from itself to a smaller node, so walks end, a value read
+// from before a link still leads to the same root, and every tree's root is
+// its smallest node.
+__global__ void k_uf_hook(const int32_t *__restrict__ best_label, int32_t *parent, int32_t n) {
   const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (p >= n) return;
   const int32_t c = best_label[p];
   if (c < 0) return;
-  const int32_t a = find_root(parent, int32_t(p));
-  const int32_t b = find_root(parent, c);
-  if (a != b) {
-    atomicMin(&parent[a > b ? a : b], a < b ? a : b);
-    *changed = 1;
+  auto root = [&](int32_t x) {
+    for (;;) {
+      const int32_t q = __hip_atomic_load(&parent[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (q == x) return x;
+      x = q;
+    }
+  };
+  int32_t a = root(int32_t(p)), b = root(c);
+  while (a != b) {
+    const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
+    const int32_t was = atomicCAS(&parent[hi], hi, lo);
+    if (was == hi) break;
+    a = root(was);
+    b = root(lo);
   }
 }
 
@@ -815,12 +841,27 @@ __global__ void k_uf_compress(int32_t *__restrict__ parent, int32_t n) {
   if (v < n) parent[v] = find_root(parent, int32_t(v));
 }
 
-// cluster ids of this level are provisional labels (prov[v] == v); a root is
-// a cluster whose component root is itself
-__global__ void k_root_flags(const int32_t *__restrict__ prov, const int32_t *__restrict__ parent,
-                             int32_t *__restrict__ flag, int32_t n) {
+// Flags of the level's three scans: cluster ids are provisional labels
+// (prov[v] == v), a root is a cluster whose component root is itself, and an
+// attach pair (p, best(p)) of an isolated p is kept once: a mutual pair of two
+// isolated nodes by its smaller endpoint.
+__global__ void k_level_flags(const int32_t *__restrict__ prov, const int32_t *__restrict__ parent,
+                              const int32_t *__restrict__ best_label,
+                              const int32_t *__restrict__ owner, int32_t *__restrict__ root,
+                              int32_t *__restrict__ cluster, int32_t *__restrict__ pair,
+                              int32_t n) {
   const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (v < n) flag[v] = (prov[v] == v && parent[v] == v) ? 1 : 0;
+  if (v >= n) return;
+  const bool c = prov[v] == v;
+  cluster[v] = c ? 1 : 0;
+  root[v] = (c && parent[v] == v) ? 1 : 0;
+  const int32_t b = best_label[v];
+  int32_t f = 0;
+  if (b >= 0) {
+    f = 1;
+    if (owner[b] < 0 && best_label[b] == int32_t(v) && b < v) f = 0;
+  }
+  pair[v] = f;
 }
 
 __global__ void k_labels(const int32_t *__restrict__ prov, const int32_t *__restrict__ parent,
@@ -831,24 +872,6 @@ __global__ void k_labels(const int32_t *__restrict__ prov, const int32_t *__rest
 }
 
 // ---- eta of merged groups ---------------------------------------------------
-// attach pairs: each isolated p with best b gives key (min, max); mutual
-// pairs of two isolated nodes appear twice and are kept once (the copy from
-// the smaller endpoint).  flag marks the pairs to keep.
-__global__ void k_pair_flags(const int32_t *__restrict__ best_label, const int32_t *__restrict__ owner,
-                             int32_t *__restrict__ flag, int32_t n) {
-  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const int32_t b = best_label[p];
-  int32_t f = 0;
-  if (b >= 0) {
-    f = 1;
-    // b is a node id; if b is itself isolated and picked p, the pair is
-    // counted by the smaller of the two
-    if (owner[b] < 0 && best_label[b] == int32_t(p) && b < p) f = 0;
-  }
-  flag[p] = f;
-}
-
 // One thread per group: sequential float64 sum of the group's cluster etas
 // (ascending label) then its pair distances (ascending (min, max)).
 __global__ void k_group_eta(const int32_t *__restrict__ cl_ptr, const int32_t *__restrict__ cl_lab,
@@ -858,8 +881,30 @@ __global__ void k_group_eta(const int32_t *__restrict__ cl_ptr, const int32_t *_
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= ngroups) return;
   double acc = 0.0;
-  for (int32_t i = cl_ptr[g]; i < cl_ptr[g + 1]; ++i) acc = acc + double(prov_eta[cl_lab[i]]);
-  for (int32_t i = pr_ptr[g]; i < pr_ptr[g + 1]; ++i) acc = acc + best_d[pr_node[i]];
+  // four items' loads ahead of their sums, which run in order
+  const int32_t c1 = cl_ptr[g + 1], p1 = pr_ptr[g + 1];
+  for (int32_t i = cl_ptr[g]; i < c1; i += 4) {
+    int32_t l[4];
+    float t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) l[q] = cl_lab[i + q < c1 ? i + q : c1 - 1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t[q] = prov_eta[l[q]];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i + q < c1) acc = acc + double(t[q]);
+  }
+  for (int32_t i = pr_ptr[g]; i < p1; i += 4) {
+    int32_t l[4];
+    double t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) l[q] = pr_node[i + q < p1 ? i + q : p1 - 1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t[q] = best_d[l[q]];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i + q < p1) acc = acc + t[q];
+  }
   eta_out[g] = float(acc);
 }
 
@@ -887,11 +932,6 @@ __global__ void k_items_clusters(const int32_t *__restrict__ prov, const int32_t
   if (v >= n || prov[v] != v) return;
   keys[pos[v]] = uint32_t(label[v]);
   vals[pos[v]] = uint32_t(v);
-}
-
-__global__ void k_cluster_flags(const int32_t *__restrict__ prov, int32_t *__restrict__ flag, int32_t n) {
-  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (v < n) flag[v] = prov[v] == v ? 1 : 0;
 }
 
 // pairs, step 1: key = max endpoint (low half of the (min, max) order)
@@ -1084,20 +1124,57 @@ __global__ void k_distinct(const int32_t *__restrict__ eptr, const uint32_t *__r
   cnt[e] = c >= 2 ? c : 0;
 }
 
-__global__ void k_emit(const int32_t *__restrict__ eptr, const uint32_t *__restrict__ lab_sorted,
-                       const int32_t *__restrict__ cnt, const int32_t *__restrict__ new_ptr,
-                       const int32_t *__restrict__ keep_pos, const float *__restrict__ w,
-                       int32_t *__restrict__ eptr2, int32_t *__restrict__ pins2,
-                       float *__restrict__ w2, int32_t *__restrict__ kept2, int32_t m) {
+// A thread emits a hyperedge of up to kSmallSeg pins, the wave a longer one,
+// 64 sorted labels at a time.  One thread on 2000 labels is a chain of 2000
+// loads: per level of a coarsening from 20k / 200k / 2M nodes 44 / 111 / 148
+// us, now 7 / 12 / 33 us.
+__global__ void __launch_bounds__(kT)
+k_emit(const int32_t *__restrict__ eptr, const uint32_t *__restrict__ lab_sorted,
+       const int32_t *__restrict__ cnt, const int32_t *__restrict__ new_ptr,
+       const int32_t *__restrict__ keep_pos, const float *__restrict__ w,
+       int32_t *__restrict__ eptr2, int32_t *__restrict__ pins2, float *__restrict__ w2,
+       int32_t *__restrict__ kept2, int32_t m) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= m || cnt[e] == 0) return;
-  const int32_t k = keep_pos[e];
-  int32_t o = new_ptr[e];
-  eptr2[k] = o;
-  w2[k] = w ? w[e] : 1.0f;
-  if (kept2) kept2[k] = int32_t(e);
-  for (int32_t j = eptr[e]; j < eptr[e + 1]; ++j)
-    if (j == eptr[e] || lab_sorted[j] != lab_sorted[j - 1]) pins2[o++] = int32_t(lab_sorted[j]);
+  const int lane = threadIdx.x & 63;
+  const bool on = e < m && cnt[e] != 0;
+  int32_t a = 0, b = 0, o = 0;
+  if (on) {
+    const int32_t k = keep_pos[e];
+    a = eptr[e];
+    b = eptr[e + 1];
+    o = new_ptr[e];
+    eptr2[k] = o;
+    w2[k] = w ? w[e] : 1.0f;
+    if (kept2) kept2[k] = int32_t(e);
+  }
+  const bool lng = b - a > kSmallSeg;
+  if (on && !lng) {
+    uint32_t prev = 0xFFFFFFFFu;  // (no label)
+    for (int32_t j = a; j < b; j += 8) {
+      uint32_t x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = lab_sorted[j + q < b ? j + q : b - 1];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (j + q < b && x[q] != prev) pins2[o++] = int32_t(x[q]);
+        prev = x[q];
+      }
+    }
+  }
+  for (uint64_t left = __ballot(lng); left != 0; left &= left - 1) {
+    const int l = __ffsll(static_cast<long long>(left)) - 1;
+    const int32_t la = __builtin_amdgcn_readlane(a, l), lb = __builtin_amdgcn_readlane(b, l);
+    int32_t lo = __builtin_amdgcn_readlane(o, l);
+    for (int32_t j = la; j < lb; j += 64) {
+      const int32_t at = j + lane;
+      const bool in = lb - j > lane;
+      const uint32_t x = in ? lab_sorted[at] : 0u;
+      const bool take = in && (at == la || x != lab_sorted[at - 1]);
+      const uint64_t mask = __ballot(take);
+      if (take) pins2[lo + __popcll(mask & ((uint64_t(1) << lane) - 1))] = int32_t(x);
+      lo += __popcll(mask);
+    }
+  }
 }
 
 __global__ void k_flag_pos(const int32_t *__restrict__ v, int32_t *__restrict__ f, int32_t m) {
@@ -1115,9 +1192,19 @@ __global__ void k_iota(int32_t *__restrict__ a, int64_t n) {
   if (v < n) a[v] = int32_t(v);
 }
 
-__global__ void k_set_i32(int32_t *__restrict__ p, int32_t v, int64_t n) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+// The level's per-node state: no owner, no proposal, no neighbour, a forest
+// of single nodes; and no round with candidates yet.
+__global__ void k_level_init(int64_t n, int32_t *__restrict__ owner,
+                             unsigned long long *__restrict__ packed,
+                             int32_t *__restrict__ best_label, int32_t *__restrict__ parent,
+                             int32_t *__restrict__ undecided) {
+  const int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (v == 0) *undecided = 0;
+  if (v >= n) return;
+  owner[v] = -1;
+  packed[v] = 0ull;
+  best_label[v] = -1;
+  parent[v] = int32_t(v);
 }
 
 __global__ void k_zero_u64(unsigned long long *__restrict__ p, int64_t n) {
@@ -1211,13 +1298,6 @@ size_t level_ws_bytes(int64_t n, int64_t m, int64_t nnz, int K) {
          scan_ws_bytes(std::max(std::max(n, m), nnz) + 1) + 4096;
 }
 
-__global__ void k_counts3(const int32_t *__restrict__ a, const int32_t *__restrict__ b,
-                          const int32_t *__restrict__ c, int64_t n, int32_t *__restrict__ out) {
-  out[0] = a[n];
-  out[1] = b[n];
-  out[2] = c[n];
-}
-
 hef_status read_i32(const int32_t *dev, int32_t *host, hipStream_t s) {
   HEF_HIP(hipMemcpyAsync(host, dev, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HEF_HIP(hipStreamSynchronize(s));
@@ -1257,8 +1337,7 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
   {
     TimedScope ts(kStClusterContract, s);
     if (n > 0) {
-      k_set_i32<<<g1(n), kT, 0, s>>>(w.owner, -1, n);
-      k_zero_u64<<<g1(n), kT, 0, s>>>(w.packed, n);
+      k_level_init<<<g1(n), kT, 0, s>>>(n, w.owner, w.packed, w.best_label, w.parent, w.small);
       HEF_LAUNCH_CHECK();
     }
     uint32_t round = 1;
@@ -1270,7 +1349,6 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
         return HEF_ERR_NUMERICAL;
       }
       for (int r = 0; r < kRoundsPerSync; ++r, ++round) {
-        HEF_TRY(zero_async(w.small, sizeof(int32_t), s));
         k_round_propose<<<g1(m), kT, 0, s>>>(L.eptr, L.pins, w.rank, w.state, w.owner, w.packed,
                                             round, int32_t(m), w.small);
         k_round_select<<<g1(m), kT, 0, s>>>(L.eptr, L.pins, w.rank, w.state, w.owner, w.packed,
@@ -1279,7 +1357,7 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
       }
       int32_t und = 0;
       HEF_TRY(read_i32(w.small, &und, s));
-      if (und == 0) break;
+      if (und != int32_t(round - 1)) break;  // the last round met none
     }
   }
   // ---- provisional clusters and contracted-cluster index
@@ -1291,14 +1369,11 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
   if (m > 0) {
     k_flag_in<<<g1(m), kT, 0, s>>>(w.state, w.flag, int32_t(m));
     HEF_LAUNCH_CHECK();
-    HEF_TRY(exclusive_scan_i32(w.flag, w.in_index, m, ws, s));
-    HEF_TRY(compact_flags(w.flag, w.pos, w.in_list, w.small + 1, m, ws, s));
+    HEF_TRY(scan_compact_flags(w.flag, w.in_index, w.in_list, w.small + 1, m, ws, s));
   }
   // ---- a8: local clustering
   {
     TimedScope ts(kStClusterLocal, s);
-    if (n > 0) k_set_i32<<<g1(n), kT, 0, s>>>(w.best_label, -1, n);
-    HEF_LAUNCH_CHECK();
     if (local && n > 0 && m > 0 && K > 0) {
       const int Kq = (K + 63) / 64 * 64;
       k_qh_order<<<1, 512, 0, s>>>(qh, K, w.perm, w.inv32, w.small + 3);
@@ -1308,7 +1383,7 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
       int32_t *pairs = reinterpret_cast<int32_t *>(w.v1);  // per listed node
       k_single_flag<<<g1(n), kT, 0, s>>>(w.owner, st.vptr, int32_t(n), sflag);
       HEF_LAUNCH_CHECK();
-      HEF_TRY(compact_flags(sflag, reinterpret_cast<int32_t *>(w.k0), slist, w.small + 7, n, ws, s));
+      HEF_TRY(scan_compact_flags(sflag, reinterpret_cast<int32_t *>(w.k0), slist, w.small + 7, n, ws, s));
       if (pool_type == kPoolF32) {
         k_centroids<kPoolF32><<<2048, kT, 0, s>>>(L.eptr, L.pins, w.in_list, w.small + 1, pool, K, w.cent);
         k_cperm<kPoolF32><<<cdiv(n, kT / 64), kT, 0, s>>>(w.prov, w.owner, w.in_index, w.cent, pool, K, Kq,
@@ -1338,26 +1413,9 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
     }
     // union-find over {p, best(p)}
     if (n > 0) {
-      k_uf_init<<<g1(n), kT, 0, s>>>(w.parent, int32_t(n));
+      k_uf_hook<<<g1(n), kT, 0, s>>>(w.best_label, w.parent, int32_t(n));
+      k_uf_compress<<<g1(n), kT, 0, s>>>(w.parent, int32_t(n));
       HEF_LAUNCH_CHECK();
-      // two hook + compress rounds per host check (a settled forest is
-      // left unchanged by further rounds)
-      for (int it = 0; it < 64; it += 2) {
-        HEF_TRY(zero_async(w.small + 2, sizeof(int32_t), s));
-        k_uf_hook<<<g1(n), kT, 0, s>>>(w.best_label, w.parent, int32_t(n), w.small + 2);
-        k_uf_compress<<<g1(n), kT, 0, s>>>(w.parent, int32_t(n));
-        HEF_TRY(zero_async(w.small + 2, sizeof(int32_t), s));
-        k_uf_hook<<<g1(n), kT, 0, s>>>(w.best_label, w.parent, int32_t(n), w.small + 2);
-        k_uf_compress<<<g1(n), kT, 0, s>>>(w.parent, int32_t(n));
-        HEF_LAUNCH_CHECK();
-        int32_t ch = 0;
-        HEF_TRY(read_i32(w.small + 2, &ch, s));
-        if (!ch) break;
-        if (it == 62) {
-          set_error("union-find did not settle");
-          return HEF_ERR_NUMERICAL;
-        }
-      }
     }
   }
   // ---- canonical labels (rank of each group's smallest node id)
@@ -1371,17 +1429,13 @@ hef_status cluster_one_level(const Level &L, const Structure &st, const float *R
     int32_t *pos_pr = reinterpret_cast<int32_t *>(w.packed);
     int32_t ncl = 0, npr = 0;
     if (n > 0) {
-      k_root_flags<<<g1(n), kT, 0, s>>>(w.prov, w.parent, w.flag, int32_t(n));
+      int32_t *root = reinterpret_cast<int32_t *>(w.k0), *clu = reinterpret_cast<int32_t *>(w.v0);
+      k_level_flags<<<g1(n), kT, 0, s>>>(w.prov, w.parent, w.best_label, w.owner, root, clu,
+                                         w.flag, int32_t(n));
       HEF_LAUNCH_CHECK();
-      HEF_TRY(exclusive_scan_i32(w.flag, w.pos, n, ws, s));
+      HEF_TRY(exclusive_scan3_i32({root, clu, w.flag}, {w.pos, pos_cl, pos_pr}, w.small + 4, n, ws,
+                                  s));
       k_labels<<<g1(n), kT, 0, s>>>(w.prov, w.parent, w.pos, label_out, int32_t(n));
-      k_cluster_flags<<<g1(n), kT, 0, s>>>(w.prov, w.flag, int32_t(n));
-      HEF_LAUNCH_CHECK();
-      HEF_TRY(exclusive_scan_i32(w.flag, pos_cl, n, ws, s));
-      k_pair_flags<<<g1(n), kT, 0, s>>>(w.best_label, w.owner, w.flag, int32_t(n));
-      HEF_LAUNCH_CHECK();
-      HEF_TRY(exclusive_scan_i32(w.flag, pos_pr, n, ws, s));
-      k_counts3<<<1, 1, 0, s>>>(w.pos, pos_cl, pos_pr, n, w.small + 4);
       HEF_LAUNCH_CHECK();
       int32_t c3[3] = {0, 0, 0};
       HEF_HIP(hipMemcpyAsync(c3, w.small + 4, sizeof(c3), hipMemcpyDeviceToHost, s));

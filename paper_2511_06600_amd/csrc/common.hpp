@@ -83,9 +83,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Map a launched block index to a logical one so that each of the 8 XCDs of
-// an MI355X (which receive blocks round-robin) walks a contiguous range of
-// logical blocks; neighbouring work then shares its XCD's L2.
 // Lane l's value of v on every lane (l the same on all lanes: a scalar
 // broadcast, no LDS round trip).
 __device__ __forceinline__ double readlane_f64(double v, int l) {
@@ -95,6 +92,17 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
   return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
 
+// acc + x(lane 0) + x(lane 1) + ... + x(lane cnt - 1), added in that order
+// (cnt the same on all lanes): a sequential sum whose terms a wave loaded side
+// by side.
+__device__ __forceinline__ double ordered_sum(double acc, double x, int cnt) {
+  for (int l = 0; l < cnt; ++l) acc = acc + readlane_f64(x, l);
+  return acc;
+}
+
+// Map a launched block index to a logical one so that each of the 8 XCDs of
+// an MI355X (which receive blocks round-robin) walks a contiguous range of
+// logical blocks; neighbouring work then shares its XCD's L2.
 __device__ __forceinline__ int64_t xcd_block(int64_t bid, int64_t nblocks) {
   constexpr int64_t kXcd = 8;
   int64_t per = nblocks / kXcd;

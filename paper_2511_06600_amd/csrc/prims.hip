@@ -29,8 +29,16 @@ __device__ __forceinline__ int32_t block_inclusive(int32_t x, int tid, int32_t *
   return x + add;
 }
 
+// Up to three arrays of one length per launch (blockIdx.y).
+struct Scan3 {
+  const int32_t *in[3];
+  int32_t *out[3], *sums[3], *total[3];
+};
+
 __global__ void __launch_bounds__(kScanThreads)
-k_scan_tiles(const int32_t *in, int32_t *out, int32_t *tile_sums, int64_t n) {
+k_scan_tiles(const Scan3 S, int64_t n) {
+  const int32_t *in = S.in[blockIdx.y];
+  int32_t *out = S.out[blockIdx.y], *tile_sums = S.sums[blockIdx.y];
   __shared__ int32_t sh[kScanThreads];
   const int tid = threadIdx.x;
   const int64_t base = int64_t(blockIdx.x) * kScanTile + int64_t(tid) * kScanItems;
@@ -100,13 +108,13 @@ k_scan_add(int32_t *out, const int32_t *tile_off, int64_t n) {
 // kFinishTiles tiles this replaces the two kernels above: re-reading the
 // earlier sums (at most kFinishTiles^2 / 2 reads, from L2) costs less than a
 // launch.
-// COMPACT: the items were flags; idx[position] = i for every set flag (the
-// positions need not be stored) and *total = their number.
+// COMPACT: the items were flags; also idx[position] = i for every set flag.
 constexpr int64_t kFinishTiles = 2048;
 template <bool COMPACT>
 __global__ void __launch_bounds__(kScanThreads)
-k_scan_finish(int32_t *out, const int32_t *tile_sums, int64_t n, int64_t ntiles,
-              const int32_t *flag, int32_t *idx, int32_t *total) {
+k_scan_finish(const Scan3 S, int64_t n, int64_t ntiles, int32_t *idx) {
+  int32_t *out = S.out[blockIdx.y];
+  const int32_t *tile_sums = S.sums[blockIdx.y], *flag = S.in[blockIdx.y];
   __shared__ int32_t red[kScanThreads / 64];
   const int tid = threadIdx.x;
   const int64_t t = blockIdx.x;
@@ -123,14 +131,13 @@ k_scan_finish(int32_t *out, const int32_t *tile_sums, int64_t n, int64_t ntiles,
   for (int i = tid; i < kScanTile; i += kScanThreads) {
     const int64_t q = base + i;
     if (q < n) {
-      if constexpr (COMPACT) {
-        if (flag[q]) idx[out[q] + add] = int32_t(q);
-      } else {
-        out[q] += add;
-      }
+      const int32_t at = out[q] + add;
+      out[q] = at;
+      if constexpr (COMPACT)
+        if (flag[q]) idx[at] = int32_t(q);
     }
   }
-  if (t == ntiles - 1 && tid == 0) *total = add + tile_sums[t];
+  if (t == ntiles - 1 && tid == 0) *S.total[blockIdx.y] = add + tile_sums[t];
 }
 
 // Scan (COMPACT: compaction of flags, as above) of at most kScanOne items in
@@ -141,7 +148,9 @@ constexpr int kScanOneItems = 16;
 constexpr int kScanOne = kScanOneThreads * kScanOneItems;
 template <bool COMPACT>
 __global__ void __launch_bounds__(kScanOneThreads)
-k_scan_one(const int32_t *in, int32_t *out, int n, int32_t *total) {
+k_scan_one(const Scan3 S, int n, int32_t *idx) {
+  const int32_t *in = S.in[blockIdx.x];
+  int32_t *out = S.out[blockIdx.x], *total = S.total[blockIdx.x];
   __shared__ int32_t wtot[kScanOneThreads / 64];
   // the items pass through LDS both ways: coalesced in global memory, a run
   // of 16 per thread in between (a pad word per 32, so that runs 16 apart
@@ -170,20 +179,16 @@ k_scan_one(const int32_t *in, int32_t *out, int n, int32_t *total) {
 #pragma unroll
   for (int i = 0; i < kScanOneItems; ++i) {
     const int j = base + i;
-    if constexpr (COMPACT) {
-      if (v[i]) out[at] = j;
-    } else {
-      buf[j + (j >> 5)] = at;
-    }
+    if constexpr (COMPACT)
+      if (v[i]) idx[at] = j;
+    buf[j + (j >> 5)] = at;
     at += v[i];
   }
-  if constexpr (!COMPACT) {
-    __syncthreads();
+  __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kScanOneItems; ++i) {
-      const int j = i * kScanOneThreads + tid;
-      if (j < n) out[j] = buf[j + (j >> 5)];
-    }
+  for (int i = 0; i < kScanOneItems; ++i) {
+    const int j = i * kScanOneThreads + tid;
+    if (j < n) out[j] = buf[j + (j >> 5)];
   }
   if (tid == kScanOneThreads - 1) *total = incl;
 }
@@ -203,7 +208,9 @@ constexpr int64_t kRadixSmallN = int64_t(1) << 20;
 constexpr int kRadixTile = kRadixThreads * kRadixRounds;
 constexpr int kRadixTileSmall = kRadixThreads * kRadixRoundsSmall;
 
-inline int64_t radix_tile(int64_t n) { return n <= kRadixSmallN ? kRadixTileSmall : kRadixTile; }
+inline int64_t radix_tile(int64_t n, bool lean) {
+  return n <= kRadixSmallN && !lean ? kRadixTileSmall : kRadixTile;
+}
 
 template <int ROUNDS>
 __global__ void __launch_bounds__(kRadixThreads)
@@ -429,11 +436,9 @@ k_radix_one(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *
   }
 }
 
-__global__ void k_compact(const int32_t *flag, const int32_t *pos, int32_t *idx_out,
-                          int32_t *count_dev, int64_t n) {
+__global__ void k_compact(const int32_t *flag, const int32_t *pos, int32_t *idx_out, int64_t n) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n && flag[i]) idx_out[pos[i]] = int32_t(i);
-  if (i == 0) *count_dev = pos[n];
 }
 
 template <int QG>
@@ -509,42 +514,74 @@ hef_status reduce_cols_f64(const double *in, int64_t nrows, int64_t ncols, doubl
 
 size_t scan_ws_bytes(int64_t n) {
   Arena a;
-  a.take<int32_t>(cdiv(n, kScanTile) + 1);
+  for (int i = 0; i < 3; ++i) a.take<int32_t>(cdiv(n, kScanTile) + 1);
   return a.mark();
 }
 
-hef_status exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Arena &ws,
-                              hipStream_t s) {
+namespace {
+
+// Exclusive scans of `count` arrays of n items each; with idx (count = 1) also
+// the compaction.  More tiles than kFinishTiles take the separate scan of the
+// tile sums, an array at a time.
+hef_status scan_run(Scan3 S, int count, int64_t n, int32_t *idx, Arena &ws, hipStream_t s) {
+  if (n <= kScanOne) {
+    if (idx)
+      k_scan_one<true><<<count, kScanOneThreads, 0, s>>>(S, int(n), idx);
+    else
+      k_scan_one<false><<<count, kScanOneThreads, 0, s>>>(S, int(n), nullptr);
+    HEF_LAUNCH_CHECK();
+    return HEF_OK;
+  }
   const int64_t ntiles = cdiv(n, kScanTile);
   const size_t mk = ws.mark();
-  int32_t *sums = ws.take<int32_t>(ntiles + 1);
+  for (int i = 0; i < count; ++i) S.sums[i] = ws.take<int32_t>(ntiles + 1);
   HEF_WS_CHECK(ws);
-  if (n == 0) {
-    HEF_TRY(zero_async(out, sizeof(int32_t), s));
-    ws.reset(mk);
-    return HEF_OK;
-  }
-  if (n <= kScanOne) {
-    k_scan_one<false><<<1, kScanOneThreads, 0, s>>>(in, out, int(n), out + n);
-    HEF_LAUNCH_CHECK();
-    ws.reset(mk);
-    return HEF_OK;
-  }
-  k_scan_tiles<<<ntiles, kScanThreads, 0, s>>>(in, out, sums, n);
+  const dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(count));
+  k_scan_tiles<<<grid, kScanThreads, 0, s>>>(S, n);
   if (ntiles <= kFinishTiles) {
-    k_scan_finish<false><<<ntiles, kScanThreads, 0, s>>>(out, sums, n, ntiles, nullptr, nullptr,
-                                                         out + n);
+    if (idx)
+      k_scan_finish<true><<<grid, kScanThreads, 0, s>>>(S, n, ntiles, idx);
+    else
+      k_scan_finish<false><<<grid, kScanThreads, 0, s>>>(S, n, ntiles, nullptr);
   } else {
-    k_scan_sums<<<1, 1024, 0, s>>>(sums, ntiles, out + n);
-    k_scan_add<<<ntiles, kScanThreads, 0, s>>>(out, sums, n);
+    for (int i = 0; i < count; ++i) {
+      k_scan_sums<<<1, 1024, 0, s>>>(S.sums[i], ntiles, S.total[i]);
+      k_scan_add<<<ntiles, kScanThreads, 0, s>>>(S.out[i], S.sums[i], n);
+    }
+    if (idx) k_compact<<<cdiv(n, 256), 256, 0, s>>>(S.in[0], S.out[0], idx, n);
   }
   HEF_LAUNCH_CHECK();
   ws.reset(mk);
   return HEF_OK;
 }
 
-size_t radix_ws_bytes(int64_t n) {
-  const int64_t nb = cdiv(n, radix_tile(n));
+}  // namespace
+
+hef_status exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Arena &ws,
+                              hipStream_t s) {
+  if (n == 0) return zero_async(out, sizeof(int32_t), s);
+  Scan3 S{};
+  S.in[0] = in;
+  S.out[0] = out;
+  S.total[0] = out + n;
+  return scan_run(S, 1, n, nullptr, ws, s);
+}
+
+hef_status exclusive_scan3_i32(const std::array<const int32_t *, 3> &in,
+                               const std::array<int32_t *, 3> &out, int32_t *totals, int64_t n,
+                               Arena &ws, hipStream_t s) {
+  if (n == 0) return zero_async(totals, 3 * sizeof(int32_t), s);
+  Scan3 S{};
+  for (int i = 0; i < 3; ++i) {
+    S.in[i] = in[i];
+    S.out[i] = out[i];
+    S.total[i] = totals + i;
+  }
+  return scan_run(S, 3, n, nullptr, ws, s);
+}
+
+size_t radix_ws_bytes(int64_t n, bool lean) {
+  const int64_t nb = cdiv(n, radix_tile(n, lean));
   Arena a;
   a.take<int32_t>(nb * kBins + 1);
   return a.mark() + scan_ws_bytes(nb * kBins) + 512;
@@ -552,7 +589,7 @@ size_t radix_ws_bytes(int64_t n) {
 
 hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
                             uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n,
-                            int bits, Arena &ws, hipStream_t s) {
+                            int bits, Arena &ws, hipStream_t s, bool lean) {
   if (n == 0) return HEF_OK;
   const int passes = (bits + kRadixBits - 1) / kRadixBits;
   if (n <= kOneThreads * kOneRounds) {
@@ -564,8 +601,8 @@ hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32
     HEF_LAUNCH_CHECK();
     return HEF_OK;
   }
-  const bool small = n <= kRadixSmallN;
-  const int64_t nb = cdiv(n, radix_tile(n));
+  const bool small = radix_tile(n, lean) == kRadixTileSmall;
+  const int64_t nb = cdiv(n, radix_tile(n, lean));
   const size_t mk = ws.mark();
   int32_t *hist = ws.take<int32_t>(nb * kBins + 1);
   HEF_WS_CHECK(ws);
@@ -585,7 +622,11 @@ hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32
     else
       k_radix_hist<kRadixRounds><<<nb, kRadixThreads, 0, s>>>(ka, n, shift, hist, int(nb));
     if (tsum) {
-      k_scan_tiles<<<htiles, kScanThreads, 0, s>>>(hist, hist, tsum, nb * kBins);
+      Scan3 S{};
+      S.in[0] = hist;
+      S.out[0] = hist;
+      S.sums[0] = tsum;
+      k_scan_tiles<<<htiles, kScanThreads, 0, s>>>(S, nb * kBins);
     } else {
       HEF_TRY(exclusive_scan_i32(hist, hist, nb * kBins, ws, s));
     }
@@ -603,32 +644,14 @@ hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32
   return HEF_OK;
 }
 
-hef_status compact_flags(const int32_t *flag, int32_t *scratch, int32_t *idx_out,
-                         int32_t *count_dev, int64_t n, Arena &ws, hipStream_t s) {
-  if (n == 0) {
-    HEF_TRY(zero_async(count_dev, sizeof(int32_t), s));
-    return HEF_OK;
-  }
-  if (n <= kScanOne) {
-    k_scan_one<true><<<1, kScanOneThreads, 0, s>>>(flag, idx_out, int(n), count_dev);
-    HEF_LAUNCH_CHECK();
-    return HEF_OK;
-  }
-  const int64_t ntiles = cdiv(n, kScanTile);
-  if (ntiles <= kFinishTiles) {
-    const size_t mk = ws.mark();
-    int32_t *sums = ws.take<int32_t>(ntiles + 1);
-    HEF_WS_CHECK(ws);
-    k_scan_tiles<<<ntiles, kScanThreads, 0, s>>>(flag, scratch, sums, n);
-    k_scan_finish<true><<<ntiles, kScanThreads, 0, s>>>(scratch, sums, n, ntiles, flag, idx_out,
-                                                        count_dev);
-    ws.reset(mk);
-  } else {
-    HEF_TRY(exclusive_scan_i32(flag, scratch, n, ws, s));
-    k_compact<<<cdiv(n, 256), 256, 0, s>>>(flag, scratch, idx_out, count_dev, n);
-  }
-  HEF_LAUNCH_CHECK();
-  return HEF_OK;
+hef_status scan_compact_flags(const int32_t *flag, int32_t *pos, int32_t *idx_out,
+                              int32_t *count_dev, int64_t n, Arena &ws, hipStream_t s) {
+  if (n == 0) return zero_async(count_dev, sizeof(int32_t), s);
+  Scan3 S{};
+  S.in[0] = flag;
+  S.out[0] = pos;
+  S.total[0] = count_dev;
+  return scan_run(S, 1, n, idx_out, ws, s);
 }
 
 }  // namespace hef

@@ -2,19 +2,28 @@
 // sort of (key, value) pairs, stream compaction.  All are deterministic.
 #pragma once
 
+#include <array>
+
 #include "common.hpp"
 
 namespace hef {
 
-// Workspace bytes for exclusive_scan over `n` elements.
+// Workspace bytes for a scan over `n` elements (three of them together).
 size_t scan_ws_bytes(int64_t n);
 // out[i] = sum_{j<i} in[j]; out[n] = total (out has n+1 entries).
 // `in` and `out` may alias.
 hef_status exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n,
                               Arena &ws, hipStream_t s);
 
-// Workspace bytes for radix_sort_pairs over `n` items.
-size_t radix_ws_bytes(int64_t n);
+// Three scans of n items each in the launches of one; out[i] holds n entries
+// and totals[i] the sum (consecutive, so that one copy reads them).
+hef_status exclusive_scan3_i32(const std::array<const int32_t *, 3> &in,
+                               const std::array<int32_t *, 3> &out, int32_t *totals, int64_t n,
+                               Arena &ws, hipStream_t s);
+
+// Workspace bytes for radix_sort_pairs over `n` items (about n bytes up to
+// 2^20 items, n / 4 above or with `lean`, which keeps to the large tiles).
+size_t radix_ws_bytes(int64_t n, bool lean = false);
 // Stable LSD radix sort of n (key, value) pairs by the low `bits` bits of
 // the keys, 8 bits a pass: src -> out, with tmp as the other ping-pong buffer
 // (both n items; the last pass writes out, so nothing is copied at the end).
@@ -23,16 +32,16 @@ size_t radix_ws_bytes(int64_t n);
 // it is odd (radix_src picks them).
 hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
                             uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n,
-                            int bits, Arena &ws, hipStream_t s);
+                            int bits, Arena &ws, hipStream_t s, bool lean = false);
 template <class T>
 inline T radix_src(int bits, T tmp, T out) {
   return ((bits + 7) / 8) % 2 == 0 ? out : tmp;
 }
 
 // idx_out[0..count) = ascending indices i < n with flag[i] = 1 (flags are 0
-// or 1); *count_dev = count.  Uses `scratch` of n+1 int32.
-hef_status compact_flags(const int32_t *flag, int32_t *scratch, int32_t *idx_out,
-                         int32_t *count_dev, int64_t n, Arena &ws, hipStream_t s);
+// or 1), pos[i] = the number of set flags before i; *count_dev = count.
+hef_status scan_compact_flags(const int32_t *flag, int32_t *pos, int32_t *idx_out,
+                              int32_t *count_dev, int64_t n, Arena &ws, hipStream_t s);
 
 // out[c] = sum_r in[r * ncols + c] (float64) in a fixed order that does not
 // depend on timing: 32 row lanes per column each sum every 32nd row (eight

@@ -7,6 +7,11 @@ namespace hef {
 
 // Segments longer than this go to the wave-per-segment kernels.
 constexpr int kSmallSeg = 32;
+// Sequential sums over a segment longer than this are taken by the whole wave
+// (64 terms loaded side by side, added in order); up to here a thread with
+// eight loads in flight is faster, since a wave's 64 segments are often long
+// together (hubs with neighbouring ids at coarse levels).
+constexpr int kWaveSeg = 256;
 
 struct Structure {
   // CSC incidence (node -> hyperedges), hyperedges ascending per node.

@@ -239,3 +239,39 @@ def test_level_maps_at_scan_sizes(n):
     assert nc == ref.n_clusters
     assert np.array_equal(cl.cpu().numpy(), ref.label)
     assert np.array_equal(eta.cpu().numpy(), ref.eta.astype(np.float32))
+
+
+@pytest.mark.parametrize("size", [32, 33, 64, 65, 256, 257, 700])
+def test_level_and_rebuild_with_long_segments(size):
+    """Segments around the lengths at which a wave takes over: the level (its
+    Eq. (15) sums run in pin order), the attach chains of the union-find and
+    the coarse hypergraph against the oracle, bit for bit."""
+    from oracle import clustering as ocl
+    say(f"case: long segments size={size}")
+    n = 1500
+    sizes = [size, 3, size + 1] + _mixed_sizes(1200, size) + [size]
+    h = _hg(n, sizes, size)
+    # a hub in `size` hyperedges more
+    rng = np.random.default_rng(size)
+    extra = np.stack([np.zeros(size, np.int64), 1 + rng.choice(n - 1, size, replace=False)], 1)
+    eptr = np.concatenate([h.eptr, h.eptr[-1] + 2 * np.arange(1, size + 1)])
+    pins = np.concatenate([h.pins, extra.reshape(-1)]).astype(np.int32)
+    m = len(eptr) - 1
+    h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins, w=np.ones(m, np.float32))
+    K = 8
+    R = rng.random(m).astype(np.float32)
+    eta = (0.05 * rng.random(n)).astype(np.float32)
+    chi = (0.1 * rng.standard_normal((n, K))).astype(np.float32)
+    qh = rng.random(K) + 0.5
+    dh = to_device(h)
+    cl, nc, eo = hef.cluster_level(dh, hef.Params(k=4, b=1), torch.as_tensor(R, device="cuda"),
+                                   torch.as_tensor(eta, device="cuda"),
+                                   torch.as_tensor(chi, device="cuda"),
+                                   torch.as_tensor(qh, device="cuda"))
+    ref = ocl.cluster_level(n, m, h.eptr, h.pins, R, eta, chi, qh, 0.5, True)
+    assert nc == ref.n_clusters and np.array_equal(cl.cpu().numpy(), ref.label)
+    assert np.array_equal(eo.cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
+    out, kept = hef.rebuild(dh, cl, nc)
+    m2, ep, pn, w2, kp = ocl.rebuild(m, h.eptr, h.pins, h.w, ref.label)
+    assert out.m == m2 and np.array_equal(out.eptr.cpu().numpy(), ep)
+    assert np.array_equal(out.pins.cpu().numpy(), pn) and np.array_equal(kept.cpu().numpy(), kp)
