@@ -92,6 +92,35 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
   return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
 
+// A Cholesky pivot: root = sqrt(d) and inv, its reciprocal to within an ulp,
+// for normal d far from the ends of the exponent range (pivots here are sums
+// of squares of float32 values, so they lie within 1e-91 .. 1e90).  Goldschmidt
+// steps from the hardware's reciprocal square root, with two residual
+// corrections of the root; root is correctly rounded, as sqrt() is.  The
+// chain is 13 operations; sqrt() and a division by it are about 35 with their
+// range checks.
+struct Pivot {
+  double root, inv;
+};
+__device__ __forceinline__ Pivot pivot_of(double d) {
+  const double y = __builtin_amdgcn_rsq(d);
+  double g = d * y, h = 0.5 * y;
+  const double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  g = __builtin_fma(__builtin_fma(-g, g, d), h, g);
+  g = __builtin_fma(__builtin_fma(-g, g, d), h, g);
+  double i = h + h;
+  i = __builtin_fma(__builtin_fma(-g, i, 1.0), i, i);
+  return {g, i};
+}
+// x / p.root, correctly rounded (Markstein: a quotient within an ulp or two,
+// its exact residual, one fused correction).
+__device__ __forceinline__ double div_pivot(double x, const Pivot &p) {
+  const double q = x * p.inv;
+  return __builtin_fma(__builtin_fma(-q, p.root, x), p.inv, q);
+}
+
 // acc + x(lane 0) + x(lane 1) + ... + x(lane cnt - 1), added in that order
 // (cnt the same on all lanes): a sequential sum whose terms a wave loaded side
 // by side.

@@ -53,7 +53,9 @@ constexpr int kMaxPB = 16;    // 32-column blocks of the widest pool (K <= 512)
 // factorisation of the whole panel.  The two run as a pipeline: the first
 // wave publishes column j of the block (multiples, pivot, keep) in LDS while
 // the rows below take column j - 1, one barrier per column.  Workgroup 0
-// also writes the diagonal block, keep and rho.
+// also writes the diagonal block, keep and rho.  15.0 us a panel (16.5 with
+// sqrt() and a division per entry); the rows after the whole block, with no
+// barrier per column, 23 us, a barrier per four columns 18.7.
 constexpr int kCT = 256;        // panel threads
 constexpr int kCR = kCT - 64;   // rows below the block per workgroup
 
@@ -65,7 +67,7 @@ k_chol_panel(const double *__restrict__ A, const double *__restrict__ G, int K, 
              double tau, double *__restrict__ LT, int32_t *__restrict__ keep,
              const int32_t *__restrict__ force_keep, double *__restrict__ rho) {
   __shared__ double Ln[kPW][kPS];  // the block's L (pivot on the diagonal)
-  __shared__ double s_piv[kPW];
+  __shared__ Pivot s_piv[kPW];
   __shared__ int s_kp[kPW];
   const int t = threadIdx.x;
   const int w = FULL ? kPW : (K - c0 < kPW ? K - c0 : kPW);
@@ -97,8 +99,9 @@ k_chol_panel(const double *__restrict__ A, const double *__restrict__ G, int K, 
     const double rf = readlane_f64(ref, jj);
     int kp = (rf > 0.0 && d > tau * tau * rf) ? 1 : 0;
     if (!__builtin_amdgcn_readlane(frc, jj)) kp = 0;
-    const double piv = kp ? sqrt(d) : 0.0;
-    const double lv = (kp && r > jj && r < w) ? x[jj] / piv : 0.0;
+    const Pivot pv = pivot_of(kp ? d : 1.0);
+    const double piv = kp ? pv.root : 0.0;
+    const double lv = (kp && r > jj && r < w) ? div_pivot(x[jj], pv) : 0.0;
     if (r == jj) {
       dkeep = d;
       pkeep = piv;
@@ -109,7 +112,7 @@ k_chol_panel(const double *__restrict__ A, const double *__restrict__ G, int K, 
     x[jj] = r == jj ? piv : lv;
     if (t < kPW) Ln[t][jj] = t >= jj ? x[jj] : 0.0;
     if (t == 0) {
-      s_piv[jj] = piv;
+      s_piv[jj] = pv;
       s_kp[jj] = kp;
     }
     if (kp) {
@@ -121,7 +124,7 @@ k_chol_panel(const double *__restrict__ A, const double *__restrict__ G, int K, 
   // column jj for a row below the block (the other waves)
   auto row_step = [&](int jj) __attribute__((always_inline)) {
     const int kp = s_kp[jj];
-    x[jj] = kp ? x[jj] / s_piv[jj] : 0.0;
+    x[jj] = kp ? div_pivot(x[jj], s_piv[jj]) : 0.0;
     if (kp) {
 #pragma unroll
       for (int tc = jj + 1; tc < kPW; ++tc)
