@@ -27,7 +27,7 @@
 // passes per million triples), and one thread per node walked its triples
 // through two indirections: 9.9 ms for the 16M triples of a 200k-node
 // netlist, the node walk itself bound by the longest node's serial chain.  Now
-// 0.68 ms: bound by the latency of the segment and pin loads of the middle and
+// 0.63 ms: bound by the latency of the segment and pin loads of the middle and
 // big classes.
 #include <cmath>
 
@@ -42,7 +42,7 @@ constexpr int kRT = 256;
 constexpr int kRateSmall = 64, kRateMid = 512;  // largest bound(p) of a class
 constexpr int kRateNG = 16;                     // nodes per workgroup of k_rate_small
 constexpr int kRateBigT = 4096;                 // table of the big class
-constexpr int kRateFill = kRateBigT / 2;        // entries a pass aims at
+constexpr int kRateFill = kRateBigT * 3 / 4;    // entries a pass aims at
 
 // flag |= 1 if an R value is not finite
 __global__ void k_rate_check(const float *__restrict__ R, int64_t m, int32_t *__restrict__ flag) {
@@ -109,16 +109,29 @@ rate_node(int32_t p, int32_t v0, int32_t deg, int gl, const int32_t *__restrict_
       eb = eptr[e + 1];
       et = rate_term(w, R, shift, e);
     }
+    // (the first G pins of the next hyperedge load during the current one; p
+    // stands for no pin)
     const int nt = deg - t0 < G ? int(deg - t0) : G;
+    int32_t a = __shfl(ea, 0, G), b = __shfl(eb, 0, G);
+    int32_t qn = a + gl < b ? pins[a + gl] : p;
     for (int t = 0; t < nt; ++t) {
-      const int32_t a = __shfl(ea, t, G), b = __shfl(eb, t, G);
       const double term = __shfl(et, t, G);
-      for (int64_t j = a + gl; j < b; j += G) {
-        const int32_t q = pins[j];
+      const int32_t b0 = b;
+      int64_t j = int64_t(a) + gl;
+      int32_t q = qn;
+      if (t + 1 < nt) {
+        a = __shfl(ea, t + 1, G);
+        b = __shfl(eb, t + 1, G);
+        qn = a + gl < b ? pins[a + gl] : p;
+      }
+      while (j < b0) {
+        const int32_t q1 = j + G < b0 ? pins[j + G] : p;
         if (q != p) {
           const int h = rate_slot<T>(key, q);
           if (h >= 0) acc[h] += term;
         }
+        q = q1;
+        j += G;
       }
       wave_sync();
     }
@@ -177,21 +190,25 @@ k_rate_small(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
                   rating);
 }
 
-__global__ void __launch_bounds__(kRT)
+// kMidSplit single-wave workgroups share a slice, so that a table is given
+// back as soon as its wave is done.
+constexpr int kMidSplit = 4;
+
+__global__ void __launch_bounds__(64)
 k_rate_mid(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
            const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
            const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
            const float *__restrict__ w, const float *__restrict__ R, double shift,
            int32_t *__restrict__ best, double *__restrict__ rating) {
-  constexpr int T = 2 * kRateMid, NW = kRT / 64;
-  __shared__ int32_t key[NW][T];
-  __shared__ double acc[NW][T];
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int32_t cnt = counts[2 * int64_t(blockIdx.x)];  // one slice per workgroup
-  for (int32_t i = wv; i < cnt; i += NW) {
-    const int32_t p = list[int64_t(blockIdx.x) * kRateNG + i];
+  constexpr int T = 2 * kRateMid;
+  __shared__ int32_t key[T];
+  __shared__ double acc[T];
+  const int64_t slice = blockIdx.x / kMidSplit;
+  const int32_t cnt = counts[2 * slice];
+  for (int32_t i = blockIdx.x % kMidSplit; i < cnt; i += kMidSplit) {
+    const int32_t p = list[slice * kRateNG + i];
     const int32_t v0 = vptr[p], deg = vptr[p + 1] - v0;
-    rate_node<64, T>(p, v0, deg, lane, eids, eptr, pins, w, R, shift, key[wv], acc[wv], best,
+    rate_node<64, T>(p, v0, deg, int(threadIdx.x), eids, eptr, pins, w, R, shift, key, acc, best,
                      rating);
     wave_sync();
   }
@@ -217,13 +234,29 @@ k_rate_big(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
   __shared__ int32_t rq[kRT / 64];
   __shared__ double rr[kRT / 64];
   __shared__ long long bsum;
+  __shared__ int32_t ea[kRT], eb[kRT];  // a batch of the node's hyperedges
+  __shared__ double et[kRT];
   const int tid = threadIdx.x;
-  // (slice, entry) pairs in turn: workgroup b takes slot b, b + grid, ... of
-  // the nslice x kRateNG slots, the entries past a slice's length skipped
-  for (int64_t i = blockIdx.x; i < int64_t(nslice) * kRateNG; i += gridDim.x) {
-    const int32_t slice = int32_t(i % nslice);
-    if (i / nslice >= counts[2 * int64_t(slice) + 1]) continue;
-    const int32_t p = list[int64_t(slice) * kRateNG + i / nslice];
+  // (slice, entry) pairs in turn: workgroup b takes slots b, b + grid, ... of
+  // the nslice x kRateNG slots (the big nodes of one slice go to different
+  // workgroups); kRT slots are looked up together, those past a slice's
+  // length are skipped
+  __shared__ int32_t found[kRT];
+  __shared__ int32_t nfound;
+  const int64_t slots = int64_t(nslice) * kRateNG;
+  for (int64_t i0 = blockIdx.x; i0 < slots; i0 += int64_t(gridDim.x) * kRT) {
+  if (tid == 0) nfound = 0;
+  __syncthreads();
+  {
+    const int64_t i = i0 + int64_t(tid) * gridDim.x;
+    const int64_t slice = i % nslice, entry = i / nslice;
+    if (i < slots && entry < counts[2 * slice + 1])
+      found[atomicAdd(&nfound, 1)] = list[slice * kRateNG + entry];
+  }
+  __syncthreads();
+  const int nf = nfound;
+  for (int f = 0; f < nf; ++f) {
+    const int32_t p = found[f];
     const int32_t v0 = vptr[p], deg = vptr[p + 1] - v0;
     if (tid == 0) bsum = 0;
     __syncthreads();
@@ -245,21 +278,36 @@ k_rate_big(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
       }
       if (tid == 0) full = 0;
       __syncthreads();
-      for (int32_t t = 0; t < deg; ++t) {
-        const int32_t e = eids[v0 + t];
-        const int32_t a = eptr[e], b = eptr[e + 1];
-        const double term = rate_term(w, R, shift, e);
-        for (int64_t j = a + tid; j < b; j += kRT) {
-          const int32_t q = pins[j];
-          // class: the hash bits right below the table's (cb = 0: one class)
-          const uint32_t cls = (rate_hash(q) << kTableBits) >> 1 >> (31 - cb);
-          if (q != p && cls == c) {
-            const int h = rate_slot<T>(key, q);
-            if (h >= 0) acc[h] += term;
-            else full = 1;
-          }
+      for (int32_t t0 = 0; t0 < deg; t0 += kRT) {
+        // kRT hyperedges' segments and terms side by side, then one at a time
+        const int nt = deg - t0 < kRT ? int(deg - t0) : kRT;
+        if (tid < nt) {
+          const int32_t e = eids[v0 + t0 + tid];
+          ea[tid] = eptr[e];
+          eb[tid] = eptr[e + 1];
+          et[tid] = rate_term(w, R, shift, e);
         }
         __syncthreads();
+        for (int t = 0; t < nt; ++t) {
+          const int32_t a = ea[t], b = eb[t];
+          const double term = et[t];
+          for (int64_t j = a + tid; j < b; j += 4 * kRT) {
+            int32_t q[4];  // four pins' loads together; p stands for no pin
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = j + u * kRT < b ? pins[j + u * kRT] : p;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              // class: the hash bits right below the table's (cb = 0: one class)
+              const uint32_t cls = (rate_hash(q[u]) << kTableBits) >> 1 >> (31 - cb);
+              if (q[u] != p && cls == c) {
+                const int h = rate_slot<T>(key, q[u]);
+                if (h >= 0) acc[h] += term;
+                else full = 1;
+              }
+            }
+          }
+          __syncthreads();
+        }
       }
       if (full) {  // (the same on every thread)
         // halve the classes and start over
@@ -290,6 +338,7 @@ k_rate_big(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
       rating[p] = bst.q < 0 ? 0.0 : bst.r;
     }
     __syncthreads();
+  }
   }
 }
 
@@ -347,7 +396,7 @@ hef_status rating_run(const Level &L, const float *R, float shift, int32_t *best
   k_rate_small<<<nslice, kRT, 0, s>>>(st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh, int32_t(n),
                                       mid, big, counts, best, rating);
   HEF_LAUNCH_CHECK();
-  k_rate_mid<<<nslice, kRT, 0, s>>>(mid, counts, st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh,
+  k_rate_mid<<<nslice * kMidSplit, 64, 0, s>>>(mid, counts, st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh,
                                     best, rating);
   HEF_LAUNCH_CHECK();
   k_rate_big<<<std::min<unsigned>(nslice * kRateNG, 4096u), kRT, 0, s>>>(

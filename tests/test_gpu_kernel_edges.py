@@ -82,10 +82,10 @@ def _star_of(n, bound, seed, pool=None, parts=3):
                       w=w)
 
 
-@pytest.mark.parametrize("bound", [62, 63, 64, 510, 511, 512, 2047, 2049, 4500, "one class"])
+@pytest.mark.parametrize("bound", [62, 63, 64, 510, 511, 512, 3071, 3073, 4500, "one class"])
 def test_rating_class_edges(bound):
     """The node's table changes at 64 and 512 triples and is swept in hash
-    classes above 2048 neighbours; in the last case the neighbours all fall
+    classes above 3072 neighbours; in the last case the neighbours all fall
     in one of the first sweep's four classes, which overflows its table."""
     from oracle import rating as orat
     say(f"case: rating bound={bound}")
