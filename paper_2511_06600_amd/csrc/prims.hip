@@ -193,8 +193,11 @@ k_scan_one(const Scan3 S, int n, int32_t *idx) {
   if (tid == kScanOneThreads - 1) *total = incl;
 }
 
-constexpr int kRadixBits = 8;
-constexpr int kBins = 1 << kRadixBits;
+// Digits of 8 bits, or of 9 where that saves a pass (9, 17, 18 or 25 to 27
+// bits: the ids of 65k to 262k nodes, for one).  A pass over 7.9M pairs takes
+// 57 us (histogram and scatter) with 8 bits and 71 us with 9, so three passes
+// of 8 bits cost more than two of 9, and 9 is no gain where the count is equal.
+inline int radix_bits(int bits) { return radix_passes(bits) < (bits + 7) / 8 ? 9 : 8; }
 constexpr int kRadixThreads = 256;
 constexpr int kRadixWaves = kRadixThreads / 64;
 // Items per workgroup of a pass: 4096, or 1024 up to kRadixSmallN items.
@@ -212,13 +215,15 @@ inline int64_t radix_tile(int64_t n, bool lean) {
   return n <= kRadixSmallN && !lean ? kRadixTileSmall : kRadixTile;
 }
 
-template <int ROUNDS>
+template <int ROUNDS, int BITS>
 __global__ void __launch_bounds__(kRadixThreads)
 k_radix_hist(const uint32_t *__restrict__ keys, int64_t n, int shift, int32_t *__restrict__ hist,
              int nblocks) {
+  constexpr int kBins = 1 << BITS;
   __shared__ int32_t cnt[kBins];
   const int tid = threadIdx.x;
-  cnt[tid] = 0;
+#pragma unroll
+  for (int b = tid; b < kBins; b += kRadixThreads) cnt[b] = 0;
   __syncthreads();
   const int64_t base = int64_t(blockIdx.x) * (kRadixThreads * ROUNDS);
 #pragma unroll 4
@@ -227,7 +232,8 @@ k_radix_hist(const uint32_t *__restrict__ keys, int64_t n, int shift, int32_t *_
     if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (kBins - 1)], 1);
   }
   __syncthreads();
-  hist[int64_t(tid) * nblocks + blockIdx.x] = cnt[tid];
+#pragma unroll
+  for (int b = tid; b < kBins; b += kRadixThreads) hist[int64_t(b) * nblocks + blockIdx.x] = cnt[b];
 }
 
 // The histogram scan folded into the scatter: when the histogram has at most
@@ -241,17 +247,17 @@ constexpr int kRadixScanTiles = kRadixThreads * kTileRun;
 // digit before them in the wave; cnt[d] (the wave's own row of LDS counters,
 // zero on entry) ends as the wave's count of digit d.  Only this wave touches
 // cnt, so the rounds need no barrier.  Items past `left` take no part.
-template <int ROUNDS>
+template <int ROUNDS, int BITS>
 __device__ __forceinline__ void wave_ranks(const uint32_t (&k)[ROUNDS], int shift, int64_t left,
                                            int lane, int32_t *cnt, int32_t (&rank)[ROUNDS]) {
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const bool valid = 64 * r + lane < left;
-    const uint32_t d = (k[r] >> shift) & (kBins - 1);
+    const uint32_t d = (k[r] >> shift) & ((1 << BITS) - 1);
     uint64_t peer = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
+    for (int b = 0; b < BITS; ++b) {
       const bool bit = (d >> b) & 1u;
       const uint64_t bb = __ballot(bit);
       peer &= bit ? bb : ~bb;
@@ -276,13 +282,15 @@ __device__ __forceinline__ void wave_ranks(const uint32_t (&k)[ROUNDS], int shif
 // offs holds the exclusive scan of the histogram (digit-major), or with
 // tile_sums given its scan within scan tiles, to which the block adds the
 // sum of the scan tiles before each entry's.
-template <int ROUNDS>
+template <int ROUNDS, int BITS>
 __global__ void __launch_bounds__(kRadixThreads)
 k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                 uint32_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t n, int shift,
                 const int32_t *__restrict__ offs, int nblocks,
                 const int32_t *__restrict__ tile_sums, int ntiles) {
   constexpr int TILE = kRadixThreads * ROUNDS;
+  constexpr int kBins = 1 << BITS;
+  constexpr int BPT = kBins / kRadixThreads;  // bins per thread (neighbours)
   __shared__ int32_t gbase[kBins];              // global position of the tile's first item per digit
   __shared__ int32_t lbase[kBins];              // its position within the tile
   __shared__ int32_t wcnt[kRadixWaves][kBins];  // per wave: counts, then offsets within the digit
@@ -302,10 +310,15 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
     k[r] = i < n ? kin[i] : 0u;
     v[r] = i < n ? vin[i] : 0u;
   }
-  const int64_t hidx = int64_t(tid) * nblocks + blockIdx.x;
-  int32_t gb = offs[hidx];
+  int64_t hidx[BPT];
+  int32_t gb[BPT];
+#pragma unroll
+  for (int b = 0; b < BPT; ++b) {
+    hidx[b] = int64_t(tid * BPT + b) * nblocks + blockIdx.x;
+    gb[b] = offs[hidx[b]];
+  }
   if (tile_sums) {
-    // the sum of the scan tiles before hidx's: a run of kTileRun per thread,
+    // the sum of the scan tiles before each hidx's: a run of kTileRun per thread,
     // scanned over the block
     int32_t run[kTileRun];
     int32_t tot = 0;
@@ -319,31 +332,45 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
 #pragma unroll
     for (int q = 0; q < kTileRun; ++q) pool[tid * kTileRun + q] = uint32_t(before + run[q]);
     __syncthreads();
-    gb += int32_t(pool[hidx / kScanTile]);
-  }
-  gbase[tid] = gb;
 #pragma unroll
-  for (int w = 0; w < kRadixWaves; ++w) wcnt[w][tid] = 0;
+    for (int b = 0; b < BPT; ++b) gb[b] += int32_t(pool[hidx[b] / kScanTile]);
+  }
+#pragma unroll
+  for (int b = 0; b < BPT; ++b) {
+    gbase[tid * BPT + b] = gb[b];
+#pragma unroll
+    for (int w = 0; w < kRadixWaves; ++w) wcnt[w][tid * BPT + b] = 0;
+  }
   __syncthreads();
   int32_t rank[ROUNDS];
-  wave_ranks<ROUNDS>(k, shift, n - wbase, lane, wcnt[wv], rank);
+  wave_ranks<ROUNDS, BITS>(k, shift, n - wbase, lane, wcnt[wv], rank);
   __syncthreads();
-  int32_t tot = 0;
+  int32_t tot[BPT], sum = 0;
 #pragma unroll
-  for (int w = 0; w < kRadixWaves; ++w) {
-    const int32_t c = wcnt[w][tid];
-    wcnt[w][tid] = tot;
-    tot += c;
+  for (int b = 0; b < BPT; ++b) {
+    tot[b] = 0;
+#pragma unroll
+    for (int w = 0; w < kRadixWaves; ++w) {
+      const int32_t c = wcnt[w][tid * BPT + b];
+      wcnt[w][tid * BPT + b] = tot[b];
+      tot[b] += c;
+    }
+    sum += tot[b];
   }
-  lbase[tid] = block_inclusive<kRadixThreads>(tot, tid, wtot) - tot;
+  int32_t at = block_inclusive<kRadixThreads>(sum, tid, wtot) - sum;
+#pragma unroll
+  for (int b = 0; b < BPT; ++b) {
+    lbase[tid * BPT + b] = at;
+    at += tot[b];
+  }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     if (wbase + 64 * r + lane < n) {
       const uint32_t d = (k[r] >> shift) & (kBins - 1);
-      const int32_t at = lbase[d] + wcnt[wv][d] + rank[r];
-      sk[at] = k[r];
-      sv[at] = v[r];
+      const int32_t to = lbase[d] + wcnt[wv][d] + rank[r];
+      sk[to] = k[r];
+      sv[to] = v[r];
     }
   }
   __syncthreads();
@@ -370,10 +397,11 @@ constexpr int kOneThreads = 1024;
 constexpr int kOneWaves = kOneThreads / 64;
 constexpr int kOneRounds = 8;
 
-template <int ROUNDS>
+template <int ROUNDS, int BITS>
 __global__ void __launch_bounds__(kOneThreads)
 k_radix_one(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout, int n,
             int passes) {
+  constexpr int kBins = 1 << BITS;
   __shared__ uint32_t buf[kOneThreads * ROUNDS];
   __shared__ int32_t wcnt[kOneWaves][kBins];
   __shared__ int32_t lbase[kBins];
@@ -390,11 +418,11 @@ k_radix_one(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *
     v[r] = i < n ? vin[i] : 0u;
   }
   for (int p = 0; p < passes; ++p) {
-    const int shift = p * kRadixBits;
+    const int shift = p * BITS;
     for (int i = tid; i < kOneWaves * kBins; i += kOneThreads) (&wcnt[0][0])[i] = 0;
     __syncthreads();
     int32_t rank[ROUNDS];
-    wave_ranks<ROUNDS>(k, shift, n - wbase, lane, wcnt[wv], rank);
+    wave_ranks<ROUNDS, BITS>(k, shift, n - wbase, lane, wcnt[wv], rank);
     __syncthreads();
     int32_t tot = 0;
     if (tid < kBins) {
@@ -581,67 +609,86 @@ hef_status exclusive_scan3_i32(const std::array<const int32_t *, 3> &in,
 }
 
 size_t radix_ws_bytes(int64_t n, bool lean) {
-  const int64_t nb = cdiv(n, radix_tile(n, lean));
+  const int64_t nb = cdiv(n, radix_tile(n, lean)), bins = lean ? 256 : 512;
   Arena a;
-  a.take<int32_t>(nb * kBins + 1);
-  return a.mark() + scan_ws_bytes(nb * kBins) + 512;
+  a.take<int32_t>(nb * bins + 1);
+  return a.mark() + scan_ws_bytes(nb * bins) + 512;
 }
 
-hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
-                            uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n,
-                            int bits, Arena &ws, hipStream_t s, bool lean) {
-  if (n == 0) return HEF_OK;
-  const int passes = (bits + kRadixBits - 1) / kRadixBits;
+namespace {
+
+template <int ROUNDS, int BITS>
+hef_status radix_pass(const uint32_t *ka, const uint32_t *va, uint32_t *kb, uint32_t *vb,
+                      int64_t n, int64_t nb, int shift, int32_t *hist, int32_t *tsum,
+                      int64_t htiles, Arena &ws, hipStream_t s) {
+  constexpr int kBins = 1 << BITS;
+  k_radix_hist<ROUNDS, BITS><<<nb, kRadixThreads, 0, s>>>(ka, n, shift, hist, int(nb));
+  if (tsum) {
+    Scan3 S{};
+    S.in[0] = hist;
+    S.out[0] = hist;
+    S.sums[0] = tsum;
+    k_scan_tiles<<<htiles, kScanThreads, 0, s>>>(S, nb * kBins);
+  } else {
+    HEF_TRY(exclusive_scan_i32(hist, hist, nb * kBins, ws, s));
+  }
+  k_radix_scatter<ROUNDS, BITS><<<nb, kRadixThreads, 0, s>>>(ka, va, kb, vb, n, shift, hist,
+                                                            int(nb), tsum, int(htiles));
+  HEF_LAUNCH_CHECK();
+  return HEF_OK;
+}
+
+template <int BITS>
+hef_status radix_run(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
+                     uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n, int passes,
+                     bool lean, Arena &ws, hipStream_t s) {
   if (n <= kOneThreads * kOneRounds) {
     if (n <= kOneThreads * 4)
-      k_radix_one<4><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n), passes);
+      k_radix_one<4, BITS><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n), passes);
     else
-      k_radix_one<kOneRounds><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n),
-                                                        passes);
+      k_radix_one<kOneRounds, BITS><<<1, kOneThreads, 0, s>>>(src_k, src_v, out_k, out_v, int(n),
+                                                              passes);
     HEF_LAUNCH_CHECK();
     return HEF_OK;
   }
   const bool small = radix_tile(n, lean) == kRadixTileSmall;
-  const int64_t nb = cdiv(n, radix_tile(n, lean));
+  const int64_t nb = cdiv(n, radix_tile(n, lean)), entries = nb << BITS;
   const size_t mk = ws.mark();
-  int32_t *hist = ws.take<int32_t>(nb * kBins + 1);
+  int32_t *hist = ws.take<int32_t>(entries + 1);
   HEF_WS_CHECK(ws);
   // the histogram's scan tiles: when there are at most kRadixScanTiles
-  // (n up to 64M keys) the scatter adds their prefixes itself
-  const int64_t htiles = cdiv(nb * kBins, kScanTile);
+  // (n up to 64M keys, 32M with 9 bits) the scatter adds their prefixes itself
+  const int64_t htiles = cdiv(entries, kScanTile);
   int32_t *tsum = htiles <= kRadixScanTiles ? ws.take<int32_t>(htiles) : nullptr;
   HEF_WS_CHECK(ws);
   const uint32_t *ka = src_k, *va = src_v;
   for (int p = 0; p < passes; ++p) {
-    const int shift = p * kRadixBits;
     // the last pass writes out, the ones before alternate
     const bool to_out = ((passes - 1 - p) & 1) == 0;
     uint32_t *kb = to_out ? out_k : tmp_k, *vb = to_out ? out_v : tmp_v;
     if (small)
-      k_radix_hist<kRadixRoundsSmall><<<nb, kRadixThreads, 0, s>>>(ka, n, shift, hist, int(nb));
+      HEF_TRY((radix_pass<kRadixRoundsSmall, BITS>(ka, va, kb, vb, n, nb, p * BITS, hist, tsum,
+                                                   htiles, ws, s)));
     else
-      k_radix_hist<kRadixRounds><<<nb, kRadixThreads, 0, s>>>(ka, n, shift, hist, int(nb));
-    if (tsum) {
-      Scan3 S{};
-      S.in[0] = hist;
-      S.out[0] = hist;
-      S.sums[0] = tsum;
-      k_scan_tiles<<<htiles, kScanThreads, 0, s>>>(S, nb * kBins);
-    } else {
-      HEF_TRY(exclusive_scan_i32(hist, hist, nb * kBins, ws, s));
-    }
-    if (small)
-      k_radix_scatter<kRadixRoundsSmall><<<nb, kRadixThreads, 0, s>>>(
-          ka, va, kb, vb, n, shift, hist, int(nb), tsum, int(htiles));
-    else
-      k_radix_scatter<kRadixRounds><<<nb, kRadixThreads, 0, s>>>(ka, va, kb, vb, n, shift, hist,
-                                                                 int(nb), tsum, int(htiles));
-    HEF_LAUNCH_CHECK();
+      HEF_TRY((radix_pass<kRadixRounds, BITS>(ka, va, kb, vb, n, nb, p * BITS, hist, tsum, htiles,
+                                              ws, s)));
     ka = kb;
     va = vb;
   }
   ws.reset(mk);
   return HEF_OK;
+}
+
+}  // namespace
+
+hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
+                            uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n,
+                            int bits, Arena &ws, hipStream_t s, bool lean) {
+  if (n == 0) return HEF_OK;
+  const int passes = radix_passes(bits, lean);
+  if (!lean && radix_bits(bits) == 9)
+    return radix_run<9>(src_k, src_v, tmp_k, tmp_v, out_k, out_v, n, passes, lean, ws, s);
+  return radix_run<8>(src_k, src_v, tmp_k, tmp_v, out_k, out_v, n, passes, lean, ws, s);
 }
 
 hef_status scan_compact_flags(const int32_t *flag, int32_t *pos, int32_t *idx_out,

@@ -21,11 +21,12 @@ hef_status exclusive_scan3_i32(const std::array<const int32_t *, 3> &in,
                                const std::array<int32_t *, 3> &out, int32_t *totals, int64_t n,
                                Arena &ws, hipStream_t s);
 
-// Workspace bytes for radix_sort_pairs over `n` items (about n bytes up to
-// 2^20 items, n / 4 above or with `lean`, which keeps to the large tiles).
+// Workspace bytes for radix_sort_pairs over `n` items (about 2 n bytes up to
+// 2^20 items, n / 2 above; n / 4 with `lean`, which keeps to large tiles and
+// 8-bit digits).
 size_t radix_ws_bytes(int64_t n, bool lean = false);
 // Stable LSD radix sort of n (key, value) pairs by the low `bits` bits of
-// the keys, 8 bits a pass: src -> out, with tmp as the other ping-pong buffer
+// the keys, 8 or 9 bits a pass: src -> out, with tmp as the other ping-pong buffer
 // (both n items; the last pass writes out, so nothing is copied at the end).
 // src may be buffers of its own (left as they are), or the buffers that the
 // first pass does not write: out when the number of passes is even, tmp when
@@ -33,9 +34,12 @@ size_t radix_ws_bytes(int64_t n, bool lean = false);
 hef_status radix_sort_pairs(const uint32_t *src_k, const uint32_t *src_v, uint32_t *tmp_k,
                             uint32_t *tmp_v, uint32_t *out_k, uint32_t *out_v, int64_t n,
                             int bits, Arena &ws, hipStream_t s, bool lean = false);
+inline int radix_passes(int bits, bool lean = false) {
+  return lean ? (bits + 7) / 8 : (bits + 8) / 9;
+}
 template <class T>
-inline T radix_src(int bits, T tmp, T out) {
-  return ((bits + 7) / 8) % 2 == 0 ? out : tmp;
+inline T radix_src(int bits, T tmp, T out, bool lean = false) {
+  return radix_passes(bits, lean) % 2 == 0 ? out : tmp;
 }
 
 // idx_out[0..count) = ascending indices i < n with flag[i] = 1 (flags are 0
@@ -119,6 +123,25 @@ inline int bits_for(int64_t maxval) {
   int b = 1;
   while (b < 32 && (int64_t(1) << b) <= maxval) ++b;
   return b;
+}
+
+// A wave takes 64 consecutive hyperedges, lane l the hyperedge e0 + l, whose
+// pins [a0, an) are contiguous: the lanes then walk that range side by side
+// (coalesced), each finding the hyperedge of its position by a search over
+// the lanes' starts.  One thread per hyperedge walking its own pins is a
+// serial chain of |e| dependent steps: with a 2000-pin hyperedge the
+// validation took 150 us at 756k pins, and 205 us at 7.9M.
+__device__ __forceinline__ int lane_of_pos(int32_t start, int32_t j, int cnt) {
+  int lo = 0, hi = cnt;  // last lane < cnt whose start is <= j
+#pragma unroll
+  for (int s = 0; s < 6; ++s) {
+    const int mid = (lo + hi) >> 1;
+    const int32_t sm = __shfl(start, mid, 64);
+    const bool up = hi - lo > 1 && sm <= j;
+    lo = up ? mid : lo;
+    hi = (hi - lo > 1 && !up) ? mid : hi;
+  }
+  return lo;
 }
 
 }  // namespace hef

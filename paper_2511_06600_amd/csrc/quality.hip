@@ -29,56 +29,69 @@ namespace {
 
 constexpr int kQT = 256;
 
-// The hyperedge holding pin position j: the last e with eptr[e] <= j.
-__device__ __forceinline__ int32_t edge_of(const int32_t *eptr, int32_t m, int32_t j) {
-  int32_t lo = 0, hi = m;
-  while (hi - lo > 1) {
-    const int32_t mid = (lo + hi) >> 1;
-    if (eptr[mid] <= j) lo = mid; else hi = mid;
-  }
-  return lo;
-}
+// Every pin position j emits (label of its node, its hyperedge e); bit e of
+// split says whether e has pins in more than one cluster.  A wave walks the
+// pins of 64 consecutive hyperedges side by side, kEmitPos positions a lane at
+// once: the kernel waits on the dependent loads pin -> label.  Every lane then
+// looks for its own hyperedge's range among the positions whose label differs
+// from their hyperedge's first, and the 64 answers are one word of split (one
+// thread per position, a search for its hyperedge and a word per hyperedge set
+// by every thread that differs took 126 us at 7.9M pins; this takes 61 us).
+constexpr int kEmitPos = 4;
 
-// One thread per pin position j, kQT consecutive positions per workgroup:
-// j emits (label of its node, its hyperedge e), and marks split[e] (zeroed
-// beforehand) when its label differs from that of e's first pin.  The
-// workgroup finds the hyperedges of its first and last positions once and
-// stages that slice of eptr in LDS (at most kQT + 1 entries, as every
-// hyperedge has a pin), where each thread finds its own hyperedge.
 __global__ void __launch_bounds__(kQT)
 k_qual_emit(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
-            const int32_t *__restrict__ label, int32_t m, int64_t nnz, int32_t nc,
+            const int32_t *__restrict__ label, int32_t m, int32_t nc,
             uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-            int32_t *__restrict__ split, int32_t *__restrict__ bad) {
-  __shared__ int32_t se[kQT + 2];
-  __shared__ int32_t ends[2];
-  const int64_t j0 = int64_t(blockIdx.x) * kQT;
-  const int64_t jl = (j0 + kQT < nnz ? j0 + kQT : nnz) - 1;
-  if (threadIdx.x < 2) ends[threadIdx.x] = edge_of(eptr, m, int32_t(threadIdx.x ? jl : j0));
-  __syncthreads();
-  const int32_t e0 = ends[0];
-  int32_t ne = ends[1] - e0;  // entries e0 .. e0 + ne
-  if (ne > kQT) ne = kQT;
-  for (int i = threadIdx.x; i <= ne; i += kQT) se[i] = eptr[e0 + i];
-  __syncthreads();
-  const int64_t j = j0 + threadIdx.x;
-  if (j > jl) return;
-  int32_t lo = 0, hi = ne + 1;
-  while (hi - lo > 1) {
-    const int32_t mid = (lo + hi) >> 1;
-    if (se[mid] <= j) lo = mid; else hi = mid;
+            uint64_t *__restrict__ split, int32_t *__restrict__ bad) {
+  const int64_t e = int64_t(blockIdx.x) * kQT + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int64_t e0 = e - lane;
+  if (e0 >= m) return;
+  const int cnt = m - e0 < 64 ? int(m - e0) : 64;
+  const bool on = lane < cnt;
+  const int32_t a = on ? eptr[e] : 0, z = on ? eptr[e + 1] : 0;
+  int32_t first = on ? label[pins[a]] : 0;
+  if (first < 0 || first >= nc) first = 0;
+  const int32_t j0 = __shfl(a, 0, 64), j1 = __shfl(z, cnt - 1, 64);
+  bool mixed = false, out = false;
+  for (int64_t jb = j0; jb < j1; jb += 64 * kEmitPos) {
+    int32_t c[kEmitPos];
+#pragma unroll
+    for (int u = 0; u < kEmitPos; ++u) {
+      const int64_t j = jb + u * 64 + lane;
+      c[u] = pins[j < j1 ? j : j1 - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kEmitPos; ++u) c[u] = label[c[u]];
+#pragma unroll
+    for (int u = 0; u < kEmitPos; ++u) {
+      const int64_t jc = jb + u * 64;
+      if (jc >= j1) break;
+      const bool in = jc + lane < j1;
+      const int32_t j = in ? int32_t(jc + lane) : j1 - 1;
+      const int k = lane_of_pos(a, j, cnt);
+      const int32_t cf = __shfl(first, k, 64);  // by every lane: k's may be past the end
+      if (c[u] < 0 || c[u] >= nc) {
+        out = true;
+        c[u] = 0;
+      }
+      if (in) {
+        keys[j] = uint32_t(c[u]);
+        vals[j] = uint32_t(e0 + k);
+      }
+      const uint64_t diff = __ballot(in && c[u] != cf);
+      // this lane's positions of the chunk: bits [lo, hi)
+      const int64_t lo = a > jc ? a - jc : 0, hi = z - jc < 64 ? z - jc : 64;
+      if (lo < hi) {
+        const uint64_t below = hi < 64 ? (uint64_t(1) << hi) - 1 : ~uint64_t(0);
+        mixed |= ((diff & below) >> lo) != 0;
+      }
+    }
   }
-  const int32_t e = e0 + lo;
-  int32_t c = label[pins[j]];
-  int32_t cf = label[pins[se[lo]]];
-  if (cf < 0 || cf >= nc) cf = 0;
-  if (c < 0 || c >= nc) {
-    *bad = 1;  // every writer stores the same value
-    c = 0;
-  }
-  keys[j] = uint32_t(c);
-  vals[j] = uint32_t(e);
-  if (c != cf) split[e] = 1;  // every writer stores the same value
+  const uint64_t word = __ballot(on && mixed);
+  if (lane == 0) split[e0 >> 6] = word;
+  if (out) *bad = 1;  // every writer stores the same value
 }
 
 // seg[c] = first sorted position with key >= c, c in [0, nc]
@@ -98,7 +111,7 @@ __global__ void k_qual_seg(const uint32_t *__restrict__ keys, int64_t nnz, int32
 // the lane sums are combined by a fixed butterfly.
 __global__ void __launch_bounds__(kQT)
 k_qual_cluster(const float *__restrict__ w, const uint32_t *__restrict__ vals, const int32_t *__restrict__ seg,
-               const int32_t *__restrict__ split, int32_t nc, double *__restrict__ cut,
+               const uint64_t *__restrict__ split, int32_t nc, double *__restrict__ cut,
                double *__restrict__ vol) {
   const int64_t c = (int64_t(blockIdx.x) * kQT + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
@@ -115,7 +128,7 @@ k_qual_cluster(const float *__restrict__ w, const uint32_t *__restrict__ vals, c
     if (t < s1) {
       const double we = w ? double(w[e]) : 1.0;
       vs += we;
-      if (e != pe && split[e]) cs += we;
+      if (e != pe && (split[e >> 6] >> (e & 63) & 1)) cs += we;
     }
   }
   for (int off = 32; off > 0; off >>= 1) {
@@ -204,7 +217,8 @@ __global__ void k_qual_zero(double *__restrict__ a, double *__restrict__ b,
 
 struct QualWs {
   uint32_t *k0, *v0, *k1, *v1;
-  int32_t *split, *seg, *bad;
+  uint64_t *split;     // a bit per hyperedge
+  int32_t *seg, *bad;  // bad: the hypergraph's flag, the labels' flag
   double *tot, *part;
 };
 
@@ -213,9 +227,9 @@ void qual_carve(Arena &a, int64_t n, int64_t m, int64_t nnz, QualWs &q) {
   q.v0 = a.take<uint32_t>(nnz);
   q.k1 = a.take<uint32_t>(nnz);
   q.v1 = a.take<uint32_t>(nnz);
-  q.split = a.take<int32_t>(m);
+  q.split = a.take<uint64_t>(cdiv(m, 64));
   q.seg = a.take<int32_t>((n > 1 ? n : 1) + 1);
-  q.bad = a.take<int32_t>(1);
+  q.bad = a.take<int32_t>(2);
   q.tot = a.take<double>(1);
   q.part = a.take<double>(kSumBlocks);
 }
@@ -261,7 +275,7 @@ extern "C" hef_status hef_conductance(const hef_hypergraph *hg, const int32_t *l
   Level L;
   L.n = hg->n; L.m = hg->m; L.nnz = hg->nnz; L.eptr = hg->eptr; L.pins = hg->pins; L.w = hg->w;
   int32_t bad = 0;
-  HEF_TRY(validate_device(L, q.bad, &bad, stream));
+  HEF_TRY(validate_device(L, q.bad, &bad, stream, 2));
   if (bad) {
     set_error("invalid hypergraph (code %d: 1 eptr ends, 2 segment bounds or |e|<2, 4 pins, 8 weights)", bad);
     return HEF_ERR_INVALID_HYPERGRAPH;
@@ -274,12 +288,10 @@ extern "C" hef_status hef_conductance(const hef_hypergraph *hg, const int32_t *l
     HEF_HIP(hipStreamSynchronize(stream));
     return HEF_OK;
   }
-  HEF_TRY(zero_async(q.bad, sizeof(int32_t), stream));
-  HEF_TRY(zero_async(q.split, m * sizeof(int32_t), stream));
   const int bits = bits_for(nc - 1);
   uint32_t *sk = radix_src(bits, q.k0, q.k1), *sv = radix_src(bits, q.v0, q.v1);
-  k_qual_emit<<<cdiv(nnz, kQT), kQT, 0, stream>>>(L.eptr, L.pins, label, int32_t(m), nnz, nc,
-                                                   sk, sv, q.split, q.bad);
+  k_qual_emit<<<cdiv(m, kQT), kQT, 0, stream>>>(L.eptr, L.pins, label, int32_t(m), nc, sk, sv,
+                                                 q.split, q.bad + 1);
   HEF_LAUNCH_CHECK();
   HEF_TRY(radix_sort_pairs(sk, sv, q.k0, q.v0, q.k1, q.v1, nnz, bits, a, stream));
   k_qual_seg<<<cdiv(int64_t(nc) + 1, kQT), kQT, 0, stream>>>(q.k1, nnz, nc, q.seg);
@@ -297,7 +309,7 @@ extern "C" hef_status hef_conductance(const hef_hypergraph *hg, const int32_t *l
   k_sum_final<<<1, kQT, 0, stream>>>(q.part, nbk, double(nc), phi_avg);
   HEF_LAUNCH_CHECK();
   int32_t badlab = 0;
-  HEF_HIP(hipMemcpyAsync(&badlab, q.bad, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+  HEF_HIP(hipMemcpyAsync(&badlab, q.bad + 1, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
   HEF_HIP(hipStreamSynchronize(stream));
   if (badlab) {
     set_error("a label lies outside [0, n_clusters)");

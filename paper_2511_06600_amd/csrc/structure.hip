@@ -9,25 +9,6 @@
 namespace hef {
 namespace {
 
-// A wave takes 64 consecutive hyperedges, lane l the hyperedge e0 + l, whose
-// pins [a0, an) are contiguous: the lanes then walk that range side by side
-// (coalesced), each finding the hyperedge of its position by a search over
-// the lanes' starts.  One thread per hyperedge walking its own pins is a
-// serial chain of |e| dependent steps: with a 2000-pin hyperedge the
-// validation took 150 us at 756k pins, and 205 us at 7.9M.
-__device__ __forceinline__ int lane_of_pos(int32_t start, int32_t j, int cnt) {
-  int lo = 0, hi = cnt;  // last lane < cnt whose start is <= j
-#pragma unroll
-  for (int s = 0; s < 6; ++s) {
-    const int mid = (lo + hi) >> 1;
-    const int32_t sm = __shfl(start, mid, 64);
-    const bool up = hi - lo > 1 && sm <= j;
-    lo = up ? mid : lo;
-    hi = (hi - lo > 1 && !up) ? mid : hi;
-  }
-  return lo;
-}
-
 __global__ void __launch_bounds__(256)
 k_validate(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
            const float *__restrict__ w, int32_t n, int32_t m, int64_t nnz,
@@ -237,12 +218,12 @@ static void carve_scale(Arena &a, int64_t m, ScaleWs &w) {
   w.tcb = a.take<double>(std::max<int64_t>(m, 1));
 }
 
-// The small tiles' histograms take up to 3 nnz / 4 bytes more than the large
-// ones'; hypergraphs of very long hyperedges keep the large ones, so that
-// this scratch stays within 12 nnz + nnz / 4 + 16 m + 8 max(n, m) bytes and
-// everything that fitted the static scratch still does.
+// The sort's histograms take up to 2 nnz bytes, nnz / 4 in the lean form;
+// hypergraphs of very long hyperedges take the lean form, so that this scratch
+// stays within 12 nnz + nnz / 4 + 16 m + 8 max(n, m) bytes and everything that
+// fitted the static scratch still does.
 static bool lean_sort(int64_t n, int64_t m, int64_t nnz) {
-  return 3 * nnz + 8192 > 4 * (16 * m + 8 * std::max(n, m));
+  return 7 * nnz + 32768 > 4 * (16 * m + 8 * std::max(n, m));
 }
 
 size_t structure_build_ws(int64_t n, int64_t m, int64_t nnz) {
@@ -277,7 +258,7 @@ hef_status structure_build(const Level &L, Structure &st, Arena &ws, hipStream_t
     HEF_WS_CHECK(ws);
     const int bits = bits_for(n > 0 ? n - 1 : 0);
     uint32_t *eids = reinterpret_cast<uint32_t *>(st.eids);
-    uint32_t *ids = radix_src(bits, w.tmp_v, eids);
+    uint32_t *ids = radix_src(bits, w.tmp_v, eids, lean_sort(n, m, nnz));
     k_edge_ids<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, ids, int32_t(m), st.n_big);
     HEF_LAUNCH_CHECK();
     HEF_TRY(radix_sort_pairs(reinterpret_cast<const uint32_t *>(L.pins), ids, w.tmp_k, w.tmp_v,

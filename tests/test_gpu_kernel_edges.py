@@ -86,7 +86,7 @@ def _star_of(n, bound, seed, pool=None, parts=3):
 def test_rating_class_edges(bound):
     """The node's table changes at 64 and 512 triples and is swept in hash
     classes above 3072 neighbours; in the last case the neighbours all fall
-    in one of the first sweep's four classes, which overflows its table."""
+    in one class of the first two sweeps, which overflows its table."""
     from oracle import rating as orat
     say(f"case: rating bound={bound}")
     n, pool = 6000, None
@@ -109,7 +109,7 @@ def test_rating_class_edges(bound):
 def test_sort_and_compaction_sizes(nnz):
     """The incidence sort runs in one workgroup up to 8192 items (4 or 8 a
     thread), in tiles of 1024 up to 2^20 and of 4096 above; node counts
-    that need one to three digit passes.  The operator's rows depend on every
+    that need one digit pass or two, of 8 bits and of 9.  The operator's rows depend on every
     node's hyperedges being complete and in order."""
     say(f"case: sort sizes nnz={nnz}")
     for n in (200, 60000, 70000):
@@ -275,3 +275,27 @@ def test_level_and_rebuild_with_long_segments(size):
     m2, ep, pn, w2, kp = ocl.rebuild(m, h.eptr, h.pins, h.w, ref.label)
     assert out.m == m2 and np.array_equal(out.eptr.cpu().numpy(), ep)
     assert np.array_equal(out.pins.cpu().numpy(), pn) and np.array_equal(kept.cpu().numpy(), kp)
+
+
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 200])
+def test_conductance_at_wave_edges(m):
+    """A wave takes 64 hyperedges' pins, 256 positions at once: hyperedges of
+    one cluster but for one pin, at either end or across a chunk's edge, and
+    whole ones.  Unit weights: the sums are whole numbers and must be equal."""
+    say(f"case: conductance wave edges m={m}")
+    n = 900
+    for long in (2, 62, 64, 255, 256, 257, 700):
+        h = _hg(n, _mixed_sizes(m, m + long, [(0, long), (m - 1, long), (m // 2, long)]), m + long)
+        deg = np.bincount(h.pins, minlength=n)
+        a, b = int(h.eptr[m // 2]), int(h.eptr[m // 2 + 1])
+        for j in (a, a + min(63, long - 1), a + min(64, long - 1), b - 1, -1):
+            label = np.zeros(n, np.int32)
+            if j >= 0:
+                label[h.pins[j]] = 2
+            cut, vol, phi, _ = hef.conductance(to_device(h), torch.as_tensor(label, device="cuda"), 3)
+            inside = np.add.reduceat(label[h.pins] == 0, h.eptr[:-1])
+            k = int(((inside > 0) & (inside < np.diff(h.eptr))).sum())
+            two = int((inside < np.diff(h.eptr)).sum())
+            assert two == k  # no hyperedge lies in the single node's cluster
+            assert cut.cpu().tolist() == [k, 0, k]
+            assert vol.cpu().tolist() == [deg[label == 0].sum(), 0, deg[label == 2].sum()]
