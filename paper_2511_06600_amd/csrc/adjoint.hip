@@ -356,8 +356,8 @@ __global__ void k_positions(uint32_t *__restrict__ vals, int64_t nnz) {
 }
 
 // ------------------------------------------------------------ 2. joint QR
-// W1 = R^-T and W2 = sym(-Mq) R^-T (float32, Kp x Kp, zero outside K x K),
-// Mq = chibar^T chi, sym(X)[i][l] = X[max(i,l)][min(i,l)].
+// W1 = R^-T and W2 = -Mq R^-T (float32, Kp x Kp, zero outside K x K),
+// Mq = sym(chibar^T chi), sym(X)[i][l] = X[max(i,l)][min(i,l)].
 __global__ void k_qradj_w(const double *__restrict__ Rinv, const double *__restrict__ Mq, int K,
                           int Kp, float *__restrict__ W1, float *__restrict__ W2) {
   const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -368,8 +368,7 @@ __global__ void k_qradj_w(const double *__restrict__ Rinv, const double *__restr
   double acc = 0.0;
   const double *rj = Rinv + int64_t(j) * Kp;
   for (int l = j; l < K; ++l) {
-    const double z = i >= l ? Mq[int64_t(i) * K + l] : Mq[int64_t(l) * K + i];
-    acc -= z * rj[l];
+    acc -= Mq[int64_t(l) * K + i] * rj[l];
   }
   W2[idx] = float(acc);
 }
@@ -378,11 +377,12 @@ __global__ void k_qradj_w(const double *__restrict__ Rinv, const double *__restr
 // X3 = [v0 | v1 | y]^T vbar (3B x B, float64): per workgroup a row range in
 // 64-row LDS slabs, one output entry (or a few) per thread, FP32 per slab,
 // float64 across slabs; partial[blk][3B*B].
-// vbar = abar + pbar[:, col .. col + B) on the first pool_rows rows, formed
-// while the cross products read it; abar is cleared for the next step.
+// vbar = abar + ay (the A ybar of the step before, if any) + pbar[:, col ..
+// col + B) on the first pool_rows rows, formed while the cross products read
+// it; abar is cleared for the next step.
 struct VbarIn {
   float *abar;
-  const float *pbar;
+  const float *ay, *pbar;
   int K, col;
   int64_t pool_rows;
   float *vbar;
@@ -400,34 +400,80 @@ struct XgramPair {
   int nb0;
 };
 
-// One SL-row slab of [v0 | v1 | y | vbar] into registers (element g of the
-// slab: row g / (C + B), column g % (C + B)); zeros past r1.
-template <int B, int SL, int PF>
-__device__ __forceinline__ void xgram_fetch(float (&pre)[PF], int tid, int64_t rs, int64_t r1,
+// VW (1, 2 or a multiple of 4) consecutive floats, aligned to their width up
+// to 16 bytes.
+template <int VW>
+__device__ __forceinline__ void load_vec(const float *p, float (&v)[VW]) {
+  if constexpr (VW == 1) {
+    v[0] = *p;
+  } else if constexpr (VW == 2) {
+    const float2 t = *reinterpret_cast<const float2 *>(p);
+    v[0] = t.x; v[1] = t.y;
+  } else {
+#pragma unroll
+    for (int q = 0; q < VW; q += 4) {
+      const float4 t = *reinterpret_cast<const float4 *>(p + q);
+      v[q] = t.x; v[q + 1] = t.y; v[q + 2] = t.z; v[q + 3] = t.w;
+    }
+  }
+}
+
+template <int VW>
+__device__ __forceinline__ void store_vec(float *p, const float (&v)[VW]) {
+  if constexpr (VW == 1) {
+    *p = v[0];
+  } else if constexpr (VW == 2) {
+    *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < VW; q += 4)
+      *reinterpret_cast<float4 *>(p + q) = make_float4(v[q], v[q + 1], v[q + 2], v[q + 3]);
+  }
+}
+
+// One SL-row slab of [v0 | v1 | y | vbar] into registers, VW neighbours of a
+// row at once: piece g of the slab is piece g % (SL B / VW) of array
+// g / (SL B / VW) (the same for a whole wave), counted along the rows.  Zeros
+// past r1.  (Element by element, 16 four-byte loads a row at B = 4, a step
+// took 26 us at 200k nodes and as many hyperedges; this takes 19.5.)
+template <int B, int SL, int VW, int PF>
+__device__ __forceinline__ void xgram_fetch(float (&pre)[PF][VW], int tid, int64_t rs, int64_t r1,
                                             const float *v0, const float *v1, const float *y,
                                             const VbarIn &vi) {
-  constexpr int C = 3 * B;
+  constexpr int per = SL * B / VW;
 #pragma unroll
   for (int i = 0; i < PF; ++i) {
     const int g = tid + i * kThreads;
-    const int r = g / (C + B), c = g % (C + B);
+    const int arr = __builtin_amdgcn_readfirstlane(g / per);
+    const int r = g % per / (B / VW), c = g % (B / VW) * VW;
     const int64_t row = rs + r;
-    float v = 0.0f;
-    if (g < SL * (C + B) && row < r1) {
-      if (c < C) {
-        const float *sp = c < B ? v0 : (c < 2 * B ? v1 : y);
-        v = sp ? sp[row * B + (c % B)] : 0.0f;
-      } else {
-        // vbar = abar + the pool adjoint's columns, written out (and abar
-        // cleared) here: every row is fetched exactly once
-        const int64_t gi = row * B + (c - C);
-        v = vi.abar[gi];
-        if (row < vi.pool_rows) v += vi.pbar[row * vi.K + vi.col + (c - C)];
-        vi.vbar[gi] = v;
-        vi.abar[gi] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < VW; ++q) pre[i][q] = 0.0f;
+    if (row >= r1) continue;
+    const int64_t gi = row * B + c;
+    if (arr < 3) {
+      const float *sp = arr == 0 ? v0 : (arr == 1 ? v1 : y);
+      if (sp) load_vec<VW>(sp + gi, pre[i]);
+    } else {
+      // vbar = abar + the last step's A ybar + the pool adjoint's columns,
+      // written out (and abar cleared) here: every row is fetched exactly once
+      float t[VW];
+      load_vec<VW>(vi.abar + gi, pre[i]);
+      if (vi.ay) {
+        load_vec<VW>(vi.ay + gi, t);
+#pragma unroll
+        for (int q = 0; q < VW; ++q) pre[i][q] += t[q];
       }
+      if (row < vi.pool_rows) {
+        load_vec<VW>(vi.pbar + row * vi.K + vi.col + c, t);
+#pragma unroll
+        for (int q = 0; q < VW; ++q) pre[i][q] += t[q];
+      }
+      store_vec<VW>(vi.vbar + gi, pre[i]);
+#pragma unroll
+      for (int q = 0; q < VW; ++q) t[q] = 0.0f;
+      store_vec<VW>(vi.abar + gi, t);
     }
-    pre[i] = v;
   }
 }
 
@@ -462,21 +508,24 @@ k_xgram(const XgramPair P) {
 #pragma unroll
   for (int u = 0; u < EPT; ++u) acc[u] = 0.0;
   // the next slab is fetched into registers while the current one is used
-  constexpr int PF = (SL * (C + B) + kThreads - 1) / kThreads;
-  float pre[PF];
-  if (r0 < r1) xgram_fetch<B, SL, PF>(pre, tid, r0, r1, v0, v1, y, vi);
+  constexpr int VW = B < 4 ? B : 4;
+  constexpr int PF = SL * 4 * B / VW / kThreads;
+  static_assert(PF * kThreads * VW == SL * 4 * B, "whole pieces");
+  float pre[PF][VW];
+  if (r0 < r1) xgram_fetch<B, SL, VW, PF>(pre, tid, r0, r1, v0, v1, y, vi);
   for (int64_t rs = r0; rs < r1; rs += SL) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
+      constexpr int per = SL * B / VW;
       const int g = tid + i * kThreads;
-      if (g < SL * (C + B)) {
-        const int r = g / (C + B), c = g % (C + B);
-        if (c < C) sm[r][c] = pre[i]; else sv[r][c - C] = pre[i];
-      }
+      const int arr = g / per, r = g % per / (B / VW), c = g % (B / VW) * VW;
+#pragma unroll
+      for (int q = 0; q < VW; ++q)
+        if (arr < 3) sm[r][arr * B + c + q] = pre[i][q]; else sv[r][c + q] = pre[i][q];
     }
     __syncthreads();
-    if (rs + SL < r1) xgram_fetch<B, SL, PF>(pre, tid, rs + SL, r1, v0, v1, y, vi);
+    if (rs + SL < r1) xgram_fetch<B, SL, VW, PF>(pre, tid, rs + SL, r1, v0, v1, y, vi);
     if (RG > 1) {
       if (grp < RG) {
         const int e = tid - grp * NE;
@@ -634,68 +683,81 @@ k_aapply(const AapplyPair P) {
   }
 }
 
-// Node part of the weight terms of one step (both expansions), and
-// Vbar_{j-1} += A ybar on node rows.
-template <int B>
-__global__ void __launch_bounds__(kThreads)
-k_wnode(int64_t n, const float *__restrict__ s, const float *__restrict__ ybs,
-        const float *__restrict__ ys, const float *__restrict__ xs, const float *__restrict__ ays,
-        const float *__restrict__ ybc, const float *__restrict__ yc, const float *__restrict__ xc,
-        const float *__restrict__ ayc, float *__restrict__ accs, float *__restrict__ accc,
-        double *__restrict__ znode, double *__restrict__ hnode) {
-  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  double z = 0.0, h = 0.0;
-  if (ybs) {
-    for (int c = 0; c < B; ++c) {
-      const int64_t i = p * B + c;
-      z += double(xs[i]) * double(ays[i]) + double(ybs[i]) * double(ys[i]);
-      if (accs) accs[i] += ays[i];
-    }
-  }
-  if (ybc) {
-    for (int c = 0; c < B; ++c) {
-      const int64_t i = p * B + c;
-      z += double(ybc[i]) * double(yc[i]) + double(xc[i]) * double(ayc[i]);
-      h += double(ybc[i]) * double(xc[i]);
-      if (accc) accc[i] += ayc[i];
-    }
-  }
-  const double s2 = double(s[p]) * double(s[p]);
-  znode[p] += s2 * z;
-  hnode[p] += s2 * h;
-}
+// The weight terms of one step, one launch: workgroups [0, nbn) take the nodes
+// (both expansions), the rest the hyperedges (star hyperedge rows at offset n
+// and the clique products T . Tbar).  Bound by its loads: rows are read as
+// vectors, and Vbar_{j-1} += A ybar is left to the cross products that read
+// it (as two kernels that also added it, 26 us a step at 200k nodes and as
+// many hyperedges, b = 4; this takes 11.4).
+struct WeightArgs {
+  int64_t n, m;
+  int nbn;
+  const float *s, *w;
+  const int32_t *eptr;
+  const float *ybs, *ys, *xs, *ays, *ybc, *yc, *xc, *ayc, *tbar, *tf;
+  double *znode, *hnode, *eacc;
+};
 
-// Hyperedge part of one step: star hyperedge rows (offset n) and the clique
-// products T . Tbar; Vbar_{j-1} += A ybar on star hyperedge rows.
 template <int B>
 __global__ void __launch_bounds__(kThreads)
-k_wedge(int64_t n, int64_t m, const int32_t *__restrict__ eptr, const float *__restrict__ w,
-        const float *__restrict__ ybs, const float *__restrict__ ys, const float *__restrict__ xs,
-        const float *__restrict__ ays, const float *__restrict__ tbar, const float *__restrict__ tf,
-        float *__restrict__ accs, double *__restrict__ eacc) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= m) return;
-  const double we = w ? double(w[e]) : 1.0;
-  double acc = 0.0;
-  if (ybs) {
-    double es = 0.0;
-    for (int c = 0; c < B; ++c) {
-      const int64_t i = (n + e) * B + c;
-      es += double(ybs[i]) * double(ys[i]) + double(xs[i]) * double(ays[i]);
-      if (accs) accs[i] += ays[i];
+k_weights(const WeightArgs P) {
+  if (int(blockIdx.x) < P.nbn) {
+    const int64_t p = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    if (p >= P.n) return;
+    double z = 0.0, h = 0.0;
+    float x[B], ay[B], yb[B], y[B];
+    if (P.ybs) {
+      load_vec<B>(P.xs + p * B, x);
+      load_vec<B>(P.ays + p * B, ay);
+      load_vec<B>(P.ybs + p * B, yb);
+      load_vec<B>(P.ys + p * B, y);
+#pragma unroll
+      for (int c = 0; c < B; ++c) z += double(x[c]) * double(ay[c]) + double(yb[c]) * double(y[c]);
     }
+    if (P.ybc) {
+      load_vec<B>(P.xc + p * B, x);
+      load_vec<B>(P.ayc + p * B, ay);
+      load_vec<B>(P.ybc + p * B, yb);
+      load_vec<B>(P.yc + p * B, y);
+#pragma unroll
+      for (int c = 0; c < B; ++c) {
+        z += double(yb[c]) * double(y[c]) + double(x[c]) * double(ay[c]);
+        h += double(yb[c]) * double(x[c]);
+      }
+    }
+    const double s2 = double(P.s[p]) * double(P.s[p]);
+    P.znode[p] += s2 * z;
+    P.hnode[p] += s2 * h;
+    return;
+  }
+  const int64_t e = int64_t(int(blockIdx.x) - P.nbn) * kThreads + threadIdx.x;
+  if (e >= P.m) return;
+  const double we = P.w ? double(P.w[e]) : 1.0;
+  double acc = 0.0;
+  if (P.ybs) {
+    const int64_t i = (P.n + e) * B;
+    float x[B], ay[B], yb[B], y[B];
+    load_vec<B>(P.xs + i, x);
+    load_vec<B>(P.ays + i, ay);
+    load_vec<B>(P.ybs + i, yb);
+    load_vec<B>(P.ys + i, y);
+    double es = 0.0;
+#pragma unroll
+    for (int c = 0; c < B; ++c) es += double(yb[c]) * double(y[c]) + double(x[c]) * double(ay[c]);
     acc += es / (2.0 * we);
   }
-  if (tbar) {
-    double ec = 0.0;
+  if (P.tbar) {
     // T_e lives in the SpMM scratch at row stride 2B, offset B
-    for (int c = 0; c < B; ++c)
-      ec += double(tbar[e * 2 * B + B + c]) * double(tf[e * 2 * B + B + c]);
-    const double k = double(eptr[e + 1] - eptr[e]);
+    float tb[B], tf[B];
+    load_vec<B>(P.tbar + e * 2 * B + B, tb);
+    load_vec<B>(P.tf + e * 2 * B + B, tf);
+    double ec = 0.0;
+#pragma unroll
+    for (int c = 0; c < B; ++c) ec += double(tb[c]) * double(tf[c]);
+    const double k = double(P.eptr[e + 1] - P.eptr[e]);
     acc += ec * (k * (k - 1.0)) / (we * we);  // = ec / (w_e beta_e)
   }
-  eacc[e] += acc;
+  P.eacc[e] += acc;
 }
 
 // dw_e = eacc_e - 1/(2|e|) sum_{p in e} znode_p - 1/(|e|(|e|-1)) sum_{p in e} hnode_p
@@ -848,6 +910,7 @@ size_t transient_bytes(int64_t n, int64_t m, int64_t nnz, const hef_params &p) {
 struct StepSide {
   int64_t rows, pool_rows;
   float *abar;
+  const float *ay;
   int col;
   float *vbar;
   const float *v0, *v1, *y;
@@ -865,7 +928,7 @@ hef_status step_kernels_t(const StepSide &a, const StepSide &b, const float *pba
     const StepSide &t = *sd[i];
     const int64_t per = std::max<int64_t>(64, cdiv(cdiv(t.rows, kXBlocks), 64) * 64);
     nb[i] = int(std::max<int64_t>(1, cdiv(t.rows, per)));
-    P.s[i] = XgramSide{t.v0, t.v1, t.y, VbarIn{t.abar, pbar, K, t.col, t.pool_rows, t.vbar},
+    P.s[i] = XgramSide{t.v0, t.v1, t.y, VbarIn{t.abar, t.ay, pbar, K, t.col, t.pool_rows, t.vbar},
                        t.rows, per, t.xpart};
   }
   P.nb0 = nb[0];
@@ -910,35 +973,25 @@ hef_status aapply(int B, const AapplySide &a, const AapplySide &b, hipStream_t s
   }
 }
 
-template <int B>
-hef_status weights_t(const Level &L, const Structure &st, const float *ybs, const float *ys,
-                     const float *xs, const float *ays, const float *ybc, const float *yc,
-                     const float *xc, const float *ayc, const float *tbar, const float *tf,
-                     float *accs, float *accc, double *znode, double *hnode, double *eacc,
-                     hipStream_t s) {
-  if (L.n > 0)
-    k_wnode<B><<<cdiv(L.n, 256), 256, 0, s>>>(L.n, st.s, ybs, ys, xs, ays, ybc, yc, xc, ayc, accs,
-                                             accc, znode, hnode);
-  if (L.m > 0)
-    k_wedge<B><<<cdiv(L.m, 256), 256, 0, s>>>(L.n, L.m, L.eptr, L.w, ybs, ys, xs, ays, tbar, tf,
-                                             accs, eacc);
-  HEF_LAUNCH_CHECK();
-  return HEF_OK;
-}
-
-hef_status weights(int B, const Level &L, const Structure &st, const float *ybs, const float *ys,
-                   const float *xs, const float *ays, const float *ybc, const float *yc,
-                   const float *xc, const float *ayc, const float *tbar, const float *tf,
-                   float *accs, float *accc, double *znode, double *hnode, double *eacc,
-                   hipStream_t s) {
+hef_status weights(int B, const Level &L, const Structure &st, WeightArgs P, hipStream_t s) {
+  P.n = L.n;
+  P.m = L.m;
+  P.nbn = int(cdiv(L.n, kThreads));
+  P.s = st.s;
+  P.w = L.w;
+  P.eptr = L.eptr;
+  const int64_t nblk = P.nbn + cdiv(L.m, kThreads);
+  if (nblk == 0) return HEF_OK;
   switch (B) {
-    case 1: return weights_t<1>(L, st, ybs, ys, xs, ays, ybc, yc, xc, ayc, tbar, tf, accs, accc, znode, hnode, eacc, s);
-    case 2: return weights_t<2>(L, st, ybs, ys, xs, ays, ybc, yc, xc, ayc, tbar, tf, accs, accc, znode, hnode, eacc, s);
-    case 4: return weights_t<4>(L, st, ybs, ys, xs, ays, ybc, yc, xc, ayc, tbar, tf, accs, accc, znode, hnode, eacc, s);
-    case 8: return weights_t<8>(L, st, ybs, ys, xs, ays, ybc, yc, xc, ayc, tbar, tf, accs, accc, znode, hnode, eacc, s);
-    case 16: return weights_t<16>(L, st, ybs, ys, xs, ays, ybc, yc, xc, ayc, tbar, tf, accs, accc, znode, hnode, eacc, s);
+    case 1: k_weights<1><<<nblk, kThreads, 0, s>>>(P); break;
+    case 2: k_weights<2><<<nblk, kThreads, 0, s>>>(P); break;
+    case 4: k_weights<4><<<nblk, kThreads, 0, s>>>(P); break;
+    case 8: k_weights<8><<<nblk, kThreads, 0, s>>>(P); break;
+    case 16: k_weights<16><<<nblk, kThreads, 0, s>>>(P); break;
     default: return HEF_ERR_UNSUPPORTED;
   }
+  HEF_LAUNCH_CHECK();
+  return HEF_OK;
 }
 
 template <int CPL>
@@ -1104,10 +1157,11 @@ hef_status reverse_sweep(const Level &L, const hef_params &p, const float *dR, f
       const int col_s = int((j - 1) * int64_t(B));
       const int col_c = int((use_star ? bk : 0) + (j - 1) * int64_t(B));
       {
-        const StepSide ss{use_star ? Ns : 0, n, as_j, col_s, w.vb_s, ps, vs(j - 1), ysj,
-                          w.xpart, w.X3};
-        const StepSide sc{use_clique ? n : 0, n, ac_j, col_c, w.vb_c, pc, vc(j - 1), ycj,
-                          w.xpart + size_t(kXBlocks) * C * B, w.X3 + C * B};
+        // (step k has no A ybar of a later step to take in)
+        const StepSide ss{use_star ? Ns : 0, n, as_j, j < k ? w.ay_s : nullptr, col_s, w.vb_s,
+                          ps, vs(j - 1), ysj, w.xpart, w.X3};
+        const StepSide sc{use_clique ? n : 0, n, ac_j, j < k ? w.ay_c : nullptr, col_c, w.vb_c,
+                          pc, vc(j - 1), ycj, w.xpart + size_t(kXBlocks) * C * B, w.X3 + C * B};
         HEF_TRY(step_kernels(B, ss, sc, pbar, K, s));
       }
       k_tadj<<<2, kThreads, 0, s>>>(w.X3, w.tape.Rinv + size_t(j) * 2 * C * C, B, mask, w.Tadj);
@@ -1121,10 +1175,25 @@ hef_status reverse_sweep(const Level &L, const hef_params &p, const float *dR, f
       }
       HEF_TRY(spmm_apply(L, st, B, use_star ? w.yb_s : nullptr, use_star ? w.ay_s : nullptr,
                          use_clique ? w.yb_c : nullptr, use_clique ? w.ay_c : nullptr, w.tbar, s));
-      HEF_TRY(weights(B, L, st, use_star ? w.yb_s : nullptr, ysj, vs(j - 1), w.ay_s,
-                      use_clique ? w.yb_c : nullptr, ycj, vc(j - 1), w.ay_c,
-                      use_clique ? w.tbar : nullptr, tj, as_1, ac_1, w.znode, w.hnode, w.eacc,
-                      s));
+      WeightArgs wa{};
+      if (use_star) {
+        wa.ybs = w.yb_s;
+        wa.ys = ysj;
+        wa.xs = vs(j - 1);
+        wa.ays = w.ay_s;
+      }
+      if (use_clique) {
+        wa.ybc = w.yb_c;
+        wa.yc = ycj;
+        wa.xc = vc(j - 1);
+        wa.ayc = w.ay_c;
+        wa.tbar = w.tbar;
+        wa.tf = tj;
+      }
+      wa.znode = w.znode;
+      wa.hnode = w.hnode;
+      wa.eacc = w.eacc;
+      HEF_TRY(weights(B, L, st, wa, s));
     }
   }
 

@@ -312,11 +312,10 @@ k_jtrinv(const double *__restrict__ LT, const int32_t *__restrict__ keep, int K,
 // super blocks).  FP32 pool: 16 waves, one 32x32 tile of the 128x128 super
 // tile each (tiles below the diagonal of a diagonal super tile are skipped).
 // BF16 pool: 8 waves of two tiles each.  Row slabs of both super blocks are
-// double-buffered in LDS (64 rows, column-major, for the FP32 pool); FP32
-// MFMA accumulators are flushed to float64 registers every 128 rows.
+// double-buffered in LDS (64 rows for the FP32 pool); FP32 MFMA accumulators
+// are flushed to float64 registers every 128 rows.
 constexpr int kSB = 128;        // super-block width (4 MFMA tiles)
 constexpr int kSlab = 64;       // rows per LDS slab
-constexpr int kSLd = kSlab + 4; // LDS column stride (floats) of a slab
 constexpr int kFlushSlabs = 2;  // FP32 accumulation over 128 rows
 constexpr int kGT = 512;        // BF16 Gram workgroup size
 constexpr int kGT32 = 1024;     // FP32 Gram workgroup size: one wave per tile
@@ -404,117 +403,79 @@ __device__ __forceinline__ void load8oct(const void *pool, int pool_type, int64_
     if (rb + q >= rows) v[q] = 0.0f;
 }
 
-// 32 rows of a 128-column super block of an FP32 pool into registers:
-// row-octet input (thread -> octet of rows, 1 column) or row-major input
-// (thread -> row, 8 columns).  The loads are unconditional (addresses
-// clamped into the chunk and the row), so nothing waits on them until the
-// values go to LDS; slab_put applies the row and column masks there and
-// stores the block column-major (column c at S + c * kSLd), an octet as two
-// 16-byte stores.  Within column c the groups of 4 rows are permuted: slab
-// row r sits at r ^ slab_swz(c).  The transposed stores of row-major input
-// (16 columns 8 apart, whose starts share a bank since 8 kSLd is a multiple
-// of 32) then spread over all banks, while each 4-row group stays
-// contiguous for the 16-byte operand reads.  Row-major input takes 16-byte
-// loads when K % 8 == 0 and single floats otherwise.
-template <bool OCT>
+// 32 rows of a 128-column super block of a row-major FP32 matrix into
+// registers: thread -> row tid / 16, columns 4 (tid % 16) and 64 past them.
+// The loads are unconditional (addresses clamped into the chunk and the row),
+// so nothing waits on them until the values go to LDS; slab_put applies the
+// row and column masks there.  A slab is kept row-major: a column's 32
+// neighbours are what one lane half reads of a row, a bank each, and since the
+// halves read rows 32 apart the second 32 rows swap their columns' groups of
+// 32, which puts the halves on the two halves of the banks.  16-byte loads
+// when K % 4 == 0, single floats otherwise.
 __device__ __forceinline__ void slab_get(const float *pool, int64_t r, int64_t r1, int cbase,
                                          int K, int tid, float (&v)[8]) {
-  if (OCT) {
-    const int64_t rb = r + 8 * (tid >> 7);
-    const int64_t rr = rb < r1 ? rb : ((r1 - 1) & ~int64_t(7));
-    const int c = cbase + (tid & 127);
-    const float *p = pool + ((rr >> 3) * K + (c < K ? c : K - 1)) * 8;
-    const float4 a = *reinterpret_cast<const float4 *>(p);
-    const float4 b = *reinterpret_cast<const float4 *>(p + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  } else {
-    const int64_t row = r + (tid >> 4);
-    const float *p = pool + (row < r1 ? row : r1 - 1) * int64_t(K);
-    const int c = cbase + (tid & 15) * 8;
-    if ((K & 7) == 0) {
-      const float *q = p + (c < K ? c : K - 8);
-      const float4 a = *reinterpret_cast<const float4 *>(q);
-      const float4 b = *reinterpret_cast<const float4 *>(q + 4);
-      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-      v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  const int64_t row = r + (tid >> 4);
+  const float *p = pool + (row < r1 ? row : r1 - 1) * int64_t(K);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int c = cbase + 64 * h + (tid & 15) * 4;
+    if ((K & 3) == 0) {
+      const float4 a = *reinterpret_cast<const float4 *>(p + (c < K ? c : K - 4));
+      v[4 * h] = a.x; v[4 * h + 1] = a.y; v[4 * h + 2] = a.z; v[4 * h + 3] = a.w;
     } else {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = p[c + q < K ? c + q : K - 1];
+      for (int q = 0; q < 4; ++q) v[4 * h + q] = p[c + q < K ? c + q : K - 1];
     }
   }
 }
 
-// the row permutation of slab column c (c < kSB): an XOR of whole 4-row groups
-__device__ __forceinline__ int slab_swz(int c) { return ((c >> 3) & 15) << 2; }
-
 // Stores the 32 rows h * 32 ... of a slab (r is the first of them).
-template <bool OCT>
 __device__ __forceinline__ void slab_put(float *S, int h, int64_t r, int64_t r1, int cbase, int K,
                                          int tid, const float (&v)[8]) {
-  float m[8];
-  if (OCT) {
-    const int64_t rb = r + 8 * (tid >> 7);
-    const int c = tid & 127;
-    const bool cok = cbase + c < K;
+  const bool rok = r + (tid >> 4) < r1;
+  float *d = S + (32 * h + (tid >> 4)) * kSB;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) m[q] = (cok && rb + q < r1) ? v[q] : 0.0f;
-    const int row = 32 * h + 8 * (tid >> 7);
-    float *d = S + c * kSLd;
-    *reinterpret_cast<float4 *>(d + (row ^ slab_swz(c))) = make_float4(m[0], m[1], m[2], m[3]);
-    *reinterpret_cast<float4 *>(d + ((row + 4) ^ slab_swz(c))) =
-        make_float4(m[4], m[5], m[6], m[7]);
-  } else {
-    const bool rok = r + (tid >> 4) < r1;
-    const int c0 = (tid & 15) * 8;
-    const int c = cbase + c0;
+  for (int g = 0; g < 2; ++g) {
+    const int c = 64 * g + (tid & 15) * 4;
+    float m[4];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) m[q] = (rok && c + q < K) ? v[q] : 0.0f;
-    const int row = (32 * h + (tid >> 4)) ^ slab_swz(c0);  // (the 8 columns share slab_swz)
-#pragma unroll
-    for (int q = 0; q < 8; ++q) S[(c0 + q) * kSLd + row] = m[q];
+    for (int q = 0; q < 4; ++q) m[q] = (rok && cbase + c + q < K) ? v[4 * g + q] : 0.0f;
+    *reinterpret_cast<float4 *>(d + (c ^ (32 * h))) = make_float4(m[0], m[1], m[2], m[3]);
   }
 }
 
 // The 32x32 tile (ti, tj) of one LDS slab's products.  The slab's rows are
-// split between the two lane halves (half h takes rows h kSlab/2 ...), so
-// that each lane reads four consecutive rows of its column at once.
+// split between the two lane halves: half h takes rows 32 h + s.
 __device__ __forceinline__ void gram_tile(const float *A, const float *Bm, int lane, int ti, int tj,
                                           floatx16 &acc) {
-  const int ca = 32 * ti + (lane & 31), cb = 32 * tj + (lane & 31);
-  const int h = (lane >> 5) * (kSlab / 2);
-  const float *pa = A + ca * kSLd;
-  const float *pb = Bm + cb * kSLd;
-  const int sa = slab_swz(ca), sb = slab_swz(cb);
+  const int h = lane >> 5;
+  const float *pa = A + h * 32 * kSB + ((32 * ti + (lane & 31)) ^ (32 * h));
+  const float *pb = Bm + h * 32 * kSB + ((32 * tj + (lane & 31)) ^ (32 * h));
 #pragma unroll
-  for (int s = 0; s < kSlab / 2; s += 4) {
-    const float4 a = *reinterpret_cast<const float4 *>(pa + ((h + s) ^ sa));
-    const float4 b = *reinterpret_cast<const float4 *>(pb + ((h + s) ^ sb));
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
-  }
+  for (int s = 0; s < kSlab / 2; ++s)
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[s * kSB], pb[s * kSB], acc, 0, 0, 0);
 }
 
-template <bool OCT>
+// Row-major Gram of `pool`, or the upper triangle of W^T pool for two matrices
+// (W non-null: the a block's columns come from W).  Bound by the matrix cores
+// (64 cycles an MFMA, whose two operand reads take 4 of the LDS's).  W^T pool
+// of 200k x 160 takes 176 us; every pair and tile of the full product, slabs
+// transposed into LDS by single floats, took 397.
 __global__ void __launch_bounds__(kGT32)
-k_jgram(const float *__restrict__ pool, const float *__restrict__ poolB, int64_t n, int K, int nsb,
+k_jgram(const float *__restrict__ pool, const float *__restrict__ W, int64_t n, int K, int nsb,
         int npairs, int64_t rows_per_chunk, double *__restrict__ partial) {
-  __shared__ __attribute__((aligned(16))) float As[2][kSB * kSLd];
-  __shared__ __attribute__((aligned(16))) float Bs[2][kSB * kSLd];
+  __shared__ __attribute__((aligned(16))) float As[2][kSB * kSlab];
+  __shared__ __attribute__((aligned(16))) float Bs[2][kSB * kSlab];
   const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
   const int pair = int(lb % npairs);
   const int64_t chunk = lb / npairs;
-  // symmetric (poolB null): super-tile pairs a <= b of V^T V;
-  // cross: every (a, b) of V^T W with W = poolB
-  const bool cross = poolB != nullptr;
-  const int2 ab = cross ? make_int2(pair / nsb, pair % nsb) : pair_of(pair, nsb);
-  const bool diag = !cross && ab.x == ab.y;
+  const int2 ab = pair_of(pair, nsb);
+  const bool diag = ab.x == ab.y;
+  const bool one = diag && !W;  // a single super block is staged
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = tid >> 6;
-  // Off-diagonal and cross pairs: wave w owns tile (w / 4, (w - w / 4) % 4),
+  // Off-diagonal pairs: wave w owns tile (w / 4, (w - w / 4) % 4),
   // so that the tiles of one row or one column of the super tile sit on the
   // four SIMDs (wave w runs on SIMD w % 4) and tiles past column K, which are
   // skipped, leave every SIMD the same share.  Diagonal pairs: waves 0..9
@@ -534,9 +495,8 @@ k_jgram(const float *__restrict__ pool, const float *__restrict__ poolB, int64_t
   }
   on = on && ab.x * kSB + 32 * ti < K && ab.y * kSB + 32 * tj < K;
   // the first half of the block stages super block a, the second half b
-  // (a diagonal pair stages one super block)
-  const bool loader = !diag || tid < kGT32 / 2;
-  const float *src = tid < kGT32 / 2 ? pool : (cross ? poolB : pool);
+  const bool loader = !one || tid < kGT32 / 2;
+  const float *src = tid < kGT32 / 2 && W ? W : pool;
   const int cb = (tid < kGT32 / 2 ? ab.x : ab.y) * kSB;
   const int lt = tid & (kGT32 / 2 - 1);
   const int64_t r0 = chunk * rows_per_chunk;
@@ -553,12 +513,12 @@ k_jgram(const float *__restrict__ pool, const float *__restrict__ poolB, int64_t
   float rv[kSlab / 32][8];
   auto fetch = [&](int64_t r) __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < kSlab / 32; ++h) slab_get<OCT>(src, r + 32 * h, r1, cb, K, lt, rv[h]);
+    for (int h = 0; h < kSlab / 32; ++h) slab_get(src, r + 32 * h, r1, cb, K, lt, rv[h]);
   };
   auto stash = [&](int b, int64_t r) __attribute__((always_inline)) {
     float *S = tid < kGT32 / 2 ? As[b] : Bs[b];
 #pragma unroll
-    for (int h = 0; h < kSlab / 32; ++h) slab_put<OCT>(S, h, r + 32 * h, r1, cb, K, lt, rv[h]);
+    for (int h = 0; h < kSlab / 32; ++h) slab_put(S, h, r + 32 * h, r1, cb, K, lt, rv[h]);
   };
   if (loader && r0 < r1) {  // (an empty chunk has nothing to stage)
     fetch(r0);
@@ -573,7 +533,7 @@ k_jgram(const float *__restrict__ pool, const float *__restrict__ poolB, int64_t
       if (r + 2 * kSlab < r1) fetch(r + 2 * kSlab);
     }
     const float *A = As[buf];
-    const float *Bm = diag ? As[buf] : Bs[buf];
+    const float *Bm = one ? As[buf] : Bs[buf];
     if (on) gram_tile(A, Bm, lane, ti, tj, acc);
     if (++slabs == kFlushSlabs) {
       slabs = 0;
@@ -727,8 +687,8 @@ k_jgram_dma(const float *__restrict__ pool, int64_t n, int K, int nsb, int npair
   }
 }
 
-// G[gi][gj] (mirrored unless `cross`; also to A, the Cholesky's trailing
-// matrix, if given) from the row chunks' tiles, in float64: the sum over the
+// G[gi][gj] and G[gj][gi] (`cross`: from the upper triangle; also to A, the
+// Cholesky's trailing matrix, if given) from the row chunks' tiles, in float64: the sum over the
 // chunks in ColSum's order (32 row lanes of 8 accumulators).  A workgroup
 // takes 64 entries of a tile, coalesced; wave v takes the row lanes
 // v, v + 4, ..., whose sums combine as ColSum's lanes do.  Only the tiles that
@@ -743,8 +703,8 @@ k_gram_finish(const double *__restrict__ partial, int nchunks, int nsb, int npai
   const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
   const int pair = int(blockIdx.x >> 8), wt = int(blockIdx.x >> 4) & 15;
   const int ti = wt / 4, tj = wt % 4;
-  const int2 ab = cross ? make_int2(pair / nsb, pair % nsb) : pair_of(pair, nsb);
-  if (!gram_tile_on(!cross && ab.x == ab.y, ab, ti, tj, K)) return;
+  const int2 ab = pair_of(pair, nsb);
+  if (!gram_tile_on(ab.x == ab.y, ab, ti, tj, K)) return;
   const int ij = (int(blockIdx.x) & 15) * 64 + lane;
   const int64_t ncols = int64_t(npairs) * 16 * 1024;
   const double *src = partial + (int64_t(pair) * 16 + wt) * 1024 + ij;
@@ -769,8 +729,9 @@ k_gram_finish(const double *__restrict__ partial, int nchunks, int nsb, int npai
   const int gi = ab.x * kSB + 32 * ti + ij / 32;
   const int gj = ab.y * kSB + 32 * tj + ij % 32;
   if (gi >= K || gj >= K) return;
+  if (cross && gi > gj) return;  // its mirror image belongs to (gj, gi)
   G[int64_t(gi) * K + gj] = s;
-  if (!cross) G[int64_t(gj) * K + gi] = s;
+  G[int64_t(gj) * K + gi] = s;
   if (A) {
     A[int64_t(gi) * K + gj] = s;
     A[int64_t(gj) * K + gi] = s;
@@ -1656,10 +1617,10 @@ struct GramPlan {
   int64_t rows_per_chunk = 0;
 };
 
-GramPlan gram_plan(int64_t n, int K, bool cross = false) {
+GramPlan gram_plan(int64_t n, int K) {
   GramPlan p;
   p.nsb = (K + kSB - 1) / kSB;
-  p.npairs = cross ? p.nsb * p.nsb : p.nsb * (p.nsb + 1) / 2;
+  p.npairs = p.nsb * (p.nsb + 1) / 2;
   int64_t want = std::max<int64_t>(1, kGramWG / p.npairs);
   int64_t per = cdiv(std::max<int64_t>(n, 1), want);
   per = std::max<int64_t>(128, cdiv(per, 128) * 128);  // whole slabs of both kernels
@@ -1670,7 +1631,7 @@ GramPlan gram_plan(int64_t n, int K, bool cross = false) {
 
 hef_status gram_run(const void *pool, const void *poolB, int pool_type, int64_t n, int K,
                     double *G, Arena &ws, hipStream_t s, bool oct = false, double *A = nullptr) {
-  const GramPlan p = gram_plan(n, K, poolB != nullptr);
+  const GramPlan p = gram_plan(n, K);
   const size_t mk = ws.mark();
   double *partial = ws.take<double>(size_t(p.nchunks) * p.npairs * 16 * 1024);
   HEF_WS_CHECK(ws);
@@ -1690,15 +1651,11 @@ hef_status gram_run(const void *pool, const void *poolB, int pool_type, int64_t 
   else if (pool_type != kPoolF32) {
     set_error("cross Gram of a BF16 pool is not supported");
     return HEF_ERR_UNSUPPORTED;
-  } else if (oct && !poolB)
+  } else if (oct)  // (no cross Gram takes the row-octet layout)
     k_jgram_dma<<<int64_t(p.npairs) * p.nchunks, kGT32, 0, s>>>(
         reinterpret_cast<const float *>(pool), n, K, p.nsb, p.npairs, p.rows_per_chunk, partial);
-  else if (oct)
-    k_jgram<true><<<int64_t(p.npairs) * p.nchunks, kGT32, 0, s>>>(
-        reinterpret_cast<const float *>(pool), reinterpret_cast<const float *>(poolB), n, K, p.nsb,
-        p.npairs, p.rows_per_chunk, partial);
   else
-    k_jgram<false><<<int64_t(p.npairs) * p.nchunks, kGT32, 0, s>>>(
+    k_jgram<<<int64_t(p.npairs) * p.nchunks, kGT32, 0, s>>>(
         reinterpret_cast<const float *>(pool), reinterpret_cast<const float *>(poolB), n, K, p.nsb,
         p.npairs, p.rows_per_chunk, partial);
   HEF_LAUNCH_CHECK();
@@ -1758,8 +1715,8 @@ hef_status apply_run(const void *V, void *Q, int pool_type, int64_t n, int K, in
 // chunk holds at least 128 rows and the plan never exceeds `want` chunks,
 // but the count is not monotone in n, so a coarser level (fewer rows) can
 // need more partials than the finest.
-int64_t gram_max_chunks(int64_t n, int K, bool cross) {
-  const GramPlan p = gram_plan(n, K, cross);
+int64_t gram_max_chunks(int64_t n, int K) {
+  const GramPlan p = gram_plan(n, K);
   const int64_t want = std::max<int64_t>(1, kGramWG / p.npairs);
   return std::max<int64_t>(1, std::min<int64_t>(want, cdiv(std::max<int64_t>(n, 1), 128)));
 }
@@ -1767,7 +1724,7 @@ int64_t gram_max_chunks(int64_t n, int K, bool cross) {
 size_t orth_ws_bytes(int64_t n, int K) {
   const int Kp = (K + 31) / 32 * 32;
   GramPlan p = gram_plan(n, K);
-  p.nchunks = int(gram_max_chunks(n, K, false));
+  p.nchunks = int(gram_max_chunks(n, K));
   Arena a;
   a.take<double>(int64_t(K) * K);    // G
   a.take<double>(int64_t(K) * K);    // trailing matrix of the Cholesky
@@ -1788,8 +1745,8 @@ hef_status gram_f32(const float *X, int64_t n, int K, double *G, Arena &ws, hipS
 }
 
 size_t gram_cross_ws_bytes(int64_t n, int K) {
-  GramPlan p = gram_plan(n, K, true);
-  p.nchunks = int(gram_max_chunks(n, K, true));
+  GramPlan p = gram_plan(n, K);
+  p.nchunks = int(gram_max_chunks(n, K));
   Arena a;
   a.take<double>(size_t(p.nchunks) * p.npairs * 16 * 1024);
   return a.mark() + 1024;

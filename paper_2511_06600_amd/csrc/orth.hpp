@@ -27,8 +27,9 @@ hef_status orthonormalize_pool(void *P, void *out, int pool_type, int64_t n, int
 // through the same matrix-core Gram kernels.
 hef_status gram_f32(const float *X, int64_t n, int K, double *G, Arena &ws, hipStream_t s);
 
-// G = X^T W (float64, K x K, not symmetric) of two row-major n x K float32
-// matrices, through the same kernels; scratch gram_cross_ws_bytes(n, K).
+// G = sym(X^T W) (float64, K x K) of two row-major n x K float32 matrices, the
+// lower triangle of X^T W mirrored, through the same kernels; scratch
+// gram_cross_ws_bytes(n, K).
 size_t gram_cross_ws_bytes(int64_t n, int K);
 hef_status gram_cross_f32(const float *X, const float *W, int64_t n, int K, double *G, Arena &ws,
                           hipStream_t s);
