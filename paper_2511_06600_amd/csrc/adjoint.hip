@@ -356,21 +356,20 @@ __global__ void k_positions(uint32_t *__restrict__ vals, int64_t nnz) {
 }
 
 // ------------------------------------------------------------ 2. joint QR
-// W1 = R^-T and W2 = -Mq R^-T (float32, Kp x Kp, zero outside K x K),
-// Mq = sym(chibar^T chi), sym(X)[i][l] = X[max(i,l)][min(i,l)].
+// The transposes (float32, Kp x Kp, zero outside K x K) of W1 = R^-T and
+// W2 = -Mq R^-T, Mq = sym(chibar^T chi), sym(X)[i][l] = X[max(i,l)][min(i,l)],
+// as gemm2_f32 takes them.
 __global__ void k_qradj_w(const double *__restrict__ Rinv, const double *__restrict__ Mq, int K,
-                          int Kp, float *__restrict__ W1, float *__restrict__ W2) {
+                          int Kp, float *__restrict__ W1T, float *__restrict__ W2T) {
   const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (idx >= int64_t(Kp) * Kp) return;
-  const int i = int(idx / Kp), j = int(idx % Kp);
-  if (i >= K || j >= K) { W1[idx] = 0.0f; W2[idx] = 0.0f; return; }
-  W1[idx] = float(Rinv[int64_t(j) * Kp + i]);
+  const int j = int(idx / Kp), i = gemm2_k(int(idx % Kp));
+  if (i >= K || j >= K) { W1T[idx] = 0.0f; W2T[idx] = 0.0f; return; }
+  W1T[idx] = float(Rinv[int64_t(j) * Kp + i]);
   double acc = 0.0;
   const double *rj = Rinv + int64_t(j) * Kp;
-  for (int l = j; l < K; ++l) {
-    acc -= Mq[int64_t(l) * K + i] * rj[l];
-  }
-  W2[idx] = float(acc);
+  for (int l = j; l < K; ++l) acc -= Mq[int64_t(l) * K + i] * rj[l];
+  W2T[idx] = float(acc);
 }
 
 // ------------------------------------------------------------ 3. Lanczos steps
@@ -1094,8 +1093,7 @@ hef_status reverse_sweep(const Level &L, const hef_params &p, const float *dR, f
   HEF_TRY(gram_cross_f32(w.chibar, w.chi, n, K, w.Mq, a, s));
   k_qradj_w<<<cdiv(int64_t(Kp) * Kp, 256), 256, 0, s>>>(w.rinvJ, w.Mq, K, Kp, w.W1, w.W2);
   HEF_LAUNCH_CHECK();
-  HEF_TRY(gemm_f32(w.chibar, n, K, w.W1, Kp, pbar, false, s));
-  HEF_TRY(gemm_f32(w.chi, n, K, w.W2, Kp, pbar, true, s));
+  HEF_TRY(gemm2_f32(w.chibar, w.W1, w.chi, w.W2, n, K, Kp, pbar, s));
 
   // ---- 3. Lanczos steps in reverse, segment by segment
   HEF_TRY(zero_async(w.abar_s, sizeof(float) * 3 * Ns * B, s));

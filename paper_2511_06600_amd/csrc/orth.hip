@@ -209,7 +209,7 @@ __device__ __forceinline__ double half_readlane_f64(double v, int l, int lane) {
 
 __global__ void __launch_bounds__(1024)
 k_jtrinv(const double *__restrict__ LT, const int32_t *__restrict__ keep, int K, int Kp,
-         double *__restrict__ Rinv, float *__restrict__ Rinv32, float *__restrict__ RinvT32) {
+         double *__restrict__ Rinv, float *__restrict__ RinvT32) {
   typedef double d4 __attribute__((ext_vector_type(4)));
   extern __shared__ double X[];  // [K][kPS]: rows of the column block J
   __shared__ double T[kPW * kPS];
@@ -301,7 +301,6 @@ k_jtrinv(const double *__restrict__ LT, const int32_t *__restrict__ keep, int K,
     const int j = e / K, i = e % K;
     const double x = X[i * kPS + j];
     Rinv[int64_t(j0 + j) * Kp + i] = x;
-    Rinv32[int64_t(j0 + j) * Kp + i] = float(x);
     if (RinvT32) RinvT32[int64_t(i) * Kp + j0 + j] = float(x);
   }
 }
@@ -332,75 +331,6 @@ __device__ __forceinline__ int2 pair_of(int p, int nsb) {
 // above the diagonal (diagonal pairs) and not past column K.
 __device__ __forceinline__ bool gram_tile_on(bool diag, int2 ab, int ti, int tj, int K) {
   return !(diag && tj < ti) && ab.x * kSB + 32 * ti < K && ab.y * kSB + 32 * tj < K;
-}
-
-// 8 consecutive pool values (columns c..c+7 of row `row`) as floats; zeros
-// past the matrix.  Vector loads when the row stride allows.
-__device__ __forceinline__ void load8(const void *pool, int pool_type, int64_t row, int64_t rows,
-                                      int c, int K, float (&v)[8]) {
-  if (row >= rows || c >= K) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = 0.0f;
-    return;
-  }
-  const int64_t off = row * K + c;
-  if (pool_type == kPoolF32) {
-    const float *p = reinterpret_cast<const float *>(pool) + off;
-    if ((K & 3) == 0 && c + 8 <= K) {
-      const float4 a = *reinterpret_cast<const float4 *>(p);
-      const float4 b = *reinterpret_cast<const float4 *>(p + 4);
-      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-      v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = (c + q < K) ? p[q] : 0.0f;
-    }
-  } else {
-    const uint16_t *p = reinterpret_cast<const uint16_t *>(pool) + off;
-    if ((K & 7) == 0 && c + 8 <= K) {
-      const uint4 a = *reinterpret_cast<const uint4 *>(p);
-      const uint32_t u[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        v[2 * q] = __uint_as_float(u[q] << 16);
-        v[2 * q + 1] = __uint_as_float(u[q] & 0xFFFF0000u);
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        v[q] = (c + q < K) ? __uint_as_float(uint32_t(p[q]) << 16) : 0.0f;
-    }
-  }
-}
-
-// The 8 rows rb..rb+7 (rb a multiple of 8) of column c of a pool in the
-// row-octet layout (element (r, c) at ((r >> 3) K + c) 8 + (r & 7)), as
-// floats; zeros past column K or row `rows`.
-__device__ __forceinline__ void load8oct(const void *pool, int pool_type, int64_t rb,
-                                         int64_t rows, int c, int K, float (&v)[8]) {
-  if (rb >= rows || c >= K) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = 0.0f;
-    return;
-  }
-  const int64_t off = ((rb >> 3) * K + c) * 8;
-  if (pool_type == kPoolF32) {
-    const float4 a = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(pool) + off);
-    const float4 b = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(pool) + off + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  } else {
-    const uint4 a = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(pool) + off);
-    const uint32_t u[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      v[2 * q] = __uint_as_float(u[q] << 16);
-      v[2 * q + 1] = __uint_as_float(u[q] & 0xFFFF0000u);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-    if (rb + q >= rows) v[q] = 0.0f;
 }
 
 // 32 rows of a 128-column super block of a row-major FP32 matrix into
@@ -849,165 +779,11 @@ k_japply_f64(const double *__restrict__ V, double *__restrict__ Q, int64_t n, in
 }
 
 // ---------------------------------------------------------------- apply
-// Q = V Rinv (n x K times upper-triangular K x K), out of place.  Block =
-// 128 x 128 output tile; 8 waves of 64 x 32 (2 x 1 MFMA tiles) for the FP32
-// pool, 4 waves of 64 x 64 for the BF16 pool.  The k loop runs over 32-wide
-// chunks up to the tile's last column (Rinv is zero below its diagonal);
-// both operand chunks are staged in LDS, the next one fetched into
-// registers during the current chunk's products.
-constexpr int kAT = 256;         // BF16 apply workgroup size
-constexpr int kAT32 = 512;       // FP32 apply workgroup size
-constexpr int kAM = 128, kAN = 128, kAK = 32;
-constexpr int kALDA = kAK + 1;   // A chunk [128][33]
-constexpr int kALDB = kAN + 1;   // B chunk [32][129]
+// Q = V Rinv (n x K times upper-triangular K x K), out of place, for a BF16
+// pool: block = 128 x 128 output tile, 4 waves of 64 x 64.
+constexpr int kAT = 256;  // BF16 apply workgroup size
+constexpr int kAM = 128, kAN = 128;
 
-template <bool RAW>
-__global__ void __launch_bounds__(kAT32)
-k_japply(const void *__restrict__ V, void *__restrict__ Q, int pool_type, int oct, int64_t n,
-         int K, int Kp, const float *__restrict__ Rinv32, int ncb, int full, int accumulate) {
-  __shared__ float As[kAM * kALDA];
-  __shared__ float Bs[kAK * kALDB];
-  const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
-  const int cb = int(lb % ncb);
-  const int64_t rt = lb / ncb;
-  const int64_t row0 = rt * kAM;
-  const int col0 = cb * kAN;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int w = tid >> 6;
-  // the column quarter of wave w rotates with the block, so that the waves
-  // which stop early (below) fall on every SIMD in turn
-  const int wr = (w >> 2) * 64, wc = int(((w & 3) + lb) & 3) * 32;
-  const bool won = col0 + wc < K;  // a wave whose columns are all past K idles
-  floatx16 acc[2][1];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 1; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
-  // Rinv is upper triangular: rows past the tile's last column are zero
-  const int kend = (!full && col0 + kAN < K) ? col0 + kAN : K;
-  // ... and the wave's own columns need rows k < col0 + wc + 32 only
-  const int kw = (!full && col0 + wc + 32 < kend) ? col0 + wc + 32 : kend;
-  // the next k chunk is fetched into registers while the current one is
-  // multiplied: A = 128 rows x 32 columns of V (2 groups of 8 values per
-  // thread), B = 32 rows x 128 columns of Rinv32 (4 float4 per thread)
-  float ra[1][8];
-  float4 rb[2];
-  // RAW (an FP32 row-major V, K % 8 == 0): loads at clamped addresses,
-  // masked in stash, which keeps them in flight during the products
-  auto fetch = [&](int k0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int h = 0; h < 1; ++h) {
-      const int g = tid + kAT32 * h;
-      if (RAW) {
-        const int r = g / (kAK / 8), c8 = (g % (kAK / 8)) * 8;
-        const int64_t row = row0 + r < n ? row0 + r : n - 1;
-        const int c = k0 + c8 < K ? k0 + c8 : K - 8;
-        const float *p = reinterpret_cast<const float *>(V) + row * K + c;
-        const float4 x = *reinterpret_cast<const float4 *>(p);
-        const float4 y = *reinterpret_cast<const float4 *>(p + 4);
-        ra[h][0] = x.x; ra[h][1] = x.y; ra[h][2] = x.z; ra[h][3] = x.w;
-        ra[h][4] = y.x; ra[h][5] = y.y; ra[h][6] = y.z; ra[h][7] = y.w;
-      } else if (oct) {
-        const int o = g / kAK, c = g % kAK;
-        load8oct(V, pool_type, row0 + 8 * o, n, k0 + c, K, ra[h]);
-      } else {
-        const int r = g / (kAK / 8), c8 = (g % (kAK / 8)) * 8;
-        load8(V, pool_type, row0 + r, n, k0 + c8, K, ra[h]);
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int g = tid + kAT32 * h;
-      const int r = g / (kAN / 4), c4 = (g % (kAN / 4)) * 4;
-      const int kk = k0 + r < kend ? k0 + r : kend - 1, cc = col0 + c4 < Kp ? col0 + c4 : Kp - 4;
-      rb[h] = *reinterpret_cast<const float4 *>(Rinv32 + int64_t(kk) * Kp + cc);
-    }
-  };
-  auto stash = [&](int k0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int h = 0; h < 1; ++h) {
-      const int g = tid + kAT32 * h;
-      if (oct) {
-        const int o = g / kAK, c = g % kAK;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) As[(8 * o + q) * kALDA + c] = (k0 + c < kend) ? ra[h][q] : 0.0f;
-      } else {
-        const int r = g / (kAK / 8), c8 = (g % (kAK / 8)) * 8;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) As[r * kALDA + c8 + q] = (k0 + c8 + q < kend) ? ra[h][q] : 0.0f;
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int g = tid + kAT32 * h;
-      const int r = g / (kAN / 4), c4 = (g % (kAN / 4)) * 4;
-      const bool ok = k0 + r < kend && col0 + c4 < Kp;
-      float *d = Bs + r * kALDB + c4;
-      d[0] = ok ? rb[h].x : 0.0f; d[1] = ok ? rb[h].y : 0.0f;
-      d[2] = ok ? rb[h].z : 0.0f; d[3] = ok ? rb[h].w : 0.0f;
-    }
-  };
-  fetch(0);
-  for (int k0 = 0; k0 < kend; k0 += kAK) {
-    __syncthreads();
-    stash(k0);
-    __syncthreads();
-    if (k0 + kAK < kend) fetch(k0 + kAK);
-    if (k0 >= kw || !won) continue;
-#pragma unroll 4
-    for (int s = 0; s < kAK / 2; ++s) {
-      const int kk = 2 * s + (lane >> 5);
-      float a_op[2], b_op[1];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) a_op[a] = As[(wr + 32 * a + (lane & 31)) * kALDA + kk];
-#pragma unroll
-      for (int b = 0; b < 1; ++b) b_op[b] = Bs[kk * kALDB + wc + 32 * b + (lane & 31)];
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 1; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_op[a], b_op[b], acc[a][b], 0, 0, 0);
-    }
-  }
-  if (accumulate) {  // float32 only: the tile's old values are read first, all at once
-    float *Qf = reinterpret_cast<float *>(Q);
-    const int col = col0 + wc + (lane & 31);
-    const int cc = col < K ? col : K - 1;
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      float old[16];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t row = row0 + wr + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        old[v] = Qf[(row < n ? row : n - 1) * K + cc];
-      }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t row = row0 + wr + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (row < n && col < K) Qf[row * K + col] = old[v] + acc[a][0][v];
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 1; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t row = row0 + wr + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int col = col0 + wc + 32 * b + (lane & 31);
-        if (row < n && col < K) {
-          if (pool_type == kPoolF32)
-            reinterpret_cast<float *>(Q)[row * K + col] = acc[a][b][v];
-          else
-            reinterpret_cast<uint16_t *>(Q)[row * K + col] = f2bf(acc[a][b][v]);
-        }
-      }
-}
 
 // Q = V Rinv for the float32 pool, Rinv upper triangular (Kp x Kp, zero
 // outside K x K), read through its transpose RT (RT[c][k] = Rinv[k][c]): no
@@ -1342,6 +1118,138 @@ __device__ __forceinline__ void store_t8(uint16_t *T, int c8, int row, uint4 v) 
   }
 }
 
+// out = X W1 + X2 W2 (n x K times K x K, float32; W1 lower triangular) from the
+// transposed W1T, W2T [column][k] (Kp x Kp, zero outside K x K, every 32 k in
+// the order of gemm2_k): each product is summed by itself and the two are added at the end.  Bound by the matrix
+// cores: a workgroup of 16 waves takes 32 RT rows of all the columns, so that
+// both matrices are read once, wave w the rows 32 (w % RT) .. + 31 and the
+// 32-column tiles w / RT and w / RT + G, G = 16 / RT (the waves of a SIMD share
+// a row tile and so its tiles whatever K is).  RT = 4 up to K = 256, 2 above:
+// a wave keeps two tiles and two sums of each in registers.  Per 32-wide k
+// chunk the operands go to LDS directly, [row][32 k] and [column][32 k], the
+// 16-byte k group x of line l at slot x ^ ((l >> 1) & 7), so that the reads of
+// 16 consecutive lines hit distinct banks; chunk c + 1 loads during chunk c's
+// products.  Step s of lane half h is k = 2 s + h of the chunk, which is where
+// the matrices W keep it: element 16 h + s of a column's 32.  Rows past n
+// and k past K read clamped addresses: such rows are never stored and W is
+// zero there.  (As two products of 128 x 128 tiles, 200k x 160 took 2 x 180 us,
+// the second tile column a quarter full; this takes 225.)
+template <bool VEC, int RT>
+__global__ void __launch_bounds__(1024)
+k_gemm2(const float *__restrict__ X, const float *__restrict__ X2, int64_t n, int K, int Kp,
+        const float *__restrict__ W1T, const float *__restrict__ W2T, float *__restrict__ out) {
+  constexpr int G = 16 / RT, NT = 2 * G;
+  // separate LDS objects: the loads into one buffer are disjoint from the
+  // reads of the other
+  __shared__ __attribute__((aligned(1024))) float A0[RT * 32 * 32];
+  __shared__ __attribute__((aligned(1024))) float A1[RT * 32 * 32];
+  __shared__ __attribute__((aligned(1024))) float B0[NT * 32 * 32];
+  __shared__ __attribute__((aligned(1024))) float B1[NT * 32 * 32];
+  const int64_t r0 = int64_t(xcd_block(blockIdx.x, gridDim.x)) * (32 * RT);
+  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, li = lane & 31, h = lane >> 5;
+  const int rt = w % RT, g = w / RT;
+  const int nct = Kp / 32;
+  // a piece is 8 lines of 32 k; lane -> line lane / 8, slot lane % 8
+  auto piece = [&](const float *line, int k, float *dst) __attribute__((always_inline)) {
+    if constexpr (VEC) {
+      __builtin_amdgcn_global_load_lds(line + (k < K ? k : K - 4), dst, 16, 0, 0);
+    } else {
+      float4 v;
+      v.x = line[k < K ? k : K - 1];
+      v.y = line[k + 1 < K ? k + 1 : K - 1];
+      v.z = line[k + 2 < K ? k + 2 : K - 1];
+      v.w = line[k + 3 < K ? k + 3 : K - 1];
+      *reinterpret_cast<float4 *>(dst + 4 * lane) = v;
+    }
+  };
+  // chunk t: of X and W1 first, then of X2 and W2
+  auto stage = [&](int t, float *A, float *B) __attribute__((always_inline)) {
+    const bool second = t >= nct;
+    const int c = second ? t - nct : t;
+    const float *V = second ? X2 : X, *WT = second ? W2T : W1T;
+    if (w < 4 * RT) {
+      const int l = 8 * w + (lane >> 3);
+      const int64_t row = r0 + l < n ? r0 + l : n - 1;
+      piece(V + row * K, 32 * c + 4 * ((lane & 7) ^ ((l >> 1) & 7)), A + 8 * w * 32);
+    }
+#pragma unroll
+    for (int u = 0; u < NT / 4; ++u) {
+      const int q = w + 16 * u, ct = q >> 2;
+      if (ct < nct && (second || ct <= c)) {
+        const int l = 8 * (q & 3) + (lane >> 3);
+        const float *line = WT + int64_t(32 * ct + l) * Kp + 32 * c;
+        const int x = 4 * ((lane & 7) ^ ((l >> 1) & 7));
+        __builtin_amdgcn_global_load_lds(line + x, B + 8 * q * 32, 16, 0, 0);
+      }
+    }
+  };
+  floatx16 acc[2], sum1[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[u][v] = 0.0f;
+  auto mul = [&](int t, const float *A, const float *B) __attribute__((always_inline)) {
+    const int last = t >= nct ? nct - 1 : t;  // the last tile with a product
+    const float *pa = A + (32 * rt + li) * 32;
+    const float *pb = B + (32 * g + li) * 32;
+    if (g > last) return;
+#pragma unroll 2
+    for (int q = 0; q < 4; ++q) {
+      const int xo = 4 * ((4 * h + q) ^ ((li >> 1) & 7));
+      float a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        a[j] = pa[4 * ((2 * q + (j >> 1)) ^ ((li >> 1) & 7)) + 2 * (j & 1) + h];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (g + G * u > last) continue;
+        const f32x4 b = *reinterpret_cast<const f32x4 *>(pb + u * G * 1024 + xo);
+        acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b.x, acc[u], 0, 0, 0);
+        acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1], b.y, acc[u], 0, 0, 0);
+        acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[2], b.z, acc[u], 0, 0, 0);
+        acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b.w, acc[u], 0, 0, 0);
+      }
+    }
+  };
+  auto turn = [&](int t) __attribute__((always_inline)) {  // before chunk t
+    if (t != nct) return;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        sum1[u][v] = acc[u][v];
+        acc[u][v] = 0.0f;
+      }
+  };
+  const int total = 2 * nct;
+  stage(0, A0, B0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's loads are in LDS
+  __syncthreads();
+  for (int t = 0; t < total; t += 2) {  // (total is even)
+    stage(t + 1, A1, B1);
+    turn(t);
+    mul(t, A0, B0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    if (t + 2 < total) stage(t + 2, A0, B0);
+    turn(t + 1);
+    mul(t + 1, A1, B1);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int col = 32 * (g + G * u) + li;
+    if (g + G * u >= nct || col >= K) continue;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int64_t row = r0 + 32 * rt + 8 * (v >> 2) + 4 * h + (v & 3);
+      if (row < n) out[row * K + col] = sum1[u][v] + acc[u][v];
+    }
+  }
+}
+
 // G partials of V^T V for a bf16 pool; block / wave / output layout as k_jgram.
 // Slabs of 64 rows are stored transposed in LDS ([column][row]) so that the
 // 8 consecutive rows an MFMA lane needs are one 16-byte read.
@@ -1669,44 +1577,34 @@ hef_status gram_run(const void *pool, const void *poolB, int pool_type, int64_t 
 }
 
 hef_status apply_run(const void *V, void *Q, int pool_type, int64_t n, int K, int Kp,
-                     const float *Rinv32, hipStream_t s, bool full = false,
-                     bool accumulate = false, bool oct = false, const float *RinvT32 = nullptr,
-                     const double *Rinv64 = nullptr) {
+                     hipStream_t s, bool oct, const float *RinvT32, const double *Rinv64) {
   if (n == 0) return HEF_OK;
   TimedScope ts(kStOrthApply, s);
   if (pool_type == kPoolF64) {
-    if (!oct || full || accumulate || !Rinv64) {
+    if (!oct) {
       set_error("the float64 pool takes the row-octet apply only");
       return HEF_ERR_UNSUPPORTED;
     }
     k_japply_f64<<<cdiv(n, 64) * ((K + 63) / 64), 256, 0, s>>>(
         reinterpret_cast<const double *>(V), reinterpret_cast<double *>(Q), n, K, Kp, Rinv64);
-    HEF_LAUNCH_CHECK();
-    return HEF_OK;
+  } else if (oct) {  // (Kp <= 512: at most 8 tiles per column set)
+    k_japply_dma<<<2 * cdiv(n, kDR), kDT, 0, s>>>(reinterpret_cast<const float *>(V),
+                                                 reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
+  } else if ((K & 3) == 0) {
+    k_japply_tri<false, true><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
+        reinterpret_cast<const float *>(V), reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
+  } else {
+    k_japply_tri<false, false><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
+        reinterpret_cast<const float *>(V), reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
   }
-  if (!full && !accumulate && pool_type == kPoolF32 && RinvT32) {
-    if (oct)  // (Kp <= 512: at most 8 tiles per column set)
-      k_japply_dma<<<2 * cdiv(n, kDR), kDT, 0, s>>>(reinterpret_cast<const float *>(V),
-                                                   reinterpret_cast<float *>(Q), n, K, Kp,
-                                                   RinvT32);
-    else if ((K & 3) == 0)
-      k_japply_tri<false, true><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
-          reinterpret_cast<const float *>(V), reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
-    else
-      k_japply_tri<false, false><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
-          reinterpret_cast<const float *>(V), reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
-    HEF_LAUNCH_CHECK();
-    return HEF_OK;
-  }
-  const int ncb = (K + kAN - 1) / kAN;
-  if (!oct && pool_type == kPoolF32 && (K & 7) == 0)
-    k_japply<true><<<cdiv(n, kAM) * ncb, kAT32, 0, s>>>(V, Q, pool_type, oct, n, K, Kp, Rinv32,
-                                                      ncb, full, accumulate);
-  else
-    k_japply<false><<<cdiv(n, kAM) * ncb, kAT32, 0, s>>>(V, Q, pool_type, oct, n, K, Kp, Rinv32,
-                                                       ncb, full, accumulate);
   HEF_LAUNCH_CHECK();
   return HEF_OK;
+}
+
+template <bool VEC, int RT>
+void gemm2_launch(const float *X, const float *W1T, const float *X2, const float *W2T, int64_t n,
+                  int K, int Kp, float *out, hipStream_t s) {
+  k_gemm2<VEC, RT><<<cdiv(n, 32 * RT), 1024, 0, s>>>(X, X2, n, K, Kp, W1T, W2T, out);
 }
 
 }  // namespace
@@ -1730,8 +1628,7 @@ size_t orth_ws_bytes(int64_t n, int K) {
   a.take<double>(int64_t(K) * K);    // trailing matrix of the Cholesky
   a.take<double>(int64_t(K) * K);    // LT
   a.take<double>(int64_t(Kp) * Kp);  // Rinv
-  a.take<float>(int64_t(Kp) * Kp);   // Rinv32
-  a.take<float>(int64_t(Kp) * Kp);   // its transpose
+  a.take<float>(int64_t(Kp) * Kp);   // RinvT32
   a.take<uint16_t>(int64_t(Kp) * Kp);  // RhT
   a.take<uint16_t>(int64_t(Kp) * Kp);  // RlT
   a.take<int32_t>(K);                // keep
@@ -1758,10 +1655,21 @@ hef_status gram_cross_f32(const float *X, const float *W, int64_t n, int K, doub
   return gram_run(X, W, kPoolF32, n, K, G, ws, s);
 }
 
-hef_status gemm_f32(const float *X, int64_t n, int K, const float *W, int Kp, float *out,
-                    bool accumulate, hipStream_t s) {
+hef_status gemm2_f32(const float *X, const float *W1T, const float *X2, const float *W2T,
+                     int64_t n, int K, int Kp, float *out, hipStream_t s) {
   if (K <= 0 || K > 512) return HEF_ERR_UNSUPPORTED;
-  return apply_run(X, out, kPoolF32, n, K, Kp, W, s, true, accumulate);
+  if (n == 0) return HEF_OK;
+  TimedScope ts(kStOrthApply, s);
+  const bool vec = (K & 3) == 0;  // rows start on 16 bytes
+  if (K <= 256) {
+    if (vec) gemm2_launch<true, 4>(X, W1T, X2, W2T, n, K, Kp, out, s);
+    else gemm2_launch<false, 4>(X, W1T, X2, W2T, n, K, Kp, out, s);
+  } else {
+    if (vec) gemm2_launch<true, 2>(X, W1T, X2, W2T, n, K, Kp, out, s);
+    else gemm2_launch<false, 2>(X, W1T, X2, W2T, n, K, Kp, out, s);
+  }
+  HEF_LAUNCH_CHECK();
+  return HEF_OK;
 }
 
 hef_status orthonormalize_pool(void *P, void *out, int pool_type, int64_t n, int K, double tau,
@@ -1779,7 +1687,6 @@ hef_status orthonormalize_pool(void *P, void *out, int pool_type, int64_t n, int
   // (LT to RinvT32 are cleared together)
   double *LT = ws.take<double>(int64_t(K) * K);
   double *Rinv = ws.take<double>(int64_t(Kp) * Kp);
-  float *Rinv32 = ws.take<float>(int64_t(Kp) * Kp);
   float *RinvT32 = ws.take<float>(int64_t(Kp) * Kp);
   uint16_t *RhT = ws.take<uint16_t>(int64_t(Kp) * Kp);
   uint16_t *RlT = ws.take<uint16_t>(int64_t(Kp) * Kp);
@@ -1813,7 +1720,7 @@ hef_status orthonormalize_pool(void *P, void *out, int pool_type, int64_t n, int
         const int nt = (K - c0 - w + kPW - 1) / kPW;
         if (nt > 0) k_chol_update<<<nt * (nt + 1) / 2, 256, 0, s>>>(A, LT, K, c0, w);
       }
-      k_jtrinv<<<(K + kPW - 1) / kPW, 1024, lds_c, s>>>(LT, keep, K, Kp, Rinv, Rinv32, RinvT32);
+      k_jtrinv<<<(K + kPW - 1) / kPW, 1024, lds_c, s>>>(LT, keep, K, Kp, Rinv, RinvT32);
       HEF_LAUNCH_CHECK();
     }
     if (pool_type == kPoolBF16) {
@@ -1829,8 +1736,7 @@ hef_status orthonormalize_pool(void *P, void *out, int pool_type, int64_t n, int
             Kp, RhT, RlT, ncb);
       HEF_LAUNCH_CHECK();
     } else {
-      HEF_TRY(apply_run(src, dst, pool_type, n, K, Kp, Rinv32, s, false, false, oct, RinvT32,
-                        Rinv));
+      HEF_TRY(apply_run(src, dst, pool_type, n, K, Kp, s, oct, RinvT32, Rinv));
     }
     if (pass == 1)
       HEF_HIP(hipMemcpyAsync(out, P,

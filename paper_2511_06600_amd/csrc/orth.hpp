@@ -34,9 +34,13 @@ size_t gram_cross_ws_bytes(int64_t n, int K);
 hef_status gram_cross_f32(const float *X, const float *W, int64_t n, int K, double *G, Arena &ws,
                           hipStream_t s);
 
-// out (n x K) = X W, or out += X W if `accumulate`, for a general K x K
-// float32 matrix W (row-major, row stride Kp), on the matrix cores.
-hef_status gemm_f32(const float *X, int64_t n, int K, const float *W, int Kp, float *out,
-                    bool accumulate, hipStream_t s);
+// out (n x K) = X W1 + X2 W2 for general row-major float32 X, X2, a lower
+// triangular W1 and a general W2 (K x K), given transposed (W1T[j][i] =
+// W1[gemm2_k(i)][j], row stride Kp, zero outside K x K), on the matrix cores.
+__host__ __device__ inline int gemm2_k(int i) {
+  return (i & ~31) + 2 * (i & 15) + ((i >> 4) & 1);
+}
+hef_status gemm2_f32(const float *X, const float *W1T, const float *X2, const float *W2T,
+                     int64_t n, int K, int Kp, float *out, hipStream_t s);
 
 }  // namespace hef

@@ -195,7 +195,7 @@ def test_krylov_step_at_workgroup_edges(b, n, m):
         assert d <= 1e-6
 
 
-@pytest.mark.parametrize("k,b", [(5, 1), (33, 2), (6, 4), (17, 8), (5, 16)])
+@pytest.mark.parametrize("k,b", [(5, 1), (20, 2), (6, 4), (17, 4), (17, 8), (5, 16)])
 def test_gradient_with_long_hyperedges(k, b):
     """Hyperedges of 32, 33, 64 and 300 pins (a workgroup each above 32) in the
     score adjoint, narrow and wide lane groups, every block width, pools of one
