@@ -630,6 +630,13 @@ struct AapplySide {
 struct AapplyPair {
   AapplySide s[2];
   int64_t nb0;
+  // the SpMM's gather rows U[p] = scale_p [ybar star | ybar clique] of the n
+  // nodes, written with ybar (a launch that read it back took 5 us a step at
+  // 200k nodes, b = 4); with one expansion its writer also zeroes the other half
+  int64_t n;
+  const float *scale;
+  float *U;
+  int both;
 };
 
 template <int B>
@@ -676,6 +683,19 @@ k_aapply(const AapplyPair P) {
   if (g == 2) {
 #pragma unroll
     for (int c = 0; c < B; ++c) d[c] = out[c];
+    if (r < P.n) {
+      const float sp = P.scale[r];
+      float *u = P.U + r * 2 * B;
+      float v[B];
+#pragma unroll
+      for (int c = 0; c < B; ++c) v[c] = out[c] * sp;
+      store_vec<B>(u + (second ? B : 0), v);
+      if (!P.both) {
+#pragma unroll
+        for (int c = 0; c < B; ++c) v[c] = 0.0f;
+        store_vec<B>(u + (second ? 0 : B), v);
+      }
+    }
   } else {
 #pragma unroll
     for (int c = 0; c < B; ++c) d[c] += out[c];
@@ -761,32 +781,60 @@ k_weights(const WeightArgs P) {
 
 // dw_e = eacc_e - 1/(2|e|) sum_{p in e} znode_p - 1/(|e|(|e|-1)) sum_{p in e} hnode_p
 //        + wdirect_e   (beta_e / w_e = 1/(|e|(|e|-1)))
-__global__ void k_wfinal(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
-                         int64_t m, const double *__restrict__ eacc,
-                         const double *__restrict__ znode, const double *__restrict__ hnode,
-                         const double *__restrict__ wdirect, float *__restrict__ dw) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= m) return;
-  const int32_t a = eptr[e], b = eptr[e + 1];
+// A lane per hyperedge, its pins 8 at a time; the wave takes those of more than
+// kWaveEdge pins together (a lane alone with 2000 pins is a chain of 250
+// gathers: 93 us at 756k pins; this takes 18).
+constexpr int kWaveEdge = 32;
+
+__global__ void __launch_bounds__(kThreads)
+k_wfinal(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins, int64_t m,
+         const double *__restrict__ eacc, const double *__restrict__ znode,
+         const double *__restrict__ hnode, const double *__restrict__ wdirect,
+         float *__restrict__ dw) {
+  const int64_t e = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const bool on = e < m;
+  const int32_t a = on ? eptr[e] : 0, b = on ? eptr[e + 1] : 0;
   double gz = 0.0, gh = 0.0;
-  // pins in chunks of 8 (loads first), added in CSR order
-  for (int32_t j0 = a; j0 < b; j0 += 8) {
+  // the 8 positions j0, j0 + step, ... (loads first), added in that order
+  auto add8 = [&](int32_t j0, int32_t step, int32_t end, double &z, double &h) {
     int32_t pp[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) pp[u] = pins[j0 + u < b ? j0 + u : b - 1];
-    double z[8], hv[8];
+    for (int u = 0; u < 8; ++u) {
+      const int64_t j = j0 + int64_t(u) * step;
+      pp[u] = pins[j < end ? j : end - 1];
+    }
+    double zv[8], hv[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      z[u] = znode[pp[u]];
+      zv[u] = znode[pp[u]];
       hv[u] = hnode[pp[u]];
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (j0 + u < b) {
-        gz += z[u];
-        gh += hv[u];
+      if (j0 + int64_t(u) * step < end) {
+        z += zv[u];
+        h += hv[u];
       }
+  };
+  if (b - a <= kWaveEdge)
+    for (int32_t j0 = a; j0 < b; j0 += 8) add8(j0, 1, b, gz, gh);
+  for (uint64_t left = __ballot(b - a > kWaveEdge); left; left &= left - 1) {
+    const int l = __builtin_ctzll(left);
+    const int32_t la = __shfl(a, l, 64), lb = __shfl(b, l, 64);
+    double z = 0.0, h = 0.0;
+    for (int64_t j0 = int64_t(la) + lane; j0 < lb; j0 += 512) add8(int32_t(j0), 64, lb, z, h);
+#pragma unroll
+    for (int t = 32; t > 0; t >>= 1) {
+      z += __shfl_xor(z, t, 64);
+      h += __shfl_xor(h, t, 64);
+    }
+    if (lane == l) {
+      gz = z;
+      gh = h;
+    }
   }
+  if (!on) return;
   const double k = double(b - a);
   dw[e] = float(eacc[e] - gz / (2.0 * k) - gh / (k * (k - 1.0)) + wdirect[e]);
 }
@@ -949,11 +997,16 @@ hef_status step_kernels(int B, const StepSide &a, const StepSide &b, const float
 }
 
 template <int B>
-hef_status aapply_t(const AapplySide &a, const AapplySide &b, hipStream_t s) {
+hef_status aapply_t(const AapplySide &a, const AapplySide &b, const Level &L, const Structure &st,
+                    float *scratch, hipStream_t s) {
   AapplyPair P;
   P.s[0] = a;
   P.s[1] = b;
   P.nb0 = cdiv(a.rows * 3, kThreads);
+  P.n = L.n;
+  P.scale = st.s;
+  P.U = scratch + spmm_u_offset(L.m, B);
+  P.both = a.rows > 0 && b.rows > 0;
   const int64_t nblk = P.nb0 + cdiv(b.rows * 3, kThreads);
   if (nblk == 0) return HEF_OK;
   k_aapply<B><<<nblk, kThreads, 0, s>>>(P);
@@ -961,13 +1014,14 @@ hef_status aapply_t(const AapplySide &a, const AapplySide &b, hipStream_t s) {
   return HEF_OK;
 }
 
-hef_status aapply(int B, const AapplySide &a, const AapplySide &b, hipStream_t s) {
+hef_status aapply(int B, const AapplySide &a, const AapplySide &b, const Level &L,
+                  const Structure &st, float *scratch, hipStream_t s) {
   switch (B) {
-    case 1: return aapply_t<1>(a, b, s);
-    case 2: return aapply_t<2>(a, b, s);
-    case 4: return aapply_t<4>(a, b, s);
-    case 8: return aapply_t<8>(a, b, s);
-    case 16: return aapply_t<16>(a, b, s);
+    case 1: return aapply_t<1>(a, b, L, st, scratch, s);
+    case 2: return aapply_t<2>(a, b, L, st, scratch, s);
+    case 4: return aapply_t<4>(a, b, L, st, scratch, s);
+    case 8: return aapply_t<8>(a, b, L, st, scratch, s);
+    case 16: return aapply_t<16>(a, b, L, st, scratch, s);
     default: return HEF_ERR_UNSUPPORTED;
   }
 }
@@ -1169,10 +1223,11 @@ hef_status reverse_sweep(const Level &L, const hef_params &p, const float *dR, f
                             w.yb_s};
         const AapplySide sc{pc, vc(j - 1), ycj, w.vb_c, w.Tadj + (C + B) * C, use_clique ? n : 0,
                             ac_2, ac_1, w.yb_c};
-        HEF_TRY(aapply(B, sa, sc, s));
+        HEF_TRY(aapply(B, sa, sc, L, st, w.tbar, s));
       }
       HEF_TRY(spmm_apply(L, st, B, use_star ? w.yb_s : nullptr, use_star ? w.ay_s : nullptr,
-                         use_clique ? w.yb_c : nullptr, use_clique ? w.ay_c : nullptr, w.tbar, s));
+                         use_clique ? w.yb_c : nullptr, use_clique ? w.ay_c : nullptr, w.tbar, s,
+                         true));
       WeightArgs wa{};
       if (use_star) {
         wa.ybs = w.yb_s;
@@ -1196,7 +1251,7 @@ hef_status reverse_sweep(const Level &L, const hef_params &p, const float *dR, f
   }
 
   // ---- 4. gather per hyperedge
-  k_wfinal<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, L.pins, m, w.eacc, w.znode, w.hnode, w.wdirect,
+  k_wfinal<<<cdiv(m, kThreads), kThreads, 0, s>>>(L.eptr, L.pins, m, w.eacc, w.znode, w.hnode, w.wdirect,
                                         dw);
   HEF_LAUNCH_CHECK();
   return HEF_OK;
