@@ -151,8 +151,8 @@ k_sadj_a(const float *__restrict__ sfwd, int K, int LPR, int64_t m, const double
 // per hyperedge the direct term sum_i qbar_i s_e^(i).  k_sadj_b takes the
 // hyperedges of up to kSmallSeg pins, a lane group each; k_sadj_long the
 // longer ones, a workgroup each (one group walking 2000 pins is a chain of
-// 500 dependent gathers: 845 us at 200k nodes, K = 160, against 420 us for
-// the two).
+// 500 dependent gathers: 845 us at 200k nodes, K = 160, against 400 us for
+// the two, 94 of it the long ones, 119 with half the threads).
 struct SadjOut {
   int32_t *slot_a, *slot_b;
   float *dbar;
@@ -258,7 +258,7 @@ k_sadj_b(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   }
 }
 
-constexpr int kLongThreads = 512;
+constexpr int kLongThreads = 1024;
 
 template <int CPL>
 __global__ void __launch_bounds__(kLongThreads)

@@ -136,8 +136,10 @@ __device__ __forceinline__ void store_cols(void *pool, int64_t row, int K, int c
 // 4 pins at a time, then their extremes meet in LDS.  Row 2 i of `ext`
 // receives the largest, row 2 i + 1 the smallest values, i = (first pin
 // position) / longseg, which no two such hyperedges share.  Maxima do not
-// depend on the order, so the ratios keep their bits.
-constexpr int kLongThreads = 512;
+// depend on the order, so the ratios keep their bits.  The longest hyperedge's
+// chain bounds it: with 512 / 1024 threads 29 / 25 us at 20k nodes, K = 464,
+// 65 / 42 at 200k, K = 160, 355 / 336 at 2M, K = 480.
+constexpr int kLongThreads = 1024;
 
 template <int CPL, int PT>
 __global__ void __launch_bounds__(kLongThreads)
@@ -205,8 +207,8 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
 // (k_score_long): one group walking 2000 pins is a chain of 500 dependent
 // gathers, 0.2 to 0.4 ms whatever the size of the launch.  Measured with
 // that chain / without (this pass plus k_score_long): 20k nodes, K = 464,
-// 204 / 128 us; 200k nodes, K = 160, 410 / 190 us; 2M nodes, K = 480,
-// 3.85 / 3.65 ms.
+// 204 / 92 us; 200k nodes, K = 160, 410 / 174 us; 2M nodes, K = 480,
+// 3.85 / 3.62 ms.
 template <int CPL, int PT>
 __global__ void __launch_bounds__(kThreads)
 k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
@@ -281,6 +283,114 @@ k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   }
 }
 
+// k_score_qh for few hyperedges: the same workgroups of kEdgesPerBlk
+// hyperedges, whose sums must keep their order, would leave most of the chip
+// idle, each group walking LPR / 2 hyperedges one after another.  Four times
+// the threads take them: group gid handles hyperedge number 4 t + gid / ngrp of
+// the old group gid % ngrp in round t, its spreads go to LDS, and the old
+// groups' sums are formed there in their old order.  A round waits for its
+// longest hyperedge, so this pays while the launch fills the chip at most once:
+// 512 workgroups of 4 columns a lane, 256 of 8.  us, k_score_qh / this:
+//   hyperedges     5k         21k        42k        65k        126k
+//   K = 20      28 / 18    30 / 17    32 / 20    40 / 23    42 / 44
+//   K = 160     59 / 41    61 / 42    73 / 55    77 / 60    95 / 106
+//   K = 464     78 / 64    85 / 67   113 / 125  124 / 151  224 / 296
+template <int CPL>
+constexpr int kFewBlocks = 2048 / CPL;
+constexpr int kFewThreads = 1024;
+
+template <int CPL, int PT>
+__global__ void __launch_bounds__(kFewThreads)
+k_score_qh_few(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+               const float *__restrict__ w, const void *__restrict__ pool, int K, int LPR,
+               int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
+               const void *__restrict__ ext) {
+  constexpr int R = kFewThreads / kThreads;
+  constexpr int NA = kThreads * CPL / kFewThreads;  // sums per thread
+  static_assert(NA * kFewThreads == kThreads * CPL, "whole sums per thread");
+  __shared__ double sp[kFewThreads * CPL];
+  __shared__ float sw[kFewThreads];
+  const int tid = threadIdx.x;
+  const int ngrp = kThreads / LPR, W = LPR * CPL;
+  const int gid = tid / LPR, g = gid % ngrp, r = gid / ngrp;
+  const int c0 = (tid % LPR) * CPL;
+  const int per = kEdgesPerBlk / ngrp;  // hyperedges of an old group
+  const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
+  const int64_t e0 = blk * kEdgesPerBlk;
+  const int64_t e1 = e0 + kEdgesPerBlk < m ? e0 + kEdgesPerBlk : m;
+  double acc[NA];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) acc[i] = 0.0;
+  int32_t na = 0, nb = 0;  // the next round's pins and weight
+  float nw = 0.0f;
+  auto fetch = [&](int k) {
+    const int64_t e = e0 + g + int64_t(ngrp) * k;
+    na = nb = 0;
+    if (k < per && e < e1) {
+      na = eptr[e];
+      nb = eptr[e + 1];
+      nw = w ? w[e] : 1.0f;
+    }
+  };
+  fetch(r);
+  for (int k0 = 0; k0 < per && e0 + int64_t(ngrp) * k0 < e1; k0 += R) {
+    const int32_t a = na, b = nb;
+    const float we = nw;
+    const int64_t e = e0 + g + int64_t(ngrp) * (k0 + r);
+    fetch(k0 + R + r);
+    if (a < b && c0 < K) {
+      double s[CPL];
+      if (b - a > longseg) {
+        PoolVal<PT> mx[CPL], mn[CPL];
+        const int64_t row = 2 * int64_t(a / longseg);
+        load_cols<CPL, PT>(ext, row, K, c0, mx);
+        load_cols<CPL, PT>(ext, row + 1, K, c0, mn);
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+          const double d = double(mx[q]) - double(mn[q]);
+          s[q] = d * d;
+        }
+      } else {
+        edge_spread<CPL, PT>(pins, pool, K, c0, a, b, s);
+      }
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) sp[gid * W + c0 + q] = s[q];
+      float *out = sbuf + e * K + c0;
+      if (c0 + CPL <= K && (K & 3) == 0) {
+#pragma unroll
+        for (int q = 0; q < CPL; q += 4)
+          *reinterpret_cast<float4 *>(out + q) =
+              make_float4(float(s[q]), float(s[q + 1]), float(s[q + 2]), float(s[q + 3]));
+      } else {
+#pragma unroll
+        for (int q = 0; q < CPL; ++q)
+          if (c0 + q < K) out[q] = float(s[q]);
+      }
+    }
+    if (c0 == 0) sw[gid] = we;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int at = tid + kFewThreads * i, og = at / W, c = at % W;
+      if (c >= K) continue;
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (k0 + q < per && e0 + og + int64_t(ngrp) * (k0 + q) < e1)
+          acc[i] = fma(double(sw[q * ngrp + og]), sp[(q * ngrp + og) * W + c], acc[i]);
+    }
+    __syncthreads();
+  }
+  // the groups' sums, added in group order
+#pragma unroll
+  for (int i = 0; i < NA; ++i) sp[tid + kFewThreads * i] = acc[i];
+  __syncthreads();
+  for (int c = tid; c < K; c += kFewThreads) {
+    double t = sp[c];
+    for (int og = 1; og < ngrp; ++og) t = t + sp[og * W + c];
+    partial[blk * K + c] = t;
+  }
+}
+
 // R_e = max_i s_e^(i) / Q_H^(i) from the stored numerators: LPR lanes per
 // hyperedge, CPL columns each (ties in the maximum are irrelevant: only the
 // value is kept).
@@ -342,8 +452,12 @@ hef_status score_t(const Level &L, const Structure &st, const void *pool, int K,
   if (nlong > 0)
     k_score_long<CPL, PT><<<nlong, kLongThreads, 0, s>>>(st.big_e, st.n_big, L.eptr, L.pins,
                                                          pool, K, LPR, longseg, ext);
-  k_score_qh<CPL, PT><<<nblk, kThreads, 0, s>>>(L.eptr, L.pins, L.w, pool, K, LPR, L.m, partial,
-                                                sbuf, longseg, ext);
+  if (nblk <= kFewBlocks<CPL>)
+    k_score_qh_few<CPL, PT><<<nblk, kFewThreads, 0, s>>>(L.eptr, L.pins, L.w, pool, K, LPR, L.m,
+                                                         partial, sbuf, longseg, ext);
+  else
+    k_score_qh<CPL, PT><<<nblk, kThreads, 0, s>>>(L.eptr, L.pins, L.w, pool, K, LPR, L.m, partial,
+                                                  sbuf, longseg, ext);
   HEF_LAUNCH_CHECK();
   }
   {

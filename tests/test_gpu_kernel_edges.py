@@ -300,3 +300,30 @@ def test_conductance_at_wave_edges(m):
             assert two == k  # no hyperedge lies in the single node's cluster
             assert cut.cpu().tolist() == [k, 0, k]
             assert vol.cpu().tolist() == [deg[label == 0].sum(), 0, deg[label == 2].sum()]
+
+
+@pytest.mark.parametrize("k,b,m", [(3, 1, 127), (7, 1, 128), (5, 2, 129), (8, 4, 40), (17, 8, 300),
+                                   (4, 2, 65536), (4, 2, 65537), (10, 4, 65409),
+                                   (17, 8, 32768), (17, 8, 32769)])
+def test_quadratic_forms_at_block_edges(k, b, m):
+    """Q_H is summed over blocks of 128 hyperedges, up to 512 of them (256 of
+    more than 256 columns) with four times the threads: blocks full and one hyperedge long, lane groups of 2 to
+    64 lanes, either side of the rule.  Bounds as in
+    test_long_hyperedge_ratios."""
+    from oracle import resistance as orr
+    say(f"case: quadratic forms k={k} b={b} m={m}")
+    n = 2000
+    rng = np.random.default_rng(m + k)
+    sizes = rng.integers(2, 5, m)
+    eptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    first = np.repeat(rng.integers(0, n - 40, m), sizes)
+    pins = first + 11 * (np.arange(eptr[-1]) - np.repeat(eptr[:-1], sizes))
+    w = rng.uniform(0.5, 2, m).astype(np.float32)
+    h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins.astype(np.int32), w=w)
+    R, qh, chi = hef.resistance(to_device(h), hef.Params(k=k, b=b), return_pool=True)
+    s = orr.edge_spread(h.eptr, h.pins, chi.cpu().double().numpy())
+    q = w.astype(np.float64) @ s
+    assert np.abs(qh.cpu().numpy() - q).max() <= 2 * max(m, 2) * 2.0 ** -53 * q.max()
+    ok = q > 0
+    ref = (s[:, ok] / q[ok]).max(1)
+    np.testing.assert_allclose(R.cpu().numpy(), ref, rtol=2.0 ** -22, atol=0)
