@@ -27,7 +27,7 @@
 // passes per million triples), and one thread per node walked its triples
 // through two indirections: 9.9 ms for the 16M triples of a 200k-node
 // netlist, the node walk itself bound by the longest node's serial chain.  Now
-// 0.63 ms: bound by the latency of the segment and pin loads of the middle and
+// 0.6 ms: bound by the latency of the segment and pin loads of the middle and
 // big classes.
 #include <cmath>
 
