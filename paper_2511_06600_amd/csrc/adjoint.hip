@@ -617,10 +617,17 @@ k_tadj(const double *__restrict__ X3all, const double *__restrict__ Rall, int B,
   }
 }
 
-// Mbar = [v0 | v1 | y | vbar] Tadj; one thread per (row, output block g):
-// g = 0 -> accP += (Vbar_{j-2}), g = 1 -> accC += (Vbar_{j-1}), g = 2 -> ybar.
-// Both expansions in one launch: logical workgroups [0, nb0) take side 0,
-// the rest side 1.
+// Mbar = [v0 | v1 | y | vbar] Tadj, output blocks g = 0 -> accP +=
+// (Vbar_{j-2}), g = 1 -> accC += (Vbar_{j-1}), g = 2 -> ybar.  Both expansions
+// in one launch: logical workgroups [0, nb0) take side 0, the rest side 1.
+// Bound by memory: a thread takes a row and all three blocks, so the row's
+// four inputs are read once; at b = 16 that takes 144 VGPRs and 154 us against
+// 120 with a thread per block, which it keeps.  us at 200k nodes and as many
+// hyperedges, a thread per block / per row: b = 1 14.5 / 9.4, b = 2 16.1 / 12.2,
+// b = 4 21.9 / 19.0, b = 8 46.7 / 42.4.
+template <int B>
+constexpr int kAapplyBlocks = B <= 8 ? 3 : 1;
+
 struct AapplySide {
   const float *v0, *v1, *y, *vb;
   const double *Tadj;
@@ -657,48 +664,59 @@ k_aapply(const AapplyPair P) {
   float *__restrict__ ybar = second ? P.s[1].ybar : P.s[0].ybar;
   for (int e = threadIdx.x; e < (C + B) * C; e += kThreads) Ts[e] = float(Tadj[e]);
   __syncthreads();
+  constexpr int NG = kAapplyBlocks<B>;
   const int64_t gid = (lb - (second ? P.nb0 : 0)) * kThreads + threadIdx.x;
-  const int64_t r = gid / 3;
-  const int g = int(gid % 3);
+  const int64_t r = gid / (3 / NG);
+  const int g0 = NG == 3 ? 0 : int(gid % 3);
   if (r >= rows) return;
-  float *dst = g == 0 ? accP : (g == 1 ? accC : ybar);
-  if (!dst) return;
-  float out[B];
+  float out[NG][B], old[NG][B];
+  float *dst[NG];
 #pragma unroll
-  for (int c = 0; c < B; ++c) out[c] = 0.0f;
+  for (int i = 0; i < NG; ++i) {
+    const int g = g0 + i;
+    dst[i] = g == 0 ? accP : (g == 1 ? accC : ybar);
+#pragma unroll
+    for (int c = 0; c < B; ++c) out[i][c] = 0.0f;
+    if (g < 2 && dst[i]) load_vec<B>(dst[i] + r * B, old[i]);
+  }
+  if (NG == 1 && !dst[0]) return;
   const float *src[4] = {v0, v1, y, vb};
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     if (!src[a]) continue;
-    const float *row = src[a] + r * B;
+    float x[B];
+    load_vec<B>(src[a] + r * B, x);
 #pragma unroll
     for (int u = 0; u < B; ++u) {
-      const float x = row[u];
-      const float *tr = Ts + (a * B + u) * C + g * B;
+      const float *tr = Ts + (a * B + u) * C + g0 * B;
 #pragma unroll
-      for (int c = 0; c < B; ++c) out[c] = fmaf(x, tr[c], out[c]);
+      for (int i = 0; i < NG; ++i)
+#pragma unroll
+        for (int c = 0; c < B; ++c) out[i][c] = fmaf(x[u], tr[i * B + c], out[i][c]);
     }
   }
-  float *d = dst + r * B;
-  if (g == 2) {
 #pragma unroll
-    for (int c = 0; c < B; ++c) d[c] = out[c];
-    if (r < P.n) {
-      const float sp = P.scale[r];
-      float *u = P.U + r * 2 * B;
-      float v[B];
+  for (int i = 0; i < NG; ++i) {
+    if (!dst[i]) continue;
+    if (g0 + i < 2) {
 #pragma unroll
-      for (int c = 0; c < B; ++c) v[c] = out[c] * sp;
-      store_vec<B>(u + (second ? B : 0), v);
-      if (!P.both) {
-#pragma unroll
-        for (int c = 0; c < B; ++c) v[c] = 0.0f;
-        store_vec<B>(u + (second ? 0 : B), v);
-      }
+      for (int c = 0; c < B; ++c) old[i][c] += out[i][c];
+      store_vec<B>(dst[i] + r * B, old[i]);
+      continue;
     }
-  } else {
+    store_vec<B>(dst[i] + r * B, out[i]);
+    if (r >= P.n) continue;
+    const float sp = P.scale[r];
+    float *u = P.U + r * 2 * B;
+    float v[B];
 #pragma unroll
-    for (int c = 0; c < B; ++c) d[c] += out[c];
+    for (int c = 0; c < B; ++c) v[c] = out[i][c] * sp;
+    store_vec<B>(u + (second ? B : 0), v);
+    if (!P.both) {
+#pragma unroll
+      for (int c = 0; c < B; ++c) v[c] = 0.0f;
+      store_vec<B>(u + (second ? 0 : B), v);
+    }
   }
 }
 
@@ -1002,12 +1020,12 @@ hef_status aapply_t(const AapplySide &a, const AapplySide &b, const Level &L, co
   AapplyPair P;
   P.s[0] = a;
   P.s[1] = b;
-  P.nb0 = cdiv(a.rows * 3, kThreads);
+  P.nb0 = cdiv(a.rows * (3 / kAapplyBlocks<B>), kThreads);
   P.n = L.n;
   P.scale = st.s;
   P.U = scratch + spmm_u_offset(L.m, B);
   P.both = a.rows > 0 && b.rows > 0;
-  const int64_t nblk = P.nb0 + cdiv(b.rows * 3, kThreads);
+  const int64_t nblk = P.nb0 + cdiv(b.rows * (3 / kAapplyBlocks<B>), kThreads);
   if (nblk == 0) return HEF_OK;
   k_aapply<B><<<nblk, kThreads, 0, s>>>(P);
   HEF_LAUNCH_CHECK();
