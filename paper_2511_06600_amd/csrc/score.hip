@@ -434,9 +434,13 @@ k_score_r(const float *__restrict__ sbuf, int K, int LPR, int64_t m,
   }
 }
 
+// At least kThreads / kEdgesPerBlk lanes, so that a workgroup has no more
+// groups than hyperedges: with one lane a group (K <= CPL) its 256 groups
+// would share 128 hyperedges, and the groups' loops, which run
+// kEdgesPerBlk / ngrp times, would visit none.
 int lanes_for(int K, int CPL) {
   int need = (K + CPL - 1) / CPL;
-  int l = 1;
+  int l = kThreads / kEdgesPerBlk;
   while (l < need) l <<= 1;
   return l;
 }

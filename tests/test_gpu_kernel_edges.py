@@ -327,3 +327,77 @@ def test_quadratic_forms_at_block_edges(k, b, m):
     ok = q > 0
     ref = (s[:, ok] / q[ok]).max(1)
     np.testing.assert_allclose(R.cpu().numpy(), ref, rtol=2.0 ** -22, atol=0)
+
+
+NARROW = [(1, 1, "star"), (1, 1, "both"), (3, 1, "clique"), (2, 1, "both"), (1, 2, "both"),
+          (1, 4, "star")]  # pools of 1, 2, 3, 4, 4 and 4 columns
+
+
+@pytest.mark.parametrize("basis", ["fp32", "bf16", "fp64"])
+@pytest.mark.parametrize("m", [127, 128, 129, 70000])
+def test_narrow_pools_are_scored(m, basis):
+    """Pools of at most four columns, one lane's worth: every hyperedge is
+    scored, up to and above the 512 blocks of the variant for few hyperedges
+    and with long ones among them, in the checked call and in the unchecked
+    one.  Bounds as in test_long_hyperedge_ratios."""
+    from oracle import resistance as orr
+    n = 900
+    rng = np.random.default_rng(m)
+    sizes = rng.integers(2, 5, m)
+    if m > 100:
+        sizes[[0, m // 2, m - 1]] = [33, 300, 64]
+    step = np.where(sizes > 4, 1, 11)
+    eptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    first = rng.integers(0, n - (sizes - 1) * step)
+    pins = np.repeat(first, sizes) + np.repeat(step, sizes) * (
+        np.arange(eptr[-1]) - np.repeat(eptr[:-1], sizes))
+    w = rng.uniform(0.5, 2, m).astype(np.float32)
+    h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins.astype(np.int32), w=w)
+    dh = to_device(h)
+    for k, b, pool in NARROW:
+        say(f"case: narrow pool k={k} b={b} {pool} m={m} {basis}")
+        kw = dict(k=k, b=b, basis=basis, star_only=pool == "star", clique_only=pool == "clique")
+        R, qh, chi = hef.resistance(dh, hef.Params(**kw), return_pool=True)
+        s = orr.edge_spread(h.eptr, h.pins, chi.cpu().double().numpy())
+        q = w.astype(np.float64) @ s
+        assert np.abs(qh.cpu().numpy() - q).max() <= 2 * max(m, 2) * 2.0 ** -53 * q.max()
+        ok = q > 0
+        ref = (s[:, ok] / q[ok]).max(1)
+        np.testing.assert_allclose(R.cpu().numpy(), ref, rtol=2.0 ** -22, atol=0)
+        Ru, qu, cu = hef.resistance_static(dh, hef.Params(assume_valid=True, **kw),
+                                           return_pool=True)
+        assert torch.equal(Ru, R) and torch.equal(qu, qh) and torch.equal(cu, chi)
+
+
+@pytest.mark.parametrize("k,b", [(1, 1), (2, 1), (1, 2)])
+def test_narrow_pools_in_gradient_and_coarsening(k, b):
+    """Pools of two and four columns through the adjoint (against the float64
+    autograd oracle, at the adjoint tests' bound of 1e-3) and through two
+    levels of coarsening, level 1 from the library's own resistances against
+    the oracle bit for bit."""
+    from oracle import clustering as ocl
+    from oracle import gradient as ogr
+    from tests.gpu_common import starts
+    say(f"case: narrow pools, gradient and coarsening k={k} b={b}")
+    sizes = _mixed_sizes(700, 3) + [65, 33, 32]
+    w = np.random.default_rng(2).uniform(0.5, 2.0, len(sizes)).astype(np.float32)
+    h = _hg(800, sizes, 21, w)
+    dh = to_device(h)
+    Xs, Xc, xs, xc = starts(h, b)
+    coef = np.random.default_rng(3).standard_normal(h.m).astype(np.float32)
+    _, ref, Rr = ogr.loss_and_grad(h.n, h.m, h.eptr, h.pins, h.w, Xs, Xc, k, coef)
+    dR = torch.as_tensor(coef, device="cuda")
+    dw = hef.resistance_backward(dh, hef.Params(k=k, b=b), dR, xs, xc)
+    assert np.linalg.norm(dw.cpu().numpy() - ref) <= 1e-3 * np.linalg.norm(ref)
+    R, tape = hef.resistance_taped(dh, hef.Params(k=k, b=b), xs, xc)
+    assert torch.equal(hef.resistance_backward(dh, hef.Params(k=k, b=b), dR, xs, xc, tape=tape), dw)
+    assert np.linalg.norm(R.cpu().numpy() - Rr) <= 1e-4 * np.linalg.norm(Rr)
+    p = hef.Params(k=k, b=b, levels=2)
+    cl, nc, R0, _, lev = hef.coarsen_levels(dh, p)
+    R1, qh, chi = hef.resistance(dh, hef.Params(k=k, b=b), return_pool=True)
+    assert torch.equal(R0, R1) and torch.equal(lev[0]["R"], R1) and torch.equal(lev[0]["qh"], qh)
+    out = ocl.cluster_level(h.n, h.m, h.eptr, h.pins, R1.cpu().numpy(), np.zeros(h.n, np.float32),
+                            chi.cpu().numpy(), qh.cpu().numpy(), 0.5, True)
+    assert np.array_equal(lev[0]["label"].cpu().numpy(), out.label)
+    assert np.array_equal(lev[0]["eta"].cpu().numpy().view(np.uint32), out.eta.view(np.uint32))
+    assert len(lev) == 2 and (lev[1]["R"] > 0).any() and (lev[1]["qh"] > 0).any()
