@@ -1064,7 +1064,12 @@ k_elab_big(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
     const int32_t e = list[bi];
     const int32_t a = eptr[e], sz = eptr[e + 1] - a;
     if (sz > kEdgeSortCap) {
-      if (tid == 0) *overflow = 1;
+      // (the emission before the host sees the flag places the hyperedges
+      // after this one by its count)
+      if (tid == 0) {
+        *overflow = 1;
+        cnt[e] = 0;
+      }
       continue;
     }
     int32_t P = 1;

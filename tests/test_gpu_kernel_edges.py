@@ -401,3 +401,29 @@ def test_narrow_pools_in_gradient_and_coarsening(k, b):
     assert np.array_equal(lev[0]["label"].cpu().numpy(), out.label)
     assert np.array_equal(lev[0]["eta"].cpu().numpy().view(np.uint32), out.eta.view(np.uint32))
     assert len(lev) == 2 and (lev[1]["R"] > 0).any() and (lev[1]["qh"] > 0).any()
+
+
+@pytest.mark.parametrize("at", ["first", "middle", "two"])
+def test_rebuild_with_a_giant_hyperedge_before_others(at):
+    """A hyperedge of more than 16384 pins (left to the global sort) with
+    hyperedges after it: the emission that runs before the host learns of it
+    places those by its count.  The coarse hypergraph and the level counts of
+    a coarsening against the oracle."""
+    from oracle import clustering as ocl
+    n = 20000
+    giant = {"first": [0], "middle": [1500], "two": [3, 2000]}[at]
+    sizes = _mixed_sizes(3000, 5, [(i, 17000 + i) for i in giant])
+    h = _hg(n, sizes, 31)
+    say(f"case: giant hyperedge {at} n={n} m={h.m} nnz={h.eptr[-1]}")
+    dh = to_device(h)
+    rng = np.random.default_rng(8)
+    nc = 5000
+    label = np.concatenate([np.arange(nc), rng.integers(0, nc, n - nc)]).astype(np.int32)
+    out, kept = hef.rebuild(dh, torch.as_tensor(label, device="cuda"), nc)
+    m2, ep, pn, w2, kp = ocl.rebuild(h.m, h.eptr, h.pins, h.w, label)
+    assert out.m == m2 and np.array_equal(out.eptr.cpu().numpy(), ep)
+    assert np.array_equal(out.pins.cpu().numpy(), pn) and np.array_equal(kept.cpu().numpy(), kp)
+    assert np.array_equal(out.w.cpu().numpy(), w2)
+    *_, lev = hef.coarsen_levels(dh, hef.Params(k=4, b=1, levels=2))
+    m1, e1, *_ = ocl.rebuild(h.m, h.eptr, h.pins, h.w, lev[0]["label"].cpu().numpy())
+    assert (lev[1]["m"], lev[1]["nnz"]) == (m1, int(e1[-1]))
