@@ -548,7 +548,9 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   // exact distances of the survivors, smallest lower bound first
   auto resolve = [&]() __attribute__((always_inline)) {
     while (nf > 0) {
-      float l = lane < nf ? fz[lane] : FLT_MAX;
+      // (no entry: behind every entry, also one whose z is infinite, as it is
+      // where 1 / Q_H exceeds float32; equal values go to the lower lane)
+      float l = lane < nf ? fz[lane] : INFINITY;
       int i = lane;
       for (int off = 1; off < 64; off <<= 1) {
         const float ol = __shfl_xor(l, off, 64);
@@ -734,7 +736,7 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       int32_t seed = -1;
       if (ub == FLT_MAX) {
         // seed u: stages B and C of the smallest (bound, label) of this batch
-        float sl = C >= 0 ? z : FLT_MAX;
+        float sl = C >= 0 ? z : INFINITY;
         int32_t sc = C >= 0 ? C : INT32_MAX;
         for (int off = 1; off < 64; off <<= 1) {
           const float ol = __shfl_xor(sl, off, 64);

@@ -427,3 +427,31 @@ def test_rebuild_with_a_giant_hyperedge_before_others(at):
     *_, lev = hef.coarsen_levels(dh, hef.Params(k=4, b=1, levels=2))
     m1, e1, *_ = ocl.rebuild(h.m, h.eptr, h.pins, h.w, lev[0]["label"].cpu().numpy())
     assert (lev[1]["m"], lev[1]["nnz"]) == (m1, int(e1[-1]))
+
+
+@pytest.mark.parametrize("K", [4, 8, 300])
+@pytest.mark.parametrize("tiny", ["one", "most", "all"])
+def test_best_neighbour_with_tiny_quadratic_forms(K, tiny):
+    """Quadratic forms below 2.9e-39, whose reciprocal float32 cannot hold, and
+    either side of that: the float16 screen decides nothing there and every
+    candidate gets its exact distance.  Nodes with one candidate and with more
+    than the 64 survivors kept at once, entries of both signs and zeros; the
+    level against the oracle, bit for bit."""
+    from oracle import clustering as ocl
+    n = 700
+    say(f"case: tiny quadratic forms K={K} {tiny}")
+    h = _hg(n, _mixed_sizes(350, K, [(0, 150), (200, 90)]), K)
+    rng = np.random.default_rng(K)
+    chi = (1e-3 * rng.choice([-1.0, 1.0, 0.0, 0.5], (n, K))
+           * (1 + 1e-2 * rng.random((n, K)))).astype(np.float32)
+    qh = rng.uniform(0.5, 2.0, K)
+    some = {"one": slice(0, 1), "most": slice(0, K - 1), "all": slice(0, K)}[tiny]
+    qh[some] = rng.choice([1e-40, 2e-39, 2.9e-39, 3e-39, 1e-38], K)[some]
+    qh[0] = 1e-40
+    R = rng.random(h.m).astype(np.float32)
+    out = hef.cluster_level(to_device(h), hef.Params(k=K // 4, b=2), torch.as_tensor(R, device="cuda"),
+                            None, torch.as_tensor(chi, device="cuda"),
+                            torch.as_tensor(qh, device="cuda"))
+    ref = ocl.cluster_level(n, h.m, h.eptr, h.pins, R, None, chi, qh, 0.5, True)
+    assert out[1] == ref.n_clusters and np.array_equal(out[0].cpu().numpy(), ref.label)
+    assert np.array_equal(out[2].cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
