@@ -129,7 +129,9 @@ int32_t hef_pool_width(const hef_params *p);
 
 /* Bytes of workspace the operation `op` needs for this hypergraph and these
  * parameters.  Host only; reads no device memory.  The bound covers every
- * coarsening level, whose hypergraphs are never larger than level 0's. */
+ * coarsening level, whose hypergraphs are never larger than level 0's: a
+ * workspace of this size serves every hypergraph of no more nodes,
+ * hyperedges and pins. */
 hef_status hef_workspace_size(const hef_hypergraph *hg, const hef_params *p,
                               int32_t op, size_t *bytes);
 
@@ -175,8 +177,9 @@ hef_status hef_resistance(const hef_hypergraph *hg, const hef_params *p,
  * caller still provides every input and output.  A hypergraph whose
  * workspace (hef_workspace_size with HEF_OP_RESISTANCE, or with chi given,
  * that size less the n x K pool) exceeds HEF_STATIC_SCRATCH_BYTES returns
- * HEF_ERR_WORKSPACE_TOO_SMALL with nothing written.  All calls on one device
- * share that device's scratch, which keeps the last call's contents (every
+ * HEF_ERR_WORKSPACE_TOO_SMALL with nothing written (scratch that this size
+ * holds only for smaller hypergraphs does not count).  All calls on one
+ * device share that device's scratch, which keeps the last call's contents (every
  * call initialises what it reads): calls that overlap on one device -- on
  * two streams or from two threads -- race and give undefined results.  With
  * HEF_FLAG_ASSUME_VALID the call synchronises nothing and enqueues only

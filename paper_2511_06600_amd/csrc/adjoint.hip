@@ -966,7 +966,7 @@ size_t transient_bytes(int64_t n, int64_t m, int64_t nnz, const hef_params &p) {
   a.take<uint32_t>(nnz);
   a.take<uint32_t>(nnz);
   a.take<uint32_t>(nnz);
-  need = std::max(need, a.mark() + radix_ws_bytes(nnz));
+  need = std::max(need, a.mark() + radix_ws_upto(nnz));
   return need + 4096;
 }
 

@@ -1301,7 +1301,7 @@ size_t level_ws_bytes(int64_t n, int64_t m, int64_t nnz, int K) {
   Arena a;
   LevelWs w;
   carve_level(a, n, m, nnz, K, w);
-  return a.mark() + radix_ws_bytes(std::max(std::max(n, m), nnz)) +
+  return a.mark() + radix_ws_upto(std::max(std::max(n, m), nnz)) +
          scan_ws_bytes(std::max(std::max(n, m), nnz) + 1) + 4096;
 }
 
@@ -1581,7 +1581,7 @@ size_t rebuild_ws_bytes(int64_t n, int64_t m, int64_t nnz) {
   for (int i = 0; i < 5; ++i) a.take<uint32_t>(nnz + 1);
   for (int i = 0; i < 4; ++i) a.take<int32_t>(m + 1);
   a.take<int32_t>(8);
-  return a.mark() + radix_ws_bytes(nnz) + scan_ws_bytes(std::max(n, m) + 1) + 4096;
+  return a.mark() + radix_ws_upto(nnz) + scan_ws_bytes(std::max(n, m) + 1) + 4096;
 }
 
 size_t rebuild_call_bytes(int64_t n, int64_t m, int64_t nnz) {

@@ -149,10 +149,12 @@ size_t pool_bytes(int64_t n, int K, int basis) {
 }
 
 // Scratch needed by one resistance estimate at these sizes (beyond the
-// Structure and the pool).
-size_t estimate_scratch(int64_t n, int64_t m, int64_t nnz, const hef_params &p) {
+// Structure and the pool); with `upto` enough for any sizes up to these, else
+// no more than these need, so that a call, and the static scratch, take every
+// hypergraph they can.
+size_t estimate_scratch(int64_t n, int64_t m, int64_t nnz, const hef_params &p, bool upto) {
   const int K = pool_width(p);
-  size_t need = structure_build_ws(n, m, nnz);
+  size_t need = upto ? structure_build_ws(n, m, nnz) : structure_build_need(n, m, nnz);
   Arena a;
   a.take<float>((n + m) * p.b);  // start blocks
   a.take<float>(n * p.b);
@@ -163,7 +165,8 @@ size_t estimate_scratch(int64_t n, int64_t m, int64_t nnz, const hef_params &p) 
   return need + 4096;
 }
 
-size_t resistance_bytes(int64_t n, int64_t m, int64_t nnz, const hef_params &p, bool own_pool) {
+size_t resistance_bytes(int64_t n, int64_t m, int64_t nnz, const hef_params &p, bool own_pool,
+                        bool upto = false) {
   Arena a;
   Structure st;
   structure_carve(a, n, m, nnz, st);
@@ -173,7 +176,7 @@ size_t resistance_bytes(int64_t n, int64_t m, int64_t nnz, const hef_params &p, 
   a.take<char>(pool_bytes(oct_rows(n), K, p.basis));  // the Krylov pool before orthonormalisation
   a.take<double>(K);  // qh
   a.take<float>(m);   // R
-  return a.mark() + estimate_scratch(n, m, nnz, p) + 1024;
+  return a.mark() + estimate_scratch(n, m, nnz, p, upto) + 1024;
 }
 
 __global__ void k_check_finite(const float *R, int64_t m, const double *qh, int K, int32_t *flag) {
@@ -219,7 +222,7 @@ hef_status estimate_level(const Level &L, const hef_params &p, uint64_t seed, in
 }
 
 size_t estimate_level_bytes(int64_t n, int64_t m, int64_t nnz, const hef_params &p) {
-  return estimate_scratch(n, m, nnz, p);
+  return estimate_scratch(n, m, nnz, p, true);
 }
 
 int pool_width_of(const hef_params &p) { return pool_width(p); }
@@ -296,7 +299,7 @@ hef_status hef_workspace_size(const hef_hypergraph *hg, const hef_params *p, int
   switch (op) {
     case HEF_OP_RESISTANCE:
       HEF_TRY(check_params(p, false, true));
-      *bytes = resistance_bytes(n, m, nnz, *p, true);
+      *bytes = resistance_bytes(n, m, nnz, *p, true, true);
       return HEF_OK;
     case HEF_OP_COARSEN:
       HEF_TRY(check_params(p, true));

@@ -615,6 +615,10 @@ size_t radix_ws_bytes(int64_t n, bool lean) {
   return a.mark() + scan_ws_bytes(nb * bins) + 512;
 }
 
+size_t radix_ws_upto(int64_t n) {
+  return std::max(radix_ws_bytes(n), radix_ws_bytes(std::min(n, kRadixSmallN)));
+}
+
 namespace {
 
 template <int ROUNDS, int BITS>

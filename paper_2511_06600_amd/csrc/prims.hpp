@@ -23,8 +23,11 @@ hef_status exclusive_scan3_i32(const std::array<const int32_t *, 3> &in,
 
 // Workspace bytes for radix_sort_pairs over `n` items (about 2 n bytes up to
 // 2^20 items, n / 2 above; n / 4 with `lean`, which keeps to large tiles and
-// 8-bit digits).
+// 8-bit digits): with n just above 2^20 less than with n just below, so a
+// workspace that also sorts fewer items is sized by radix_ws_upto.
 size_t radix_ws_bytes(int64_t n, bool lean = false);
+// Workspace bytes for sorts of any number of items up to n.
+size_t radix_ws_upto(int64_t n);
 // Stable LSD radix sort of n (key, value) pairs by the low `bits` bits of
 // the keys, 8 or 9 bits a pass: src -> out, with tmp as the other ping-pong buffer
 // (both n items; the last pass writes out, so nothing is copied at the end).

@@ -242,7 +242,7 @@ size_t conductance_bytes(int64_t n, int64_t m, int64_t nnz) {
   Arena a;
   QualWs q;
   qual_carve(a, n, m, nnz, q);
-  return a.mark() + radix_ws_bytes(nnz) + 1024;
+  return a.mark() + radix_ws_upto(nnz) + 1024;
 }
 
 }  // namespace hef

@@ -222,17 +222,28 @@ static void carve_scale(Arena &a, int64_t m, ScaleWs &w) {
 // hypergraphs of very long hyperedges take the lean form, so that this scratch
 // stays within 12 nnz + nnz / 4 + 16 m + 8 max(n, m) bytes and everything that
 // fitted the static scratch still does.
-static bool lean_sort(int64_t n, int64_t m, int64_t nnz) {
-  return 7 * nnz + 32768 > 4 * (16 * m + 8 * std::max(n, m));
+static int64_t most_full(int64_t n, int64_t m) {  // pins up to which it is not lean
+  return std::max<int64_t>(0, (4 * (16 * m + 8 * std::max(n, m)) - 32768) / 7);
+}
+static bool lean_sort(int64_t n, int64_t m, int64_t nnz) { return nnz > most_full(n, m); }
+
+static size_t sort_bytes(int64_t nnz, size_t radix) {
+  Arena a;
+  SortWs w;
+  carve_sort(a, nnz, w);
+  return a.mark() + radix;
+}
+
+size_t structure_build_need(int64_t n, int64_t m, int64_t nnz) {
+  Arena c;
+  ScaleWs w;
+  carve_scale(c, m, w);
+  return std::max(sort_bytes(nnz, radix_ws_bytes(nnz, lean_sort(n, m, nnz))), c.mark()) + 4096;
 }
 
 size_t structure_build_ws(int64_t n, int64_t m, int64_t nnz) {
-  Arena a, c;
-  SortWs sw;
-  ScaleWs cw;
-  carve_sort(a, nnz, sw);
-  carve_scale(c, m, cw);
-  return std::max(a.mark() + radix_ws_bytes(nnz, lean_sort(n, m, nnz)), c.mark()) + 4096;
+  const int64_t full = std::min(nnz, most_full(n, m));
+  return std::max(structure_build_need(n, m, nnz), sort_bytes(full, radix_ws_upto(full)) + 4096);
 }
 
 hef_status validate_device(const Level &L, int32_t *flag_dev, int32_t *bad_host,

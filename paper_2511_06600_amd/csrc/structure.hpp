@@ -31,6 +31,9 @@ struct Structure {
 
 // Workspace of a Structure plus the temporaries to build it.
 void structure_carve(Arena &a, int64_t n, int64_t m, int64_t nnz, Structure &st);
+// Scratch of structure_build at these sizes (with which it need not grow: see
+// radix_ws_bytes), and the scratch that serves any sizes up to these.
+size_t structure_build_need(int64_t n, int64_t m, int64_t nnz);
 size_t structure_build_ws(int64_t n, int64_t m, int64_t nnz);
 
 // Device validation of a CSR hypergraph; *bad_host != 0 if invalid.  Clears

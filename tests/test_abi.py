@@ -117,3 +117,39 @@ def test_status_strings():
     for code in range(7):
         assert lib.hef_status_string(code)
     assert lib.hef_status_string(0) == b"ok"
+
+
+def test_workspace_serves_every_smaller_hypergraph():
+    """A workspace sized for one hypergraph is enough for any of no more nodes,
+    hyperedges and pins, whatever the operation: the levels of a coarsening
+    and the sorts within a level rely on it.  Sizes around 2^20 pins, where
+    the sort changes its tile, and where the incidence sort changes its form."""
+    lib = _lib.load()
+    rng = np.random.default_rng(1)
+    ops = (_lib.OP_RESISTANCE, _lib.OP_COARSEN, _lib.OP_CLUSTER_LEVEL, _lib.OP_BACKWARD,
+           _lib.OP_APPLY, _lib.OP_CONDUCTANCE, _lib.OP_REBUILD, _lib.OP_RATING)
+
+    def size(op, n, m, nnz, k, b):
+        p = _lib.HefParams()
+        lib.hef_params_default(C.byref(p))
+        p.k, p.b, p.levels = k, b, 3
+        out = C.c_size_t(0)
+        assert lib.hef_workspace_size(C.byref(_hg(n, m, nnz)), C.byref(p), op,
+                                      C.byref(out)) == _lib.HEF_OK
+        return out.value
+
+    for i in range(1500):
+        n, m = (int(2 ** rng.uniform(4, 22)) for _ in range(2))
+        nnz = int(m * 2 ** rng.uniform(1, 6))
+        if i % 3 == 0:
+            nnz = (1 << 20) + int(rng.integers(1, 2000))
+        if i % 5 == 0:  # where the incidence sort changes its form
+            nnz = (64 * m + 32 * max(n, m)) // 7 + int(rng.integers(0, 5000))
+        m = min(m, nnz // 2)
+        less = [max(int(x * rng.choice([1.0, 0.999, 0.97, 0.6])), 1) for x in (n, m, nnz)]
+        if i % 3 == 0 and nnz > 1 << 20:
+            less[2] = (1 << 20) - int(rng.integers(0, 1000))
+        less[1] = min(less[1], less[2] // 2)
+        k, b = [(1, 1), (2, 1), (10, 1), (20, 4)][i % 4]
+        for op in ops:
+            assert size(op, *less, k, b) <= size(op, n, m, nnz, k, b), (op, n, m, nnz, less, k, b)

@@ -455,3 +455,36 @@ def test_best_neighbour_with_tiny_quadratic_forms(K, tiny):
     ref = ocl.cluster_level(n, h.m, h.eptr, h.pins, R, None, chi, qh, 0.5, True)
     assert out[1] == ref.n_clusters and np.array_equal(out[0].cpu().numpy(), ref.label)
     assert np.array_equal(out[2].cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
+
+
+def test_level_sorts_fit_just_above_a_million_pins():
+    """Slightly more than 2^20 pins and about as many clusters as nodes: the
+    level's largest sort is not its pins' but its clusters', in the smaller
+    tiles.  The level against the oracle, bit for bit (no local clustering),
+    and a coarsening whose level scratch is the largest part."""
+    from oracle import clustering as ocl
+    n, m, nnz = 1_000_000, 500_000, 1_100_000
+    say(f"case: level sorts n={n} m={m} nnz={nnz}")
+    rng = np.random.default_rng(4)
+    sizes = np.full(m, 2)
+    sizes[rng.permutation(m)[:nnz - 2 * m]] += 1
+    eptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    assert eptr[-1] == nnz
+    pins = np.repeat(rng.integers(0, n - 30, m), sizes) + 13 * (
+        np.arange(nnz) - np.repeat(eptr[:-1], sizes))
+    w = rng.uniform(0.5, 2.0, m).astype(np.float32)
+    h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins.astype(np.int32), w=w)
+    dh = to_device(h)
+    R = rng.random(m).astype(np.float32)
+    eta = rng.random(n).astype(np.float32)
+    p = hef.Params(k=4, b=1, local_clustering=False)
+    cl, nc, eo = hef.cluster_level(dh, p, torch.as_tensor(R, device="cuda"),
+                                   torch.as_tensor(eta, device="cuda"),
+                                   torch.zeros((n, 8), device="cuda"),
+                                   torch.ones(8, dtype=torch.float64, device="cuda"))
+    ref = ocl.cluster_level(n, m, h.eptr, h.pins, R, eta, None, np.ones(8), 0.5, False)
+    assert nc == ref.n_clusters and np.array_equal(cl.cpu().numpy(), ref.label)
+    assert np.array_equal(eo.cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
+    cl, nc, _, _ = hef.coarsen(dh, hef.Params(k=20, b=2, levels=2))
+    cl = cl.cpu().numpy()
+    assert 0 < nc < n and cl.min() == 0 and np.unique(cl).size == nc
