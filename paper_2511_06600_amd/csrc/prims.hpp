@@ -147,4 +147,52 @@ __device__ __forceinline__ int lane_of_pos(int32_t start, int32_t j, int cnt) {
   return lo;
 }
 
+// Such a wave walks at most kSpan positions.  Where 64 hyperedges have more,
+// the rest goes to waves of its own, span_extra(nnz) of them ahead of the
+// others: extra wave x takes what lies in positions [(x + 1) kSpan,
+// (x + 2) kSpan) of the 64 hyperedges that hold the first of these positions,
+// past their first kSpan pins (the rest of any later 64 starts behind them).
+// With short hyperedges only, an extra wave ends after its search.  200
+// hyperedges of 5000 pins, four waves' work otherwise: the validation 2600 us
+// to 38 us, the labels of a partition 3070 us to 44 us.
+constexpr int kSpan = 4096;
+inline int64_t span_extra(int64_t nnz) { return nnz > 0 ? (nnz - 1) / kSpan : 0; }
+// Workgroups of 256 threads of a walk over m hyperedges.
+inline int64_t span_blocks(int64_t m, int64_t nnz) {
+  return cdiv(span_extra(nnz) + cdiv(m, 64), 4);
+}
+
+struct PinSpan {
+  int64_t e0;   // first of the 64 hyperedges (m or more: no such wave)
+  int64_t pos;  // first position of an extra wave's span, -1 for the others
+  // the span's part [lo, hi) of the 64 hyperedges' positions [j0, j1)
+  __device__ __forceinline__ int64_t lo(int64_t j0) const {
+    return pos < 0 ? j0 : pos > j0 + kSpan ? pos : j0 + kSpan;
+  }
+  __device__ __forceinline__ int64_t hi(int64_t j0, int64_t j1) const {
+    const int64_t end = (pos < 0 ? j0 : pos) + kSpan;
+    return end < j1 ? end : j1;
+  }
+};
+
+// This wave among the waves of its launch, in a scalar register.
+__device__ __forceinline__ int64_t wave_index() {
+  return int64_t(blockIdx.x) * (blockDim.x >> 6) +
+         __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+}
+
+// The span of a wave (eptr need not be valid: only its entries 0, 64, ... are
+// read, and the search ends whatever they hold).
+__device__ __forceinline__ PinSpan pin_span(const int32_t *__restrict__ eptr, int64_t m,
+                                            int64_t wave, int64_t extra) {
+  if (wave >= extra) return {64 * (wave - extra), -1};
+  const int64_t pos = (wave + 1) * kSpan;
+  int64_t lo = 0, hi = (m + 63) / 64;
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (eptr[64 * mid] <= pos) lo = mid; else hi = mid;
+  }
+  return {64 * lo, pos};
+}
+
 }  // namespace hef

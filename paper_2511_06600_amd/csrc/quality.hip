@@ -37,23 +37,28 @@ constexpr int kQT = 256;
 // from their hyperedge's first, and the 64 answers are one word of split (one
 // thread per position, a search for its hyperedge and a word per hyperedge set
 // by every thread that differs took 126 us at 7.9M pins; this takes 61 us).
+// Where more than one wave walks the 64 hyperedges (pin_span) their answers
+// meet in the word, which is zero before.
 constexpr int kEmitPos = 4;
 
 __global__ void __launch_bounds__(kQT)
 k_qual_emit(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
-            const int32_t *__restrict__ label, int32_t m, int32_t nc,
+            const int32_t *__restrict__ label, int32_t m, int32_t nc, int64_t extra,
             uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-            uint64_t *__restrict__ split, int32_t *__restrict__ bad) {
-  const int64_t e = int64_t(blockIdx.x) * kQT + threadIdx.x;
+            unsigned long long *__restrict__ split, int32_t *__restrict__ bad) {
   const int lane = threadIdx.x & 63;
-  const int64_t e0 = e - lane;
+  const PinSpan sp = pin_span(eptr, m, wave_index(), extra);
+  const int64_t e0 = sp.e0, e = e0 + lane;
   if (e0 >= m) return;
   const int cnt = m - e0 < 64 ? int(m - e0) : 64;
+  const int32_t s0 = eptr[e0], s1 = eptr[e0 + cnt];  // the 64 hyperedges' positions
+  const int64_t j0 = sp.lo(s0);
+  const int32_t j1 = int32_t(sp.hi(s0, s1));
+  if (j0 >= j1) return;
   const bool on = lane < cnt;
   const int32_t a = on ? eptr[e] : 0, z = on ? eptr[e + 1] : 0;
   int32_t first = on ? label[pins[a]] : 0;
   if (first < 0 || first >= nc) first = 0;
-  const int32_t j0 = __shfl(a, 0, 64), j1 = __shfl(z, cnt - 1, 64);
   bool mixed = false, out = false;
   for (int64_t jb = j0; jb < j1; jb += 64 * kEmitPos) {
     int32_t c[kEmitPos];
@@ -82,6 +87,7 @@ k_qual_emit(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       }
       const uint64_t diff = __ballot(in && c[u] != cf);
       // this lane's positions of the chunk: bits [lo, hi)
+      // (diff is zero past the span's end)
       const int64_t lo = a > jc ? a - jc : 0, hi = z - jc < 64 ? z - jc : 64;
       if (lo < hi) {
         const uint64_t below = hi < 64 ? (uint64_t(1) << hi) - 1 : ~uint64_t(0);
@@ -90,7 +96,12 @@ k_qual_emit(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
     }
   }
   const uint64_t word = __ballot(on && mixed);
-  if (lane == 0) split[e0 >> 6] = word;
+  if (lane == 0) {
+    if (s1 - s0 <= kSpan)
+      split[e0 >> 6] = word;
+    else if (word)
+      atomicOr(&split[e0 >> 6], static_cast<unsigned long long>(word));
+  }
   if (out) *bad = 1;  // every writer stores the same value
 }
 
@@ -113,7 +124,7 @@ __global__ void k_qual_seg(const uint32_t *__restrict__ keys, int64_t nnz, int32
 // 97 us at 7.9M pins and 118k clusters; now 59).
 __global__ void __launch_bounds__(kQT)
 k_qual_cluster(const float *__restrict__ w, const uint32_t *__restrict__ vals, const int32_t *__restrict__ seg,
-               const uint64_t *__restrict__ split, int32_t nc, double *__restrict__ cut,
+               const unsigned long long *__restrict__ split, int32_t nc, double *__restrict__ cut,
                double *__restrict__ vol) {
   const int64_t c = (int64_t(blockIdx.x) * kQT + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
@@ -219,8 +230,8 @@ __global__ void k_qual_zero(double *__restrict__ a, double *__restrict__ b,
 
 struct QualWs {
   uint32_t *k0, *v0, *k1, *v1;
-  uint64_t *split;     // a bit per hyperedge
   int32_t *seg, *bad;  // bad: the hypergraph's flag, the labels' flag
+  unsigned long long *split;  // a bit per hyperedge; cleared with the flags
   double *tot, *part;
 };
 
@@ -229,9 +240,9 @@ void qual_carve(Arena &a, int64_t n, int64_t m, int64_t nnz, QualWs &q) {
   q.v0 = a.take<uint32_t>(nnz);
   q.k1 = a.take<uint32_t>(nnz);
   q.v1 = a.take<uint32_t>(nnz);
-  q.split = a.take<uint64_t>(cdiv(m, 64));
   q.seg = a.take<int32_t>((n > 1 ? n : 1) + 1);
   q.bad = a.take<int32_t>(2);
+  q.split = a.take<unsigned long long>(cdiv(m, 64));
   q.tot = a.take<double>(1);
   q.part = a.take<double>(kSumBlocks);
 }
@@ -277,7 +288,8 @@ extern "C" hef_status hef_conductance(const hef_hypergraph *hg, const int32_t *l
   Level L;
   L.n = hg->n; L.m = hg->m; L.nnz = hg->nnz; L.eptr = hg->eptr; L.pins = hg->pins; L.w = hg->w;
   int32_t bad = 0;
-  HEF_TRY(validate_device(L, q.bad, &bad, stream, 2));
+  const int64_t clear = reinterpret_cast<int32_t *>(q.split + cdiv(m, 64)) - q.bad;
+  HEF_TRY(validate_device(L, q.bad, &bad, stream, int(clear)));
   if (bad) {
     set_error("invalid hypergraph (code %d: 1 eptr ends, 2 segment bounds or |e|<2, 4 pins, 8 weights)", bad);
     return HEF_ERR_INVALID_HYPERGRAPH;
@@ -292,8 +304,8 @@ extern "C" hef_status hef_conductance(const hef_hypergraph *hg, const int32_t *l
   }
   const int bits = bits_for(nc - 1);
   uint32_t *sk = radix_src(bits, q.k0, q.k1), *sv = radix_src(bits, q.v0, q.v1);
-  k_qual_emit<<<cdiv(m, kQT), kQT, 0, stream>>>(L.eptr, L.pins, label, int32_t(m), nc, sk, sv,
-                                                 q.split, q.bad + 1);
+  k_qual_emit<<<span_blocks(m, nnz), kQT, 0, stream>>>(L.eptr, L.pins, label, int32_t(m), nc,
+                                                       span_extra(nnz), sk, sv, q.split, q.bad + 1);
   HEF_LAUNCH_CHECK();
   HEF_TRY(radix_sort_pairs(sk, sv, q.k0, q.v0, q.k1, q.v1, nnz, bits, a, stream));
   k_qual_seg<<<cdiv(int64_t(nc) + 1, kQT), kQT, 0, stream>>>(q.k1, nnz, nc, q.seg);

@@ -11,13 +11,15 @@ namespace {
 
 __global__ void __launch_bounds__(256)
 k_validate(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
-           const float *__restrict__ w, int32_t n, int32_t m, int64_t nnz,
+           const float *__restrict__ w, int32_t n, int32_t m, int64_t nnz, int64_t extra,
            int32_t *__restrict__ flag) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
-  const int64_t e0 = e - lane;
+  const PinSpan sp = pin_span(eptr, m, wave_index(), extra);
+  const int64_t e0 = sp.e0, e = e0 + lane;
   if (e0 >= m) return;
   const int cnt = m - e0 < 64 ? int(m - e0) : 64;
+  // an extra wave past its hyperedges' pins (wherever they claim to lie)
+  if (sp.pos >= 0 && sp.lo(eptr[e0]) >= eptr[e0 + cnt]) return;
   const bool on = lane < cnt;
   int bad = 0;
   const int64_t a = on ? eptr[e] : 0, b = on ? eptr[e + 1] : 2;
@@ -34,8 +36,9 @@ k_validate(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
     // every segment of the wave lies in [0, nnz) and starts where the one
     // before it ends
     const int32_t a32 = int32_t(a);
-    const int32_t j0 = __shfl(a32, 0, 64), j1 = __shfl(int32_t(b), cnt - 1, 64);
-    for (int64_t jb = j0; jb < j1; jb += 64) {
+    const int32_t j0 = __shfl(a32, 0, 64);
+    const int32_t j1 = int32_t(sp.hi(j0, __shfl(int32_t(b), cnt - 1, 64)));
+    for (int64_t jb = sp.lo(j0); jb < j1; jb += 64) {
       const bool in = jb + lane < j1;
       const int32_t j = in ? int32_t(jb + lane) : j1 - 1;
       const int32_t p = in ? pins[j] : 0;
@@ -43,7 +46,7 @@ k_validate(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       const int32_t start = __shfl(a32, lane_of_pos(a32, j, cnt), 64);
       if (in && (p < 0 || p >= n || (j != start && p <= q))) bad |= 4;
     }
-  } else if (on && !(bad & 3)) {
+  } else if (sp.pos < 0 && on && !(bad & 3)) {
     int32_t prev = -1;
     for (int64_t j = a; j < b; ++j) {
       const int32_t p = pins[j];
@@ -58,20 +61,23 @@ k_validate(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
 }
 
 // eid[j] = the hyperedge of pin position j (same walk: 36 us to about 12 us at
-// 756k pins with a 2000-pin hyperedge among them); also clears the list
-// lengths of the long segments for the kernels after it.
+// 756k pins with a 2000-pin hyperedge among them, 544 us to 30 us for 200
+// hyperedges of 5000 pins); also clears the list lengths of the long segments
+// for the kernels after it.
 __global__ void __launch_bounds__(256)
-k_edge_ids(const int32_t *__restrict__ eptr, uint32_t *__restrict__ eid, int32_t m,
+k_edge_ids(const int32_t *__restrict__ eptr, uint32_t *__restrict__ eid, int32_t m, int64_t extra,
            int32_t *__restrict__ n_big) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e < 2) n_big[e] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 2) n_big[threadIdx.x] = 0;
   const int lane = threadIdx.x & 63;
-  const int64_t e0 = e - lane;
+  const PinSpan sp = pin_span(eptr, m, wave_index(), extra);
+  const int64_t e0 = sp.e0;
   if (e0 >= m) return;
   const int cnt = m - e0 < 64 ? int(m - e0) : 64;
-  const int32_t a = lane < cnt ? eptr[e] : 0;
-  const int32_t j0 = __shfl(a, 0, 64), j1 = eptr[e0 + cnt];
-  for (int64_t jb = j0; jb < j1; jb += 64) {
+  const int64_t jlo = sp.lo(eptr[e0]);
+  const int32_t j1 = int32_t(sp.hi(eptr[e0], eptr[e0 + cnt]));
+  if (jlo >= j1) return;
+  const int32_t a = lane < cnt ? eptr[e0 + lane] : 0;
+  for (int64_t jb = jlo; jb < j1; jb += 64) {
     const bool in = jb + lane < j1;
     const int32_t j = in ? int32_t(jb + lane) : j1 - 1;
     const int k = lane_of_pos(a, j, cnt);
@@ -250,7 +256,8 @@ hef_status validate_device(const Level &L, int32_t *flag_dev, int32_t *bad_host,
                            hipStream_t s, int clear) {
   HEF_TRY(zero_async(flag_dev, clear * sizeof(int32_t), s));
   if (L.m > 0)
-    k_validate<<<cdiv(L.m, 256), 256, 0, s>>>(L.eptr, L.pins, L.w, L.n, L.m, L.nnz, flag_dev);
+    k_validate<<<span_blocks(L.m, L.nnz), 256, 0, s>>>(L.eptr, L.pins, L.w, L.n, L.m, L.nnz,
+                                                      span_extra(L.nnz), flag_dev);
   HEF_LAUNCH_CHECK();
   HEF_HIP(hipMemcpyAsync(bad_host, flag_dev, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HEF_HIP(hipStreamSynchronize(s));
@@ -270,7 +277,8 @@ hef_status structure_build(const Level &L, Structure &st, Arena &ws, hipStream_t
     const int bits = bits_for(n > 0 ? n - 1 : 0);
     uint32_t *eids = reinterpret_cast<uint32_t *>(st.eids);
     uint32_t *ids = radix_src(bits, w.tmp_v, eids, lean_sort(n, m, nnz));
-    k_edge_ids<<<cdiv(m, 256), 256, 0, s>>>(L.eptr, ids, int32_t(m), st.n_big);
+    k_edge_ids<<<span_blocks(m, nnz), 256, 0, s>>>(L.eptr, ids, int32_t(m), span_extra(nnz),
+                                                  st.n_big);
     HEF_LAUNCH_CHECK();
     HEF_TRY(radix_sort_pairs(reinterpret_cast<const uint32_t *>(L.pins), ids, w.tmp_k, w.tmp_v,
                              w.out_k, eids, nnz, bits, ws, s, lean_sort(n, m, nnz)));

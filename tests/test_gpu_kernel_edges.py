@@ -488,3 +488,56 @@ def test_level_sorts_fit_just_above_a_million_pins():
     cl, nc, _, _ = hef.coarsen(dh, hef.Params(k=20, b=2, levels=2))
     cl = cl.cpu().numpy()
     assert 0 < nc < n and cl.min() == 0 and np.unique(cl).size == nc
+
+
+LAYOUTS = {"long": [1000] * 130, "giant": [3] * 70 + [13000] + [3] * 100,
+           "long then short": [700] * 64 + [2] * 300, "short then long": [2] * 64 + [4096] * 3 + [9],
+           "span": [4096], "below": [2] * 63 + [4096 - 126], "above": [2] * 63 + [4097 - 126]}
+
+
+@pytest.mark.parametrize("layout", list(LAYOUTS))
+def test_long_pin_ranges_are_split(layout):
+    """64 hyperedges of more than 4096 pins are walked by several waves, which
+    start at multiples of 4096 positions: bad pins at every start and end of
+    such a span are found, every incidence carries its hyperedge, and a
+    hyperedge is split if any of the waves sees it (whole-number sums, equal)."""
+    say(f"case: long pin ranges {layout}")
+    sizes = np.array(LAYOUTS[layout])
+    m, n, nnz = len(sizes), 14000, int(sizes.sum())
+    rng = np.random.default_rng(m)
+    eptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    first = (rng.random(m) * (n - sizes)).astype(np.int64)
+    pins = (np.repeat(first, sizes) + np.arange(nnz) - np.repeat(eptr[:-1], sizes)).astype(np.int32)
+    w = rng.integers(1, 9, m).astype(np.float32)
+    eid = np.repeat(np.arange(m), sizes)
+    spans = [x * 4096 for x in range(1, nnz // 4096 + 1)]
+    blocks = [int(eptr[b]) + 4096 for b in range(0, m, 64)] + [int(x) for x in eptr[64:m:64]]
+    at = sorted({p + d for p in [0, nnz - 1] + spans + blocks for d in (-1, 0, 1) if 0 <= p + d < nnz})
+    at = [j for j in at if j > eptr[eid[j]]]
+    at = at if len(at) <= 40 else at[:10] + [at[i] for i in rng.choice(len(at), 30, replace=False)]
+    label0 = torch.zeros(n, dtype=torch.int32, device="cuda")
+    for j in at:
+        p = pins.copy()
+        p[j] = p[j - 1]
+        with pytest.raises(hef.HefError, match="code 4"):
+            hef.conductance(hef.DeviceHypergraph.from_arrays(n, m, eptr, p, w), label0, 1)
+    h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins, w=w)
+    dh = to_device(h)
+    # one node apart from the others, at the same places
+    for j in at[:12]:
+        label = np.zeros(n, np.int32)
+        label[pins[j]] = 1
+        cut, vol, _, _ = hef.conductance(dh, torch.as_tensor(label, device="cuda"), 2)
+        k = float(w[eid[pins == pins[j]]].sum())
+        assert cut.cpu().tolist() == [k, k]
+        assert vol.cpu().tolist() == [float((w * sizes).sum()) - k, k]
+    # every incidence: a value per hyperedge, summed at the nodes by the star operator
+    x = torch.zeros((n + m, 1), device="cuda")
+    x[n:, 0] = torch.arange(m, device="cuda") % 13
+    y = hef.debug_apply(dh, 0, x).cpu().numpy()[:n, 0].astype(np.float64)
+    alpha = np.sqrt(w.astype(np.float64)) / sizes
+    db = np.bincount(pins, weights=np.repeat(w / sizes, sizes), minlength=n)
+    ref = np.bincount(pins, weights=np.repeat(alpha * (np.arange(m) % 13), sizes), minlength=n)
+    ref = np.where(db > 0, ref / np.sqrt(np.where(db > 0, db, 1.0)), 0.0)
+    deg = np.bincount(pins, minlength=n).max()
+    assert np.abs(y - ref).max() <= (deg + 4) * 2.0 ** -24 * max(np.abs(ref).max(), 1.0)
