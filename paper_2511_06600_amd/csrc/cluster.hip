@@ -1131,55 +1131,59 @@ __global__ void k_distinct(const int32_t *__restrict__ eptr, const uint32_t *__r
   cnt[e] = c >= 2 ? c : 0;
 }
 
-// A thread emits a hyperedge of up to kSmallSeg pins, the wave a longer one,
-// 64 sorted labels at a time.  One thread on 2000 labels is a chain of 2000
+// A thread emits a hyperedge of up to kSmallSeg pins; workgroups
+// [0, kEmitBig) walk the structure's list of the longer ones, a wave each, 64
+// sorted labels at a time.  One thread on 2000 labels is a chain of 2000
 // loads: per level of a coarsening from 20k / 200k / 2M nodes 44 / 111 / 148
-// us, now 7 / 12 / 33 us.
+// us, now 5 / 9 / 32 us; 200 hyperedges of 5000 pins 1400 us (2590 with a wave
+// taking the long ones among its own 64), now 46.
+constexpr int kEmitBig = 256;
+
 __global__ void __launch_bounds__(kT)
-k_emit(const int32_t *__restrict__ eptr, const uint32_t *__restrict__ lab_sorted,
+k_emit(const int32_t *__restrict__ big_e, const int32_t *__restrict__ n_big,
+       const int32_t *__restrict__ eptr, const uint32_t *__restrict__ lab_sorted,
        const int32_t *__restrict__ cnt, const int32_t *__restrict__ new_ptr,
        const int32_t *__restrict__ keep_pos, const float *__restrict__ w,
        int32_t *__restrict__ eptr2, int32_t *__restrict__ pins2, float *__restrict__ w2,
        int32_t *__restrict__ kept2, int32_t m) {
-  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & 63;
-  const bool on = e < m && cnt[e] != 0;
-  int32_t a = 0, b = 0, o = 0;
-  if (on) {
-    const int32_t k = keep_pos[e];
-    a = eptr[e];
-    b = eptr[e + 1];
-    o = new_ptr[e];
-    eptr2[k] = o;
-    w2[k] = w ? w[e] : 1.0f;
-    if (kept2) kept2[k] = int32_t(e);
-  }
-  const bool lng = b - a > kSmallSeg;
-  if (on && !lng) {
-    uint32_t prev = 0xFFFFFFFFu;  // (no label)
-    for (int32_t j = a; j < b; j += 8) {
-      uint32_t x[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) x[q] = lab_sorted[j + q < b ? j + q : b - 1];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        if (j + q < b && x[q] != prev) pins2[o++] = int32_t(x[q]);
-        prev = x[q];
+  if (int(blockIdx.x) < kEmitBig) {
+    const int lane = threadIdx.x & 63;
+    const int32_t nb = *n_big;
+    for (int32_t i = int32_t(wave_index()); i < nb; i += kEmitBig * (kT / 64)) {
+      const int32_t e = big_e[i];
+      if (cnt[e] == 0) continue;
+      const int32_t a = eptr[e], b = eptr[e + 1];
+      int32_t o = new_ptr[e];
+      for (int32_t j = a; j < b; j += 64) {
+        const int32_t at = j + lane;
+        const bool in = b - j > lane;
+        const uint32_t x = in ? lab_sorted[at] : 0u;
+        const bool take = in && (at == a || x != lab_sorted[at - 1]);
+        const uint64_t mask = __ballot(take);
+        if (take) pins2[o + __popcll(mask & ((uint64_t(1) << lane) - 1))] = int32_t(x);
+        o += __popcll(mask);
       }
     }
+    return;
   }
-  for (uint64_t left = __ballot(lng); left != 0; left &= left - 1) {
-    const int l = __ffsll(static_cast<long long>(left)) - 1;
-    const int32_t la = __builtin_amdgcn_readlane(a, l), lb = __builtin_amdgcn_readlane(b, l);
-    int32_t lo = __builtin_amdgcn_readlane(o, l);
-    for (int32_t j = la; j < lb; j += 64) {
-      const int32_t at = j + lane;
-      const bool in = lb - j > lane;
-      const uint32_t x = in ? lab_sorted[at] : 0u;
-      const bool take = in && (at == la || x != lab_sorted[at - 1]);
-      const uint64_t mask = __ballot(take);
-      if (take) pins2[lo + __popcll(mask & ((uint64_t(1) << lane) - 1))] = int32_t(x);
-      lo += __popcll(mask);
+  const int64_t e = int64_t(int(blockIdx.x) - kEmitBig) * kT + threadIdx.x;
+  if (e >= m || cnt[e] == 0) return;
+  const int32_t k = keep_pos[e];
+  const int32_t a = eptr[e], b = eptr[e + 1];
+  int32_t o = new_ptr[e];
+  eptr2[k] = o;
+  w2[k] = w ? w[e] : 1.0f;
+  if (kept2) kept2[k] = int32_t(e);
+  if (b - a > kSmallSeg) return;
+  uint32_t prev = 0xFFFFFFFFu;  // (no label)
+  for (int32_t j = a; j < b; j += 8) {
+    uint32_t x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = lab_sorted[j + q < b ? j + q : b - 1];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (j + q < b && x[q] != prev) pins2[o++] = int32_t(x[q]);
+      prev = x[q];
     }
   }
 }
@@ -1525,8 +1529,8 @@ hef_status rebuild_level(const Level &L, const Structure &st, const int32_t *lab
     k_flag_pos<<<g1(m), kT, 0, s>>>(cnt, flag, int32_t(m));
     HEF_LAUNCH_CHECK();
     HEF_TRY(exclusive_scan_i32(flag, kpos, m, ws, s));
-    k_emit<<<g1(m), kT, 0, s>>>(L.eptr, k0, cnt, nptr, kpos, L.w, eptr2, pins2, w2, kept2,
-                                int32_t(m));
+    k_emit<<<kEmitBig + g1(m), kT, 0, s>>>(st.big_e, st.n_big, L.eptr, k0, cnt, nptr, kpos, L.w,
+                                           eptr2, pins2, w2, kept2, int32_t(m));
     k_rebuild_tail<<<1, 1, 0, s>>>(kpos, nptr, m, ovf, eptr2, misc + 4);
     HEF_LAUNCH_CHECK();
     int32_t t3[3] = {0, 0, 0};
