@@ -149,10 +149,12 @@ k_sadj_a(const float *__restrict__ sfwd, int K, int LPR, int64_t m, const double
 // adjoint sbar = [i = i*] c_e / Q_H(i) + w_e qbar_i, the positions of the
 // largest / smallest pin (first in CSR order) and dbar = 2 (max - min) sbar;
 // per hyperedge the direct term sum_i qbar_i s_e^(i).  k_sadj_b takes the
-// hyperedges of up to kSmallSeg pins, a lane group each; k_sadj_long the
-// longer ones, a workgroup each (one group walking 2000 pins is a chain of
-// 500 dependent gathers: 845 us at 200k nodes, K = 160, against 400 us for
-// the two, 94 of it the long ones, 119 with half the threads).
+// hyperedges of up to long_from(kSmallSeg) pins, a lane group each;
+// k_sadj_long the longer ones, a workgroup each (one group walking 2000 pins
+// is a chain of 500 dependent gathers: 845 us at 200k nodes, K = 160, against
+// 398 us for the two, 92 of it the long ones).  20000 hyperedges of 100 pins,
+// K = 24: 104 us by lane groups, 5670 by a workgroup each whose first group
+// took in all the others one after the other.
 struct SadjOut {
   int32_t *slot_a, *slot_b;
   float *dbar;
@@ -237,7 +239,9 @@ __global__ void __launch_bounds__(kThreads)
 k_sadj_b(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
          const float *__restrict__ chi, int K, int LPR, int64_t m, const double *__restrict__ qh,
          const float *__restrict__ dR, const float *__restrict__ w,
-         const int32_t *__restrict__ istar, const double *__restrict__ qsum, const SadjOut o) {
+         const int32_t *__restrict__ istar, const double *__restrict__ qsum,
+         const int32_t *__restrict__ n_big, const SadjOut o) {
+  const int from = long_from(kSmallSeg, *n_big);
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -249,7 +253,7 @@ k_sadj_b(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   sadj_cols<CPL>(c0, K, qh, qsum, inv, qb);
   for (int64_t e = e0 + grp; e < e1; e += ngrp) {
     const int32_t a = eptr[e], b = eptr[e + 1];
-    if (b - a > kSmallSeg) continue;
+    if (b - a > from) continue;
     Extremes<CPL> x;
     x.start(chi, pins, a, K, c0);
     for (int64_t j0 = a + 1; j0 < b; j0 += 4) x.take4(chi, pins, j0, b, K, c0);
@@ -277,35 +281,47 @@ k_sadj_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
   double inv[CPL], qb[CPL];
   sadj_cols<CPL>(c0, K, qh, qsum, inv, qb);
   const int32_t cnt = *count;
+  const int from = long_from(kSmallSeg, cnt);
   for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
     const int32_t e = list[bi];
     const int32_t a = eptr[e], b = eptr[e + 1];
+    if (b - a <= from) continue;  // (the same on every thread)
+    const int use = b - a < 4 * ngrp ? (b - a + 3) / 4 : ngrp;  // groups with pins
     // group g takes pins a + 4 g .. + 3, then every 4 ngrp on (the first of
     // them starts its extremes)
     Extremes<CPL> x;
     const int64_t first = a + 4 * int64_t(grp);
     x.start(chi, pins, int32_t(first < b ? first : b - 1), K, c0);
     for (int64_t j0 = first; j0 < b; j0 += 4 * ngrp) x.take4(chi, pins, j0, b, K, c0);
+    auto put = [&]() {
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      smx[grp * W + c0 + q] = x.mx[q];
-      smn[grp * W + c0 + q] = x.mn[q];
-      sja[grp * W + c0 + q] = x.ja[q];
-      sjb[grp * W + c0 + q] = x.jb[q];
-    }
+      for (int q = 0; q < CPL; ++q) {
+        smx[grp * W + c0 + q] = x.mx[q];
+        smn[grp * W + c0 + q] = x.mn[q];
+        sja[grp * W + c0 + q] = x.ja[q];
+        sjb[grp * W + c0 + q] = x.jb[q];
+      }
+    };
+    put();
     __syncthreads();
-    if (grp == 0) {
-      // the first position among equal values
-      for (int g = 1; g < ngrp; ++g) {
+    int half = 1;
+    while (2 * half < use) half *= 2;
+    for (; half > 0; half /= 2) {  // groups [0, half) take in [half, 2 half)
+      if (grp < half && grp + half < use) {
+        // the first position among equal values
 #pragma unroll
         for (int q = 0; q < CPL; ++q) {
-          const int at = g * W + c0 + q;
+          const int at = (grp + half) * W + c0 + q;
           const float vx = smx[at], vn = smn[at];
           const int32_t px = sja[at], pn = sjb[at];
           if (vx > x.mx[q] || (vx == x.mx[q] && px < x.ja[q])) { x.mx[q] = vx; x.ja[q] = px; }
           if (vn < x.mn[q] || (vn == x.mn[q] && pn < x.jb[q])) { x.mn[q] = vn; x.jb[q] = pn; }
         }
+        put();
       }
+      __syncthreads();
+    }
+    if (grp == 0) {
       sadj_finish<CPL>(e, x, c0, K, LPR, inv, qb, istar[e], double(dR[e]),
                        w ? double(w[e]) : 1.0, o);
     }
@@ -1083,7 +1099,7 @@ hef_status score_adjoint_t(const Level &L, const Structure &st, const float *chi
     k_sadj_long<CPL><<<nlong, kLongThreads, 0, s>>>(st.big_e, st.n_big, L.eptr, L.pins, chi, K, LPR,
                                                 qh, dR, L.w, w.istar, w.qsum, so);
   k_sadj_b<CPL><<<nblk, kThreads, 0, s>>>(L.eptr, L.pins, chi, K, LPR, L.m, qh, dR, L.w, w.istar,
-                                          w.qsum, so);
+                                          w.qsum, st.n_big, so);
   HEF_LAUNCH_CHECK();
   const int ngrp = kThreads / LPR;
   if (L.n > 0) {

@@ -131,14 +131,17 @@ __device__ __forceinline__ void store_cols(void *pool, int64_t row, int K, int c
   }
 }
 
-// Largest and smallest pool values of every hyperedge of more than longseg
-// pins, a workgroup per hyperedge of the list: its groups of LPR lanes take
-// 4 pins at a time, then their extremes meet in LDS.  Row 2 i of `ext`
+// Largest and smallest pool values of every long hyperedge (of more than
+// long_from(longseg) pins), a workgroup per hyperedge of the list: as many of
+// its groups of LPR lanes as it has fours of pins take 4 at a time, then their
+// extremes meet in LDS, in a tree over those groups.  Row 2 i of `ext`
 // receives the largest, row 2 i + 1 the smallest values, i = (first pin
 // position) / longseg, which no two such hyperedges share.  Maxima do not
 // depend on the order, so the ratios keep their bits.  The longest hyperedge's
-// chain bounds it: with 512 / 1024 threads 29 / 25 us at 20k nodes, K = 464,
-// 65 / 42 at 200k, K = 160, 355 / 336 at 2M, K = 480.
+// chain bounds it: 28 us at 20k nodes, K = 464, 47 at 200k, K = 160, 117 at 2M,
+// K = 480.  With the groups' extremes taken in one after the other, all of
+// them for a hyperedge of any length, 50000 hyperedges of 40 pins at K = 24
+// took 727 us, seven times a lane group each.
 constexpr int kLongThreads = 1024;
 
 template <int CPL, int PT>
@@ -155,10 +158,12 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
   const int c0 = (tid % LPR) * CPL;
   const int W = LPR * CPL;  // columns of a group's LDS row
   const int32_t cnt = *count;
+  const int from = long_from(longseg, cnt);
   for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
     const int32_t e = list[bi];
     const int32_t a = eptr[e], b = eptr[e + 1];
-    if (b - a <= longseg) continue;  // (the same on every thread)
+    if (b - a <= from) continue;  // (the same on every thread)
+    const int use = b - a < 4 * ngrp ? (b - a + 3) / 4 : ngrp;  // groups with pins
     T mx[CPL], mn[CPL];
 #pragma unroll
     for (int q = 0; q < CPL; ++q) { mx[q] = -kBig; mn[q] = kBig; }
@@ -185,13 +190,21 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
       smn[grp * W + c0 + q] = mn[q];
     }
     __syncthreads();
-    if (grp == 0 && c0 < K) {
-      for (int g = 1; g < ngrp; ++g)
+    int half = 1;
+    while (2 * half < use) half *= 2;
+    for (; half > 0; half /= 2) {  // groups [0, half) take in [half, 2 half)
+      if (grp < half && grp + half < use) {
 #pragma unroll
         for (int q = 0; q < CPL; ++q) {
-          mx[q] = vmax(mx[q], smx[g * W + c0 + q]);
-          mn[q] = vmin(mn[q], smn[g * W + c0 + q]);
+          mx[q] = vmax(mx[q], smx[(grp + half) * W + c0 + q]);
+          mn[q] = vmin(mn[q], smn[(grp + half) * W + c0 + q]);
+          smx[grp * W + c0 + q] = mx[q];
+          smn[grp * W + c0 + q] = mn[q];
         }
+      }
+      __syncthreads();
+    }
+    if (grp == 0 && c0 < K) {
       const int64_t row = 2 * int64_t(a / longseg);
       store_cols<CPL, PT>(ext, row, K, c0, mx);
       store_cols<CPL, PT>(ext, row + 1, K, c0, mn);
@@ -203,7 +216,7 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
 // A workgroup takes kEdgesPerBlk consecutive hyperedges [e0, e1); group grp
 // (LPR lanes, ngrp groups) takes e0 + grp + ngrp k, in rounds of LPR: lane j
 // of the group fetches the pin range of the round's j-th hyperedge up front.
-// Hyperedges of more than longseg pins take their extremes from `ext`
+// Hyperedges of more than long_from(longseg) pins take their extremes from `ext`
 // (k_score_long): one group walking 2000 pins is a chain of 500 dependent
 // gathers, 0.2 to 0.4 ms whatever the size of the launch.  Measured with
 // that chain / without (this pass plus k_score_long): 20k nodes, K = 464,
@@ -214,8 +227,9 @@ __global__ void __launch_bounds__(kThreads)
 k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
            const float *__restrict__ w, const void *__restrict__ pool, int K, int LPR,
            int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
-           const void *__restrict__ ext) {
+           const int32_t *__restrict__ n_big, const void *__restrict__ ext) {
   __shared__ double comb[kThreads * CPL];
+  const int from = long_from(longseg, *n_big);
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -243,7 +257,7 @@ k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       const double we = double(__shfl(ew, k, LPR));
       if (c0 < K) {
         double s[CPL];
-        if (b - a > longseg) {
+        if (b - a > from) {
           PoolVal<PT> mx[CPL], mn[CPL];
           const int64_t row = 2 * int64_t(a / longseg);
           load_cols<CPL, PT>(ext, row, K, c0, mx);
@@ -304,7 +318,8 @@ __global__ void __launch_bounds__(kFewThreads)
 k_score_qh_few(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
                const float *__restrict__ w, const void *__restrict__ pool, int K, int LPR,
                int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
-               const void *__restrict__ ext) {
+               const int32_t *__restrict__ n_big, const void *__restrict__ ext) {
+  const int from = long_from(longseg, *n_big);
   constexpr int R = kFewThreads / kThreads;
   constexpr int NA = kThreads * CPL / kFewThreads;  // sums per thread
   static_assert(NA * kFewThreads == kThreads * CPL, "whole sums per thread");
@@ -340,7 +355,7 @@ k_score_qh_few(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pin
     fetch(k0 + R + r);
     if (a < b && c0 < K) {
       double s[CPL];
-      if (b - a > longseg) {
+      if (b - a > from) {
         PoolVal<PT> mx[CPL], mn[CPL];
         const int64_t row = 2 * int64_t(a / longseg);
         load_cols<CPL, PT>(ext, row, K, c0, mx);
@@ -458,10 +473,10 @@ hef_status score_t(const Level &L, const Structure &st, const void *pool, int K,
                                                          pool, K, LPR, longseg, ext);
   if (nblk <= kFewBlocks<CPL>)
     k_score_qh_few<CPL, PT><<<nblk, kFewThreads, 0, s>>>(L.eptr, L.pins, L.w, pool, K, LPR, L.m,
-                                                         partial, sbuf, longseg, ext);
+                                                         partial, sbuf, longseg, st.n_big, ext);
   else
     k_score_qh<CPL, PT><<<nblk, kThreads, 0, s>>>(L.eptr, L.pins, L.w, pool, K, LPR, L.m, partial,
-                                                  sbuf, longseg, ext);
+                                                  sbuf, longseg, st.n_big, ext);
   HEF_LAUNCH_CHECK();
   }
   {

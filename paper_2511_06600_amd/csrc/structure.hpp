@@ -13,6 +13,20 @@ constexpr int kSmallSeg = 32;
 // together (hubs with neighbouring ids at coarse levels).
 constexpr int kWaveSeg = 256;
 
+// The passes that give a long hyperedge a workgroup (the ratios and their
+// adjoint) take those of more than kSmallSeg pins while these are few, and
+// those of more than kMidSeg where there are more than kFewLong.  512 such
+// workgroups run at a time, a few us each, so 2048 hyperedges are four turns
+// (less than a lane group's chain over 256 pins), while thousands of lane groups
+// run at once: estimates over 50000 hyperedges of 40 pins, K = 24, 981 us by
+// this rule and 1618 without; 2M nodes, K = 480, 15k hyperedges above 32 pins,
+// 3.63 ms of ratios with and without.
+constexpr int kMidSeg = 256;
+constexpr int kFewLong = 2048;
+__device__ __forceinline__ int long_from(int least, int32_t n_big) {
+  return n_big > kFewLong && least < kMidSeg ? kMidSeg : least;
+}
+
 struct Structure {
   // CSC incidence (node -> hyperedges), hyperedges ascending per node.
   int32_t *vptr = nullptr;  // [n+1]

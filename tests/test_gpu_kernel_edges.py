@@ -541,3 +541,34 @@ def test_long_pin_ranges_are_split(layout):
     ref = np.where(db > 0, ref / np.sqrt(np.where(db > 0, db, 1.0)), 0.0)
     deg = np.bincount(pins, minlength=n).max()
     assert np.abs(y - ref).max() <= (deg + 4) * 2.0 ** -24 * max(np.abs(ref).max(), 1.0)
+
+
+@pytest.mark.parametrize("k,b", [(5, 1), (8, 4)])
+@pytest.mark.parametrize("many", [2048, 2049])
+def test_many_long_hyperedges(many, k, b):
+    """Up to 2048 hyperedges of more than 32 pins each take a workgroup in the
+    ratios and in their adjoint, more than that only those above 256 pins: as
+    many fours of pins as lane groups and fewer, whole and not.  Ratios
+    against float64 on the pool (bounds as in test_long_hyperedge_ratios), the
+    gradient against the float64 autograd oracle at the adjoint tests' 1e-3."""
+    from oracle import gradient as ogr
+    from oracle import resistance as orr
+    from tests.gpu_common import starts
+    say(f"case: many long hyperedges {many} k={k} b={b}")
+    special = [255, 256, 257, 300, 513, 36, 37, 63]
+    sizes = special + [33 + i % 4 for i in range(many - len(special))] + _mixed_sizes(300, 3) + [32]
+    assert sum(s > 32 for s in sizes) == many
+    w = np.random.default_rng(2).uniform(0.5, 2.0, len(sizes)).astype(np.float32)
+    h = _hg(9000, sizes, 5, w)
+    dh = to_device(h)
+    Xs, Xc, xs, xc = starts(h, b)
+    R, qh, chi = hef.resistance(dh, hef.Params(k=k, b=b), xs, xc, return_pool=True)
+    s = orr.edge_spread(h.eptr, h.pins, chi.cpu().double().numpy())
+    q = h.w.astype(np.float64) @ s
+    assert np.abs(qh.cpu().numpy() - q).max() <= 2 * h.m * 2.0 ** -53 * q.max()
+    np.testing.assert_allclose(R.cpu().numpy(), (s / q[None, :]).max(1), rtol=2.0 ** -22, atol=0)
+    coef = np.random.default_rng(3).standard_normal(h.m).astype(np.float32)
+    _, ref, _ = ogr.loss_and_grad(h.n, h.m, h.eptr, h.pins, h.w, Xs, Xc, k, coef)
+    dw = hef.resistance_backward(dh, hef.Params(k=k, b=b), torch.as_tensor(coef, device="cuda"),
+                                 xs, xc).cpu().numpy()
+    assert np.linalg.norm(dw - ref) <= 1e-3 * np.linalg.norm(ref)
