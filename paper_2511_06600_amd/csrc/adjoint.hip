@@ -815,21 +815,20 @@ k_weights(const WeightArgs P) {
 
 // dw_e = eacc_e - 1/(2|e|) sum_{p in e} znode_p - 1/(|e|(|e|-1)) sum_{p in e} hnode_p
 //        + wdirect_e   (beta_e / w_e = 1/(|e|(|e|-1)))
-// A lane per hyperedge, its pins 8 at a time; the wave takes those of more than
-// kWaveEdge pins together (a lane alone with 2000 pins is a chain of 250
-// gathers: 93 us at 756k pins; this takes 18).
-constexpr int kWaveEdge = 32;
+// A lane per hyperedge of up to kSmallSeg pins, 8 at a time in pin order;
+// workgroups [0, kWfinalBig) take the structure's list of the longer ones, a
+// wave each, whose lanes add every 64th pin and meet in a butterfly (a lane
+// alone with 2000 pins is a chain of 250 gathers: 93 us at 756k pins; this takes
+// 18; a wave taking the long ones among its own 64 in turn, 103 us for 20000
+// hyperedges of 100 pins, this 24).
+constexpr int kWfinalBig = 1024;
 
 __global__ void __launch_bounds__(kThreads)
-k_wfinal(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins, int64_t m,
+k_wfinal(const int32_t *__restrict__ big_e, const int32_t *__restrict__ n_big,
+         const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins, int64_t m,
          const double *__restrict__ eacc, const double *__restrict__ znode,
          const double *__restrict__ hnode, const double *__restrict__ wdirect,
          float *__restrict__ dw) {
-  const int64_t e = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  const int lane = threadIdx.x & 63;
-  const bool on = e < m;
-  const int32_t a = on ? eptr[e] : 0, b = on ? eptr[e + 1] : 0;
-  double gz = 0.0, gh = 0.0;
   // the 8 positions j0, j0 + step, ... (loads first), added in that order
   auto add8 = [&](int32_t j0, int32_t step, int32_t end, double &z, double &h) {
     int32_t pp[8];
@@ -851,26 +850,34 @@ k_wfinal(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins, int
         h += hv[u];
       }
   };
-  if (b - a <= kWaveEdge)
-    for (int32_t j0 = a; j0 < b; j0 += 8) add8(j0, 1, b, gz, gh);
-  for (uint64_t left = __ballot(b - a > kWaveEdge); left; left &= left - 1) {
-    const int l = __builtin_ctzll(left);
-    const int32_t la = __shfl(a, l, 64), lb = __shfl(b, l, 64);
-    double z = 0.0, h = 0.0;
-    for (int64_t j0 = int64_t(la) + lane; j0 < lb; j0 += 512) add8(int32_t(j0), 64, lb, z, h);
+  auto finish = [&](int64_t e, int32_t size, double z, double h) {
+    const double k = double(size);
+    dw[e] = float(eacc[e] - z / (2.0 * k) - h / (k * (k - 1.0)) + wdirect[e]);
+  };
+  if (int(blockIdx.x) < kWfinalBig) {
+    const int lane = threadIdx.x & 63;
+    const int32_t nb = *n_big;
+    for (int32_t i = int32_t(wave_index()); i < nb; i += kWfinalBig * (kThreads / 64)) {
+      const int32_t e = big_e[i];
+      const int32_t a = eptr[e], b = eptr[e + 1];
+      double z = 0.0, h = 0.0;
+      for (int64_t j0 = int64_t(a) + lane; j0 < b; j0 += 512) add8(int32_t(j0), 64, b, z, h);
 #pragma unroll
-    for (int t = 32; t > 0; t >>= 1) {
-      z += __shfl_xor(z, t, 64);
-      h += __shfl_xor(h, t, 64);
+      for (int t = 32; t > 0; t >>= 1) {
+        z += __shfl_xor(z, t, 64);
+        h += __shfl_xor(h, t, 64);
+      }
+      if (lane == 0) finish(e, b - a, z, h);
     }
-    if (lane == l) {
-      gz = z;
-      gh = h;
-    }
+    return;
   }
-  if (!on) return;
-  const double k = double(b - a);
-  dw[e] = float(eacc[e] - gz / (2.0 * k) - gh / (k * (k - 1.0)) + wdirect[e]);
+  const int64_t e = int64_t(int(blockIdx.x) - kWfinalBig) * kThreads + threadIdx.x;
+  if (e >= m) return;
+  const int32_t a = eptr[e], b = eptr[e + 1];
+  if (b - a > kSmallSeg) return;
+  double z = 0.0, h = 0.0;
+  for (int32_t j0 = a; j0 < b; j0 += 8) add8(j0, 1, b, z, h);
+  finish(e, b - a, z, h);
 }
 
 int lanes_for(int K, int CPL) {
@@ -1285,8 +1292,8 @@ hef_status reverse_sweep(const Level &L, const hef_params &p, const float *dR, f
   }
 
   // ---- 4. gather per hyperedge
-  k_wfinal<<<cdiv(m, kThreads), kThreads, 0, s>>>(L.eptr, L.pins, m, w.eacc, w.znode, w.hnode, w.wdirect,
-                                        dw);
+  k_wfinal<<<kWfinalBig + cdiv(m, kThreads), kThreads, 0, s>>>(
+      st.big_e, st.n_big, L.eptr, L.pins, m, w.eacc, w.znode, w.hnode, w.wdirect, dw);
   HEF_LAUNCH_CHECK();
   return HEF_OK;
 }

@@ -1137,7 +1137,7 @@ __global__ void k_distinct(const int32_t *__restrict__ eptr, const uint32_t *__r
 // loads: per level of a coarsening from 20k / 200k / 2M nodes 44 / 111 / 148
 // us, now 5 / 9 / 32 us; 200 hyperedges of 5000 pins 1400 us (2590 with a wave
 // taking the long ones among its own 64), now 46.
-constexpr int kEmitBig = 256;
+constexpr int kEmitBig = 1024;
 
 __global__ void __launch_bounds__(kT)
 k_emit(const int32_t *__restrict__ big_e, const int32_t *__restrict__ n_big,
