@@ -50,8 +50,8 @@ constexpr int kRoundsPerSync = 4;
 constexpr int32_t kStUndecided = 0, kStIn = 1, kStOut = 2, kStNone = 3;
 
 // ---- a6: Eq. (15) -----------------------------------------------------------
-// A thread per hyperedge of up to kWaveSeg pins, the wave for a longer one
-// (64 pins' eta side by side, added in pin order).
+// A thread per hyperedge, or the wave for the long ones (64 pins' eta side by
+// side, added in pin order) while they are few (wave_takes).
 __global__ void __launch_bounds__(kT)
 k_eta_update(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
              const float *__restrict__ R, const float *__restrict__ eta,
@@ -62,7 +62,8 @@ k_eta_update(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   double acc = 0.0;
   if (eta) {
     const int32_t a = e < m ? eptr[e] : 0, b = e < m ? eptr[e + 1] : 0;
-    const bool lng = b - a > kWaveSeg;
+    const int32_t len = b - a > kWaveSeg ? b - a : 0;
+    const bool lng = wave_takes(len) && len > 0;
     // pins loaded eight at a time ahead of the dependent loads; the terms are
     // added in pin order
     if (!lng) {
@@ -81,13 +82,13 @@ k_eta_update(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
     for (uint64_t left = __ballot(lng); left != 0; left &= left - 1) {
       const int l = __ffsll(static_cast<long long>(left)) - 1;
       const int32_t la = __builtin_amdgcn_readlane(a, l), lb = __builtin_amdgcn_readlane(b, l);
-      double sum = 0.0;
+      double sum[1] = {0.0};
       for (int32_t j = la; j < lb; j += 64) {
         const int cnt = lb - j < 64 ? lb - j : 64;
-        const double t = double(eta[pins[lane < cnt ? j + lane : lb - 1]]);
-        sum = ordered_sum(sum, t, cnt);
+        const double t[1] = {double(eta[pins[lane < cnt ? j + lane : lb - 1]])};
+        ordered_sums(sum, t, cnt);
       }
-      if (lane == l) acc = sum;
+      if (lane == l) acc = sum[0];
     }
   }
   if (e >= m) return;

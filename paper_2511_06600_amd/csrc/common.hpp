@@ -121,12 +121,21 @@ __device__ __forceinline__ double div_pivot(double x, const Pivot &p) {
   return __builtin_fma(__builtin_fma(-q, p.root, x), p.inv, q);
 }
 
-// acc + x(lane 0) + x(lane 1) + ... + x(lane cnt - 1), added in that order
-// (cnt the same on all lanes): a sequential sum whose terms a wave loaded side
-// by side.
-__device__ __forceinline__ double ordered_sum(double acc, double x, int cnt) {
-  for (int l = 0; l < cnt; ++l) acc = acc + readlane_f64(x, l);
-  return acc;
+// acc[i] + x[i](lane 0) + x[i](lane 1) + ... + x[i](lane cnt - 1), added in that
+// order (cnt the same on all lanes): N sequential sums whose terms a wave loaded
+// side by side.
+template <int N>
+__device__ __forceinline__ void ordered_sums(double (&acc)[N], const double (&x)[N], int cnt) {
+  if (cnt == 64) {  // (lane numbers known: no loop between the additions)
+#pragma unroll
+    for (int l = 0; l < 64; ++l)
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] = acc[i] + readlane_f64(x[i], l);
+    return;
+  }
+  for (int l = 0; l < cnt; ++l)
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = acc[i] + readlane_f64(x[i], l);
 }
 
 // Map a launched block index to a logical one so that each of the 8 XCDs of

@@ -133,12 +133,13 @@ __global__ void k_edge_scales(const int32_t *__restrict__ eptr, const float *__r
 
 // Per node, over its hyperedges in ascending order, in float64:
 // d_b = sum w_e/|e|, cb = sum beta_e; s = d_b^-1/2, gam = s^2 cb.  A thread
-// takes a node of up to kWaveSeg hyperedges, eight loads at a time; the longer
-// ones of a wave's 64 nodes are taken by the whole wave one after the other.
+// takes a node, eight loads at a time; a wave's nodes of more than kWaveSeg
+// hyperedges are taken by the whole wave one after the other while they are
+// few (wave_takes).
 // Average over the three levels of a coarsening from 20k / 200k / 2M nodes:
-// 23 / 30 / 157 us; four loads at a time without the wave 20 / 27 / 174 us
-// (and 1 us more per eight hyperedges of the largest hub); the wave from
-// kSmallSeg on 61 / 81 / 189 us.
+// 19 / 26 / 144 us; four loads at a time without the wave 20 / 27 / 174 us
+// (and 1 us more per eight hyperedges of the largest hub); the wave always, 23
+// / 30 / 157 us, and from kSmallSeg on 61 / 81 / 189 us.
 __global__ void __launch_bounds__(256)
 k_node_scales(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
               const double *__restrict__ tdb, const double *__restrict__ tcb,
@@ -147,8 +148,9 @@ k_node_scales(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids
   const int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
   const int32_t a = u < n ? vptr[u] : 0, b = u < n ? vptr[u + 1] : 0;
-  const bool lng = b - a > kWaveSeg;
   append_ids(b - a > kSmallSeg, int32_t(u), big, n_big);
+  const int32_t len = b - a > kWaveSeg ? b - a : 0;
+  const bool lng = wave_takes(len) && len > 0;
   double db = 0.0, cb = 0.0;
   if (!lng) {
     // eight incidences' loads ahead of their sums, which run in order
@@ -173,17 +175,16 @@ k_node_scales(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids
   for (uint64_t left = __ballot(lng); left != 0; left &= left - 1) {
     const int l = __ffsll(static_cast<long long>(left)) - 1;
     const int32_t la = __builtin_amdgcn_readlane(a, l), lb = __builtin_amdgcn_readlane(b, l);
-    double sd = 0.0, sc = 0.0;
+    double sum[2] = {0.0, 0.0};
     for (int32_t j = la; j < lb; j += 64) {
       const int cnt = lb - j < 64 ? lb - j : 64;
       const int32_t e = eids[lane < cnt ? j + lane : lb - 1];
-      const double td = tdb[e], tc = tcb[e];
-      sd = ordered_sum(sd, td, cnt);
-      sc = ordered_sum(sc, tc, cnt);
+      const double t[2] = {tdb[e], tcb[e]};
+      ordered_sums(sum, t, cnt);
     }
     if (lane == l) {
-      db = sd;
-      cb = sc;
+      db = sum[0];
+      cb = sum[1];
     }
   }
   if (u >= n) return;

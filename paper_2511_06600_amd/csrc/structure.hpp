@@ -7,11 +7,29 @@ namespace hef {
 
 // Segments longer than this go to the wave-per-segment kernels.
 constexpr int kSmallSeg = 32;
-// Sequential sums over a segment longer than this are taken by the whole wave
+// Sequential sums over a segment longer than this may be taken by the whole wave
 // (64 terms loaded side by side, added in order); up to here a thread with
-// eight loads in flight is faster, since a wave's 64 segments are often long
-// together (hubs with neighbouring ids at coarse levels).
+// eight loads in flight is faster.  A lane's chain takes about 75 ns a term, the
+// wave's 25 ns a term of all its long segments together, so the wave takes them
+// while their terms are at most three times the longest's.  Nodes of 5000
+// hyperedges, 1 / 3 / 64 of them in a wave: 126 / 372 / 630 us (a thread each
+// 286 / 377 / 818, the wave always 1600 for 64).
 constexpr int kWaveSeg = 256;
+constexpr int kWaveRatio = 3;
+// Whether the wave takes its lanes' long segments (len on the lanes that have
+// one, 0 on the others), the same on every lane.
+__device__ __forceinline__ bool wave_takes(int32_t len) {
+  if (__ballot(len > 0) == 0) return false;
+  int64_t sum = len;
+  int32_t most = len;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    sum += __shfl_xor(sum, off, 64);
+    const int32_t o = __shfl_xor(most, off, 64);
+    most = o > most ? o : most;
+  }
+  return sum <= kWaveRatio * int64_t(most);
+}
 
 // The passes that give a long hyperedge a workgroup (the ratios and their
 // adjoint) take those of more than kSmallSeg pins while these are few, and

@@ -572,3 +572,48 @@ def test_many_long_hyperedges(many, k, b):
     dw = hef.resistance_backward(dh, hef.Params(k=k, b=b), torch.as_tensor(coef, device="cuda"),
                                  xs, xc).cpu().numpy()
     assert np.linalg.norm(dw - ref) <= 1e-3 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("together", [1, 3, 4, 64])
+@pytest.mark.parametrize("length", [256, 257, 321, 640])
+def test_long_segments_side_by_side(together, length):
+    """Nodes of `length` hyperedges and hyperedges of `length` pins, so many of
+    them among 64 neighbours: up to three times the longest's terms the wave
+    takes them above 256, else a lane each.  Eq. (15) sums eta in pin order
+    either way (bit for bit); the node scales through the star operator, with
+    (degree + 4) roundings of relative 2^-24."""
+    from oracle import clustering as ocl
+    say(f"case: long segments side by side {together} of {length}")
+    n, gap = 4000, {1: 64, 3: 20, 4: 16, 64: 1}[together]
+    rng = np.random.default_rng(together + length)
+    long_at = [(64 + gap * i, length + (i % 2)) for i in range(together)]
+    h = _hg(n, _mixed_sizes(300, length, long_at), length + together)
+    hubs = 128 + gap * np.arange(together)
+    others = 1000 + np.array([rng.choice(n - 1000, length, replace=False) for _ in hubs])
+    extra = np.stack([np.repeat(hubs, length), others.reshape(-1)], 1)
+    eptr = np.concatenate([h.eptr, h.eptr[-1] + 2 * np.arange(1, len(extra) + 1)])
+    pins = np.concatenate([h.pins, extra.reshape(-1)]).astype(np.int32)
+    m = len(eptr) - 1
+    w = rng.uniform(0.5, 2.0, m).astype(np.float32)
+    h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins, w=w)
+    dh = to_device(h)
+    R = (rng.random(m) * 10.0 ** rng.integers(-3, 3, m)).astype(np.float32)
+    eta = (rng.random(n) * 10.0 ** rng.integers(-6, 3, n)).astype(np.float32)
+    cl, nc, eo = hef.cluster_level(dh, hef.Params(k=4, b=1, local_clustering=False, percentile=1.0),
+                                   torch.as_tensor(R, device="cuda"),
+                                   torch.as_tensor(eta, device="cuda"),
+                                   torch.zeros((n, 8), device="cuda"),
+                                   torch.ones(8, dtype=torch.float64, device="cuda"))
+    ref = ocl.cluster_level(n, m, eptr, pins, R, eta, None, np.ones(8), 1.0, False)
+    assert nc == ref.n_clusters and np.array_equal(cl.cpu().numpy(), ref.label)
+    assert np.array_equal(eo.cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
+    x = torch.zeros((n + m, 1), device="cuda")
+    x[n:, 0] = torch.arange(m, device="cuda") % 13
+    y = hef.debug_apply(dh, 0, x).cpu().numpy()[:n, 0].astype(np.float64)
+    sizes = np.diff(eptr)
+    alpha = np.sqrt(w.astype(np.float64)) / sizes
+    db = np.bincount(pins, weights=np.repeat(w / sizes, sizes), minlength=n)
+    r = np.bincount(pins, weights=np.repeat(alpha * (np.arange(m) % 13), sizes), minlength=n)
+    r = np.where(db > 0, r / np.sqrt(np.where(db > 0, db, 1.0)), 0.0)
+    deg = np.bincount(pins, minlength=n).max()
+    assert np.abs(y - r).max() <= (deg + 4) * 2.0 ** -24 * max(np.abs(r).max(), 1.0)
