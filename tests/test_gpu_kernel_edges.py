@@ -617,3 +617,36 @@ def test_long_segments_side_by_side(together, length):
     r = np.where(db > 0, r / np.sqrt(np.where(db > 0, db, 1.0)), 0.0)
     deg = np.bincount(pins, minlength=n).max()
     assert np.abs(y - r).max() <= (deg + 4) * 2.0 ** -24 * max(np.abs(r).max(), 1.0)
+
+
+@pytest.mark.parametrize("order", ["up", "down", "mixed"])
+def test_attach_chain(order):
+    """A chain of 1500 isolated nodes that each pick the next (gaps that
+    shrink), numbered along it, against it and at random, beside short chains:
+    the union-find joins it to one cluster; the level against the oracle, bit
+    for bit."""
+    from oracle import clustering as ocl
+    say(f"case: attach chain {order}")
+    L, n = 1500, 2400
+    at = np.cumsum(np.linspace(2, 1, L))
+    rng = np.random.default_rng(6)
+    pos = np.concatenate([at, 4000 + np.sort(rng.uniform(0, 4000, n - L))]).astype(np.float32)
+    num = {"up": np.arange(n), "down": np.arange(n)[::-1], "mixed": rng.permutation(n)}[order]
+    edges = np.stack([num[:-1], num[1:]], 1)
+    edges = np.delete(edges, L - 1, 0)  # (the chain is a component of its own)
+    m = len(edges)
+    eptr, pins = 2 * np.arange(m + 1), np.sort(edges, 1).reshape(-1).astype(np.int32)
+    chi = np.zeros((n, 8), np.float32)
+    chi[num, 3] = pos
+    qh = np.ones(8)
+    R = np.ones(m, np.float32)  # none below the threshold: every node is isolated
+    h = Hypergraph(n=n, m=m, eptr=eptr.astype(np.int64), pins=pins, w=np.ones(m, np.float32))
+    cl, nc, eo = hef.cluster_level(to_device(h), hef.Params(k=4, b=1),
+                                   torch.as_tensor(R, device="cuda"), None,
+                                   torch.as_tensor(chi, device="cuda"),
+                                   torch.as_tensor(qh, device="cuda"))
+    ref = ocl.cluster_level(n, m, h.eptr, h.pins, R, None, chi, qh, 0.5, True)
+    chain = np.unique(ref.label[num[:L]])
+    assert len(chain) < L / 20  # (float32 positions may tie a few gaps)
+    assert nc == ref.n_clusters and np.array_equal(cl.cpu().numpy(), ref.label)
+    assert np.array_equal(eo.cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
