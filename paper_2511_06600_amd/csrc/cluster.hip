@@ -324,21 +324,25 @@ k_cperm(const int32_t *__restrict__ prov, const int32_t *__restrict__ owner,
   }
 }
 
-// The screen of one candidate: z = max_i |x_i - h_i| sv_i with h the float16
-// copy of the centroid c and sv = sqrt(1 / Q_H), over the columns met so far.
-// |h - c| <= 2^-10 |h| + 2^-24 (float16 rounding of the float32 rounding of c,
-// subnormals included; the factor 2^-10 is twice the rounding bound, which
-// leaves room for the float32 roundings here), and |h| <= |x| + |x - h|, so
-// with t = max_i sv_i (2^-10 |x_i| + 2^-24), one number per node p,
-//   kLoScale z - t  <=  max_i |x_i - c_i| sv_i  <=  kHiScale z + t
-// (the right side once all columns are in).  Distances are of the order of
-// |x| sv in every column (Q_H scales them), so a common t costs little: the
-// survivors do not grow, while a column takes a mixed-precision fused
-// multiply-add and a maximum instead of an unpack, a subtraction, three
-// fused multiply-adds and two maxima, and a candidate carries one number
-// instead of two.
-constexpr float kLoScale = 1.0f - 0x1.02p-10f;
-constexpr float kHiScale = 1.0f + 0x1.02p-10f;
+// The screen of one candidate: z = max_i (|x_i - h_i| - e |x_i|) sv_i, at least
+// 0, with h the float16 copy of the centroid c and sv = sqrt(1 / Q_H), over the
+// columns met so far.  |h - c| <= 2^-11 (1 + 2^-9) |h| + 2^-25 (float16
+// rounding, subnormals included, of the float32 rounding of c), and
+// |h| <= |x| + |x - h|, so that with the e of kScreen, which leaves 2^-18 |x|
+// for the float32 roundings here, and with t0 = 2^-25 (1 + 2^-6) max_i sv_i,
+//   kLoScale z - t0  <=  max_i |x_i - c_i| sv_i  <=  kHiScale z + t,
+// t = 2 e (1 + 2^-8) max_i |x_i| sv_i + t0 (the right side once all columns are
+// in): one number per candidate and two per node p.  A column takes a
+// mixed-precision fused multiply-add, another for its own error bound and a
+// maximum.  Three levels from 2M nodes, K = 480: 12.0 ms; a level of 90000 nodes
+// on a grid, K = 160 smooth vectors, all isolated: 0.71 ms.  With separate lower
+// and upper bounds per column 14.2 and 0.73; with one error bound for all
+// columns, against which the differences of smooth vectors are small, 11.8 and
+// 1.56.
+constexpr float kScreen = 0x1.02p-11f;
+constexpr float kScreen1 = 0x1.03p-11f;  // kScreen / (1 - kScreen), rounded up
+constexpr float kLoScale = 1.0f - 0x1.04p-11f;
+constexpr float kHiScale = 1.0f + 0x1.04p-11f;
 
 // z over the 8 float16 values of v, columns q0 .. q0+8; xv = x sv, nv = -sv
 __device__ __forceinline__ void screen16_8(const uint4 v, const float *xv, const float *nv, int q0,
@@ -347,9 +351,12 @@ __device__ __forceinline__ void screen16_8(const uint4 v, const float *xv, const
   const h8 h = __builtin_bit_cast(h8, v);
   float d[8];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) d[u] = __builtin_fmaf(float(h[u]), nv[q0 + u], xv[q0 + u]);
+  for (int u = 0; u < 8; ++u) {
+    const float x = xv[q0 + u];
+    d[u] = __builtin_fmaf(-kScreen1, fabsf(x), fabsf(__builtin_fmaf(float(h[u]), nv[q0 + u], x)));
+  }
 #pragma unroll
-  for (int u = 0; u < 8; u += 2) z = fmaxf(z, fmaxf(fabsf(d[u]), fabsf(d[u + 1])));
+  for (int u = 0; u < 8; u += 2) z = fmaxf(z, fmaxf(d[u], d[u + 1]));
 }
 
 // Exact float64 distance d(p, C) = max_i (chi_p^(i) - c_C^(i))^2 / Q_H(i)
@@ -427,9 +434,8 @@ __device__ __forceinline__ double exact_d(int32_t C, int32_t cr, int lane, const
 // seeds u with stages B and C of its smallest stage-A bound; hyperedges of
 // at most kSeedSeg pins are visited first.
 // Bound by the float16 rows' gather latency and the screen's arithmetic: at
-// 2M nodes, K = 480, three levels, 11.9 ms; 14.2 ms with separate lower and
-// upper bounds per column.  Held to 4 waves per SIMD it spills 31 registers:
-// 14 ms.
+// 2M nodes, K = 480, three levels, 12.0 ms.  Held to 4 waves per SIMD it spills
+// 31 registers: 14 ms.
 constexpr int kQCap = 72;   // stage-B queue: 8 + one batch of 64
 constexpr int kQ2Cap = 16;  // stage-C queue: 8 + one stage-B batch
 constexpr int kFCap = 64;   // stage-C survivors awaiting their exact distance
@@ -502,7 +508,7 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   int32_t *fc = fc_all[w];
   int32_t *fr = fr_all[w];
   float *fz = fz_all[w];
-  float tn = 0.0f;  // t of screen16_8
+  float t0 = 0.0f, tn = 0.0f;  // t0 and t of the screen
   {
     // p's row: unconditional loads (column clamped to K - 1), then selects
     float t[8];
@@ -519,16 +525,20 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
       const int q = lane + 64 * j;
       const float x = q < Kq ? xn[perm[q]] : 0.0f;
       xv[q] = -x * nv[q];
-      tn = fmaxf(tn, -nv[q] * __builtin_fmaf(fabsf(x), 0x1p-10f, 0x1p-24f));
+      t0 = fmaxf(t0, -nv[q]);
+      tn = fmaxf(tn, fabsf(xv[q]));
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) tn = fmaxf(tn, __shfl_xor(tn, off, 64));
-    // (room for the roundings of t itself and of the two uses below)
-    tn *= 1.0f + 0x1p-20f;
+    for (int off = 32; off > 0; off >>= 1) {
+      t0 = fmaxf(t0, __shfl_xor(t0, off, 64));
+      tn = fmaxf(tn, __shfl_xor(tn, off, 64));
+    }
+    t0 *= 0x1.04p-25f;
+    tn = __builtin_fmaf(tn, 2.0f * kScreen * (1.0f + 0x1p-8f), t0);
   }
   // whether a candidate of screen value z lies above u
   auto above = [&](float z, float u) __attribute__((always_inline)) {
-    const float lo = fmaxf(__builtin_fmaf(z, kLoScale, -tn), 0.0f);
+    const float lo = fmaxf(__builtin_fmaf(z, kLoScale, -t0), 0.0f);
     return lo * lo > u;
   };
   const int ka = Kq < kAq ? Kq : kAq;  // stage-A width (a multiple of 64)
@@ -549,8 +559,8 @@ k_best(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
   // exact distances of the survivors, smallest lower bound first
   auto resolve = [&]() __attribute__((always_inline)) {
     while (nf > 0) {
-      // (no entry: behind every entry, also one whose z is infinite, as it is
-      // where 1 / Q_H exceeds float32; equal values go to the lower lane)
+      // (no entry: behind every entry, whatever its z; equal values go to the
+      // lower lane)
       float l = lane < nf ? fz[lane] : INFINITY;
       int i = lane;
       for (int off = 1; off < 64; off <<= 1) {

@@ -650,3 +650,37 @@ def test_attach_chain(order):
     assert len(chain) < L / 20  # (float32 positions may tie a few gaps)
     assert nc == ref.n_clusters and np.array_equal(cl.cpu().numpy(), ref.label)
     assert np.array_equal(eo.cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-6, 3e4])
+@pytest.mark.parametrize("K", [8, 40, 160])
+def test_best_neighbour_on_smooth_vectors(K, scale):
+    """Pools whose rows differ little against their entries, in entries from
+    float16's subnormal range to near its largest: the screen's error bounds
+    decide which candidates get their exact distance.  The level against the
+    oracle, bit for bit."""
+    from oracle import clustering as ocl
+    side = 40
+    say(f"case: smooth vectors K={K} scale={scale}")
+    n = side * side
+    x = np.arange(side) / side
+    modes = [(i, j) for i in range(16) for j in range(16)][1:K + 1]
+    chi = np.stack([np.outer(np.cos(np.pi * i * x), np.cos(np.pi * j * x)).reshape(-1)
+                    for i, j in modes], 1)
+    chi = (scale * chi).astype(np.float32)
+    qh = np.array([0.1 * (i * i + j * j) for i, j in modes])
+    g = np.arange(n).reshape(side, side)
+    e = np.stack([g[a:a + 3, b:b + 3].reshape(-1) for a in range(side - 2)
+                  for b in range(0, side - 2, 2)])
+    m = len(e)
+    h = Hypergraph(n=n, m=m, eptr=9 * np.arange(m + 1), pins=e.reshape(-1).astype(np.int32),
+                   w=np.ones(m, np.float32))
+    R = np.random.default_rng(K).random(m).astype(np.float32)
+    for pct in (1e-6, 0.3):
+        out = hef.cluster_level(to_device(h), hef.Params(k=K // 2, b=1, percentile=pct),
+                                torch.as_tensor(R, device="cuda"), None,
+                                torch.as_tensor(chi, device="cuda"),
+                                torch.as_tensor(qh, device="cuda"))
+        ref = ocl.cluster_level(n, m, h.eptr, h.pins, R, None, chi, qh, pct, True)
+        assert out[1] == ref.n_clusters and np.array_equal(out[0].cpu().numpy(), ref.label)
+        assert np.array_equal(out[2].cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
