@@ -34,12 +34,13 @@ __device__ __forceinline__ bool wave_takes(int32_t len) {
 // The passes that give a long hyperedge a workgroup (the ratios and their
 // adjoint) take those of more than kSmallSeg pins while these are few, and
 // those of more than kMidSeg where there are more than kFewLong.  512 such
-// workgroups run at a time, a few us each, so 2048 hyperedges are four turns
-// (less than a lane group's chain over 256 pins), while thousands of lane groups
-// run at once: estimates over 50000 hyperedges of 40 pins, K = 24, 981 us by
-// this rule and 1618 without; 2M nodes, K = 480, 15k hyperedges above 32 pins,
-// 3.63 ms of ratios with and without.
-constexpr int kMidSeg = 256;
+// workgroups run at a time, a few us each, so 2048 hyperedges are four turns,
+// about a lane group's chain over 128 pins, while thousands of lane groups run at
+// once: estimates over 50000 hyperedges of 40 pins, K = 24, 981 us by this rule
+// and 1618 without.  The ratios of three levels from 2M nodes, K = 480 (15k
+// hyperedges above 32 pins), 8.32 ms without and 8.35 with it; 8.40 from 64 or
+// 256 pins on.
+constexpr int kMidSeg = 128;
 constexpr int kFewLong = 2048;
 __device__ __forceinline__ int long_from(int least, int32_t n_big) {
   return n_big > kFewLong && least < kMidSeg ? kMidSeg : least;
