@@ -316,8 +316,11 @@ hef_status hef_rebuild(const hef_hypergraph *hg, const int32_t *label, int32_t n
  *           to the smallest q; -1 for a node without neighbours;
  *   rating  DEVICE [n] float64 output: r(p, best[p]) (0 without neighbours);
  *   ws      DEVICE workspace of hef_workspace_size(hg, NULL, HEF_OP_RATING).
- * Work and memory are proportional to sum_e |e| (|e| - 1).  The hypergraph is
- * validated on the device.  Synchronises `stream`. */
+ * Memory is that of the incidence.  A node's hyperedges are walked once for up
+ * to about 500 distinct neighbours and once per 800 to 3000 above, so work is
+ * proportional to sum_e |e| (|e| - 1) but for nodes of very many neighbours;
+ * a node of 256 hyperedges or more has its walks run side by side.  The
+ * hypergraph is validated on the device.  Synchronises `stream`. */
 hef_status hef_rating(const hef_hypergraph *hg, const float *R, float shift, int32_t *best,
                       double *rating, void *ws, size_t ws_bytes, hipStream_t stream);
 

@@ -20,9 +20,11 @@
 // and no (p, q, e) triple is stored.  bound(p) = sum over the hyperedges of
 // p of (|e| - 1), at least the number of distinct q, selects the group:
 //   up to 64     16 lanes, 128 entries   (16 nodes per workgroup);
-//   up to 512    a wave, 1024 entries    (4 nodes per workgroup);
+//   up to 512    a wave, 1024 entries    (single-wave workgroups);
 //   above        256 threads, 4096 entries, in passes over hash classes of
-//                the q when they do not fit at once (k_rate_big).
+//                the q when they do not fit at once (k_rate_big);
+//   above, in kHubDeg or more hyperedges: waves of 1024 entries, each for its
+//                share of the hash classes (rate_unit).
 // Earlier every triple was emitted and sorted by q, then by p (six radix
 // passes per million triples), and one thread per node walked its triples
 // through two indirections: 9.9 ms for the 16M triples of a 200k-node
@@ -43,6 +45,35 @@ constexpr int kRateSmall = 64, kRateMid = 512;  // largest bound(p) of a class
 constexpr int kRateNG = 16;                     // nodes per workgroup of k_rate_small
 constexpr int kRateBigT = 4096;                 // table of the big class
 constexpr int kRateFill = kRateBigT * 3 / 4;    // entries a pass aims at
+
+// A node of many hyperedges (a hub) is the work of several waves.  Each walks
+// all of the node's hyperedges, in order and without a barrier, and keeps the q
+// of its own hash classes.  One workgroup that takes the classes one after the
+// other, with a barrier behind every hyperedge, is quadratic in the node's
+// degree: 6.0 / 58.8 / 861 ms a call with one node of the 200k in 3000 / 10000 /
+// 40000 hyperedges of 4 pins, now 1.3 / 3.5 / 13.5.  From 256 hyperedges on
+// the waves are faster even with one class (one node in 300 hyperedges, 447
+// and 403 us).
+constexpr int kHubDeg = 256;
+constexpr int kUnitT = kRateBigT / (kRT / 64);  // a wave's table
+constexpr int kUnitBits = 10;
+constexpr int kUnitFill = kUnitT * 3 / 4;       // entries a class aims at
+constexpr int kUnitEdges = 16;                  // least hyperedges of a node per wave
+static_assert(1 << kUnitBits == kUnitT, "table size");
+
+// Unit u of 1 << lu of hub p: the classes [u, u + 1) << (cb - lu) of 1 << cb;
+// `first` is the place of the hub's unit 0.
+struct RateUnit {
+  int32_t p, first, u, lu_cb;
+};
+// The units' results, and how many of a hub's units have stored theirs (at the
+// hub's first place).
+struct RateHubs {
+  int32_t *n_units;
+  RateUnit *unit;
+  int32_t *q, *done;
+  unsigned long long *r;
+};
 
 // flag |= 1 if an R value is not finite
 __global__ void k_rate_check(const float *__restrict__ R, int64_t m, int32_t *__restrict__ flag) {
@@ -86,14 +117,23 @@ struct RateBest {
   }
 };
 
-// One node of the classes that fit their table: G lanes of one wave.
-// bound is the same on all G lanes and at most T / 2.
-template <int G, int T>
-__device__ __forceinline__ void
-rate_node(int32_t p, int32_t v0, int32_t deg, int gl, const int32_t *__restrict__ eids,
+// The class of q among 1 << cb: the hash bits right below the BITS that index
+// the table (cb = 0: one class).
+template <int BITS>
+__device__ __forceinline__ uint32_t rate_class(int32_t q, int cb) {
+  return (rate_hash(q) << BITS) >> 1 >> (31 - cb);
+}
+
+// The best of a node's q (CLS: of class c among 1 << cb) by G lanes of one
+// wave, the same on all of them.  Without CLS the q fit the table.  *full is set
+// (to the same on all lanes) where they do not; the result is then of no use.
+template <int G, int T, bool CLS>
+__device__ __forceinline__ RateBest
+rate_walk(int32_t p, int32_t v0, int32_t deg, int gl, const int32_t *__restrict__ eids,
           const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
           const float *__restrict__ w, const float *__restrict__ R, double shift, int32_t *key,
-          double *acc, int32_t *__restrict__ best, double *__restrict__ rating) {
+          double *acc, uint32_t c, int cb, bool *full) {
+  bool over = false;
   for (int i = gl; i < T; i += G) {
     key[i] = -1;
     acc[i] = 0.0;
@@ -126,17 +166,24 @@ rate_node(int32_t p, int32_t v0, int32_t deg, int gl, const int32_t *__restrict_
       }
       while (j < b0) {
         const int32_t q1 = j + G < b0 ? pins[j + G] : p;
-        if (q != p) {
+        if (q != p && (!CLS || rate_class<__builtin_ctz(T)>(q, cb) == c)) {
           const int h = rate_slot<T>(key, q);
           if (h >= 0) acc[h] += term;
+          else over = true;
         }
         q = q1;
         j += G;
       }
       wave_sync();
     }
+    if (CLS && __ballot(over)) break;
   }
   RateBest bst{-1, 0.0};
+  if (CLS) {
+    static_assert(!CLS || G == 64, "a whole wave");
+    *full = __ballot(over) != 0;
+    if (*full) return bst;
+  }
   for (int i = gl; i < T; i += G) bst.take(key[i], acc[i]);
 #pragma unroll
   for (int off = G / 2; off > 0; off >>= 1) {
@@ -144,15 +191,89 @@ rate_node(int32_t p, int32_t v0, int32_t deg, int gl, const int32_t *__restrict_
     const double orr = __shfl_xor(bst.r, off, G);
     bst.take(oq, orr);
   }
-  if (gl == 0) {
-    best[p] = bst.q;
-    rating[p] = bst.q < 0 ? 0.0 : bst.r;
-  }
+  return bst;
 }
 
-// Every node: bound(p), then the node itself (small class) or its place in
-// the workgroup's own slice of a list: mid[NG blk ..] and big[NG blk ..], their
-// lengths in counts[2 blk], counts[2 blk + 1].  (One counter per list served
+__device__ __forceinline__ void rate_store(int32_t p, const RateBest &b,
+                                           int32_t *__restrict__ best,
+                                           double *__restrict__ rating) {
+  best[p] = b.q;
+  rating[p] = b.q < 0 ? 0.0 : b.r;
+}
+
+// One node of the classes that fit their table: G lanes of one wave.
+// bound is the same on all G lanes and at most T / 2.
+template <int G, int T>
+__device__ __forceinline__ void
+rate_node(int32_t p, int32_t v0, int32_t deg, int gl, const int32_t *__restrict__ eids,
+          const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
+          const float *__restrict__ w, const float *__restrict__ R, double shift, int32_t *key,
+          double *acc, int32_t *__restrict__ best, double *__restrict__ rating) {
+  const RateBest b = rate_walk<G, T, false>(p, v0, deg, gl, eids, eptr, pins, w, R, shift, key,
+                                            acc, 0u, 0, nullptr);
+  if (gl == 0) rate_store(p, b, best, rating);
+}
+
+// One unit of a hub, by a wave: the best q of its classes.  A class that fills
+// the table is halved, and so are those after it; the hash is a bijection, so
+// this ends.  The wave that stores the last of the hub's results takes the
+// best of them.
+__device__ void rate_unit(const RateHubs &H, int32_t i, int lane, const int32_t *__restrict__ vptr,
+                          const int32_t *__restrict__ eids, const int32_t *__restrict__ eptr,
+                          const int32_t *__restrict__ pins, const float *__restrict__ w,
+                          const float *__restrict__ R, double shift, int32_t *key, double *acc,
+                          int32_t *__restrict__ best, double *__restrict__ rating) {
+  const RateUnit x = H.unit[i];
+  const int lu = x.lu_cb >> 8;
+  int cb = x.lu_cb & 255;
+  const int32_t v0 = vptr[x.p], deg = vptr[x.p + 1] - v0;
+  RateBest bst{-1, 0.0};
+  uint32_t c = uint32_t(x.u) << (cb - lu), end = uint32_t(x.u + 1) << (cb - lu);
+  while (c < end) {
+    bool full = false;
+    const RateBest b = rate_walk<64, kUnitT, true>(x.p, v0, deg, lane, eids, eptr, pins, w, R,
+                                                   shift, key, acc, c, cb, &full);
+    wave_sync();
+    if (full) {
+      ++cb;
+      c *= 2;
+      end *= 2;
+      continue;
+    }
+    bst.take(b.q, b.r);
+    ++c;
+  }
+  int32_t before = 0;
+  if (lane == 0) {
+    __hip_atomic_store(&H.q[i], bst.q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&H.r[i], __builtin_bit_cast(unsigned long long, bst.r), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    before = __hip_atomic_fetch_add(&H.done[x.first], 1, __ATOMIC_ACQ_REL,
+                                    __HIP_MEMORY_SCOPE_AGENT);
+  }
+  before = __builtin_amdgcn_readfirstlane(before);
+  if (before != (1 << lu) - 1) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  RateBest all{-1, 0.0};
+  for (int k = lane; k < 1 << lu; k += 64) {
+    const int32_t q = __hip_atomic_load(&H.q[x.first + k], __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long r = __hip_atomic_load(&H.r[x.first + k], __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    all.take(q, __builtin_bit_cast(double, r));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const int32_t oq = __shfl_xor(all.q, off, 64);
+    const double orr = __shfl_xor(all.r, off, 64);
+    all.take(oq, orr);
+  }
+  if (lane == 0) rate_store(x.p, all, best, rating);
+}
+
+// Every node: bound(p), then the node itself (small class), its units (hub) or
+// its place in the workgroup's own slice of a list: mid[NG blk ..] and
+// big[NG blk ..], their lengths in counts[2 blk], counts[2 blk + 1].  (One counter per list served
 // 60k nodes of a 200k-node netlist one after the other: 473 us, now
 // 96 us.)
 __global__ void __launch_bounds__(kRT)
@@ -160,12 +281,12 @@ k_rate_small(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
              const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
              const float *__restrict__ w, const float *__restrict__ R, double shift, int32_t n,
              int32_t *__restrict__ mid, int32_t *__restrict__ big, int32_t *__restrict__ counts,
-             int32_t *__restrict__ best, double *__restrict__ rating) {
+             const RateHubs H, int32_t *__restrict__ best, double *__restrict__ rating) {
   constexpr int G = 16, T = 2 * kRateSmall, NG = kRateNG;
   static_assert(NG * G == kRT, "lanes");
   __shared__ int32_t key[NG][T];
   __shared__ double acc[NG][T];
-  __shared__ int32_t cls[NG];  // 0 small, 1 middle, 2 big
+  __shared__ int32_t cls[NG];  // 0 small, 1 middle, 2 big, 3 hub
   const int gi = threadIdx.x / G, gl = threadIdx.x % G;
   const int64_t p0 = int64_t(blockIdx.x) * NG, p = p0 + gi;
   const int32_t v0 = p < n ? vptr[p] : 0, deg = p < n ? vptr[p + 1] - v0 : 0;
@@ -176,7 +297,22 @@ k_rate_small(const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
   }
 #pragma unroll
   for (int off = G / 2; off > 0; off >>= 1) bound += __shfl_xor(bound, off, G);
-  if (gl == 0) cls[gi] = bound <= kRateSmall ? 0 : bound <= kRateMid ? 1 : 2;
+  const bool hub = bound > kRateMid && deg >= kHubDeg;
+  if (gl == 0) cls[gi] = bound <= kRateSmall ? 0 : bound <= kRateMid ? 1 : hub ? 3 : 2;
+  if (hub) {
+    const int32_t most = bound < n - 1 ? bound : n - 1;  // distinct q
+    int cb = 0, lu = 0;
+    while (cb < 32 - kUnitBits && (most >> cb) > kUnitFill) ++cb;
+    while (lu < cb && (deg >> (lu + 1)) >= kUnitEdges) ++lu;
+    int32_t first = 0;
+    if (gl == 0) {
+      first = atomicAdd(H.n_units, 1 << lu);
+      H.done[first] = 0;
+    }
+    first = __shfl(first, 0, G);
+    for (int32_t u = gl; u < 1 << lu; u += G)
+      H.unit[first + u] = RateUnit{int32_t(p), first, u, (lu << 8) | cb};
+  }
   __syncthreads();
   if (threadIdx.x < 2) {
     int32_t *list = threadIdx.x == 0 ? mid : big;
@@ -214,7 +350,8 @@ k_rate_mid(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
   }
 }
 
-// A workgroup per node.  The q are split into 2^cb classes by bits of their
+// The units of the hubs, a wave each; then a workgroup per node of the big
+// class.  The q are split into 2^cb classes by bits of their
 // hash below the table's; pass c takes class c.  cb starts so that a pass
 // meets about kRateFill distinct q at most and grows by one, restarting the
 // class sweep, whenever a table fills up; the hash is a bijection, so the
@@ -224,7 +361,8 @@ k_rate_big(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
            const int32_t *__restrict__ vptr, const int32_t *__restrict__ eids,
            const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
            const float *__restrict__ w, const float *__restrict__ R, double shift, int32_t n,
-           int32_t nslice, int32_t *__restrict__ best, double *__restrict__ rating) {
+           int32_t nslice, const RateHubs H, int32_t *__restrict__ best,
+           double *__restrict__ rating) {
   constexpr int T = kRateBigT;
   constexpr int kTableBits = 12;  // the hash bits that index the table
   static_assert(1 << kTableBits == T, "table size");
@@ -237,6 +375,14 @@ k_rate_big(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
   __shared__ int32_t ea[kRT], eb[kRT];  // a batch of the node's hyperedges
   __shared__ double et[kRT];
   const int tid = threadIdx.x;
+  {
+    const int wv = tid >> 6;
+    const int32_t nu = *H.n_units;
+    for (int32_t i = int32_t(wave_index()); i < nu; i += gridDim.x * (kRT / 64))
+      rate_unit(H, i, tid & 63, vptr, eids, eptr, pins, w, R, shift, key + wv * kUnitT,
+                acc + wv * kUnitT, best, rating);
+    __syncthreads();
+  }
   // (slice, entry) pairs in turn: workgroup b takes slots b, b + grid, ... of
   // the nslice x kRateNG slots (the big nodes of one slice go to different
   // workgroups); kRT slots are looked up together, those past a slice's
@@ -297,9 +443,7 @@ k_rate_big(const int32_t *__restrict__ list, const int32_t *__restrict__ counts,
             for (int u = 0; u < 4; ++u) q[u] = j + u * kRT < b ? pins[j + u * kRT] : p;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-              // class: the hash bits right below the table's (cb = 0: one class)
-              const uint32_t cls = (rate_hash(q[u]) << kTableBits) >> 1 >> (31 - cb);
-              if (q[u] != p && cls == c) {
+              if (q[u] != p && rate_class<kTableBits>(q[u], cb) == c) {
                 const int h = rate_slot<T>(key, q[u]);
                 if (h >= 0) acc[h] += term;
                 else full = 1;
@@ -370,13 +514,12 @@ hef_status rating_run(const Level &L, const float *R, float shift, int32_t *best
   int32_t *counts = a.take<int32_t>(2 * cdiv(n, kRateNG) + 2);
   HEF_WS_CHECK(a);
   int32_t bad = 0;
-  HEF_TRY(validate_device(L, flags, &bad, s));
+  HEF_TRY(validate_device(L, flags, &bad, s, 2));
   if (bad) {
     set_error("invalid hypergraph (code %d)", bad);
     return HEF_ERR_INVALID_HYPERGRAPH;
   }
-  if (m > 0) {
-    HEF_TRY(zero_async(flags, sizeof(int32_t), s));
+  if (m > 0) {  // (flags[0] is still 0)
     k_rate_check<<<gr(m), kRT, 0, s>>>(R, m, flags);
     HEF_LAUNCH_CHECK();
     int32_t f = 0;
@@ -391,16 +534,25 @@ hef_status rating_run(const Level &L, const float *R, float shift, int32_t *best
   TimedScope ts(kStRating, s);
   HEF_TRY(structure_build(L, st, a, s));
   const double sh = double(shift);
-  // (the lists' lengths stay on the device)
+  // (the lists' lengths stay on the device; a hub has at most a unit per
+  // kUnitEdges hyperedges, and the structure's scratch is free again)
+  const int64_t units = nnz / kUnitEdges + 1;
+  RateHubs H;
+  H.n_units = flags + 1;
+  H.unit = a.take<RateUnit>(units);
+  H.q = a.take<int32_t>(units);
+  H.done = a.take<int32_t>(units);
+  H.r = a.take<unsigned long long>(units);
+  HEF_WS_CHECK(a);
   const unsigned nslice = unsigned(cdiv(n, kRateNG));
   k_rate_small<<<nslice, kRT, 0, s>>>(st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh, int32_t(n),
-                                      mid, big, counts, best, rating);
+                                      mid, big, counts, H, best, rating);
   HEF_LAUNCH_CHECK();
   k_rate_mid<<<nslice * kMidSplit, 64, 0, s>>>(mid, counts, st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh,
                                     best, rating);
   HEF_LAUNCH_CHECK();
   k_rate_big<<<std::min<unsigned>(nslice * kRateNG, 4096u), kRT, 0, s>>>(
-      big, counts, st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh, int32_t(n), int32_t(nslice),
+      big, counts, st.vptr, st.eids, L.eptr, L.pins, L.w, R, sh, int32_t(n), int32_t(nslice), H,
       best, rating);
   HEF_LAUNCH_CHECK();
   HEF_HIP(hipStreamSynchronize(s));

@@ -684,3 +684,67 @@ def test_best_neighbour_on_smooth_vectors(K, scale):
         ref = ocl.cluster_level(n, m, h.eptr, h.pins, R, None, chi, qh, pct, True)
         assert out[1] == ref.n_clusters and np.array_equal(out[0].cpu().numpy(), ref.label)
         assert np.array_equal(out[2].cpu().numpy().view(np.uint32), ref.eta.view(np.uint32))
+
+
+def _hub(n, deg, size, seed, pool=None, hub=0):
+    """Node `hub` in `deg` hyperedges of `size` pins drawn from `pool`, and one
+    hyperedge apart."""
+    rng = np.random.default_rng(seed)
+    pool = np.setdiff1d(np.arange(n), [hub]) if pool is None else np.asarray(pool)
+    step = rng.integers(1, max(2, len(pool) // size), deg)
+    draw = (rng.integers(0, len(pool), deg)[:, None] + step[:, None] * np.arange(size - 1)) % len(pool)
+    edges = [np.sort(np.append(pool[d], hub)) for d in draw]
+    edges.insert(deg // 2, np.array([1, 2, 3]))
+    eptr = np.concatenate([[0], np.cumsum([len(e) for e in edges])]).astype(np.int64)
+    w = rng.uniform(0.5, 2.0, len(edges)).astype(np.float32)
+    return Hypergraph(n=n, m=len(edges), eptr=eptr, pins=np.concatenate(edges).astype(np.int32), w=w)
+
+
+@pytest.mark.parametrize("deg,size", [(255, 4), (256, 3), (256, 4), (511, 3), (512, 8), (1100, 3),
+                                      (3000, 5), (300, 200), (20000, 2)])
+def test_rating_of_hubs(deg, size):
+    """A node of 256 hyperedges or more is shared by waves, a range of hash
+    classes each: one class and many, fewer waves than classes, hyperedges of
+    less and of more pins than lanes, and repeated neighbours, whose terms
+    must add up in hyperedge order."""
+    from oracle import rating as orat
+    say(f"case: rating hub deg={deg} size={size}")
+    for n, pool in ((30000, None), (30000, np.arange(500, 500 + max(40, 2 * size)))):
+        hg = _hub(n, deg, size, deg + size, pool, hub=7 if pool is None else n - 1)
+        R = np.random.default_rng(5).uniform(0.01, 1.0, hg.m).astype(np.float32)
+        for shift in (0.0, 1.0):
+            best, val = hef.rating(to_device(hg), torch.as_tensor(R, device="cuda"), shift)
+            nodes = np.unique(np.concatenate([[0, 1, 2, 7, n - 1], hg.pins[:40]]))
+            rb, rv = orat.best_neighbours(hg.n, hg.m, hg.eptr, hg.pins, hg.w, R, shift, nodes)
+            assert np.array_equal(best.cpu().numpy()[nodes], rb)
+            assert np.array_equal(val.cpu().numpy()[nodes], rv)
+
+
+def test_rating_of_hubs_with_full_tables():
+    """Neighbours that all fall in one class of the first sweep overflow its
+    table, which is halved until they fit; and many hubs at once."""
+    from oracle import rating as orat
+    say("case: rating hubs, full tables and many hubs")
+    n = 400000
+    q = np.arange(8, n, dtype=np.uint64)
+    hsh = (q * 2654435769) & 0xFFFFFFFF
+    pool = q[((hsh >> 19) & 7) == 5].astype(np.int64)[:6000]  # one of 8 classes below 10 bits
+    hg = _hub(n, 3000, 3, 3, pool)
+    R = np.random.default_rng(5).uniform(0.01, 1.0, hg.m).astype(np.float32)
+    best, val = hef.rating(to_device(hg), torch.as_tensor(R, device="cuda"), 0.0)
+    nodes = np.unique(np.concatenate([[0, 1, 2], hg.pins[:30]]))
+    rb, rv = orat.best_neighbours(hg.n, hg.m, hg.eptr, hg.pins, hg.w, R, 0.0, nodes)
+    assert np.array_equal(best.cpu().numpy()[nodes], rb)
+    assert np.array_equal(val.cpu().numpy()[nodes], rv)
+    n, m = 700, 90000  # every node in about 390 hyperedges
+    rng = np.random.default_rng(9)
+    pins = np.sort(np.stack([3 * rng.choice(n // 3, m), 3 * rng.choice(n // 3, m) + 1,
+                             3 * rng.choice(n // 3, m) + 2], 1), 1).reshape(-1)
+    hg = Hypergraph(n=n, m=m, eptr=3 * np.arange(m + 1), pins=pins.astype(np.int32),
+                    w=rng.uniform(0.5, 2.0, m).astype(np.float32))
+    R = rng.uniform(0.01, 1.0, m).astype(np.float32)
+    best, val = hef.rating(to_device(hg), torch.as_tensor(R, device="cuda"), 0.0)
+    nodes = np.arange(0, n, 23)
+    rb, rv = orat.best_neighbours(hg.n, hg.m, hg.eptr, hg.pins, hg.w, R, 0.0, nodes)
+    assert np.array_equal(best.cpu().numpy()[nodes], rb)
+    assert np.array_equal(val.cpu().numpy()[nodes], rv)
