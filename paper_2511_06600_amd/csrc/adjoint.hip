@@ -241,7 +241,7 @@ k_sadj_b(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
          const float *__restrict__ dR, const float *__restrict__ w,
          const int32_t *__restrict__ istar, const double *__restrict__ qsum,
          const int32_t *__restrict__ n_big, const SadjOut o) {
-  const int from = long_from(kSmallSeg, *n_big);
+  const int from = long_from(kSmallSeg, LPR, *n_big);
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -281,7 +281,7 @@ k_sadj_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
   double inv[CPL], qb[CPL];
   sadj_cols<CPL>(c0, K, qh, qsum, inv, qb);
   const int32_t cnt = *count;
-  const int from = long_from(kSmallSeg, cnt);
+  const int from = long_from(kSmallSeg, LPR, cnt);
   for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
     const int32_t e = list[bi];
     const int32_t a = eptr[e], b = eptr[e + 1];

@@ -158,7 +158,7 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
   const int c0 = (tid % LPR) * CPL;
   const int W = LPR * CPL;  // columns of a group's LDS row
   const int32_t cnt = *count;
-  const int from = long_from(longseg, cnt);
+  const int from = long_from(longseg, LPR, cnt);
   for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
     const int32_t e = list[bi];
     const int32_t a = eptr[e], b = eptr[e + 1];
@@ -229,7 +229,7 @@ k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
            int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
            const int32_t *__restrict__ n_big, const void *__restrict__ ext) {
   __shared__ double comb[kThreads * CPL];
-  const int from = long_from(longseg, *n_big);
+  const int from = long_from(longseg, LPR, *n_big);
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -319,7 +319,7 @@ k_score_qh_few(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pin
                const float *__restrict__ w, const void *__restrict__ pool, int K, int LPR,
                int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
                const int32_t *__restrict__ n_big, const void *__restrict__ ext) {
-  const int from = long_from(longseg, *n_big);
+  const int from = long_from(longseg, LPR, *n_big);
   constexpr int R = kFewThreads / kThreads;
   constexpr int NA = kThreads * CPL / kFewThreads;  // sums per thread
   static_assert(NA * kFewThreads == kThreads * CPL, "whole sums per thread");

@@ -543,11 +543,12 @@ def test_long_pin_ranges_are_split(layout):
     assert np.abs(y - ref).max() <= (deg + 4) * 2.0 ** -24 * max(np.abs(ref).max(), 1.0)
 
 
-@pytest.mark.parametrize("k,b", [(5, 1), (8, 4)])
+@pytest.mark.parametrize("k,b", [(5, 1), (8, 4), (9, 4), (17, 8)])
 @pytest.mark.parametrize("many", [2048, 2049])
 def test_many_long_hyperedges(many, k, b):
     """Up to 2048 hyperedges of more than 32 pins each take a workgroup in the
-    ratios and in their adjoint, more than that only those above 128 pins: as
+    ratios and in their adjoint, more than that only those above 128 pins, or
+    64 with lane groups of 32 and more: as
     many fours of pins as lane groups and fewer, whole and not.  Ratios
     against float64 on the pool (bounds as in test_long_hyperedge_ratios), the
     gradient against the float64 autograd oracle at the adjoint tests' 1e-3."""
@@ -555,7 +556,7 @@ def test_many_long_hyperedges(many, k, b):
     from oracle import resistance as orr
     from tests.gpu_common import starts
     say(f"case: many long hyperedges {many} k={k} b={b}")
-    special = [127, 128, 129, 130, 255, 300, 513, 36, 37, 63]
+    special = [127, 128, 129, 130, 255, 300, 513, 36, 37, 63, 64, 65, 66]
     sizes = special + [33 + i % 4 for i in range(many - len(special))] + _mixed_sizes(300, 3) + [32]
     assert sum(s > 32 for s in sizes) == many
     w = np.random.default_rng(2).uniform(0.5, 2.0, len(sizes)).astype(np.float32)
