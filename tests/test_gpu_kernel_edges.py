@@ -749,3 +749,63 @@ def test_rating_of_hubs_with_full_tables():
     rb, rv = orat.best_neighbours(hg.n, hg.m, hg.eptr, hg.pins, hg.w, R, 0.0, nodes)
     assert np.array_equal(best.cpu().numpy()[nodes], rb)
     assert np.array_equal(val.cpu().numpy()[nodes], rv)
+
+
+@pytest.mark.parametrize("nnz", [4095, 4096, 4097, 8191, 8192, 8193, 16385, 70001, 1048575, 1048576,
+                                 1048577, 1052673])
+def test_sorts_of_exact_sizes(nnz):
+    """The incidence and label sorts at exactly the counts where they change:
+    4 or 8 items a thread in one workgroup (4096), several workgroups (8192),
+    tiles of 1024 or 4096 items (2^20); ids of 8, 16, 17 and 20 bits, i.e. one
+    to three digits of 8 bits or two of 9.  Every node's degree from the
+    conductance of single-node clusters (whole numbers), its hyperedges from the
+    star operator."""
+    say(f"case: exact sort sizes nnz={nnz}")
+    for n in (200, 60000, 70000, 600000):
+        rng = np.random.default_rng(nnz + n)
+        m = nnz // 3
+        sizes = np.full(m, 3)
+        sizes[rng.permutation(m)[:nnz - 3 * m]] += 1
+        eptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+        assert eptr[-1] == nnz
+        first = rng.integers(0, n - 40, m)
+        pins = np.repeat(first, sizes) + 11 * (np.arange(nnz) - np.repeat(eptr[:-1], sizes))
+        h = Hypergraph(n=n, m=m, eptr=eptr, pins=pins.astype(np.int32), w=np.ones(m, np.float32))
+        dh = to_device(h)
+        deg = np.bincount(pins, minlength=n).astype(np.float64)
+        perm = rng.permutation(n).astype(np.int32)
+        cut, vol, _, _ = hef.conductance(dh, torch.as_tensor(perm, device="cuda"), n)
+        assert np.array_equal(vol.cpu().numpy()[perm], deg)
+        assert np.array_equal(cut.cpu().numpy()[perm], deg)
+        x = torch.zeros((n + m, 1), device="cuda")
+        x[n:, 0] = torch.arange(m, device="cuda") % 13
+        y = hef.debug_apply(dh, 0, x).cpu().numpy()[:n, 0].astype(np.float64)
+        db = np.bincount(pins, weights=np.repeat(1.0 / sizes, sizes), minlength=n)
+        ref = np.bincount(pins, weights=np.repeat((np.arange(m) % 13) / sizes, sizes), minlength=n)
+        ref = np.where(db > 0, ref / np.sqrt(np.where(db > 0, db, 1.0)), 0.0)
+        assert np.abs(y - ref).max() <= (deg.max() + 4) * 2.0 ** -24 * max(np.abs(ref).max(), 1.0)
+
+
+@pytest.mark.parametrize("m", [4096, 4097, 8192, 8193, 1048576, 1048577])
+def test_level_order_at_sort_sizes(m):
+    """The 32-bit sort of the updated resistances (four digits) at the same
+    counts, with many equal values, whose order is the hyperedges': the
+    contraction of one level against the oracle."""
+    from oracle import clustering as ocl
+    n = 3 * m // 2
+    say(f"case: level order m={m}")
+    rng = np.random.default_rng(m)
+    first = rng.integers(0, n - 9, m)
+    pins = np.stack([first, first + rng.integers(1, 9, m)], 1).reshape(-1).astype(np.int32)
+    h = Hypergraph(n=n, m=m, eptr=2 * np.arange(m + 1), pins=pins, w=np.ones(m, np.float32))
+    R = (rng.integers(1, 1 + m // 4, m) * np.float32(2.0) ** rng.integers(-90, 20, m)).astype(np.float32)
+    cl, nc, _ = hef.cluster_level(to_device(h), hef.Params(k=4, b=1, local_clustering=False),
+                                  torch.as_tensor(R, device="cuda"), None,
+                                  torch.zeros((n, 8), device="cuda"),
+                                  torch.ones(8, dtype=torch.float64, device="cuda"))
+    owner, _ = ocl.greedy_contract(n, h.eptr, h.pins, R, ocl.threshold(R, 0.5))
+    prov = np.arange(n)
+    taken = owner >= 0
+    prov[taken] = pins[2 * owner[taken]]
+    roots = np.unique(prov)
+    assert nc == len(roots) and np.array_equal(cl.cpu().numpy(), np.searchsorted(roots, prov))
