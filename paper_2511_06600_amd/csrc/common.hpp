@@ -93,17 +93,17 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
 }
 
 // A Cholesky pivot: root = sqrt(d) and inv, its reciprocal to within an ulp,
-// for normal d far from the ends of the exponent range (pivots here are sums
-// of squares of float32 values, so they lie within 1e-91 .. 1e90).  Goldschmidt
-// steps from the hardware's reciprocal square root, with two residual
-// corrections of the root; root is correctly rounded, as sqrt() is.  The
-// chain is 13 operations; sqrt() and a division by it are about 35 with their
-// range checks.
+// for d within 1e-200 .. 1e200.  A kept pivot exceeds tau^2 times its Gram
+// diagonal, a sum of squares of float32 values (1e-90 .. 1e90), or with tau = 0
+// is what their roundings leave of it, 1e-16 of it or so.  Goldschmidt steps
+// from an approximate reciprocal square root y (relative error 2^-20 or less),
+// with two residual corrections of the root; over that range root equals
+// sqrt(d) to the bit.  The chain is 13 operations; sqrt() and a division by it
+// are about 35 with their range checks.
 struct Pivot {
   double root, inv;
 };
-__device__ __forceinline__ Pivot pivot_of(double d) {
-  const double y = __builtin_amdgcn_rsq(d);
+__host__ __device__ __forceinline__ Pivot pivot_from(double d, double y) {
   double g = d * y, h = 0.5 * y;
   const double r = __builtin_fma(-h, g, 0.5);
   g = __builtin_fma(g, r, g);
@@ -114,9 +114,14 @@ __device__ __forceinline__ Pivot pivot_of(double d) {
   i = __builtin_fma(__builtin_fma(-g, i, 1.0), i, i);
   return {g, i};
 }
-// x / p.root, correctly rounded (Markstein: a quotient within an ulp or two,
-// its exact residual, one fused correction).
-__device__ __forceinline__ double div_pivot(double x, const Pivot &p) {
+// (from the hardware's reciprocal square root)
+__device__ __forceinline__ Pivot pivot_of(double d) {
+  return pivot_from(d, __builtin_amdgcn_rsq(d));
+}
+// x / p.root by a quotient within an ulp or two, its exact residual and one
+// fused correction (Markstein): equal to the division, or an ulp off in the
+// few cases where inv is not the nearest to 1 / root.
+__host__ __device__ __forceinline__ double div_pivot(double x, const Pivot &p) {
   const double q = x * p.inv;
   return __builtin_fma(__builtin_fma(-q, p.root, x), p.inv, q);
 }
