@@ -1133,7 +1133,6 @@ hef_status taped_forward(const Level &L, const hef_params &p, const float *start
                          const float *start_clique, BwdWs &w, Arena &a, hipStream_t s) {
   const int64_t n = L.n, m = L.m;
   const int B = p.b, k = p.k, K = pool_width_of(p);
-  const int64_t Ns = n + m;
   const bool use_star = !(p.flags & HEF_FLAG_CLIQUE_ONLY);
   const bool use_clique = !(p.flags & HEF_FLAG_STAR_ONLY);
   const Structure &st = w.st;

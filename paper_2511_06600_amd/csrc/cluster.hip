@@ -927,7 +927,6 @@ __global__ void k_group_eta(const int32_t *__restrict__ cl_ptr, const int32_t *_
   eta_out[g] = float(acc);
 }
 
-// segment starts of a sorted key array: ptr[k] = first index with key >= k
 // ptr[k] = the first position of a key >= k in the ascending keys[0, cnt),
 // for k = 0 .. nseg (one binary search per segment, so a long run of empty
 // segments costs no single thread more than another)
@@ -1000,7 +999,6 @@ __global__ void k_gather_u32(const uint32_t *__restrict__ src, const uint32_t *_
   if (i < cnt) dst[i] = src[idx[i]];
 }
 
-// after sorting slots by (edge, label): count distinct labels per edge
 // ---- a9: per-hyperedge sorted labels -----------------------------------------
 // lab_sorted[eptr[e] .. eptr[e+1]) = the labels of e's pins in ascending order
 // and cnt[e] = their number of distinct values (0 when below 2).  Hyperedges
@@ -1138,6 +1136,7 @@ __global__ void k_rebuild_tail(const int32_t *__restrict__ kpos, const int32_t *
   out3[2] = overflow ? *overflow : 0;
 }
 
+// after the global sort of the slots by (hyperedge, label): distinct labels
 __global__ void k_distinct(const int32_t *__restrict__ eptr, const uint32_t *__restrict__ lab_sorted,
                            int32_t *__restrict__ cnt, int32_t m) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;

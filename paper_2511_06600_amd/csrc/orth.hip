@@ -17,13 +17,6 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-
-__device__ __forceinline__ float pool_at(const void *pool, int pool_type, int64_t idx) {
-  if (pool_type == kPoolF32) return reinterpret_cast<const float *>(pool)[idx];
-  const uint16_t h = reinterpret_cast<const uint16_t *>(pool)[idx];
-  return __uint_as_float(uint32_t(h) << 16);
-}
-
 __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
@@ -36,7 +29,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 // its column of L is zero.
 constexpr int kPW = 32;
 constexpr int kPS = kPW + 1;  // LDS row stride of a panel
-constexpr int kMaxPB = 16;    // 32-column blocks of the widest pool (K <= 512)
 
 // Right-looking: A holds G minus the contributions of the finished panels
 // (lower triangle).  Panel [c0, c0+w) is factored by k_chol_panel;
@@ -91,7 +83,7 @@ k_chol_panel(const double *__restrict__ A, const double *__restrict__ G, int K, 
 #pragma unroll
     for (int j = 0; j < kPW; ++j) x[j] = j < w ? ar[j] : 0.0;
   }
-  double dkeep = 0.0, pkeep = 0.0;  // lane r: column r's Schur pivot and L_rr
+  double dkeep = 0.0;  // lane r: column r's Schur pivot
   int kkeep = 0;
   // column jj of the diagonal block (first wave)
   auto diag_step = [&](int jj) __attribute__((always_inline)) {
@@ -104,7 +96,6 @@ k_chol_panel(const double *__restrict__ A, const double *__restrict__ G, int K, 
     const double lv = (kp && r > jj && r < w) ? div_pivot(x[jj], pv) : 0.0;
     if (r == jj) {
       dkeep = d;
-      pkeep = piv;
       kkeep = kp;
     }
     // column jj of L below the pivot (entries above the diagonal of the
@@ -785,28 +776,27 @@ constexpr int kAT = 256;  // BF16 apply workgroup size
 constexpr int kAM = 128, kAN = 128;
 
 
-// Q = V Rinv for the float32 pool, Rinv upper triangular (Kp x Kp, zero
-// outside K x K), read through its transpose RT (RT[c][k] = Rinv[k][c]): no
-// LDS and no barriers.  A workgroup of four waves takes 64 rows; the
-// 32-column output tiles are dealt to the waves in snake order of their work
-// (tile c needs the c + 1 leading 32-row chunks of Rinv), so the waves'
-// shares of the triangle are about equal, at most 4 tiles each.  Operands
-// come straight from global memory into registers, kA2G k steps at a time,
-// the next group loaded while the current one is multiplied:
+// Q = V Rinv for a row-major float32 pool (the second pass), Rinv upper
+// triangular (Kp x Kp, zero outside K x K), read through its transpose RT
+// (RT[c][k] = Rinv[k][c]): no LDS and no barriers.  A workgroup of four waves
+// takes 64 rows; the 32-column output tiles are dealt to the waves in snake
+// order of their work (tile c needs the c + 1 leading 32-row chunks of Rinv), so
+// the waves' shares of the triangle are about equal, at most 4 tiles each.
+// Operands come straight from global memory into registers, kA2G k steps at a
+// time, the next group loaded while the current one is multiplied:
 //  * MFMA step s of a 32-wide k chunk pairs k = 32 kc + s (lanes 0-31) with
 //    32 kc + 16 + s (lanes 32-63), so a lane's B values for kA2G steps are
 //    kA2G consecutive entries of one row of RT (one 16-byte load);
 //  * the wave's two row tiles interleave: lane i of row tile r holds local
-//    row 2i + r, so in the row-octet layout one 8-byte load gives a lane its
-//    A values of both row tiles;
-//  * a row-major pool with K % 4 == 0 (VEC) gives a lane its kA2G k values
-//    of one row as one 16-byte load (a group's first k is a multiple of 4,
-//    so the group lies wholly inside or wholly past column K).
+//    row 2i + r;
+//  * with K % 4 == 0 (VEC) a lane's kA2G k values of one row are one 16-byte
+//    load (a group's first k is a multiple of 4, so the group lies wholly
+//    inside or wholly past column K).
 constexpr int kA2T = 256;
 constexpr int kA2Rows = 64;
 constexpr int kA2G = 4;  // k steps per register group (4 groups per 32-wide chunk)
 
-template <bool OCT, bool VEC, int NA>
+template <bool VEC, int NA>
 __device__ __forceinline__ void tri_chunks(const float *__restrict__ Vw,
                                            const float *__restrict__ RT, uint32_t vo,
                                            uint32_t vo1, int K, int Kp,
@@ -842,15 +832,8 @@ __device__ __forceinline__ void tri_chunks(const float *__restrict__ Vw,
         const int k = kb + s;
         kin[buf][s] = k < K;
         const uint32_t kk = k < K ? uint32_t(k) : 0u;
-        if constexpr (OCT) {
-          // rows 2i and 2i + 1 sit side by side in their octet
-          const float2 t = *reinterpret_cast<const float2 *>(vb + 4u * (vo + 8u * kk));
-          a[buf][s][0] = t.x;
-          a[buf][s][1] = t.y;
-        } else {
-          a[buf][s][0] = *reinterpret_cast<const float *>(vb + 4u * (vo + kk));
-          a[buf][s][1] = *reinterpret_cast<const float *>(vb + 4u * (vo1 + kk));
-        }
+        a[buf][s][0] = *reinterpret_cast<const float *>(vb + 4u * (vo + kk));
+        a[buf][s][1] = *reinterpret_cast<const float *>(vb + 4u * (vo1 + kk));
       }
     }
 #pragma unroll
@@ -883,12 +866,11 @@ __device__ __forceinline__ void tri_chunks(const float *__restrict__ Vw,
   if (g < g1) mul(0);
 }
 
-template <bool OCT, bool VEC>
+template <bool VEC>
 __global__ void __launch_bounds__(kA2T) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_japply_tri(const float *__restrict__ V, float *__restrict__ Q, int64_t n, int K, int Kp,
              const float *__restrict__ RT) {
   static_assert(kA2G == 4, "a group's B values (and VEC's A values) are one float4");
-  static_assert(!(OCT && VEC), "VEC is the row-major layout");
   const int64_t row0 = int64_t(xcd_block(blockIdx.x, gridDim.x)) * kA2Rows;
   // the wave index and everything derived from it are wave-uniform (scalar)
   const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
@@ -905,13 +887,13 @@ k_japply_tri(const float *__restrict__ V, float *__restrict__ Q, int64_t n, int 
     if (t < nct) ct[nt++] = nct - 1 - t;
   }
   if (nt == 0) return;
-  // the workgroup's rows of V from a uniform base (row0 is a multiple of 8)
-  const float *Vw = OCT ? V + (row0 >> 3) * int64_t(K) * 8 : V + row0 * int64_t(K);
+  // the workgroup's rows of V from a uniform base
+  const float *Vw = V + row0 * int64_t(K);
   const int64_t last = n - 1 - row0;  // the last valid local row
   // a valid row pair to read (masked out above when past the end)
   const uint32_t r0 = uint32_t(2 * li <= last ? 2 * li : (last & ~int64_t(1)));
   const uint32_t r1 = uint32_t(2 * li + 1 <= last ? 2 * li + 1 : last);
-  const uint32_t vo = OCT ? ((r0 >> 3) * uint32_t(K)) * 8u + (r0 & 7u) : r0 * uint32_t(K);
+  const uint32_t vo = r0 * uint32_t(K);
   const uint32_t vo1 = r1 * uint32_t(K);
   uint32_t rb[4];
 #pragma unroll
@@ -929,10 +911,10 @@ k_japply_tri(const float *__restrict__ V, float *__restrict__ Q, int64_t n, int 
   const int e2 = nt >= 3 ? ct[2] + 1 : 0;
   const int e1 = nt >= 2 ? ct[1] + 1 : 0;
   const int e0 = ct[0] + 1;
-  if (nt >= 4) tri_chunks<OCT, VEC, 4>(Vw, RT, vo, vo1, K, Kp, rb, h, 0, e3, acc);
-  if (nt >= 3) tri_chunks<OCT, VEC, 3>(Vw, RT, vo, vo1, K, Kp, rb, h, e3, e2, acc);
-  if (nt >= 2) tri_chunks<OCT, VEC, 2>(Vw, RT, vo, vo1, K, Kp, rb, h, e2, e1, acc);
-  tri_chunks<OCT, VEC, 1>(Vw, RT, vo, vo1, K, Kp, rb, h, e1, e0, acc);
+  if (nt >= 4) tri_chunks<VEC, 4>(Vw, RT, vo, vo1, K, Kp, rb, h, 0, e3, acc);
+  if (nt >= 3) tri_chunks<VEC, 3>(Vw, RT, vo, vo1, K, Kp, rb, h, e3, e2, acc);
+  if (nt >= 2) tri_chunks<VEC, 2>(Vw, RT, vo, vo1, K, Kp, rb, h, e2, e1, acc);
+  tri_chunks<VEC, 1>(Vw, RT, vo, vo1, K, Kp, rb, h, e1, e0, acc);
   float *Qw = Q + row0 * int64_t(K);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -1591,10 +1573,10 @@ hef_status apply_run(const void *V, void *Q, int pool_type, int64_t n, int K, in
     k_japply_dma<<<2 * cdiv(n, kDR), kDT, 0, s>>>(reinterpret_cast<const float *>(V),
                                                  reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
   } else if ((K & 3) == 0) {
-    k_japply_tri<false, true><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
+    k_japply_tri<true><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
         reinterpret_cast<const float *>(V), reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
   } else {
-    k_japply_tri<false, false><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
+    k_japply_tri<false><<<cdiv(n, kA2Rows), kA2T, 0, s>>>(
         reinterpret_cast<const float *>(V), reinterpret_cast<float *>(Q), n, K, Kp, RinvT32);
   }
   HEF_LAUNCH_CHECK();
