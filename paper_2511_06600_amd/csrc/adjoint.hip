@@ -152,9 +152,16 @@ k_sadj_a(const float *__restrict__ sfwd, int K, int LPR, int64_t m, const double
 // hyperedges of up to long_from(kSmallSeg) pins, a lane group each;
 // k_sadj_long the longer ones, a workgroup each (one group walking 2000 pins
 // is a chain of 500 dependent gathers: 845 us at 200k nodes, K = 160, against
-// 398 us for the two, 92 of it the long ones).  20000 hyperedges of 100 pins,
+// 390 us for the two, 81 of it the long ones).  20000 hyperedges of 100 pins,
 // K = 24: 104 us by lane groups, 5670 by a workgroup each whose first group
 // took in all the others one after the other.
+// Where many hyperedges are long (long_from), the line lies at 128 pins, or 64
+// with lane groups of 32 lanes or more.  us, a gradient with a workgroup for
+// every one / above 64 / above 128 pins: 50000 hyperedges of 40 pins, K = 24,
+// 15412 / 1382 / 1362, K = 160, 6031 / 3926 / 3922; 20000 of 100 pins, K = 24, 6901
+// / 1655 / 1254, K = 160, 4466 / 3958 / 4113.
+__device__ __forceinline__ int sadj_many(int lanes) { return lanes >= 32 ? 64 : 128; }
+
 struct SadjOut {
   int32_t *slot_a, *slot_b;
   float *dbar;
@@ -241,7 +248,7 @@ k_sadj_b(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
          const float *__restrict__ dR, const float *__restrict__ w,
          const int32_t *__restrict__ istar, const double *__restrict__ qsum,
          const int32_t *__restrict__ n_big, const SadjOut o) {
-  const int from = long_from(kSmallSeg, LPR, *n_big);
+  const int from = long_from(kSmallSeg, sadj_many(LPR), *n_big);
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -281,7 +288,7 @@ k_sadj_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
   double inv[CPL], qb[CPL];
   sadj_cols<CPL>(c0, K, qh, qsum, inv, qb);
   const int32_t cnt = *count;
-  const int from = long_from(kSmallSeg, LPR, cnt);
+  const int from = long_from(kSmallSeg, sadj_many(LPR), cnt);
   for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
     const int32_t e = list[bi];
     const int32_t a = eptr[e], b = eptr[e + 1];
@@ -306,6 +313,7 @@ k_sadj_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
     __syncthreads();
     int half = 1;
     while (2 * half < use) half *= 2;
+#pragma unroll 1
     for (; half > 0; half /= 2) {  // groups [0, half) take in [half, 2 half)
       if (grp < half && grp + half < use) {
         // the first position among equal values

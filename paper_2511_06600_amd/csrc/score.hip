@@ -134,18 +134,30 @@ __device__ __forceinline__ void store_cols(void *pool, int64_t row, int K, int c
 // Largest and smallest pool values of every long hyperedge (of more than
 // long_from(longseg) pins), a workgroup per hyperedge of the list: as many of
 // its groups of LPR lanes as it has fours of pins take 4 at a time, then their
-// extremes meet in LDS, in a tree over those groups.  Row 2 i of `ext`
+// extremes meet in LDS, by halves down to 16 groups.  Row 2 i of `ext`
 // receives the largest, row 2 i + 1 the smallest values, i = (first pin
 // position) / longseg, which no two such hyperedges share.  Maxima do not
 // depend on the order, so the ratios keep their bits.  The longest hyperedge's
-// chain bounds it: 28 us at 20k nodes, K = 464, 47 at 200k, K = 160, 117 at 2M,
-// K = 480.  With the groups' extremes taken in one after the other, all of
+// chain bounds it at small sizes, the gathers at large ones: 26 us at 20k nodes,
+// K = 464, 43 at 200k, K = 160, 337 at 2M, K = 480 (206 with the bfloat16 pool).  With the groups' extremes taken in one after the other, all of
 // them for a hyperedge of any length, 50000 hyperedges of 40 pins at K = 24
 // took 727 us, seven times a lane group each.
 constexpr int kLongThreads = 1024;
+constexpr int kLongLast = 16;
 
+// The line where many hyperedges are long (long_from): 128 pins, but none with
+// lane groups of 32 lanes or more, of which a workgroup has 32 at most.  us, an
+// estimate with a workgroup for every one / above 64 / above 128 pins: 50000
+// hyperedges of 40 pins, K = 24, 1618 / 982 / 984, K = 160, 2946 / 2870 / 2864;
+// 20000 of 100 pins, K = 24, 1172 / 1025 / 937, K = 160, 2810 / 2821 / 2953; 2M
+// nodes, bfloat16, K = 480 (15k hyperedges above 32 pins), 28579 / 28695 / -.
+__device__ __forceinline__ int score_many(int lanes) { return lanes >= 32 ? 0 : 128; }
+
+// (held to 64 VGPRs but for the float64 pool: two workgroups a CU, 206 us
+// against 308 at 2M nodes, K = 480, bfloat16)
 template <int CPL, int PT>
 __global__ void __launch_bounds__(kLongThreads)
+__attribute__((amdgpu_waves_per_eu(PT == kPoolF64 ? 4 : 8, 8)))
 k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
              const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
              const void *__restrict__ pool, int K, int LPR, int longseg, void *__restrict__ ext) {
@@ -158,7 +170,7 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
   const int c0 = (tid % LPR) * CPL;
   const int W = LPR * CPL;  // columns of a group's LDS row
   const int32_t cnt = *count;
-  const int from = long_from(longseg, LPR, cnt);
+  const int from = long_from(longseg, score_many(LPR), cnt);
   for (int32_t bi = blockIdx.x; bi < cnt; bi += gridDim.x) {
     const int32_t e = list[bi];
     const int32_t a = eptr[e], b = eptr[e + 1];
@@ -190,10 +202,13 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
       smn[grp * W + c0 + q] = mn[q];
     }
     __syncthreads();
-    int half = 1;
-    while (2 * half < use) half *= 2;
-    for (; half > 0; half /= 2) {  // groups [0, half) take in [half, 2 half)
-      if (grp < half && grp + half < use) {
+    // groups [0, half) take in [half, 2 half) down to kLongLast groups, whose
+    // extremes the first takes in (a barrier costs more than the reads it saves)
+    int left = use;
+#pragma unroll 1
+    for (int half = kLongThreads / 2; half >= kLongLast; half /= 2) {
+      if (half >= left) continue;
+      if (grp < half && grp + half < left) {
 #pragma unroll
         for (int q = 0; q < CPL; ++q) {
           mx[q] = vmax(mx[q], smx[(grp + half) * W + c0 + q]);
@@ -202,9 +217,17 @@ k_score_long(const int32_t *__restrict__ list, const int32_t *__restrict__ count
           smn[grp * W + c0 + q] = mn[q];
         }
       }
+      left = half;
       __syncthreads();
     }
     if (grp == 0 && c0 < K) {
+#pragma unroll 1
+      for (int g = 1; g < left; ++g)
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+          mx[q] = vmax(mx[q], smx[g * W + c0 + q]);
+          mn[q] = vmin(mn[q], smn[g * W + c0 + q]);
+        }
       const int64_t row = 2 * int64_t(a / longseg);
       store_cols<CPL, PT>(ext, row, K, c0, mx);
       store_cols<CPL, PT>(ext, row + 1, K, c0, mn);
@@ -229,7 +252,7 @@ k_score_qh(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pins,
            int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
            const int32_t *__restrict__ n_big, const void *__restrict__ ext) {
   __shared__ double comb[kThreads * CPL];
-  const int from = long_from(longseg, LPR, *n_big);
+  const int from = long_from(longseg, score_many(LPR), *n_big);
   const int tid = threadIdx.x;
   const int ngrp = kThreads / LPR;
   const int grp = tid / LPR;
@@ -319,7 +342,7 @@ k_score_qh_few(const int32_t *__restrict__ eptr, const int32_t *__restrict__ pin
                const float *__restrict__ w, const void *__restrict__ pool, int K, int LPR,
                int64_t m, double *__restrict__ partial, float *__restrict__ sbuf, int longseg,
                const int32_t *__restrict__ n_big, const void *__restrict__ ext) {
-  const int from = long_from(longseg, LPR, *n_big);
+  const int from = long_from(longseg, score_many(LPR), *n_big);
   constexpr int R = kFewThreads / kThreads;
   constexpr int NA = kThreads * CPL / kFewThreads;  // sums per thread
   static_assert(NA * kFewThreads == kThreads * CPL, "whole sums per thread");

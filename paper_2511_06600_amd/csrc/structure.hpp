@@ -33,19 +33,13 @@ __device__ __forceinline__ bool wave_takes(int32_t len) {
 
 // The passes that give a long hyperedge a workgroup of 1024 threads (the ratios
 // and their adjoint) take those of more than kSmallSeg pins while these are
-// few, and where there are more than kFewLong those above 64 pins (lane groups
-// of 32 or 64 lanes, pools of more than 64 columns) or 128 (narrower groups).
-// 512 such workgroups run at a time, a few us each, so 2048 hyperedges are four
+// few, and where there are more than kFewLong those of more than `many`.  512
+// such workgroups run at a time, a few us each, so 2048 hyperedges are four
 // turns, about a lane group's chain over 128 pins, while thousands of lane
-// groups run at once.  us, an estimate with a workgroup for every one / above
-// 64 / above 128 pins: 50000 hyperedges of 40 pins, K = 24, 1618 / 982 / 984, K =
-// 160, 2946 / 2870 / 2864; 20000 of 100 pins, K = 24, 1172 / 1025 / 937, K = 160,
-// 2810 / 2821 / 2953.  The ratios of three levels from 2M nodes, K = 480 (15k
-// hyperedges above 32 pins): 8.32 / 8.40 / 8.35 ms.
+// groups run at once.
 constexpr int kFewLong = 2048;
-__device__ __forceinline__ int long_from(int least, int lanes, int32_t n_big) {
-  const int mid = lanes >= 32 ? 64 : 128;
-  return n_big > kFewLong && least < mid ? mid : least;
+__device__ __forceinline__ int long_from(int least, int many, int32_t n_big) {
+  return n_big > kFewLong && least < many ? many : least;
 }
 
 struct Structure {

@@ -547,9 +547,9 @@ def test_long_pin_ranges_are_split(layout):
 @pytest.mark.parametrize("many", [2048, 2049])
 def test_many_long_hyperedges(many, k, b):
     """Up to 2048 hyperedges of more than 32 pins each take a workgroup in the
-    ratios and in their adjoint, more than that only those above 128 pins, or
-    64 with lane groups of 32 and more: as
-    many fours of pins as lane groups and fewer, whole and not.  Ratios
+    ratios and in their adjoint, more than that only those above 128 pins; with
+    lane groups of 32 lanes and more every one in the ratios, those above 64 in
+    the adjoint.  As many fours of pins as lane groups and fewer, whole and not.  Ratios
     against float64 on the pool (bounds as in test_long_hyperedge_ratios), the
     gradient against the float64 autograd oracle at the adjoint tests' 1e-3."""
     from oracle import gradient as ogr
