@@ -139,9 +139,10 @@ __device__ __forceinline__ void store_cols(void *pool, int64_t row, int K, int c
 // position) / longseg, which no two such hyperedges share.  Maxima do not
 // depend on the order, so the ratios keep their bits.  The longest hyperedge's
 // chain bounds it at small sizes, the gathers at large ones: 26 us at 20k nodes,
-// K = 464, 43 at 200k, K = 160, 337 at 2M, K = 480 (206 with the bfloat16 pool).  With the groups' extremes taken in one after the other, all of
-// them for a hyperedge of any length, 50000 hyperedges of 40 pins at K = 24
-// took 727 us, seven times a lane group each.
+// K = 464, 43 at 200k, K = 160, 337 at 2M, K = 480 (206 with the bfloat16 pool).
+// With the groups' extremes taken in one after the other, all of them for a
+// hyperedge of any length, 50000 hyperedges of 40 pins at K = 24 took 727 us,
+// seven times a lane group each.
 constexpr int kLongThreads = 1024;
 constexpr int kLongLast = 16;
 
